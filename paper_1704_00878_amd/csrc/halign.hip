@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <fstream>
+#include <initializer_list>
 #include <map>
 #include <sstream>
 #include <cstdarg>
@@ -2166,19 +2167,43 @@ int gemm(const hk::GemmArgs &g, hipStream_t st) {
     return HALIGN_OK;
 }
 
-// fixed-order column sums of a rows x cols fp32 matrix into out[cols]
-int colsum(halign_ctx *ctx, DevBuf &scratch, const float *A, int rows, int cols, int lda, float *out, hipStream_t st) {
-    const int nblk = std::max(1, (rows + 1023) / 1024);
+// The pipelined product (packed B, rows of A 16-byte aligned).
+template <int BM, int BN, int WM, int WN, bool TA, int EPI, int PF>
+int gemm_tile(const hk::GemmArgs &g, hipStream_t st) {
+    if (g.M <= 0) return HALIGN_OK;
+    // epilogue 3 also writes the zero rows that pad its packed output
+    const int rows = EPI == 3 ? (g.M + hk::kGK - 1) / hk::kGK * hk::kGK : g.M;
+    const int mt = (rows + BM - 1) / BM, nt = g.N / BN;
+    hipLaunchKernelGGL((hk::gemm_tile_kernel<BM, BN, WM, WN, TA, EPI, PF>), dim3((mt + 7) / 8 * 8 * nt),
+                       dim3(64 * (BM / WM) * (BN / WN)), 0, st, g, mt, nt);
+    HCHK(hipGetLastError());
+    return HALIGN_OK;
+}
+
+// Whether the pipelined products may run: their 16-byte loads of A need
+// aligned operands (the callers' pointers may have any alignment the element
+// type allows), and their scratch `buf` must be there or be allocatable (not
+// while `st` is being captured).
+bool tile_ok(const DevBuf &buf, size_t bytes, hipStream_t st, std::initializer_list<const void *> ptrs) {
+    for (const void *p : ptrs)
+        if ((uintptr_t)p & 15) return false;
+    if (bytes <= buf.cap) return true;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+}
+
+// fixed-order column sums of one or two rows x cols fp32 matrices (cols
+// multiples of 64) into out
+int colsum(halign_ctx *ctx, DevBuf &scratch, hk::ColsumArgs a, hipStream_t st) {
+    const int nblk = std::max(1, (a.rows + hk::kColRows - 1) / hk::kColRows), cols = a.cols[0] + a.cols[1];
     RCHK(grow(ctx, scratch, (size_t)nblk * cols * 4 + 256));
-    float *part = (float *)scratch.p;
-    if (rows > 0) {
-        hipLaunchKernelGGL(hk::colsum_partial_kernel, dim3((cols + 255) / 256, nblk), dim3(256), 0, st, A, rows, cols,
-                           lda, part);
-    } else {
-        RCHK(launch_fill((uint32_t *)part, 0u, cols, st));
-    }
-    hipLaunchKernelGGL(hk::colsum_final_kernel, dim3((cols + 255) / 256), dim3(256), 0, st, (const float *)part,
-                       rows > 0 ? nblk : 1, cols, out);
+    a.part[0] = (float *)scratch.p;
+    a.part[1] = a.part[0] + (size_t)nblk * a.cols[0];
+    if (a.rows > 0)
+        hipLaunchKernelGGL(hk::colsum_partial_kernel, dim3(cols / 64, nblk), dim3(1024), 0, st, a);
+    else
+        RCHK(launch_fill((uint32_t *)scratch.p, 0u, cols, st));
+    hipLaunchKernelGGL(hk::colsum_final_kernel, dim3((cols + 255) / 256), dim3(256), 0, st, a, nblk);
     HCHK(hipGetLastError());
     return HALIGN_OK;
 }
@@ -2214,16 +2239,36 @@ int halign_mlp_forward(halign_ctx *ctx, const halign_model *model, const uint16_
                        uint16_t *Hb, float *E, void *stream) {
     if (!ctx || nrows < 0 || (nrows > 0 && (!X || !Hb || !E))) return fail(HALIGN_E_INVALID, "bad arguments");
     RCHK(check_model(model));
+    if (nrows == 0) return HALIGN_OK;
     hipStream_t st = (hipStream_t)stream;
     hk::GemmArgs g1{};
     g1.A = X; g1.B = model->W1; g1.M = nrows; g1.N = hk::kHid; g1.K = hk::kFeat; g1.lda = hk::kFeat; g1.ldb = hk::kHid;
     g1.C = Z; g1.ldc = hk::kHid; g1.bias = model->b1; g1.Cb = Hb; g1.ldcb = hk::kHid;
-    RCHK((gemm<false, false, 1>(g1, st)));
     hk::GemmArgs g2{};
     g2.A = Hb; g2.B = model->W2; g2.M = nrows; g2.N = hk::kEmb; g2.K = hk::kHid; g2.lda = hk::kHid; g2.ldb = hk::kEmb;
     g2.C = E; g2.ldc = hk::kEmb; g2.bias = model->b2;
-    RCHK((gemm<false, false, 0>(g2, st)));
-    return HALIGN_OK;
+    const size_t b_p1 = (size_t)hk::kPackW1 * 16, b_p2 = (size_t)hk::kPackW2 * 16;
+    if (!tile_ok(ctx->mlp[9], b_p1 + b_p2, st, {X, Hb})) {
+        RCHK((gemm<false, false, 1>(g1, st)));
+        return gemm<false, false, 0>(g2, st);
+    }
+    RCHK(grow(ctx, ctx->mlp[9], b_p1 + b_p2));
+    uint16_t *P1 = (uint16_t *)ctx->mlp[9].p, *P2 = (uint16_t *)((char *)ctx->mlp[9].p + b_p1);
+    hipLaunchKernelGGL(hk::pack_weights_kernel, dim3((hk::kPackW1 + hk::kPackW2 + 255) / 256), dim3(256), 0, st,
+                       model->W1, model->W2, P1, P2);
+    HCHK(hipGetLastError());
+    g1.B = P1;
+    g2.B = P2;
+    // X . W1: the smallest tile that leaves at most one workgroup per CU (us,
+    // K = 8000, N = 256): 2,048 rows 22 / 28 / 47 / 62 for the four tiles,
+    // 4,096 rows 37 / 31 / 47 / 62, 8,192 rows 67 / 56 / 51 / 65, 16,384 rows
+    // 169 / 144 / 129 / 100; a smaller tile reads W1 more often, a larger one
+    // leaves CUs idle
+    if ((nrows + 31) / 32 * 4 <= ctx->num_cu) RCHK((gemm_tile<32, 64, 32, 32, false, 1, 4>(g1, st)));
+    else if ((nrows + 63) / 64 * 4 <= ctx->num_cu) RCHK((gemm_tile<64, 64, 32, 32, false, 1, 4>(g1, st)));
+    else if ((nrows + 63) / 64 * 2 <= ctx->num_cu) RCHK((gemm_tile<64, 128, 32, 64, false, 1, 4>(g1, st)));
+    else RCHK((gemm_tile<64, 256, 64, 64, false, 1, 4>(g1, st)));
+    return gemm_tile<32, 32, 32, 32, false, 0, 2>(g2, st);
 }
 
 int halign_pair_loss(halign_ctx *ctx, const float *E, const float *target, int32_t npairs, float *dE,
@@ -2231,12 +2276,11 @@ int halign_pair_loss(halign_ctx *ctx, const float *E, const float *target, int32
     if (!ctx || npairs < 0 || (npairs > 0 && (!E || !target || !dE || !loss_out)))
         return fail(HALIGN_E_INVALID, "bad arguments");
     hipStream_t st = (hipStream_t)stream;
-    RCHK(grow(ctx, ctx->mlp[0], (size_t)npairs * 4 + (size_t)2 * npairs * hk::kEmb * 2 + 512));
+    RCHK(grow(ctx, ctx->mlp[0], (size_t)npairs * 4 + 512));
     float *sq = (float *)ctx->mlp[0].p;
-    uint16_t *dEb = (uint16_t *)((char *)ctx->mlp[0].p + (((size_t)npairs * 4 + 255) & ~size_t(255)));
     if (npairs > 0) {
-        hipLaunchKernelGGL(hk::pair_loss_kernel, dim3((npairs + 255) / 256), dim3(256), 0, st, E, target, npairs, dE,
-                           dEb, sq);
+        hipLaunchKernelGGL(hk::pair_loss_kernel, dim3((npairs + hk::kLossPairs - 1) / hk::kLossPairs), dim3(256), 0, st,
+                           E, target, npairs, dE, sq);
         HCHK(hipGetLastError());
     }
     hipLaunchKernelGGL(hk::mean_kernel, dim3(1), dim3(256), 0, st, (const float *)sq, npairs, loss_out);
@@ -2275,38 +2319,49 @@ int halign_mlp_backward(halign_ctx *ctx, const halign_model *model, const uint16
         return fail(HALIGN_E_INVALID, "bad arguments");
     RCHK(check_model(model));
     hipStream_t st = (hipStream_t)stream;
-    const size_t b_dEb = ((size_t)nrows * hk::kEmb * 2 + 255) & ~size_t(255);
-    const size_t b_dZ = ((size_t)nrows * hk::kHid * 4 + 255) & ~size_t(255);
-    const size_t b_dZb = ((size_t)nrows * hk::kHid * 2 + 255) & ~size_t(255);
-    RCHK(grow(ctx, ctx->mlp[1], b_dEb + b_dZ + b_dZb + 256));
-    uint16_t *dEb = (uint16_t *)ctx->mlp[1].p;
-    float *dZ = (float *)((char *)ctx->mlp[1].p + b_dEb);
-    uint16_t *dZb = (uint16_t *)((char *)ctx->mlp[1].p + b_dEb + b_dZ);
-    if (nrows > 0) {
+    auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
+    const size_t rpad = ((size_t)nrows + 63) / 64 * 64;
+    const size_t b_dEb = al((size_t)nrows * hk::kEmb * 2), b_dZ = al((size_t)nrows * hk::kHid * 4),
+                 b_dZb = al(rpad * hk::kHid * 2), b_Pd = al(rpad * hk::kEmb * 2), b_P2t = al((size_t)hk::kPackW2T * 16);
+    RCHK(grow(ctx, ctx->mlp[1], b_dEb + b_dZ + b_dZb + b_Pd + b_P2t));
+    char *w = (char *)ctx->mlp[1].p;
+    uint16_t *dEb = (uint16_t *)w, *dZb = (uint16_t *)(w + b_dEb + b_dZ), *Pd = (uint16_t *)(w + b_dEb + b_dZ + b_dZb),
+             *P2t = (uint16_t *)(w + b_dEb + b_dZ + b_dZb + b_Pd);
+    float *dZ = (float *)(w + b_dEb);
+    // dW2 = Hb^T dEb, dZ = (dEb W2^T) * (Z > 0), dW1 = X^T dZb
+    hk::GemmArgs a{}, b{}, c{};
+    a.A = Hb; a.B = dEb; a.M = hk::kHid; a.N = hk::kEmb; a.K = nrows; a.lda = hk::kHid; a.ldb = hk::kEmb;
+    a.C = dW2; a.ldc = hk::kEmb;
+    b.A = dEb; b.B = model->W2; b.M = nrows; b.N = hk::kHid; b.K = hk::kEmb; b.lda = hk::kEmb; b.ldb = hk::kEmb;
+    b.C = dZ; b.ldc = hk::kHid; b.Cb = dZb; b.ldcb = hk::kHid; b.Hpre = Z; b.ldh = hk::kHid;
+    c.A = X; c.B = dZb; c.M = hk::kFeat; c.N = hk::kHid; c.K = nrows; c.lda = hk::kFeat; c.ldb = hk::kHid;
+    c.C = dW1; c.ldc = hk::kHid;
+    const bool tile = tile_ok(ctx->mlp[1], 0, st, {X, Hb});
+    if (nrows == 0) {
+        RCHK(launch_fill((uint32_t *)dW2, 0u, (int64_t)hk::kHid * hk::kEmb, st));
+        RCHK(launch_fill((uint32_t *)dW1, 0u, (int64_t)hk::kFeat * hk::kHid, st));
+    } else if (tile) {
+        hipLaunchKernelGGL(hk::pack_backward_kernel, dim3((hk::pack_octets(nrows, hk::kEmb) + hk::kPackW2T + 255) / 256),
+                           dim3(256), 0, st, dE, nrows, dEb, Pd, model->W2, P2t);
+        HCHK(hipGetLastError());
+        a.B = Pd;
+        b.B = P2t;
+        RCHK((gemm_tile<32, 32, 32, 32, true, 0, 2>(a, st)));
+        RCHK((gemm_tile<32, 64, 32, 32, false, 3, 2>(b, st)));
+        RCHK((gemm_tile<64, 128, 32, 64, true, 0, 4>(c, st)));
+    } else {
         hipLaunchKernelGGL(hk::f32_to_bf16_kernel, dim3(grid_for((int64_t)nrows * hk::kEmb, 256, 4096)), dim3(256), 0,
                            st, dE, dEb, (int64_t)nrows * hk::kEmb);
         HCHK(hipGetLastError());
+        RCHK((gemm<true, false, 0>(a, st)));
+        RCHK((gemm<false, true, 2>(b, st)));
+        RCHK((gemm<true, false, 0>(c, st)));
     }
-    hk::GemmArgs a{};
-    // dW2 = Hb^T dEb
-    a.A = Hb; a.B = dEb; a.M = hk::kHid; a.N = hk::kEmb; a.K = nrows; a.lda = hk::kHid; a.ldb = hk::kEmb;
-    a.C = dW2; a.ldc = hk::kEmb;
-    if (nrows > 0) RCHK((gemm<true, false, 0>(a, st)));
-    else RCHK(launch_fill((uint32_t *)dW2, 0u, (int64_t)hk::kHid * hk::kEmb, st));
-    RCHK(colsum(ctx, ctx->mlp[2], dE, nrows, hk::kEmb, hk::kEmb, db2, st));
-    // dZ = (dEb W2^T) * (Z > 0)
-    hk::GemmArgs b{};
-    b.A = dEb; b.B = model->W2; b.M = nrows; b.N = hk::kHid; b.K = hk::kEmb; b.lda = hk::kEmb; b.ldb = hk::kEmb;
-    b.C = dZ; b.ldc = hk::kHid; b.Cb = dZb; b.ldcb = hk::kHid; b.Hpre = Z; b.ldh = hk::kHid;
-    RCHK((gemm<false, true, 2>(b, st)));
-    RCHK(colsum(ctx, ctx->mlp[2], dZ, nrows, hk::kHid, hk::kHid, db1, st));
-    // dW1 = X^T dZb
-    hk::GemmArgs c{};
-    c.A = X; c.B = dZb; c.M = hk::kFeat; c.N = hk::kHid; c.K = nrows; c.lda = hk::kFeat; c.ldb = hk::kHid;
-    c.C = dW1; c.ldc = hk::kHid;
-    if (nrows > 0) RCHK((gemm<true, false, 0>(c, st)));
-    else RCHK(launch_fill((uint32_t *)dW1, 0u, (int64_t)hk::kFeat * hk::kHid, st));
-    return HALIGN_OK;
+    hk::ColsumArgs cs{};
+    cs.A[0] = dE; cs.cols[0] = hk::kEmb; cs.out[0] = db2;
+    cs.A[1] = dZ; cs.cols[1] = hk::kHid; cs.out[1] = db1;
+    cs.rows = nrows;
+    return colsum(ctx, ctx->mlp[2], cs, st);
 }
 
 int halign_f32_to_bf16(const float *src, uint16_t *dst, int64_t n, void *stream) {
@@ -2336,7 +2391,9 @@ int halign_topk_center(halign_ctx *ctx, const float *E, int32_t nrows, int32_t k
     hipStream_t st = (hipStream_t)stream;
     RCHK(grow(ctx, ctx->mlp[3], 4096));
     float *S = (float *)ctx->mlp[3].p;
-    RCHK(colsum(ctx, ctx->mlp[2], E, nrows, hk::kEmb, hk::kEmb, S, st));
+    hk::ColsumArgs cs{};
+    cs.A[0] = E; cs.cols[0] = hk::kEmb; cs.out[0] = S; cs.rows = nrows;
+    RCHK(colsum(ctx, ctx->mlp[2], cs, st));
     hipLaunchKernelGGL(hk::center_score_kernel, dim3((nrows + 255) / 256), dim3(256), 0, st, E, (const float *)S, nrows,
                        u);
     HCHK(hipGetLastError());
