@@ -372,6 +372,63 @@ void launch_inter(const hk::InterArgs &a, bool tb, bool endc, int grid, hipStrea
         hipLaunchKernelGGL((hk::sw_inter_kernel<false, false>), dim3(grid), dim3(64), 0, st, a);
 }
 
+// Geometry of the wavefront forward for a batch.
+struct StreamGeom {
+    int R = 8, passes = 1, LS = 64, pk = 0;
+};
+
+// Streams of a batch of `np` non-empty pairs (lengths plen, longest first) when
+// `cap` streams are resident, and the columns that a wavefront's share of them
+// takes: the mean of the average and the longest stream (streams end apart,
+// and those that end early leave their issue slots to the others).
+double stream_cols(const int32_t *plen, int np, int64_t sum_len, int cap) {
+    if (cap >= np) return 0.5 * ((double)sum_len / np + plen[0]);
+    const double avg = (double)sum_len / cap;
+    double top = std::max<double>(plen[0], 1.05 * avg);
+    if (np < 2 * cap)   // the shortest pairs join the streams of the shortest long ones
+        for (int i : {0, (np - cap) / 2, np - cap - 1}) top = std::max<double>(top, plen[cap - 1 - i] + plen[cap + i]);
+    return 0.5 * (avg + top);
+}
+
+// Cycles that a SIMD needs for the batch with geometry g and `w` wavefronts per
+// SIMD of it resident.  A step issues about ops(R) instructions of 4 cycles;
+// w wavefronts on a SIMD take kShare[w] issue times per step of each (a serial
+// chain alone: 1.28; four together fill the issue slots), and no stream ends
+// before its longest pair.  Against the measured forward times (20,000 pairs of
+// 200-500 on m = 311, 4,000 on 450, 300 of 300-900 on 800, 64 of 80-160 on 120,
+// 50,000 of a long tail on 101, 300,000 of 50-1000 on 93 and 200) this is within
+// 25%, and it orders the geometries as measured: packed streams of 32 or 16
+// lanes where they fill the chip, 64 lanes below.
+constexpr double kShare[7] = {1.28, 1.28, 2.2, 3.15, 4, 5, 6};
+double stream_cost(const halign_ctx *ctx, const StreamGeom &g, bool tb, const int32_t *plen, int np, int64_t sum_len,
+                   int w) {
+    const int per_wave = 64 / g.LS * (g.pk ? 2 : 1), simds = ctx->num_cu * 4;
+    const double ops = g.pk ? (tb ? (g.R > 11 ? 21.8 : 17.8) * g.R + 65 : 10.5 * g.R + 65)
+                            : (tb ? 16.4 * g.R + 38 : 9.0 * g.R + 30);
+    const double cols = stream_cols(plen, np, sum_len, simds * w * per_wave);
+    const int waves = (std::min(np, simds * w * per_wave) + per_wave - 1) / per_wave;
+    const int weff = (waves + simds - 1) / simds;
+    return 4.0 * ops * g.passes *
+           std::max((cols + g.LS - 1) * kShare[std::min(6, weff)], (plen[0] + g.LS - 1) * kShare[1]);
+}
+
+// Resident wavefronts per SIMD that the packed kernel's streams are sized for
+// (at most four fit its registers): four, or fewer where more pairs per stream
+// end closer together.
+int packed_waves(const halign_ctx *ctx, const StreamGeom &g, bool tb, const int32_t *plen, int np, int64_t sum_len,
+                 int wmax) {
+    int best = std::min(4, wmax);
+    double cost = stream_cost(ctx, g, tb, plen, np, sum_len, best);
+    for (int w = best - 1; w >= 1; --w) {
+        const double c = stream_cost(ctx, g, tb, plen, np, sum_len, w);
+        if (c < 0.97 * cost) {
+            cost = c;
+            best = w;
+        }
+    }
+    return best;
+}
+
 struct BatchOut {
     int32_t *score, *cells, *endcell;
     uint16_t *ins;
@@ -443,46 +500,88 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
     int R = 8, passes = 1, LS = 64;
     pick_geom(m, &R, &passes);
     if (tune.route >= 0) route = tune.route;
-    if (tune.R > 0 && stream_supported(tune.R, tune.LS > 0 ? tune.LS : 64, p16)) {
-        LS = tune.LS > 0 ? tune.LS : 64;
-        R = tune.R;
-        passes = std::max(1, (m + LS * R - 1) / (LS * R));
-    } else if (const char *e = getenv("HALIGN_STREAM_LANES")) {   // test knob: narrower streams
-        const int ls = atoi(e);
-        const int ps = std::max(1, (m + ls * 16 - 1) / std::max(1, ls * 16));
-        const int r = std::max(2, (m + ls * ps - 1) / std::max(1, ls * ps));
-        if ((ls == 32 || ls == 16) && stream_supported(r, ls, p16)) {
-            LS = ls;
-            R = r;
-            passes = ps;
-        }
-    }
-    // packed 16-bit wavefront kernel: asked for by the tuner (or the test knob
-    // HALIGN_STREAM_PACK=1 with the lanes knob), traceback with end cells only,
-    // and only when every H stays below 15000 and the gap costs are small
+    // packed 16-bit wavefront kernel: only when every H stays below 15000 and
+    // the gap costs are small
+    const bool pk_fits = p16 && (int64_t)smax * std::min(m, nlong) < 15000 && S.goe <= 256 && S.ge <= 256;
     bool pk = false;
-    {
-        const char *e = getenv("HALIGN_STREAM_PACK");
-        const bool want = tune.R > 0 ? tune.pk > 0 : (e && atoi(e) != 0);
-        const bool fits = p16 && tb && endc && (int64_t)smax * std::min(m, nlong) < 15000 && S.goe <= 256 &&
-                          S.ge <= 256;
-        pk = want && fits && route == kRouteIntra && stream16_supported(R, LS);
+    int nonempty_all = np;   // (empty pairs sort last)
+    while (nonempty_all > 0 && plen[nonempty_all - 1] == 0) --nonempty_all;
+    auto narrow = [&](int ls) {   // the fewest passes of streams of ls lanes, and the rows that fills
+        StreamGeom g;
+        g.LS = ls;
+        g.passes = std::max(1, (m + ls * 16 - 1) / (ls * 16));
+        g.R = std::max(2, (m + ls * g.passes - 1) / (ls * g.passes));
+        return g;
+    };
+    const char *env_ls = getenv("HALIGN_STREAM_LANES");   // test knobs: narrower streams,
+    const char *env_pk = getenv("HALIGN_STREAM_PACK");    // and the packed kernel on them
+    if (tune.R > 0) {
+        if (stream_supported(tune.R, tune.LS > 0 ? tune.LS : 64, p16)) {
+            LS = tune.LS > 0 ? tune.LS : 64;
+            R = tune.R;
+            passes = std::max(1, (m + LS * R - 1) / (LS * R));
+        }
+        pk = tune.pk > 0 && pk_fits && stream16_supported(R, LS);
+    } else if (env_ls) {
+        const int ls = atoi(env_ls);
+        if ((ls == 32 || ls == 16) && stream_supported(narrow(ls).R, ls, p16)) {
+            const StreamGeom g = narrow(ls);
+            LS = ls;
+            R = g.R;
+            passes = g.passes;
+        }
+        pk = env_pk && atoi(env_pk) != 0 && pk_fits && stream16_supported(R, LS);
+    } else if (route == kRouteIntra && p16 && nonempty_all > 0 && !env_pk) {
+        // no plan given: the cheapest geometry by stream_cost
+        StreamGeom best{R, passes, 64, 0};
+        double cost = stream_cost(ctx, best, tb, plen, nonempty_all, sum_len, R > 6 ? 4 : 6);
+        for (int ls : {32, 16})
+            for (int k = 0; k <= (pk_fits ? 1 : 0); ++k) {
+                StreamGeom g = narrow(ls);
+                g.pk = k;
+                const int w = k ? packed_waves(ctx, g, tb, plen, nonempty_all, sum_len, 4) : (g.R > 6 ? 4 : 6);
+                const double c = stream_cost(ctx, g, tb, plen, nonempty_all, sum_len, w);
+                if (c < cost) {
+                    cost = c;
+                    best = g;
+                }
+            }
+        R = best.R;
+        passes = best.passes;
+        LS = best.LS;
+        pk = best.pk != 0;
     }
+    pk = pk && route == kRouteIntra;
     const int W = (R + 7) / 8, NS = 64 / LS;
     const int WQ = pk ? (R + 3) / 4 : W;   // code words per step
     const size_t prof_bytes =
         p16 ? (size_t)(S.alpha + 1) * LS * 16 * W : (size_t)hk::kAlphaMax * LS * R * 4;
-    const size_t lds_stream = prof_bytes + (tb ? (pk ? (size_t)8 * 256 * 4 * WQ : (size_t)8 * 512 * 4 * W) : 0);
+    // wavefronts per workgroup: one per SIMD, so that any number per SIMD spreads
+    // evenly over the CUs (300 pairs of 300-900 on m = 800: 0.71 against 1.08 ms);
+    // eight in large batches of the 32-bit kernel, which share a profile
+    const int wg_waves = pk || (int64_t)nonempty_all <= (int64_t)ctx->num_cu * 16 * NS ? 4 : 8;
+    const size_t lds_stream =
+        prof_bytes + std::max<size_t>(p16 ? hk::kProfTmp : 0,
+                                      tb ? (size_t)wg_waves * 1024 * (pk ? WQ : 2 * W) : (size_t)0);
+    const StreamGeom geom{R, passes, LS, pk ? 1 : 0};
     if (route == kRouteIntra && lds_stream > ctx->lds_max) route = kRouteInter;
     ctx->last_stats[2] = route;
     ctx->last_pk = pk ? 1 : 0;
 
+    const char *deal_env = getenv("HALIGN_DEAL");   // test knob: snake dealing
+    const bool deal_lpt = !(deal_env && !strcmp(deal_env, "snake"));
     // chunk the pairs so that codes + boundary rows fit the cap
     const size_t cap = ctx->cap ? ctx->cap : (size_t)1 << 62;
     std::vector<std::pair<int, int>> chunks;  // [lo, hi) in pids
+    // columns that the codes cover: every pair's, and a fill and drain per
+    // stream (at most one per pair).  Two streams of the packed kernel share
+    // theirs, sized by the longer one: dealt to the least loaded, they end
+    // within one pair of each other.
+    size_t code_cols = (size_t)sum_len + (size_t)(LS + 8) * (size_t)np;
+    if (pk && deal_lpt)
+        code_cols = std::min(code_cols, ((size_t)sum_len + (size_t)nlong * nonempty_all / 2) / 2 + (size_t)(LS + 8) * np);
     const size_t intra_bytes =
-        (tb ? (size_t)passes * LS * 4 * WQ * ((size_t)sum_len + (size_t)(LS + 8) * (size_t)np) : 0) +
-        (size_t)(passes - 1) * 8 * (size_t)sum_len;
+        (tb ? (size_t)passes * LS * 4 * WQ * code_cols : 0) + (size_t)(passes - 1) * 8 * (size_t)sum_len;
     if (route == kRouteIntra && intra_bytes <= cap) {
         chunks.push_back({0, np});
     } else {
@@ -533,21 +632,21 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
         size_t o_sbeg = 0, o_slot0 = 0, o_scb = 0, o_sbb = 0, o_spid = 0, o_scol = 0, o_sstr = 0;
         size_t o_order = 0, o_gnmax = 0, o_gcb = 0;
         int nstreams = 0, nslots = 0, ngroups = 0;
-        int64_t total_cols = 0;
+        int64_t total_cols = 0, ch_len = 0;
         int nonempty = 0;   // pairs [0, nonempty) of the chunk are non-empty: empty pairs sort last
         for (int x = hi - 1; x >= lo && plen[x] == 0; --x) ++nonempty;
         nonempty = cn - nonempty;
-        const char *deal_env = getenv("HALIGN_DEAL");   // test knob: snake dealing
-        const bool deal_lpt = !(deal_env && !strcmp(deal_env, "snake"));
         if (route == kRouteIntra) {
-            // streams: snake-deal the (longest first) non-empty pairs over the
-            // resident waves so that every stream has about the same columns
-            // resident workgroups per CU: by LDS, and by registers (the packed
-            // kernel and the 32-bit one with R > 6 hold four waves per SIMD,
-            // the 32-bit one with R <= 6 six)
-            const int waves_simd = (pk || R > 6) ? 4 : 6;
-            const int wg_per_cu = std::max(1, std::min({4, (int)(ctx->lds_max / lds_stream), waves_simd * 4 / 8}));
-            const int resident = ctx->num_cu * wg_per_cu * 8 * NS * std::max(1, tune.smul) * (pk ? 2 : 1);
+            // streams: the pairs are dealt, longest first, over the resident
+            // wavefronts so that every stream has about the same columns.
+            // Resident workgroups per CU: by LDS, and by registers (the
+            // 32-bit kernel holds four waves per SIMD with R > 6, else six)
+            for (int x = 0; x < nonempty; ++x) ch_len += plen[lo + x];
+            const int wg_lds = std::max(1, (int)((pk ? ctx->lds_cu : ctx->lds_max) / lds_stream));
+            const int wg_per_cu =
+                pk ? (nonempty > 0 ? packed_waves(ctx, geom, tb, plen + lo, nonempty, ch_len, wg_lds) : 1)
+                   : std::max(1, std::min({4, wg_lds, (R > 6 ? 4 : 6) * 4 / 8}));
+            const int resident = ctx->num_cu * wg_per_cu * (pk ? 4 : 8) * NS * std::max(1, tune.smul) * (pk ? 2 : 1);
             nstreams = std::max(1, std::min(nonempty, (int)std::max(1.0, resident * tune.scale)));
             if (const char *e = getenv("HALIGN_MAX_STREAMS")) {   // test knob: many pairs per stream
                 const int cap_s = atoi(e);
@@ -595,9 +694,7 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
             scount.assign(nstreams, 0);
             scols.assign(nstreams, 0);
             std::vector<int32_t> &sof = ctx->h_sof;   // least-loaded dealing: stream of each non-empty pair
-            int64_t sum_ne = 0;
-            for (int x = 0; x < nonempty; ++x) sum_ne += plen[lo + x];
-            const int64_t maxload = (nonempty > 0 ? sum_ne / nstreams + plen[lo] : 0) + 1;
+            const int64_t maxload = (nonempty > 0 ? ch_len / nstreams + plen[lo] : 0) + 1;
             const bool lpt = deal_lpt && maxload <= ((int64_t)1 << 22);
             hmark(ctx, "p_setup");
             if (lpt) {
@@ -761,8 +858,10 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
             a.scbase = (const int64_t *)(dplan + o_scb);
             a.bound = (int2 *)ctx->bound.p;
             a.sbbase = (const int64_t *)(dplan + o_sbb);
-            if (pk) launch_stream16(R, LS, a, (((nstreams + 1) / 2 + NS - 1) / NS + 7) / 8, lds_stream, st);
-            else launch_stream(R, LS, a, tb, endc, p16, ((nstreams + NS - 1) / NS + 7) / 8, lds_stream, st);
+            const int waves = ((pk ? (nstreams + 1) / 2 : nstreams) + NS - 1) / NS;
+            const int grid = (waves + wg_waves - 1) / wg_waves;
+            if (pk) launch_stream16(R, LS, a, tb, grid, wg_waves * 64, lds_stream, st);
+            else launch_stream(R, LS, a, tb, endc, p16, grid, wg_waves * 64, lds_stream, st);
             HCHK(hipGetLastError());
             RCHK(record(ctx, (*tv)[1], st));
             hipLaunchKernelGGL(hk::decode_keys_kernel, dim3(grid_for(nslots, 256, 1 << 30)), dim3(256), 0, st,
@@ -964,7 +1063,7 @@ int autotune(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, co
         cands.push_back({kRouteIntra, r, 1, scale, ls});
         // the packed 16-bit kernel on the same geometry (run_batch falls back to
         // the 32-bit one where it does not apply)
-        if (tb && endc) cands.push_back({kRouteIntra, r, 1, scale, ls, 1});
+        cands.push_back({kRouteIntra, r, 1, scale, ls, 1});
     }
     cands.push_back({kRouteInter, 0, 1, scale, 64});
     // the forward kernels are timed in the same traceback mode as the call
@@ -1077,17 +1176,28 @@ int validate_now(halign_ctx *ctx, int alpha, const uint8_t *res, int64_t nres, c
     return validate_check(ctx);
 }
 
-int route_of(uint32_t flags, int m, int N) {
+// Streams, unless there are pairs enough for every lane of the chip (4 waves
+// per SIMD) and their scores need 32 bits (16 with traceback), where one pair
+// per lane does as well or better.  300,000 pairs with traceback on a center of
+// 200 (93): packed streams 11.4 (5.1) ms, 32-bit streams of 16 lanes 16.7
+// (8.5), one pair per lane 20.7 (10.1); 270,000 pairs score-only on 200: packed
+// streams 3.7 ms, one pair per lane 7.3.
+int route_of(uint32_t flags, const halign_scoring *sc, int m, const halign_seqs *sq, bool tb) {
     const uint32_t r = flags & (3u << 4);
     if (r == HALIGN_ROUTE_INTER) return kRouteInter;
     if (r == HALIGN_ROUTE_INTRA) return kRouteIntra;
-    (void)m;
     if (const char *e = getenv("HALIGN_ROUTE")) {
         if (!strcmp(e, "intra")) return kRouteIntra;
         if (!strcmp(e, "inter")) return kRouteInter;
     }
-    // enough independent lanes for the chip: 4 waves per SIMD in inter form
-    return (N >= 64 * 4 * 1024) ? kRouteInter : kRouteIntra;
+    if (sq->n < 64 * 4 * 1024) return kRouteIntra;
+    int64_t longest = 0;
+    for (int k = 0; k < sq->n; ++k) longest = std::max(longest, sq->offsets_host[k + 1] - sq->offsets_host[k]);
+    int smax = 1;
+    for (int x = 0; x < sc->alphabet * sc->alphabet; ++x) smax = std::max(smax, (int)sc->matrix_host[x]);
+    const int64_t top = smax * std::min<int64_t>(m, longest);
+    if (tb) return top <= 32000 ? kRouteIntra : kRouteInter;
+    return top < 15000 && sc->gap_open + sc->gap_extend <= 256 ? kRouteIntra : kRouteInter;
 }
 
 }  // namespace
@@ -1340,7 +1450,7 @@ static int sw_batch_body(halign_ctx *ctx, const halign_scoring *sc, const uint8_
     // residues run on the wavefront kernel, one pair per stream, in a launch
     // of their own; the rest keep the strip kernel.  Both write the same
     // outputs, each at its own pair ids.
-    const int route = tune.route >= 0 ? tune.route : route_of(flags, m, N);
+    const int route = tune.route >= 0 ? tune.route : route_of(flags, sc, m, seqs, tb);
     const int64_t *oh = seqs->offsets_host;
     const bool split = route == kRouteInter && (flags & (3u << 4)) == HALIGN_ROUTE_AUTO;
     int nlong = 0;

@@ -3,9 +3,9 @@
 
 namespace hk {
 
-void launch_stream_r6(int R, int LS, const StreamArgs &a, bool tb, bool endc, bool p16, int grid, size_t lds,
+void launch_stream_r6(int R, int LS, const StreamArgs &a, bool tb, bool endc, bool p16, int grid, int threads, size_t lds,
                       hipStream_t st) {
-    launch_stream_range<6, 10>(R, LS, a, tb, endc, p16, grid, lds, st);
+    launch_stream_range<6, 10>(R, LS, a, tb, endc, p16, grid, threads, lds, st);
 }
 
 }  // namespace hk

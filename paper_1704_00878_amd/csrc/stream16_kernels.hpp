@@ -1,5 +1,9 @@
-// Packed 16-bit wavefront kernel for gfx950: the traceback forward pass of
-// the wavefront kernel (sw_kernels.hpp) with two streams per lane group.
+// Packed 16-bit wavefront kernel for gfx950: the forward pass of the wavefront
+// kernel (sw_kernels.hpp), with traceback codes or score-only (TB), with two
+// streams per lane group.  Bound by VALU issue: about 18 operations per row and
+// step for two cells with traceback, 11 without.  20,000 pairs of 200-500 on a
+// center of 311: 0.78 ms (2.8 T cells/s); 20,011 of 150-600 on 400 score-only:
+// 0.60 ms (5.0 T cells/s; the 32-bit kernel 1.10).
 // Lane group g of a wavefront runs stream 2q (A) in the low and stream 2q+1
 // (B) in the high half of every register, q = wave * NS + g, with v_pk_* 16-bit
 // ops.  The lane group's columns are the longer stream's; the other half runs
@@ -83,14 +87,14 @@ __device__ __forceinline__ int row_take(int x) {
     else return __builtin_amdgcn_update_dpp(x, x, kDppRowShl + U, 0xf, 0xf, false);
 }
 
-template <int R, int LS>
+template <int R, int LS, bool TB>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
 sw_stream16_kernel(StreamArgs a) {
     static_assert(LS == 32 || LS == 16, "lanes per stream");
     static_assert(R >= 2 && R <= 16, "rows per lane");
-    // packed end cells need R more registers: up to R = 11 they fit the
-    // 128 of four waves per SIMD
-    constexpr bool SNAP = R <= 11;
+    // packed end cells need R more registers: with code words, up to R = 11
+    // they fit the 128 of four waves per SIMD
+    constexpr bool SNAP = R <= 11 || !TB;
     constexpr int NW = (R + 1) / 2;          // profile dwords a step reads per stream
     // profile planes per residue: rows 0..7 (NA dwords per lane, lane stride
     // SA dwords), then rows 8..R-1 (NB dwords, stride SB); strides of 1, 2 or 4
@@ -105,7 +109,7 @@ sw_stream16_kernel(StreamArgs a) {
     // profile int16 per residue r (PRW dwords): plane A [lane][SA dwords] holds
     // lane l's rows 0..7 (two rows per dword), plane B [lane][SB dwords] its
     // rows 8..R-1, so the lanes of a read touch consecutive slots whatever
-    // residue each one reads; then the code staging [8 waves][4 steps][WQ][64 lanes]
+    // residue each one reads; then the code staging [waves][4 steps][WQ][64 lanes]
     extern __shared__ int prof[];
     const int nprow = a.alpha + 1;
     const int prof_words = nprow * PRW;
@@ -169,6 +173,9 @@ sw_stream16_kernel(StreamArgs a) {
         const int row0 = pass * SPAN;
         __syncthreads();
         {
+            uint8_t *tmp = reinterpret_cast<uint8_t *>(prof + prof_words);   // (where code words are staged later)
+            stage_center(tmp, a, row0, SPAN, tid, nthreads);
+            __syncthreads();
             int16_t *p16 = reinterpret_cast<int16_t *>(prof);
             for (int x = tid; x < nprow * PRW * 2; x += nthreads) {
                 // int16 x of residue r: plane A (lane l, row tt < 8) or plane B
@@ -176,10 +183,7 @@ sw_stream16_kernel(StreamArgs a) {
                 int l, tt;
                 if (y < LS * SA * 2) { l = y / (SA * 2); tt = y - l * (SA * 2); }
                 else { const int z = y - LS * SA * 2; l = z / (SB * 2); tt = 8 + z - l * (SB * 2); }
-                const int i = row0 + l * R + tt;
-                int v = kPadProf16;
-                if (r < a.alpha && tt < R && i < a.m) v = (int)a.mat[(a.center[i] & 31) * a.alpha + r] + goe;
-                p16[x] = (int16_t)v;
+                p16[x] = (int16_t)(tt < R ? staged_score(tmp, a.alpha, l * R + tt, r, goe, kPadProf16) : kPadProf16);
             }
         }
         __syncthreads();
@@ -187,7 +191,7 @@ sw_stream16_kernel(StreamArgs a) {
         const int myrow = row0 + ll * R;
         const int2 *bin = (pass > 0 && actA) ? a.bound + a.sbbase[sA] + (int64_t)(pass - 1) * C : nullptr;
         int2 *bout = (pass + 1 < a.passes && actA) ? a.bound + a.sbbase[sA] + (int64_t)pass * C : nullptr;
-        uint32_t *cw = actA ? a.codes + a.scbase[sA] + (int64_t)pass * G * LS * 8 * WQ + ll * 8 * WQ : nullptr;
+        uint32_t *cw = TB && actA ? a.codes + a.scbase[sA] + (int64_t)pass * G * LS * 8 * WQ + ll * 8 * WQ : nullptr;
         auto run = [&](auto hb_tag) __attribute__((always_inline)) {
             constexpr bool HB = decltype(hb_tag)::value;
             // boundary rows of the previous pass (Hg, F*) of the stream columns
@@ -327,14 +331,16 @@ sw_stream16_kernel(StreamArgs a) {
                     const pk16 fn = max3h(fext, upg, bias2);     // F* = max(F, 0)
                     const pk16 hd = diag + p;
                     const pk16 h = max3h(hd, en, fn);
-                    // bytes (notd A, notd B, eext A, eext B) and (note A, note B, fext A, fext B)
-                    const uint32_t f0 = __builtin_amdgcn_perm(as_u(hg[t] - eext), as_u(hd - h), 0x0b0a0908u);
-                    const uint32_t f1 = __builtin_amdgcn_perm(as_u(upg - fext), as_u(en - h), 0x0b0a0908u);
-                    const uint32_t m0 = 0x01010101u << (2 * (t & 3)), m1 = m0 << 1;
-                    uint32_t wd = word[t >> 2];
-                    wd = bfi_s(m0, f0, wd);
-                    wd = bfi_s(m1, f1, wd);
-                    word[t >> 2] = wd;
+                    if constexpr (TB) {
+                        // bytes (notd A, notd B, eext A, eext B) and (note A, note B, fext A, fext B)
+                        const uint32_t f0 = __builtin_amdgcn_perm(as_u(hg[t] - eext), as_u(hd - h), 0x0b0a0908u);
+                        const uint32_t f1 = __builtin_amdgcn_perm(as_u(upg - fext), as_u(en - h), 0x0b0a0908u);
+                        const uint32_t m0 = 0x01010101u << (2 * (t & 3)), m1 = m0 << 1;
+                        uint32_t wd = word[t >> 2];
+                        wd = bfi_s(m0, f0, wd);
+                        wd = bfi_s(m1, f1, wd);
+                        word[t >> 2] = wd;
+                    }
                     if constexpr (SNAP) {
                         if (t & 1) sm = max3h(sm, hprev, h);
                         else if (t == R - 1) sm = pmax(sm, h);
@@ -362,9 +368,11 @@ sw_stream16_kernel(StreamArgs a) {
                 }
                 botg = as_u(upg);
                 botf = as_u(upf);
+                if constexpr (TB) {
 #pragma unroll
-                for (int w = 0; w < WQ; ++w) stage[64 * ((u & 3) * WQ + w)] = word[w];
-                if ((u & 3) == 3 && cw && k8 < steps_s) {
+                    for (int w = 0; w < WQ; ++w) stage[64 * ((u & 3) * WQ + w)] = word[w];
+                }
+                if (TB && (u & 3) == 3 && cw && k8 < steps_s) {
                     // half a tile (4 steps, 16*WQ bytes of the lane's 32*WQ)
                     uint4 *dst = reinterpret_cast<uint4 *>(cw + (int64_t)(k8 >> 3) * LS * 8 * WQ) + (u >> 2) * WQ;
 #pragma unroll

@@ -144,6 +144,24 @@ __device__ __forceinline__ unsigned long long cell_key(const BestCell &b, bool e
     return k;
 }
 
+// The substitution matrix and the center codes of `span` rows from row0 (255
+// beyond m) in LDS at tmp (kProfTmp bytes; the caller puts barriers around the
+// use).  Building a profile straight from global memory waits for two
+// dependent loads per entry: about 25 us per pass for 512 threads on a 64-lane
+// profile, most of a small batch's forward.
+constexpr int kProfTmp = 2048;
+__device__ __forceinline__ void stage_center(uint8_t *tmp, const StreamArgs &a, int row0, int span, int tid,
+                                             int nthreads) {
+    for (int x = tid; x < a.alpha * a.alpha; x += nthreads) tmp[x] = (uint8_t)a.mat[x];
+    for (int x = tid; x < span; x += nthreads)
+        tmp[kAlphaMax * kAlphaMax + x] = row0 + x < a.m ? (uint8_t)(a.center[row0 + x] & 31) : (uint8_t)255;
+}
+// s(center row x of the staged span, r) + goe, or pad beyond the center
+__device__ __forceinline__ int staged_score(const uint8_t *tmp, int alpha, int x, int r, int goe, int pad) {
+    const int c = tmp[kAlphaMax * kAlphaMax + x];
+    return c == 255 || r >= alpha ? pad : (int)(int8_t)tmp[c * alpha + r] + goe;
+}
+
 // The step loop is unrolled by 8: a lane's 8 steps of code words are staged
 // in LDS and go out as one 32*W-byte tile, and the loop runs over whole tiles
 // (steps rounded up to a multiple of 8, to the longest stream of the
@@ -162,7 +180,7 @@ sw_stream_kernel(StreamArgs a) {
     constexpr int W = (R + 7) / 8;           // code words per step
     constexpr int NS = 64 / LS;              // streams per wavefront
     constexpr int SPAN = LS * R;             // rows per pass
-    extern __shared__ int prof[];   // profile, then code staging [8 waves][8 steps][W][64 lanes]
+    extern __shared__ int prof[];   // profile, then code staging [waves][8 steps][W][64 lanes]
     const int nprow = P16 ? a.alpha + 1 : kAlphaMax;
     const int prof_words = P16 ? nprow * LS * 4 * W : kAlphaMax * SPAN;
     uint32_t *stage = reinterpret_cast<uint32_t *>(prof + prof_words) + (threadIdx.x >> 6) * 512 * W +
@@ -195,14 +213,15 @@ sw_stream_kernel(StreamArgs a) {
         const int row0 = pass * SPAN;
         __syncthreads();
         if (P16) {
+            // the matrix and the center codes wait where code words are staged later
+            uint8_t *tmp = reinterpret_cast<uint8_t *>(prof + prof_words);
+            stage_center(tmp, a, row0, SPAN, tid, nthreads);
+            __syncthreads();
             int16_t *p16 = reinterpret_cast<int16_t *>(prof);
             constexpr int PER = 8 * W;               // halves per (residue, lane)
             for (int x = tid; x < nprow * LS * PER; x += nthreads) {
                 const int r = x / (LS * PER), l = (x / PER) & (LS - 1), tt = x % PER;
-                const int i = row0 + l * R + tt;
-                int v = -32768;
-                if (r < a.alpha && tt < R && i < a.m) v = (int)a.mat[(a.center[i] & 31) * a.alpha + r] + goe;
-                p16[x] = (int16_t)v;
+                p16[x] = (int16_t)(tt < R ? staged_score(tmp, a.alpha, l * R + tt, r, goe, -32768) : -32768);
             }
         } else {
             for (int x = tid; x < kAlphaMax * SPAN; x += nthreads) {

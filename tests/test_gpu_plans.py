@@ -1,0 +1,97 @@
+"""Plans that the library chooses by itself against the one-pair-per-lane
+kernel: the same pairs give the same scores, end cells, insertion counts and
+aligned bits on every plan (integers, compared exactly; the one-pair-per-lane
+kernel is compared with the oracle elsewhere)."""
+import numpy as np
+import pytest
+
+from paper_1704_00878_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def H():
+    import paper_1704_00878_amd as H
+    H.lib()
+    return H
+
+
+@pytest.fixture(scope="module")
+def ctx(H):
+    c = H.Context(0)
+    yield c
+    c.close()
+
+
+def _same(H, ctx, sc, ds, center, tb):
+    import torch
+    got = H.sw_batch(ctx, sc, ds, 0, traceback=tb, center_seq=center)
+    torch.cuda.synchronize()
+    plan, route = ctx.last_plan(), ctx.last_stats()["route"]
+    want = H.sw_batch(ctx, sc, ds, 0, traceback=tb, center_seq=center, route=H.HALIGN_ROUTE_INTER)
+    torch.cuda.synchronize()
+    assert ctx.last_stats()["route"] == 1
+    for k in ("score", "cells", "ins", "aligned"):
+        if got[k] is not None:
+            assert torch.equal(got[k], want[k]), k
+    return plan, route
+
+
+def _center(rng, m):
+    import torch
+    return torch.from_numpy(rng.integers(0, 20, m).astype(np.uint8)).cuda()
+
+
+# rows per lane at both ends of the packed kernel's range (2 and 16), around
+# its change of end-cell tracking (11, 12), one and two passes; few pairs (one
+# per stream, most streams idle) and several per stream; empty sequences
+@pytest.mark.parametrize("lanes", [16, 32])
+@pytest.mark.parametrize("rows", [2, 11, 12, 16, 17])
+@pytest.mark.parametrize("n,streams", [(3, 0), (700, 0), (700, 37)])
+def test_packed_score_only(H, ctx, lanes, rows, n, streams, monkeypatch):
+    monkeypatch.setenv("HALIGN_STREAM_LANES", str(lanes))
+    monkeypatch.setenv("HALIGN_STREAM_PACK", "1")
+    if streams:
+        monkeypatch.setenv("HALIGN_MAX_STREAMS", str(streams))
+    rng = np.random.default_rng(rows * 100 + n)
+    seqs = [rng.integers(0, 20, int(L)).astype(np.uint8) for L in rng.integers(1, 90, n)]
+    seqs[n // 2] = np.zeros(0, np.uint8)
+    seqs[0] = rng.integers(17, 18, 300).astype(np.uint8)
+    center = _center(rng, lanes * rows - 3)
+    center[5:40] = 17
+    ds = H.DeviceSeqs(synth.SeqSet.from_list(seqs))
+    for tb in (False, True):
+        plan, route = _same(H, ctx, H.Scoring(), ds, center, tb)
+        assert plan["packed"] == 1 and route == 0
+
+
+# batches on both sides of what fills the chip with 64-lane, 32-lane and
+# 16-lane streams, and with one center pass and several
+@pytest.mark.parametrize("n,lo,hi,m", [(1, 30, 30, 700), (40, 50, 200, 33), (900, 100, 300, 520), (3000, 20, 400, 90),
+                                       (9000, 100, 200, 250), (30000, 10, 120, 61)])
+def test_default_plan(H, ctx, n, lo, hi, m):
+    rng = np.random.default_rng(n)
+    ds = H.DeviceSeqs(synth.random_set(rng, n, lo, hi))
+    for tb in (False, True):
+        _same(H, ctx, H.Scoring(), ds, _center(rng, m), tb)
+
+
+# 262,144 pairs and more: streams where scores fit, one pair per lane where
+# they do not (a matrix entry of 127 on 300 residues)
+@pytest.mark.parametrize("tall", [False, True])
+def test_default_plan_many_pairs(H, ctx, tall):
+    rng = np.random.default_rng(3)
+    seqs = synth.random_set(rng, 262144, 0, 24)
+    if tall:
+        seqs = synth.SeqSet(np.concatenate([seqs.residues, np.full(300, 17, np.uint8)]),
+                            np.append(seqs.offsets, len(seqs.residues) + 300))
+    mat = synth.BLOSUM62.copy()
+    if tall:
+        mat[17, 17] = 127
+    center = _center(rng, 300 if tall else 20)
+    if tall:
+        center[:] = 17
+    for tb in (False, True):
+        plan, route = _same(H, ctx, H.Scoring(mat), H.DeviceSeqs(seqs), center, tb)
+        assert route == (1 if tall else 0) and plan["packed"] == (0 if tall else 1)
