@@ -120,6 +120,9 @@ struct halign_ctx {
     int64_t *mail_host = nullptr, *mail_dev = nullptr;   // coherent pinned mailbox: width, sequence number
     DevBuf nuctab, nucscr, nucdp;   // nucleotide path: segment table, matches and chains, stretch scratch
     DevBuf rowck;                   // chunked rows: residues before each chunk of blocks, per row
+    HostBuf njhost, njout;          // pinned: the tree's distances and the trees coming back
+    DevBuf njF;                     // all rows' distances (sets where they are computed at once)
+    hipEvent_t ev_nj = nullptr;     // the distances are in place (for aux_stream)
     DevBuf njrows, njD, njS, njacc, njB; // phylogeny: row lists and group tables, distance matrices, join scratch, slice counts, chip-wide join scratch
     int64_t mail_seq = 0;
     uint32_t vtag = 0;        // tag of the last eager code check
@@ -178,6 +181,18 @@ int grow(halign_ctx *ctx, DevBuf &b, size_t bytes) {
     }
     b.cap = want;
     (void)ctx;
+    return HALIGN_OK;
+}
+
+// Pinned host memory kept between calls (nothing may be in flight to it).
+int grow_host(HostBuf &b, size_t bytes) {
+    if (bytes <= b.cap) return HALIGN_OK;
+    if (b.p) HCHK(hipHostFree(b.p));
+    b.p = nullptr;
+    b.cap = 0;
+    const size_t want = (bytes + bytes / 2 + 65535) & ~size_t(65535);
+    HCHK(hipHostMalloc(&b.p, want, hipHostMallocDefault));
+    b.cap = want;
     return HALIGN_OK;
 }
 
@@ -1275,11 +1290,13 @@ void halign_ctx_destroy(halign_ctx *ctx) {
     if (ctx->aux_stream) (void)hipStreamDestroy(ctx->aux_stream);
     for (DevBuf *b : {&ctx->codes, &ctx->bound, &ctx->plan, &ctx->counter, &ctx->pairbuf, &ctx->msabuf, &ctx->spbuf,
                       &ctx->sbuf, &ctx->nuctab, &ctx->nucscr, &ctx->nucdp, &ctx->rowck,
-                      &ctx->njrows, &ctx->njD, &ctx->njS, &ctx->njacc, &ctx->njB})
+                      &ctx->njrows, &ctx->njD, &ctx->njS, &ctx->njacc, &ctx->njB, &ctx->njF})
         if (b->p) (void)hipFree(b->p);
     for (DevBuf &b : ctx->mlp)
         if (b.p) (void)hipFree(b.p);
-    if (ctx->stage.p) (void)hipHostFree(ctx->stage.p);
+    for (HostBuf *b : {&ctx->stage, &ctx->njhost, &ctx->njout})
+        if (b->p) (void)hipHostFree(b->p);
+    if (ctx->ev_nj) (void)hipEventDestroy(ctx->ev_nj);
     if (ctx->flag_host) (void)hipHostFree(ctx->flag_host);
     if (ctx->mail_host) (void)hipHostFree(ctx->mail_host);
     for (auto &t : ctx->tev)
@@ -3039,41 +3056,29 @@ namespace {
 
 inline size_t al256z(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// The distance launch: whole width per tile, or, when the tiles are too few
-// to fill the chip several times over (under 8,192) and the MSA is wide,
-// column slices (256 or 1,024 columns and up) added atomically into zeroed
-// counts and a finalize pass.  nout:
-// outputs the groups address (for the counts).
-int pdist_launch(halign_ctx *ctx, hk::PdArgs a, int64_t tiles, int64_t nout, hipStream_t st) {
-    int64_t nslice = 1;
-    // few tiles: slices of 256 columns, about 256 workgroups in all (each
-    // slice's atomics cost more than a further slice hides); more tiles:
-    // slices of 1,024 columns up to 8,192 workgroups
-    if (tiles < 64 && a.width > 512)
-        nslice = std::min<int64_t>((a.width + 255) / 256, (256 + tiles - 1) / tiles);
-    else if (tiles < 8192 && a.width > 2048)
-        nslice = std::min<int64_t>((a.width + 1023) / 1024, (8192 + tiles - 1) / tiles);
-    a.nslice = 1;
-    a.cslice = a.width;
+// The distance launch: whole width per tile, or, when the tiles are too few to
+// fill the chip, column slices and a pass that adds them.
+int pdist_launch(halign_ctx *ctx, hk::PdArgs a, int64_t tiles, hipStream_t st) {
+    // up to 2,048 workgroups (eight per CU, what its registers hold) in slices
+    // of at least 256 columns: 3,001 x 4,030 rows 0.62 ms (0.68 unsliced, 0.68
+    // up to 1,024 workgroups), 672 x 18,611 0.20 (1.07, 0.23), 64 x 18,000 0.05
+    // (0.85, 0.05)
+    int64_t nslice = tiles < 2048 ? std::min<int64_t>((a.width + 255) / 256, (2047 + tiles) / tiles) : 1;
+    nslice = std::max<int64_t>(1, nslice);
+    a.cslice = std::max<int64_t>(1, ((a.width + nslice - 1) / nslice + hk::kPdChunk - 1) / hk::kPdChunk) * hk::kPdChunk;
+    nslice = std::max<int64_t>(1, (a.width + a.cslice - 1) / a.cslice);
+    a.nslice = (int)nslice;
     a.acc = nullptr;
-    a.mode = 0;
     if (nslice > 1) {
-        a.nslice = (int)nslice;
-        a.cslice = (((a.width + nslice - 1) / nslice) + hk::kPdChunk - 1) / hk::kPdChunk * hk::kPdChunk;
-        RCHK(grow(ctx, ctx->njacc, 8 * (size_t)nout));
-        a.acc = (int32_t *)ctx->njacc.p;
-        RCHK(launch_fill((uint32_t *)a.acc, 0u, 2 * nout, st));
-        a.mode = 1;
-        // under four workgroups per CU the next pass's loads go out early
-        if (tiles * nslice < 1024)
-            hipLaunchKernelGGL(hk::pdist_kernel<true>, dim3((unsigned)(tiles * nslice)), dim3(256), 0, st, a);
-        else
-            hipLaunchKernelGGL(hk::pdist_kernel<false>, dim3((unsigned)(tiles * nslice)), dim3(256), 0, st, a);
-        HCHK(hipGetLastError());
-        a.mode = 2;
+        RCHK(grow(ctx, ctx->njacc, (size_t)(tiles * nslice) * 16 * 256 * sizeof(int2)));
+        a.acc = (int2 *)ctx->njacc.p;
     }
-    hipLaunchKernelGGL(hk::pdist_kernel<false>, dim3((unsigned)tiles), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(hk::pdist_kernel, dim3((unsigned)(tiles * nslice)), dim3(256), 0, st, a);
     HCHK(hipGetLastError());
+    if (nslice > 1) {
+        hipLaunchKernelGGL(hk::pd_final_kernel, dim3((unsigned)(tiles * 16)), dim3(256), 0, st, a);
+        HCHK(hipGetLastError());
+    }
     return HALIGN_OK;
 }
 
@@ -3085,7 +3090,7 @@ int pdist_groups(halign_ctx *ctx, const uint8_t *msa, int64_t width, const std::
     for (auto &g : groups) {
         g.tiles_b = (g.nb + hk::kPdTile - 1) / hk::kPdTile;
         g.tile0 = tiles;
-        tiles += (int64_t)((g.na + hk::kPdTile - 1) / hk::kPdTile) * g.tiles_b;
+        tiles += hk::pd_tiles(g);
     }
     if (tiles == 0) return HALIGN_OK;
     if (tiles > 0x7fffffff) return fail(HALIGN_E_UNSUPPORTED, "%lld distance tiles", (long long)tiles);
@@ -3094,11 +3099,11 @@ int pdist_groups(halign_ctx *ctx, const uint8_t *msa, int64_t width, const std::
     char *b = (char *)ctx->njrows.p;
     if (!rows.empty()) HCHK(hipMemcpyAsync(b, rows.data(), 4 * rows.size(), hipMemcpyHostToDevice, st));
     HCHK(hipMemcpyAsync(b + o_g, groups.data(), sizeof(hk::PdGroup) * groups.size(), hipMemcpyHostToDevice, st));
-    int64_t nout = 0;
-    for (auto &g : groups)
-        if (g.na > 0 && g.nb > 0) nout = std::max<int64_t>(nout, g.o + (int64_t)(g.na - 1) * g.ld + g.nb);
-    hk::PdArgs a{msa, width, (const int32_t *)b, (const hk::PdGroup *)(b + o_g), (int)groups.size(), D, mism, comp};
-    RCHK(pdist_launch(ctx, a, tiles, nout, st));
+    hk::PdArgs a{};
+    a.msa = msa; a.width = width; a.rows_a = a.rows_b = (const int32_t *)b;
+    a.groups = (const hk::PdGroup *)(b + o_g); a.ngroups = (int)groups.size();
+    a.D = D; a.mism = mism; a.comp = comp;
+    RCHK(pdist_launch(ctx, a, tiles, st));
     HCHK(hipStreamSynchronize(st));
     return HALIGN_OK;
 }
@@ -3146,14 +3151,15 @@ int nj_groups_launch(halign_ctx *ctx, std::vector<hk::NjGroup> &groups, double *
 
 int nj_groups_finish(halign_ctx *ctx, const NjLaunch &L, std::vector<int32_t> &parent, std::vector<double> &blen,
                      std::vector<int32_t> &nodes, hipStream_t st) {
-    char *b = (char *)ctx->njS.p;
-    parent.resize(L.nt);
-    blen.resize(L.nt);
-    nodes.resize(L.G);
-    HCHK(hipMemcpyAsync(parent.data(), b + L.o_p, 4 * L.nt, hipMemcpyDeviceToHost, st));
-    HCHK(hipMemcpyAsync(blen.data(), b + L.o_b, 8 * L.nt, hipMemcpyDeviceToHost, st));
-    HCHK(hipMemcpyAsync(nodes.data(), b + L.o_nd, 4 * L.G, hipMemcpyDeviceToHost, st));
+    // parents, lengths and node counts lie together: one copy
+    const size_t bytes = L.o_nd + 4 * L.G - L.o_p;
+    RCHK(grow_host(ctx->njout, bytes));
+    const char *h = (const char *)ctx->njout.p;
+    HCHK(hipMemcpyAsync(ctx->njout.p, (const char *)ctx->njS.p + L.o_p, bytes, hipMemcpyDeviceToHost, st));
     HCHK(hipStreamSynchronize(st));
+    parent.assign((const int32_t *)h, (const int32_t *)h + L.nt);
+    blen.assign((const double *)(h + L.o_b - L.o_p), (const double *)(h + L.o_b - L.o_p) + L.nt);
+    nodes.assign((const int32_t *)(h + L.o_nd - L.o_p), (const int32_t *)(h + L.o_nd - L.o_p) + L.G);
     return HALIGN_OK;
 }
 
@@ -3164,9 +3170,20 @@ int nj_groups(halign_ctx *ctx, std::vector<hk::NjGroup> &groups, double *dbase, 
     return nj_groups_finish(ctx, L, parent, blen, nodes, st);
 }
 
-// Problems above this many nodes are joined over the whole chip (three
-// launches per join); smaller ones one workgroup each, all in one launch.
+// Problems above this many nodes are joined over the whole chip; smaller ones
+// of a tree one workgroup each, all in one launch.
 constexpr int kNjBigMin = 256;
+// Problems from this many nodes that are joined alone (halign_nj, the seeds of a
+// tree) go to the mesh too: 10 nodes 135 us against 161 on one workgroup, 64
+// 385 against 840, 256 1,520 against 3,740 (whole calls).
+constexpr int kNjMeshMin = 8;
+
+// Whether a problem of n nodes fits the mesh of workgroups that hold 16 rows each in LDS.
+bool nj_mesh_ok(const halign_ctx *ctx, int n) {
+    const char *env = getenv("HALIGN_NJ_MESH");   // test knob: 0 = the other kernels
+    return n <= hk::kNjMeshMax && (n + hk::kNjMeshRows - 1) / hk::kNjMeshRows <= ctx->num_cu &&
+           hk::nj_mesh_lds(n) + 1024 <= ctx->lds_max && !(env && atoi(env) == 0);
+}
 
 // Neighbour joining of one problem over the chip: D (device, n x n, modified);
 // the tree to the host (2n + 1 entries).
@@ -3175,14 +3192,45 @@ int nj_big(halign_ctx *ctx, double *D, int n, std::vector<int32_t> &parent, std:
     const int64_t nn = (int64_t)n * n;
     const int nparts = (int)std::max<int64_t>(1, std::min<int64_t>(2048, (nn + 255) / 256));
     const size_t nt = 2 * (size_t)n + 1;
+    const int G = (n + hk::kNjMeshRows - 1) / hk::kNjMeshRows;
+    const bool mesh = nj_mesh_ok(ctx, n);
+    // (parents, lengths and the node count lie together: they come back in one copy)
     const size_t o_r = 0, o_id = al256z(8 * (size_t)n), o_p = o_id + al256z(4 * (size_t)n), o_b = o_p + al256z(4 * nt),
-                 o_part = o_b + al256z(8 * nt), o_pd = o_part + al256z(sizeof(hk::NjBest) * nparts),
-                 o_ctrl = o_pd + al256z(8 * (size_t)nparts),
-                 o_nodes = o_ctrl + 256, o_act = o_nodes + 256, bytes = o_act + al256z(n);
+                 o_nodes = o_b + al256z(8 * nt), o_fail = o_nodes + 64, o_part = o_nodes + 256,
+                 o_pd = o_part + al256z(sizeof(hk::NjBest) * nparts), o_ctrl = o_pd + al256z(8 * (size_t)nparts),
+                 o_act = o_ctrl + 256, o_mesh = o_act + al256z(n),
+                 o_M = o_mesh + (mesh ? al256z(8 * (3 * (size_t)n + 9 * (size_t)G)) : 0),
+                 bytes = o_M + (mesh ? al256z(8 * (size_t)nn) : 0);
     RCHK(grow(ctx, ctx->njB, bytes));
+    RCHK(grow_host(ctx->njout, o_nodes + 4 - o_p));
     char *b = (char *)ctx->njB.p;
     hk::NjBigArgs a{n, D, (double *)(b + o_r), (uint8_t *)(b + o_act), (int32_t *)(b + o_id), (int32_t *)(b + o_p),
                     (double *)(b + o_b), (hk::NjBest *)(b + o_part), (double *)(b + o_pd), nparts, (hk::NjCtrl *)(b + o_ctrl)};
+    int32_t nd = 0;
+    auto finish = [&](double *M, const uint32_t *failed) -> int {
+        hk::NjBigArgs f = a;
+        f.D = M;
+        hipLaunchKernelGGL(hk::nj_big_finish_kernel, dim3(1), dim3(1), 0, st, f, failed, (int32_t *)(b + o_nodes));
+        HCHK(hipGetLastError());
+        const char *h = (const char *)ctx->njout.p;
+        HCHK(hipMemcpyAsync(ctx->njout.p, b + o_p, o_nodes + 4 - o_p, hipMemcpyDeviceToHost, st));
+        HCHK(hipStreamSynchronize(st));
+        parent.assign((const int32_t *)h, (const int32_t *)h + nt);
+        blen.assign((const double *)(h + o_b - o_p), (const double *)(h + o_b - o_p) + nt);
+        memcpy(&nd, h + o_nodes - o_p, 4);
+        *nodes = nd;
+        return HALIGN_OK;
+    };
+    if (mesh) {
+        hk::NjMeshArgs g{n, G, D, (double *)(b + o_M), (uint64_t *)(b + o_mesh), (uint64_t *)(b + o_mesh) + 3 * (size_t)n,
+                         (uint32_t *)(b + o_fail), a};
+        RCHK(launch_fill((uint32_t *)(b + o_mesh), 0xffffffffu, 2 * (3 * (int64_t)n + 9 * (int64_t)G), st));
+        RCHK(launch_fill(g.failed, 0u, 1, st));
+        hipLaunchKernelGGL(hk::nj_mesh_kernel, dim3((unsigned)G), dim3(256), hk::nj_mesh_lds(n), st, g);
+        HCHK(hipGetLastError());
+        RCHK(finish(g.M, g.failed));
+        if (nd >= 0) return HALIGN_OK;
+    }
     const unsigned rg = (unsigned)((n + 255) / 256);
     hipLaunchKernelGGL(hk::nj_big_init_kernel, dim3(rg), dim3(256), 0, st, a);
     HCHK(hipGetLastError());
@@ -3193,17 +3241,7 @@ int nj_big(halign_ctx *ctx, double *D, int n, std::vector<int32_t> &parent, std:
         hipLaunchKernelGGL(hk::nj_big_join_kernel, dim3(1), dim3(256), 0, st, a);
     }
     HCHK(hipGetLastError());
-    hipLaunchKernelGGL(hk::nj_big_finish_kernel, dim3(1), dim3(1), 0, st, a, (int32_t *)(b + o_nodes));
-    HCHK(hipGetLastError());
-    parent.resize(nt);
-    blen.resize(nt);
-    int32_t nd = 0;
-    HCHK(hipMemcpyAsync(parent.data(), b + o_p, 4 * nt, hipMemcpyDeviceToHost, st));
-    HCHK(hipMemcpyAsync(blen.data(), b + o_b, 8 * nt, hipMemcpyDeviceToHost, st));
-    HCHK(hipMemcpyAsync(&nd, b + o_nodes, 4, hipMemcpyDeviceToHost, st));
-    HCHK(hipStreamSynchronize(st));
-    *nodes = nd;
-    return HALIGN_OK;
+    return finish(D, nullptr);
 }
 
 // labels[i] = nearest of the nb columns of D (na x nb, device), to the host
@@ -3260,39 +3298,15 @@ int halign_pdist(halign_ctx *ctx, const uint8_t *msa, int32_t n, int64_t width, 
     HCHK(hipSetDevice(ctx->device));
     hipStream_t st = (hipStream_t)stream;
     if ((int64_t)na * nb == 0) return HALIGN_OK;
-    // the row lists: given ones copied into the ctx buffer behind an identity prefix
-    std::vector<int32_t> rows;
-    if (!a_rows || !b_rows) {
-        rows.resize(std::max(a_rows ? 0 : na, b_rows ? 0 : nb));
-        for (size_t x = 0; x < rows.size(); ++x) rows[x] = (int32_t)x;
-    }
-    const int64_t ida = (int64_t)rows.size();
-    std::vector<hk::PdGroup> groups(1);
-    hk::PdGroup &g = groups[0];
-    g.a0 = a_rows ? ida : 0;
-    g.b0 = b_rows ? ida + (a_rows ? na : 0) : 0;
-    g.na = na;
-    g.nb = nb;
-    g.o = 0;
-    g.ld = nb;
-    g.diag0 = 0;
-    rows.resize(ida + (a_rows ? na : 0) + (b_rows ? nb : 0));   // placeholders, filled on the device below
-    // upload the identity part with the table, then the given lists device to device
-    int64_t tiles = (int64_t)((na + hk::kPdTile - 1) / hk::kPdTile) * ((nb + hk::kPdTile - 1) / hk::kPdTile);
-    if (tiles > 0x7fffffff) return fail(HALIGN_E_UNSUPPORTED, "%lld distance tiles", (long long)tiles);
-    g.tiles_b = (nb + hk::kPdTile - 1) / hk::kPdTile;
-    g.tile0 = 0;
-    const size_t o_g = al256z(4 * rows.size());
-    RCHK(grow(ctx, ctx->njrows, o_g + sizeof(hk::PdGroup)));
-    char *b = (char *)ctx->njrows.p;
-    if (ida > 0) HCHK(hipMemcpyAsync(b, rows.data(), 4 * (size_t)ida, hipMemcpyHostToDevice, st));
-    if (a_rows) HCHK(hipMemcpyAsync(b + 4 * g.a0, a_rows, 4 * (size_t)na, hipMemcpyDeviceToDevice, st));
-    if (b_rows) HCHK(hipMemcpyAsync(b + 4 * g.b0, b_rows, 4 * (size_t)nb, hipMemcpyDeviceToDevice, st));
-    HCHK(hipMemcpyAsync(b + o_g, groups.data(), sizeof(hk::PdGroup), hipMemcpyHostToDevice, st));
-    hk::PdArgs a{msa, width, (const int32_t *)b, (const hk::PdGroup *)(b + o_g), 1, D, mism, comp};
-    RCHK(pdist_launch(ctx, a, tiles, (int64_t)na * nb, st));
-    HCHK(hipStreamSynchronize(st));   // the host vectors above were copied from
-    return HALIGN_OK;
+    hk::PdArgs a{};
+    a.msa = msa; a.width = width; a.rows_a = a_rows; a.rows_b = b_rows;
+    a.D = D; a.mism = mism; a.comp = comp;
+    a.g.na = na; a.g.nb = nb; a.g.ld = nb;
+    a.g.tiles_b = (nb + hk::kPdTile - 1) / hk::kPdTile;
+    a.g.sym = a_rows == b_rows && na == nb;   // the same rows on both sides: one triangle is computed
+    if ((int64_t)((na + hk::kPdTile - 1) / hk::kPdTile) * a.g.tiles_b > 0x7fffffff)
+        return fail(HALIGN_E_UNSUPPORTED, "distance tiles");
+    return pdist_launch(ctx, a, hk::pd_tiles(a.g), st);
 }
 
 int halign_nj(halign_ctx *ctx, const double *D, int32_t n, int32_t *parent_host, double *blen_host, int32_t *nodes,
@@ -3305,7 +3319,7 @@ int halign_nj(halign_ctx *ctx, const double *D, int32_t n, int32_t *parent_host,
     HCHK(hipMemcpyAsync(ctx->njD.p, D, bytes, hipMemcpyDeviceToDevice, st));
     std::vector<int32_t> parent, nd;
     std::vector<double> blen;
-    if (n > kNjBigMin) {
+    if (n > kNjBigMin || (n >= kNjMeshMin && nj_mesh_ok(ctx, n))) {
         int nn = 0;
         RCHK(nj_big(ctx, (double *)ctx->njD.p, n, parent, blen, &nn, st));
         nd.assign(1, nn);
@@ -3337,14 +3351,49 @@ int halign_nj_tree(halign_ctx *ctx, const uint8_t *msa, int32_t n, int64_t width
     hipStream_t st = (hipStream_t)stream;
     const int N = n, S = (N + 9) / 10;
     std::vector<int32_t> seed(perm_host, perm_host + S);
+    // Where all rows' distances are cheap (up to 2e10 pair-columns in one
+    // triangle, about 0.5 ms, and 2,048 rows, 32 MB), they are computed at once
+    // and copied to the host, which labels and divides from them: a divide pass
+    // costs a distance launch, a nearest launch and two waits otherwise, about
+    // 0.2 ms, and there are up to 20.  The values are the same either way.
+    const char *env_full = getenv("HALIGN_NJ_FULL");   // test knob: 0 = per step
+    const bool full =
+        N <= 2048 && 0.5 * (double)N * N * (double)width <= 2e10 && !(env_full && atoi(env_full) == 0);
+    const double *F = nullptr;
+    // the first of `nb` rows b with the smallest distance to row x
+    auto nearest = [&](int x, const int32_t *rb, int nb) {
+        const double *f = F + (size_t)x * N;
+        int best = 0;
+        double bd = f[rb[0]];
+        for (int e = 1; e < nb; ++e)
+            if (f[rb[e]] < bd) {
+                bd = f[rb[e]];
+                best = e;
+            }
+        return best;
+    };
     // every row against the sample: nearest seed
     std::vector<int32_t> label;
-    {
+    if (full) {
+        const size_t bytes = 8 * (size_t)N * N;
+        RCHK(grow(ctx, ctx->njF, bytes));
+        RCHK(grow_host(ctx->njhost, bytes));
+        hk::PdArgs a{};
+        a.msa = msa; a.width = width; a.D = (double *)ctx->njF.p;
+        a.g.na = a.g.nb = N; a.g.ld = N; a.g.sym = 1;
+        a.g.tiles_b = (N + hk::kPdTile - 1) / hk::kPdTile;
+        RCHK(pdist_launch(ctx, a, hk::pd_tiles(a.g), st));
+        HCHK(hipMemcpyAsync(ctx->njhost.p, ctx->njF.p, bytes, hipMemcpyDeviceToHost, st));
+        HCHK(hipStreamSynchronize(st));
+        F = (const double *)ctx->njhost.p;
+        label.resize(N);
+        for (int x = 0; x < N; ++x) label[x] = nearest(x, seed.data(), S);
+    } else {
         std::vector<int32_t> rows(N + S);
         for (int x = 0; x < N; ++x) rows[x] = x;
         for (int c = 0; c < S; ++c) rows[N + c] = seed[c];
         std::vector<hk::PdGroup> gr(1);
-        gr[0] = hk::PdGroup{0, N, N, S, 0, S, 0, 0, 0};
+        gr[0] = hk::PdGroup{0, N, N, S, 0, S, 0, 0, 0, 0};
         RCHK(grow(ctx, ctx->njD, 8 * (size_t)N * S));
         RCHK(pdist_groups(ctx, msa, width, rows, gr, (double *)ctx->njD.p, nullptr, nullptr, st));
         RCHK(nearest_host(ctx, (const double *)ctx->njD.p, N, S, label, st));
@@ -3357,18 +3406,22 @@ int halign_nj_tree(halign_ctx *ctx, const uint8_t *msa, int32_t n, int64_t width
     bool small = false;
     for (int c = 0; c < K; ++c) small = small || (size[c] > 0 && size[c] < 3);
     if (small && K > 1) {
-        std::vector<int32_t> rows(S);
-        for (int c = 0; c < S; ++c) rows[c] = seed[c];
-        std::vector<hk::PdGroup> gr(1);
-        gr[0] = hk::PdGroup{0, 0, S, S, 0, S, 0, 0, 0};
-        RCHK(grow(ctx, ctx->njD, 8 * (size_t)S * S));
-        RCHK(pdist_groups(ctx, msa, width, rows, gr, (double *)ctx->njD.p, nullptr, nullptr, st));
         std::vector<int> to(K);   // cluster a small one moved to (itself when kept)
         for (int c = 0; c < K; ++c) to[c] = c;
-        // the seeds' distances to the host in one copy
+        // the seeds' distances on the host
         std::vector<double> dss((size_t)S * S);
-        HCHK(hipMemcpyAsync(dss.data(), ctx->njD.p, 8 * (size_t)S * S, hipMemcpyDeviceToHost, st));
-        HCHK(hipStreamSynchronize(st));
+        if (full) {
+            for (int c = 0; c < S; ++c)
+                for (int e = 0; e < S; ++e) dss[(size_t)c * S + e] = F[(size_t)seed[c] * N + seed[e]];
+        } else {
+            std::vector<int32_t> rows(seed.begin(), seed.begin() + S);
+            std::vector<hk::PdGroup> gr(1);
+            gr[0] = hk::PdGroup{0, 0, S, S, 0, S, 0, 0, 0, 1};
+            RCHK(grow(ctx, ctx->njD, 8 * (size_t)S * S));
+            RCHK(pdist_groups(ctx, msa, width, rows, gr, (double *)ctx->njD.p, nullptr, nullptr, st));
+            HCHK(hipMemcpyAsync(dss.data(), ctx->njD.p, 8 * (size_t)S * S, hipMemcpyDeviceToHost, st));
+            HCHK(hipStreamSynchronize(st));
+        }
         for (int c = 0; c < K; ++c) {
             if (size[c] == 0 || size[c] >= 3) continue;
             const double *drow = dss.data() + (size_t)c * S;
@@ -3436,18 +3489,25 @@ int halign_nj_tree(halign_ctx *ctx, const uint8_t *msa, int32_t n, int64_t width
             rows.insert(rows.end(), mem[c].begin(), mem[c].end());
             rows.insert(rows.end(), nseed.begin() + base, nseed.end());
             const int nm = (int)mem[c].size();
-            gr.push_back(hk::PdGroup{r0, r0 + nm, nm, nsd, dtot, nsd, 0, 0, 0});
+            gr.push_back(hk::PdGroup{r0, r0 + nm, nm, nsd, dtot, nsd, 0, 0, 0, 0});
             gbase.push_back(base);
             dtot += (int64_t)nm * nsd;
         }
         for (int x = 0; x < N; ++x)   // rows of kept clusters: their seed's position
             if (kpos[label[x]] >= 0) nlab[x] = kpos[label[x]];
-        RCHK(grow(ctx, ctx->njD, 8 * (size_t)dtot));
-        RCHK(pdist_groups(ctx, msa, width, rows, gr, (double *)ctx->njD.p, nullptr, nullptr, st));
-        // the nearest new seed of every row of each divided cluster, on the GPU
-        // (one launch per cluster, one copy back)
+        // the nearest new seed of every row of each divided cluster
         std::vector<std::vector<int32_t>> glab(gr.size());
-        RCHK(nearest_groups(ctx, (const double *)ctx->njD.p, gr, glab, st));
+        if (full) {
+            for (size_t q = 0; q < gr.size(); ++q) {
+                glab[q].resize(gr[q].na);
+                for (int t = 0; t < gr[q].na; ++t)
+                    glab[q][t] = nearest(rows[gr[q].a0 + t], rows.data() + gr[q].b0, gr[q].nb);
+            }
+        } else {   // on the GPU (one launch per cluster, one copy back)
+            RCHK(grow(ctx, ctx->njD, 8 * (size_t)dtot));
+            RCHK(pdist_groups(ctx, msa, width, rows, gr, (double *)ctx->njD.p, nullptr, nullptr, st));
+            RCHK(nearest_groups(ctx, (const double *)ctx->njD.p, gr, glab, st));
+        }
         // nearest new seed per row (ties to the earlier), or runs in permutation order
         std::vector<int> remap(nseed.size(), -1);
         {
@@ -3530,83 +3590,115 @@ int halign_nj_tree(halign_ctx *ctx, const uint8_t *msa, int32_t n, int64_t width
     for (int c = 0; c <= K; ++c) {
         const int64_t r0 = c < K ? coff[c] : N;
         const int sz = c < K ? csize[c] : K;
-        gr[c] = hk::PdGroup{r0, r0, sz, sz, dtot, sz, 1, 0, 0};
+        gr[c] = hk::PdGroup{r0, r0, sz, sz, dtot, sz, 1, 0, 0, 1};
         ng[c].n = sz;
         ng[c].d0 = dtot;
         dtot += (int64_t)sz * sz;
     }
-    // clusters of at most 64 rows, consecutive in `rows`, share 64-row tiles:
-    // one square group over the span (its pairs across clusters are computed
-    // and not used), each cluster's block then copied to its own matrix; a
-    // distance depends on its two rows alone, so the values are the same
-    std::vector<hk::PdGroup> gp;
-    std::vector<hk::PdExtract> ext;
-    int64_t ttot = dtot;
-    for (int c = 0; c < K;) {
-        if (csize[c] > hk::kPdTile) {
-            gp.push_back(gr[c++]);
-            continue;
+    if (full) {   // every matrix out of the full one
+        const size_t nr = rows.size(), o_lx = al256z(4 * nr), o_ls = o_lx + al256z(4 * nr),
+                     bytes = o_ls + sizeof(hk::PdList) * (size_t)(K + 1);
+        RCHK(grow(ctx, ctx->njD, 8 * (size_t)dtot));
+        RCHK(grow(ctx, ctx->njrows, bytes));
+        RCHK(stage_begin(ctx));
+        char *hs = nullptr;
+        RCHK(stage_host(ctx, bytes, &hs));
+        memcpy(hs, rows.data(), 4 * nr);
+        int32_t *lx = (int32_t *)(hs + o_lx);
+        hk::PdList *ls = (hk::PdList *)(hs + o_ls);
+        for (int c = 0; c <= K; ++c) {
+            ls[c] = hk::PdList{gr[c].a0, ng[c].d0, ng[c].n};
+            for (int t = 0; t < ng[c].n; ++t) lx[gr[c].a0 + t] = c;
         }
-        const int first = c;
-        const int64_t R0 = coff[c];
-        int span = 0;
-        while (c < K && csize[c] <= hk::kPdTile && span + csize[c] <= hk::kPdTile) span += csize[c++];
-        if (c - first == 1) {
-            gp.push_back(gr[first]);
-            continue;
-        }
-        gp.push_back(hk::PdGroup{R0, R0, span, span, ttot, span, 1, 0, 0});
-        for (int q = first; q < c; ++q)
-            if (csize[q] > 0) {
-                const int64_t off = coff[q] - R0;
-                ext.push_back(hk::PdExtract{ttot + off * span + off, span, ng[q].d0, csize[q]});
-            }
-        ttot += (int64_t)span * span;
-    }
-    gp.push_back(gr[K]);
-    RCHK(grow(ctx, ctx->njD, 8 * (size_t)ttot));
-    RCHK(pdist_groups(ctx, msa, width, rows, gp, (double *)ctx->njD.p, nullptr, nullptr, st));
-    if (!ext.empty()) {
-        RCHK(grow(ctx, ctx->njrows, sizeof(hk::PdExtract) * ext.size()));
-        HCHK(hipMemcpyAsync(ctx->njrows.p, ext.data(), sizeof(hk::PdExtract) * ext.size(), hipMemcpyHostToDevice,
-                            st));
-        hipLaunchKernelGGL(hk::pd_extract_kernel, dim3((unsigned)ext.size()), dim3(256), 0, st,
-                           (double *)ctx->njD.p, (const hk::PdExtract *)ctx->njrows.p);
+        char *d = (char *)ctx->njrows.p;
+        HCHK(hipMemcpyAsync(d, hs, bytes, hipMemcpyHostToDevice, st));
+        RCHK(record(ctx, ctx->ev_stage, st));
+        ctx->stage_pending = true;
+        hipLaunchKernelGGL(hk::pd_gather_kernel, dim3((unsigned)nr), dim3(256), 0, st, (const double *)ctx->njF.p, N,
+                           (const int32_t *)d, (const int32_t *)(d + o_lx), (const hk::PdList *)(d + o_ls),
+                           (double *)ctx->njD.p);
         HCHK(hipGetLastError());
-        HCHK(hipStreamSynchronize(st));   // the small joins may run on another stream
+    } else {
+        // clusters of at most 64 rows, consecutive in `rows`, share 64-row tiles:
+        // one square group over the span (its pairs across clusters are computed
+        // and not used), each cluster's block then copied to its own matrix; a
+        // distance depends on its two rows alone, so the values are the same
+        std::vector<hk::PdGroup> gp;
+        std::vector<hk::PdExtract> ext;
+        int64_t ttot = dtot;
+        for (int c = 0; c < K;) {
+            if (csize[c] > hk::kPdTile) {
+                gp.push_back(gr[c++]);
+                continue;
+            }
+            const int first = c;
+            const int64_t R0 = coff[c];
+            int span = 0;
+            while (c < K && csize[c] <= hk::kPdTile && span + csize[c] <= hk::kPdTile) span += csize[c++];
+            if (c - first == 1) {
+                gp.push_back(gr[first]);
+                continue;
+            }
+            gp.push_back(hk::PdGroup{R0, R0, span, span, ttot, span, 1, 0, 0, 1});
+            for (int q = first; q < c; ++q)
+                if (csize[q] > 0) {
+                    const int64_t off = coff[q] - R0;
+                    ext.push_back(hk::PdExtract{ttot + off * span + off, span, ng[q].d0, csize[q]});
+                }
+            ttot += (int64_t)span * span;
+        }
+        gp.push_back(gr[K]);
+        RCHK(grow(ctx, ctx->njD, 8 * (size_t)ttot));
+        RCHK(pdist_groups(ctx, msa, width, rows, gp, (double *)ctx->njD.p, nullptr, nullptr, st));
+        if (!ext.empty()) {
+            RCHK(grow(ctx, ctx->njrows, sizeof(hk::PdExtract) * ext.size()));
+            HCHK(hipMemcpyAsync(ctx->njrows.p, ext.data(), sizeof(hk::PdExtract) * ext.size(), hipMemcpyHostToDevice,
+                                st));
+            hipLaunchKernelGGL(hk::pd_extract_kernel, dim3((unsigned)ext.size()), dim3(256), 0, st,
+                               (double *)ctx->njD.p, (const hk::PdExtract *)ctx->njrows.p);
+            HCHK(hipGetLastError());
+            HCHK(hipStreamSynchronize(st));   // the host vector was copied from
+        }
     }
     // the joins: small problems in one launch, large ones over the chip; tree
     // g at tp/tb offset ng[g].t0 (2n + 1 entries each), node count tn[g]
     std::vector<int32_t> tp, tn(K + 1);
     std::vector<double> tb;
     {
+        // joined by itself: large problems, and the seeds' where the mesh takes it
+        auto alone = [&](int c) {
+            return ng[c].n > kNjBigMin || (c == K && ng[c].n >= kNjMeshMin && nj_mesh_ok(ctx, ng[c].n));
+        };
         std::vector<hk::NjGroup> small;
         std::vector<int> sidx;
         int64_t nt = 0;
         for (int c = 0; c <= K; ++c) {
             ng[c].t0 = nt;
             nt += 2 * (int64_t)ng[c].n + 1;
-            if (ng[c].n <= kNjBigMin) {
+            if (!alone(c)) {
                 small.push_back(ng[c]);
                 sidx.push_back(c);
             }
         }
         tp.assign(nt, 0);
         tb.assign(nt, 0.0);
-        // the small problems on a second stream, beside the chip-wide joins
-        // (their matrices, scratch and trees are disjoint; the distances are
-        // complete, pdist_groups having synchronised st)
+        // the small problems on a second stream, beside the joins of the large
+        // (their matrices, scratch and trees are disjoint), once the distances
+        // are in place
         bool any_big = false;
-        for (int c = 0; c <= K; ++c) any_big = any_big || ng[c].n > kNjBigMin;
+        for (int c = 0; c <= K; ++c) any_big = any_big || alone(c);
         hipStream_t sst = st;
         if (any_big && !small.empty()) {
             if (!ctx->aux_stream) HCHK(hipStreamCreateWithFlags(&ctx->aux_stream, hipStreamNonBlocking));
+            if (!ctx->ev_nj) HCHK(hipEventCreateWithFlags(&ctx->ev_nj, hipEventDisableTiming));
             sst = ctx->aux_stream;
+            HCHK(hipEventRecord(ctx->ev_nj, st));
+            HCHK(hipStreamWaitEvent(sst, ctx->ev_nj, 0));
         }
         NjLaunch L;
         if (!small.empty()) RCHK(nj_groups_launch(ctx, small, (double *)ctx->njD.p, L, sst));
         for (int c = 0; c <= K; ++c) {
-            if (ng[c].n <= kNjBigMin) continue;
+            if (!alone(c)) continue;
             if (ctx->progress) fprintf(stderr, "halign_nj_tree: joining %d nodes over the chip\n", ng[c].n);
             std::vector<int32_t> bp;
             std::vector<double> bb;

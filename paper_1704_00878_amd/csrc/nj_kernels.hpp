@@ -29,24 +29,75 @@ struct PdGroup {
     int diag0;
     int tiles_b;      // ceil(nb / 64)
     int64_t tile0;    // first tile of this group (prefix over groups)
+    int sym;          // both sides are the same rows: tiles (ta <= tb) only, each written to both triangles
 };
+// tiles of a group with tiles_b set (ta rows of tiles when not sym)
+inline int64_t pd_tiles(const PdGroup &g) {
+    return g.sym ? (int64_t)g.tiles_b * (g.tiles_b + 1) / 2 : (int64_t)((g.na + kPdTile - 1) / kPdTile) * g.tiles_b;
+}
 
 struct PdArgs {
     const uint8_t *msa;
     int64_t width;
-    const int32_t *rows;
-    const PdGroup *groups;
+    const int32_t *rows_a, *rows_b;   // row lists that a0 and b0 index (null: the index itself)
+    const PdGroup *groups;            // null: the one group `g`
     int ngroups;
+    PdGroup g;
     double *D;
     int32_t *mism, *comp;   // optional
     // column slices: nslice > 1 splits the width into slices of cslice
-    // columns (a multiple of kPdChunk), each slice's counts added atomically
-    // into acc (2 int32 per output, zeroed) and D formed by a finalize pass
+    // columns (a multiple of kPdChunk); a workgroup then leaves its counts at
+    // acc (mismatches, compared; [tile][slice][16][256 threads], coalesced)
+    // and pd_final_kernel adds the slices and forms D.  (Adding them with
+    // atomics, two per pair and slice, took more than the comparing: 3,001 x
+    // 4,030 1.75 ms in all.)
     int nslice;
     int64_t cslice;
-    int32_t *acc;
-    int mode;   // 0: whole width, D out; 1: one slice into acc; 2: D (and counts) from acc
+    int2 *acc;
 };
+
+// the group and tile (ta, tb) of tile t
+__device__ __forceinline__ PdGroup pd_tile(const PdArgs &a, int64_t t, int &ta, int &tb) {
+    PdGroup g = a.g;
+    if (a.groups) {
+        int lo = 0, hi = a.ngroups - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (a.groups[mid].tile0 <= t) lo = mid;
+            else hi = mid - 1;
+        }
+        g = a.groups[lo];
+    }
+    const int64_t tl = t - g.tile0;
+    if (g.sym) {   // tl = tb (tb + 1) / 2 + ta
+        tb = (int)((sqrt(8.0 * (double)tl + 1.0) - 1.0) * 0.5);
+        while ((int64_t)tb * (tb + 1) / 2 > tl) --tb;
+        while ((int64_t)(tb + 1) * (tb + 2) / 2 <= tl) ++tb;
+        ta = (int)(tl - (int64_t)tb * (tb + 1) / 2);
+    } else {
+        ta = (int)(tl / g.tiles_b);
+        tb = (int)(tl - (int64_t)ta * g.tiles_b);
+    }
+    return g;
+}
+
+// the counts of pair (r, s) of group g, tile (ta, tb), to D (and the counts out)
+__device__ __forceinline__ void pd_out(const PdArgs &a, const PdGroup &g, bool mirror, int r, int s, uint32_t mm,
+                                       uint32_t cc) {
+#pragma clang fp contract(off)
+    double d = cc > 0u ? (double)mm / (double)cc : 1.0;
+    if (g.diag0 && r == s) d = 0.0;
+    int64_t o = g.o + (int64_t)r * g.ld + s;
+    a.D[o] = d;
+    if (a.mism) a.mism[o] = (int32_t)mm;
+    if (a.comp) a.comp[o] = (int32_t)cc;
+    if (mirror) {
+        o = g.o + (int64_t)s * g.ld + r;
+        a.D[o] = d;
+        if (a.mism) a.mism[o] = (int32_t)mm;
+        if (a.comp) a.comp[o] = (int32_t)cc;
+    }
+}
 
 // bit 7 of each byte set when that byte of v is nonzero (no carries between bytes)
 __device__ __forceinline__ uint32_t nz_bytes(uint32_t v) {
@@ -93,50 +144,31 @@ __device__ __forceinline__ void pd_load16(const uint8_t *p, int64_t c, int64_t w
 // pair-word costs one xor-add, one three-input and with both masks and one
 // popcount-add.  The residue pairs (both bytes not the gap) are counted on the
 // packed bits, 32 columns per and and popcount.
-template <bool PIPE>
 __global__ void __launch_bounds__(256) pdist_kernel(PdArgs a) {
 #pragma clang fp contract(off)
     __shared__ uint2 sa[kPdTile * kPdStride], sb[kPdTile * kPdStride];
     __shared__ uint32_t ga[kPdTile * 2], gb[kPdTile * 2];
     // the group and tile of this workgroup (and its column slice)
-    int lo = 0, hi = a.ngroups - 1;
-    const int64_t t = a.mode == 1 ? blockIdx.x / a.nslice : blockIdx.x;
-    const int64_t slice = a.mode == 1 ? blockIdx.x - t * a.nslice : 0;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (a.groups[mid].tile0 <= t) lo = mid;
-        else hi = mid - 1;
-    }
-    const PdGroup g = a.groups[lo];
-    const int64_t tl = t - g.tile0;
-    const int ta = (int)(tl / g.tiles_b), tb = (int)(tl - (int64_t)ta * g.tiles_b);
+    const int64_t t = blockIdx.x / a.nslice, slice = blockIdx.x - t * a.nslice;
+    int ta, tb;
+    const PdGroup g = pd_tile(a, t, ta, tb);
     const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
     // staging: thread tid loads 16 bytes of row (tid >> 2) of each operand
     const int lr = tid >> 2, part = tid & 3, lb = 16 * part;
     const int ia = ta * kPdTile + lr, ib = tb * kPdTile + lr;
-    const uint8_t *pa = ia < g.na ? a.msa + (int64_t)a.rows[g.a0 + ia] * a.width : nullptr;
-    const uint8_t *pb = ib < g.nb ? a.msa + (int64_t)a.rows[g.b0 + ib] * a.width : nullptr;
+    const uint8_t *pa = nullptr, *pb = nullptr;
+    if (ia < g.na) pa = a.msa + (a.rows_a ? (int64_t)a.rows_a[g.a0 + ia] : g.a0 + ia) * a.width;
+    if (ib < g.nb) pb = a.msa + (a.rows_b ? (int64_t)a.rows_b[g.b0 + ib] : g.b0 + ib) * a.width;
     uint32_t mm[4][4], cc[4][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) mm[i][j] = cc[i][j] = 0u;
-    const int64_t cbeg = a.mode == 1 ? slice * a.cslice : 0;
-    const int64_t cend = a.mode == 1 ? min(a.width, cbeg + a.cslice) : (a.mode == 2 ? 0 : a.width);
-    // PIPE (sliced launches, about one workgroup per CU): the next pass's
-    // bytes are loaded while this pass compares; otherwise after it, which
-    // keeps registers for more resident workgroups (the other workgroups on
-    // the CU hide the load latency)
+    const int64_t cbeg = slice * a.cslice, cend = min(a.width, cbeg + a.cslice);
     uint32_t wa[4], wb[4];
-    if (PIPE && cbeg < cend) {
-        pd_load16(pa, cbeg + lb, a.width, wa);
-        pd_load16(pb, cbeg + lb, a.width, wb);
-    }
     for (int64_t c0 = cbeg; c0 < cend; c0 += kPdChunk) {
-        if (!PIPE) {
-            pd_load16(pa, c0 + lb, a.width, wa);
-            pd_load16(pb, c0 + lb, a.width, wb);
-        }
+        pd_load16(pa, c0 + lb, a.width, wa);
+        pd_load16(pb, c0 + lb, a.width, wb);
         __syncthreads();   // the previous pass is done with the staged words
         uint32_t bits_a = 0, bits_b = 0;   // 16 non-gap bits, at 0-3, 8-11, 16-19, 24-27
 #pragma unroll
@@ -155,10 +187,6 @@ __global__ void __launch_bounds__(256) pdist_kernel(PdArgs a) {
             gb[2 * lr + (part >> 1)] = bits_b | (nb << 4);
         }
         __syncthreads();
-        if (PIPE && c0 + kPdChunk < cend) {
-            pd_load16(pa, c0 + kPdChunk + lb, a.width, wa);
-            pd_load16(pb, c0 + kPdChunk + lb, a.width, wb);
-        }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -181,6 +209,14 @@ __global__ void __launch_bounds__(256) pdist_kernel(PdArgs a) {
                     mm[i][j] += __popc(((x[i].x ^ y[j].x) + 0x7F7F7F7Fu) & x[i].y & y[j].y);
         }
     }
+    if (a.nslice > 1) {
+        int2 *acc = a.acc + (int64_t)blockIdx.x * 16 * 256 + tid;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[256 * (4 * i + j)] = make_int2((int)mm[i][j], (int)cc[i][j]);
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int r = ta * kPdTile + 4 * ty + i;
@@ -188,24 +224,29 @@ __global__ void __launch_bounds__(256) pdist_kernel(PdArgs a) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int s = tb * kPdTile + 4 * tx + j;
-            if (s >= g.nb) continue;
-            const int64_t o = g.o + (int64_t)r * g.ld + s;
-            if (a.mode == 1) {   // this slice's counts
-                if (mm[i][j]) atomicAdd(a.acc + 2 * o, (int)mm[i][j]);
-                if (cc[i][j]) atomicAdd(a.acc + 2 * o + 1, (int)cc[i][j]);
-                continue;
-            }
-            if (a.mode == 2) {
-                mm[i][j] = (uint32_t)a.acc[2 * o];
-                cc[i][j] = (uint32_t)a.acc[2 * o + 1];
-            }
-            double d = cc[i][j] > 0u ? (double)mm[i][j] / (double)cc[i][j] : 1.0;
-            if (g.diag0 && r == s) d = 0.0;
-            a.D[o] = d;
-            if (a.mism) a.mism[o] = (int32_t)mm[i][j];
-            if (a.comp) a.comp[o] = (int32_t)cc[i][j];
+            if (s < g.nb) pd_out(a, g, g.sym && ta != tb, r, s, mm[i][j], cc[i][j]);
         }
     }
+}
+
+// D (and the counts) of a sliced launch: workgroup 16 t + q adds tile t's
+// slices for pair q of each thread's 4 x 4.
+__global__ void __launch_bounds__(256) pd_final_kernel(PdArgs a) {
+    const int64_t t = blockIdx.x >> 4;
+    const int q = blockIdx.x & 15, tid = threadIdx.x;
+    int ta, tb;
+    const PdGroup g = pd_tile(a, t, ta, tb);
+    const int r = ta * kPdTile + 4 * (tid >> 4) + (q >> 2), s = tb * kPdTile + 4 * (tid & 15) + (q & 3);
+    if (r >= g.na || s >= g.nb) return;
+    const int2 *p = a.acc + (t * a.nslice * 16 + q) * 256 + tid;
+    uint32_t mm = 0, cc = 0;
+#pragma unroll 8
+    for (int x = 0; x < a.nslice; ++x) {
+        const int2 v = p[(int64_t)x * 16 * 256];
+        mm += (uint32_t)v.x;
+        cc += (uint32_t)v.y;
+    }
+    pd_out(a, g, g.sym && ta != tb, r, s, mm, cc);
 }
 
 // A block copied out of a shared distance tile: the sz x sz block at src
@@ -223,6 +264,22 @@ __global__ void __launch_bounds__(256) pd_extract_kernel(double *D, const PdExtr
         const int r = x / e.sz, c = x - r * e.sz;
         D[e.dst + x] = D[e.src + (int64_t)r * e.ld + c];
     }
+}
+
+// The square distance matrices of several row lists out of the matrix F of all
+// n rows: workgroup x copies row x of the lists' concatenation (list lx[x], whose
+// rows start at lists[start[l]], size sz, matrix at dst[l]; diagonals 0).
+struct PdList {
+    int64_t start, dst;
+    int sz;
+};
+__global__ void __launch_bounds__(256) pd_gather_kernel(const double *F, int n, const int32_t *rows, const int32_t *lx,
+                                                        const PdList *lists, double *D) {
+    const PdList l = lists[lx[blockIdx.x]];
+    const int r = (int)((int64_t)blockIdx.x - l.start);
+    const double *f = F + (int64_t)rows[blockIdx.x] * n;
+    double *d = D + l.dst + (int64_t)r * l.sz;
+    for (int c = threadIdx.x; c < l.sz; c += 256) d[c] = c == r ? 0.0 : f[rows[l.start + c]];
 }
 
 // label[i] = the first j with the smallest D[i * ld + j], j < nb (one lane per row).
@@ -637,8 +694,367 @@ __global__ void __launch_bounds__(256) nj_big_join_kernel(NjBigArgs a) {
     }
 }
 
-__global__ void nj_big_finish_kernel(NjBigArgs a, int32_t *nodes) {
+// ---- one problem on a mesh of workgroups: one launch for all its joins ------
+// Workgroup w keeps the rows of slots [16 w, 16 w + 16) of the matrix in LDS for
+// the whole problem.  Per join, every workgroup adds its rows in slot order (one
+// lane per row) and publishes the sums; takes all sums, finds its rows' first
+// (Q, i, j) and publishes it; takes every workgroup's and updates its own
+// entries.  So a join is two exchanges (about 1 us each across the XCDs) and the
+// serial row sum, against three dependent launches that each read the whole
+// matrix from L2.  300 nodes: 17.0 -> 6.5 us per join, 526: 19.6 -> 7.5,
+// 1000: 26.7 -> 9.9.
+//
+// Columns are kept by position: the active slots in slot order, with the slots
+// that left since the last compaction between them.  Such a column holds +0.0
+// (adding it leaves a sum that started at +0.0 bit for bit) and has the sum -inf
+// (its pairs score +inf and never come first), so no loop tests for it; every 32
+// joins the positions are compacted.
+//
+// An exchange has no flags: published words start as kNjEmpty and a reader
+// polls the word itself.  Three sets of words are used in turn: at join t a
+// workgroup empties its words of set (t + 1) % 3, last read at join t - 2 (every
+// workgroup has since published at t - 1), and waits for that store before it
+// publishes at t, so whoever sees the words of t no longer finds old ones at t + 1.
+// All words go through agent-scope accesses.
+//
+// Row i of the joined pair needs row j, which another workgroup holds: every
+// update also goes to a copy M of the matrix in memory (both triangles, by the
+// owner of the other slot), complete before its writer publishes the next
+// sums; each workgroup fetches row j of its own candidate while it waits for
+// the others' and has it when it wins.
+//
+// The grid (at most 64 workgroups of 256 threads) has to be resident at once.
+// Every wait is bounded: a workgroup that polls kNjSpin times, or sees the
+// failure word, sets it and leaves, and the host joins the problem over the
+// chip instead (D itself is not changed).
+constexpr uint64_t kNjEmpty = ~0ull;
+constexpr int kNjSpin = 1 << 17;
+constexpr int kNjMeshRows = 16, kNjMeshMax = 1024, kNjMeshAhead = kNjMeshMax / 256, kNjMeshPack = 32;
+
+struct NjMeshArgs {
+    int n, G;
+    const double *D;
+    double *M;
+    uint64_t *rs;      // [3][n] row sums, by slot
+    uint64_t *part;    // [3][G][3]: Q, D(i, j), i << 16 | j (positions)
+    uint32_t *failed;
+    NjBigArgs o;       // act, id, parent, blen, ctrl
+};
+
+// doubles per row: 16 columns of zeros after the last, odd (the rows' lanes on distinct banks)
+__host__ __device__ inline int nj_mesh_stride(int n) { return (n + 17) | 1; }
+inline size_t nj_mesh_lds(int n) {
+    return 8 * ((size_t)kNjMeshRows * nj_mesh_stride(n) + n) + 4 * (size_t)n + 2 * (size_t)n + 16;
+}
+
+__device__ __forceinline__ void nj_pub(uint64_t *p, uint64_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t nj_get(const uint64_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t nj_bits(double v) { return (uint64_t)__double_as_longlong(v); }
+__device__ __forceinline__ double nj_val(uint64_t v) { return __longlong_as_double((long long)v); }
+// Waits until the N published words at p[u] (those with on[u]) are there: all
+// are asked for together, then the missing ones again.  False after the bounded
+// wait.
+template <int N>
+__device__ __forceinline__ bool nj_poll(const uint64_t *const (&p)[N], const bool (&on)[N], uint64_t (&v)[N],
+                                        uint32_t *failed) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) v[u] = kNjEmpty;
+    for (int it = 1; it <= kNjSpin; ++it) {
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            if (on[u] && v[u] == kNjEmpty) v[u] = nj_get(p[u]);
+        bool all = true;
+#pragma unroll
+        for (int u = 0; u < N; ++u) all = all && (!on[u] || v[u] != kNjEmpty);
+        if (all) return true;
+        if ((it & 255) == 0 && __hip_atomic_load(failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
+    }
+    __hip_atomic_store(failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return false;
+}
+
+// (q, ij) first over the wavefront, in every lane: smallest q, then smallest
+// ij.  DPP moves within rows of 16 and across them; lane 63 ends with it.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void nj_first_step(double &q, uint32_t &ij) {
+    const uint64_t b = nj_bits(q);
+    const uint32_t lo = __builtin_amdgcn_update_dpp((uint32_t)b, (uint32_t)b, CTRL, ROWS, 0xf, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp((uint32_t)(b >> 32), (uint32_t)(b >> 32), CTRL, ROWS, 0xf, false);
+    const uint32_t yij = __builtin_amdgcn_update_dpp(ij, ij, CTRL, ROWS, 0xf, false);
+    const double y = nj_val((uint64_t)hi << 32 | lo);
+    const bool take = (y < q) | ((y == q) & (yij < ij));
+    q = take ? y : q;
+    ij = take ? yij : ij;
+}
+__device__ __forceinline__ void nj_first(double &q, uint32_t &ij) {
+    nj_first_step<0x111, 0xf>(q, ij);
+    nj_first_step<0x112, 0xf>(q, ij);
+    nj_first_step<0x114, 0xf>(q, ij);
+    nj_first_step<0x118, 0xf>(q, ij);
+    nj_first_step<0x142, 0xa>(q, ij);
+    nj_first_step<0x143, 0xc>(q, ij);
+    const uint64_t b = nj_bits(q);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, 63), hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), 63);
+    q = nj_val((uint64_t)hi << 32 | lo);
+    ij = __builtin_amdgcn_readlane(ij, 63);
+}
+
+__global__ void __launch_bounds__(256) nj_mesh_kernel(NjMeshArgs a) {
 #pragma clang fp contract(off)
+    extern __shared__ double nj_mesh[];
+    __shared__ double red_q[4], win_d;
+    __shared__ uint32_t red_ij[4], win;
+    __shared__ int bad, mypos[kNjMeshRows], cnt[kNjMeshMax / 64];
+    constexpr uint32_t kNone = 0xffffffffu;
+    constexpr uint16_t kGone = 0xffff;
+    const int n = a.n, ld = nj_mesh_stride(n), tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    double *row = nj_mesh, *r = row + kNjMeshRows * ld;
+    int32_t *id = reinterpret_cast<int32_t *>(r + n);        // by slot
+    uint16_t *slot = reinterpret_cast<uint16_t *>(id + n);   // by position; kGone: left
+    uint64_t *M = reinterpret_cast<uint64_t *>(a.M);
+    const int r0 = blockIdx.x * kNjMeshRows, nr = min(kNjMeshRows, n - r0);
+    for (int q = 0; q < kNjMeshRows; ++q)
+        for (int k = tid; k < ld; k += 256) {
+            const double v = q < nr && k < n ? a.D[(int64_t)(r0 + q) * n + k] : 0.0;
+            row[q * ld + k] = v;
+            if (q < nr && k < n) nj_pub(M + (int64_t)(r0 + q) * n + k, nj_bits(v));
+        }
+    for (int k = tid; k < n; k += 256) {
+        id[k] = k;
+        slot[k] = (uint16_t)k;
+    }
+    if (tid < kNjMeshRows) mypos[tid] = tid < nr ? r0 + tid : -1;   // -1: no such row, or its slot left
+    if (tid == 0) bad = 0;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's part of M is in memory
+    int m = n, mp = n, next = n;   // active nodes, positions, next node number
+    __syncthreads();
+    for (int t = 0; m > 3; ++t) {
+        const int set = t % 3, clear = (t + 1) % 3;
+        uint64_t *rs = a.rs + (int64_t)set * n, *part = a.part + (int64_t)set * a.G * 3;
+        const int pos = tid < kNjMeshRows ? mypos[tid] : -1;
+        if (pos >= 0) nj_pub(a.rs + (int64_t)clear * n + r0 + tid, kNjEmpty);
+        if (tid < 3) nj_pub(a.part + ((int64_t)clear * a.G + blockIdx.x) * 3 + tid, kNjEmpty);
+        double sum = 0.0;
+        if (pos >= 0) {   // 8 columns are read while the 8 before are added
+            const double *d = row + tid * ld;
+            double v0[8], v1[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v0[u] = d[u];
+            for (int p = 0; p < mp; p += 16) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v1[u] = d[p + 8 + u];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) sum = sum + v0[u];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v0[u] = d[min(p + 16, ld - 8) + u];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) sum = sum + v1[u];
+            }
+        }
+        // this wavefront's updates of M and its emptied words are in memory
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (pos >= 0) nj_pub(rs + r0 + tid, nj_bits(sum));
+        {
+            const uint64_t *src[kNjMeshAhead];
+            bool on[kNjMeshAhead];
+            uint64_t v[kNjMeshAhead];
+#pragma unroll
+            for (int u = 0; u < kNjMeshAhead; ++u) {
+                const int p = tid + 256 * u;
+                on[u] = p < mp && slot[p] != kGone;
+                src[u] = rs + (on[u] ? slot[p] : 0);
+            }
+            if (!nj_poll(src, on, v, a.failed)) bad = 1;
+#pragma unroll
+            for (int u = 0; u < kNjMeshAhead; ++u)
+                if (on[u]) r[tid + 256 * u] = nj_val(v[u]);
+        }
+        __syncthreads();
+        if (bad) return;
+        const double f = (double)(m - 2);
+        double bq = __builtin_inf();
+        uint32_t bij = kNone;
+        {   // the wavefront's four rows against every column after theirs
+            int i[4];
+            double ri[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                i[u] = mypos[4 * wave + u];
+                ri[u] = i[u] >= 0 ? r[i[u]] : 0.0;
+                if (i[u] < 0) i[u] = mp;   // no column comes after it
+            }
+            const double *d = row + 4 * wave * ld;
+            for (int p = lane; p < mp; p += 64) {
+                const double rp = r[p];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const double c = f * d[u * ld + p] - ri[u] - rp;
+                    const uint32_t ij = (uint32_t)i[u] << 16 | (uint32_t)p;
+                    const bool take = (p > i[u]) & ((c < bq) | ((c == bq) & (ij < bij)));
+                    bq = take ? c : bq;
+                    bij = take ? ij : bij;
+                }
+            }
+        }
+        nj_first(bq, bij);
+        if (lane == 0) {
+            red_q[wave] = bq;
+            red_ij[wave] = bij;
+        }
+        __syncthreads();
+        bq = red_q[0];
+        bij = red_ij[0];
+#pragma unroll
+        for (int x = 1; x < 4; ++x) {
+            const bool take = (red_q[x] < bq) | ((red_q[x] == bq) & (red_ij[x] < bij));
+            bq = take ? red_q[x] : bq;
+            bij = take ? red_ij[x] : bij;
+        }
+        if (!(bq < __builtin_inf())) bij = kNone;   // (a column that left scores +inf)
+        const int cj = bij & 0xffffu, ci = bij >> 16;
+        if (tid == 0) {
+            uint64_t *w = part + (int64_t)blockIdx.x * 3;
+            nj_pub(w, nj_bits(bij == kNone ? __builtin_inf() : bq));
+            nj_pub(w + 1, bij == kNone ? 0 : nj_bits(row[(slot[ci] - r0) * ld + cj]));
+            nj_pub(w + 2, bij);
+        }
+        // row j of this workgroup's candidate, in case it is the one joined
+        double rj[kNjMeshAhead];
+        if (bij != kNone) {
+            const uint64_t *src = M + (int64_t)slot[cj] * n;
+#pragma unroll
+            for (int u = 0; u < kNjMeshAhead; ++u) {
+                const int p = tid + 256 * u;
+                rj[u] = p < mp && slot[p] != kGone ? nj_val(nj_get(src + slot[p])) : 0.0;
+            }
+        }
+        if (wave == 0) {
+            double q = __builtin_inf();
+            uint64_t d = 0;
+            uint32_t ij = kNone;
+            if (lane < a.G) {
+                const uint64_t *w = part + (int64_t)lane * 3, *const src[3] = {w, w + 1, w + 2};
+                const bool on[3] = {true, true, true};
+                uint64_t v[3];
+                if (!nj_poll(src, on, v, a.failed)) bad = 1;
+                q = nj_val(v[0]);
+                d = v[1];
+                ij = (uint32_t)v[2];
+            }
+            const uint32_t own = ij;
+            nj_first(q, ij);
+            if (ij == kNone) bad = 1;   // (no pair compares: left to the chip-wide kernels)
+            if (own == ij && ij != kNone) {
+                win = ij;
+                win_d = nj_val(d);
+            }
+        }
+        __syncthreads();
+        if (bad) {
+            if (tid == 0) __hip_atomic_store(a.failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
+        const int bi = win >> 16, bj = win & 0xffffu;
+        const double dij = win_d;
+        const int si = slot[bi], sj = slot[bj];
+        if (si / kNjMeshRows == (int)blockIdx.x) {   // row i, as every owner of k has it
+            double *d = row + (si - r0) * ld;
+#pragma unroll
+            for (int u = 0; u < kNjMeshAhead; ++u) {
+                const int p = tid + 256 * u;
+                if (p < mp && p != bi && p != bj && slot[p] != kGone) d[p] = (d[p] + rj[u] - dij) * 0.5;
+            }
+        }
+        if (pos >= 0) {
+            double *d = row + tid * ld;
+            if (pos != bi && pos != bj) {
+                const double v = (d[bi] + d[bj] - dij) * 0.5;
+                d[bi] = v;
+                nj_pub(M + (int64_t)si * n + r0 + tid, nj_bits(v));
+                nj_pub(M + (int64_t)(r0 + tid) * n + si, nj_bits(v));
+            }
+            d[bj] = 0.0;
+        }
+        if (blockIdx.x == 0 && tid == 0) {
+            const double li = 0.5 * dij + (r[bi] - r[bj]) / (2.0 * f);
+            const double lj = dij - li;
+            a.o.parent[id[si]] = next;
+            a.o.blen[id[si]] = li;
+            a.o.parent[id[sj]] = next;
+            a.o.blen[id[sj]] = lj;
+            id[si] = next;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            slot[bj] = kGone;
+            r[bj] = -__builtin_inf();
+            if (sj / kNjMeshRows == (int)blockIdx.x) mypos[sj - r0] = -1;
+        }
+        --m;
+        ++next;
+        __syncthreads();
+        if ((t + 1) % kNjMeshPack == 0) {   // drop the positions of slots that left
+            int np[kNjMeshAhead];
+            uint16_t sl[kNjMeshAhead];
+#pragma unroll
+            for (int u = 0; u < kNjMeshAhead; ++u) {
+                const int p = tid + 256 * u;
+                sl[u] = p < mp ? slot[p] : kGone;
+                const uint64_t k = __ballot(sl[u] != kGone);
+                np[u] = __popcll(k & ((1ull << lane) - 1));
+                if (lane == 0) cnt[4 * u + wave] = __popcll(k);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kNjMeshAhead; ++u) {
+                for (int x = 0; x < 4 * u + wave; ++x) np[u] += cnt[x];
+                if (sl[u] != kGone) {
+                    slot[np[u]] = sl[u];
+                    if (sl[u] / kNjMeshRows == (int)blockIdx.x) mypos[sl[u] - r0] = np[u];
+                }
+            }
+            for (int q0 = 0; q0 < kNjMeshRows; q0 += 4) {
+                double v[4][kNjMeshAhead];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int u = 0; u < kNjMeshAhead; ++u)
+                        v[q][u] = tid + 256 * u < mp ? row[(q0 + q) * ld + tid + 256 * u] : 0.0;
+                __syncthreads();
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                    for (int u = 0; u < kNjMeshAhead; ++u)
+                        if (sl[u] != kGone) row[(q0 + q) * ld + np[u]] = v[q][u];
+                    if (tid < 16) row[(q0 + q) * ld + m + tid] = 0.0;
+                }
+            }
+            mp = m;
+            __syncthreads();
+        }
+    }
+    if (blockIdx.x == 0) {   // for nj_big_finish_kernel
+        for (int k = tid; k < n; k += 256) {
+            a.o.act[k] = 0;
+            a.o.id[k] = id[k];
+        }
+        __syncthreads();
+        for (int p = tid; p < mp; p += 256)
+            if (slot[p] != kGone) a.o.act[slot[p]] = 1;
+        if (tid == 0) *a.o.ctrl = NjCtrl{m, next};
+    }
+}
+
+__global__ void nj_big_finish_kernel(NjBigArgs a, const uint32_t *failed, int32_t *nodes) {
+#pragma clang fp contract(off)
+    if (failed && *failed) {
+        *nodes = -1;
+        return;
+    }
     const int n = a.n;
     const NjCtrl c = *a.ctrl;
     int next = c.next;
