@@ -78,6 +78,7 @@ struct HostBuf {
 
 struct halign_ctx {
     int device = 0;
+    bool counted = false;    // counted among its device's contexts (eval_contexts)
     size_t cap = 0;          // workspace cap for codes + boundary rows (0 = none)
     int num_cu = 256;
     size_t lds_max = 65536;
@@ -143,6 +144,8 @@ struct halign_ctx {
     int64_t tkey[4] = {-1, -1, -1, -1};
     std::array<int, 5> tval = {-1, 0, 1, 64, 0};
 };
+
+static void eval_contexts(int device, int change);
 
 namespace {
 
@@ -1277,6 +1280,8 @@ int halign_ctx_create(int device, size_t workspace_cap_bytes, halign_ctx **out) 
         halign_ctx_destroy(ctx);
         return fail(HALIGN_E_DEVICE, "event create");
     }
+    eval_contexts(device, 1);
+    ctx->counted = true;
     *out = ctx;
     return HALIGN_OK;
 }
@@ -1284,6 +1289,7 @@ int halign_ctx_create(int device, size_t workspace_cap_bytes, halign_ctx **out) 
 void halign_ctx_destroy(halign_ctx *ctx) {
     if (!ctx) return;
     (void)hipSetDevice(ctx->device);
+    if (ctx->counted) eval_contexts(ctx->device, -1);
     (void)hipDeviceSynchronize();
     graph_drop(ctx);
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
@@ -2102,10 +2108,9 @@ int halign_sw_score_noalloc(const halign_scoring *sc, const uint8_t *center, int
 
 }  // extern "C"
 
-// Column profile into prof, *dbad raised on a byte that is neither a residue
-// code below alpha nor the gap.  Rows are split into slabs (at most
-// kProfMaxSlab rows, for 16-bit partial counts) so that the grid has a few
-// thousand workgroups; the slabs' counts meet in a second pass, not in
+// Column profile, *dbad raised to tag on a byte that is neither a residue code
+// below alpha nor the gap.  Rows are split into slabs (at most kProfMaxSlab rows,
+// for 16-bit partial counts); the slabs' counts meet in a second pass, not in
 // atomics (many workgroups adding into the same profile line serialise).
 // part: at least column_profile_part_bytes() bytes of device scratch.
 static void column_profile_shape(int32_t n, int64_t width, int64_t *ncb, int64_t *nslab, int *slab) {
@@ -2115,8 +2120,11 @@ static void column_profile_shape(int32_t n, int64_t width, int64_t *ncb, int64_t
         return;
     }
     *ncb = (width + hk::kProfCols - 1) / hk::kProfCols;
+    // about two workgroups per CU, of at least 128 rows: each slab writes its
+    // counts and the next pass reads them (20,000 x 4,030: 51 us a call with 32
+    // slabs, 62 with 79, 61 with 20; 2,000 x 4,030: 33 with 16, 39 with 4)
     int64_t ns = std::max<int64_t>((n + hk::kProfMaxSlab - 1) / hk::kProfMaxSlab,
-                                   std::min<int64_t>((3072 + *ncb - 1) / *ncb, (n + 255) / 256));
+                                   std::min<int64_t>((512 + *ncb - 1) / *ncb, (n + 127) / 128));
     int sl = (int)((n + ns - 1) / std::max<int64_t>(ns, 1));
     if (const char *e = getenv("HALIGN_PROFILE_SLAB"))   // test knob: rows per slab
         if (atoi(e) > 0) sl = std::min(atoi(e), hk::kProfMaxSlab);
@@ -2131,22 +2139,105 @@ static size_t column_profile_part_bytes(int32_t n, int64_t width, int32_t alpha)
     return (size_t)nslab * (size_t)width * (size_t)(alpha + 1) * 2;
 }
 
-static int column_profile_launch(const uint8_t *msa, int32_t n, int64_t width, int32_t alpha, int32_t *prof,
-                                 uint16_t *part, int *dbad, hipStream_t st) {
-    const int nsym = alpha + 1;
-    if (n <= 0 || width <= 0) return launch_fill((uint32_t *)prof, 0u, width * nsym, st);
+// The slabs' counts into part (n > 0 and width > 0).
+static int column_profile_launch(const uint8_t *msa, int32_t n, int64_t width, int32_t alpha, uint16_t *part,
+                                 uint32_t *dbad, uint32_t tag, hipStream_t st, int *nslab_out) {
     int64_t ncb, nslab;
     int slab;
     column_profile_shape(n, width, &ncb, &nslab, &slab);
+    *nslab_out = (int)nslab;
     if (ncb > 0x7fffffff || nslab > 65535) return fail(HALIGN_E_UNSUPPORTED, "%d x %lld MSA", n, (long long)width);
     hipLaunchKernelGGL(hk::colprof_kernel, dim3((unsigned)ncb, (unsigned)nslab), dim3(256),
-                       (size_t)(alpha + 3) * 256 * 4, st, msa, n, width, alpha, slab, part, dbad);
-    HCHK(hipGetLastError());
-    const int64_t nelem = width * nsym;
-    hipLaunchKernelGGL(hk::colprof_sum_kernel, dim3((unsigned)((nelem + 255) / 256)), dim3(256), 0, st,
-                       (const uint16_t *)part, (int)nslab, nelem, prof);
+                       (size_t)(alpha + 3) * 256 * 4, st, msa, n, width, alpha, slab, part, dbad, tag);
     HCHK(hipGetLastError());
     return HALIGN_OK;
+}
+
+// Scratch of the two evaluation calls, which have no context: a device buffer
+// with its pinned mailbox, kept per device between calls while a context lives
+// there (at most kEvalKeep bytes; allocating and freeing took 0.1 ms of a 0.13
+// ms call).  Both calls synchronise before they return, so a buffer handed back
+// is idle; a call that finds none kept (another thread holds it) allocates its
+// own.
+namespace {
+constexpr size_t kEvalKeep = (size_t)64 << 20;
+constexpr int kEvalDevices = 64;
+// device: the flag word (raised to the call's tag, so it is never cleared), the
+// workgroups' SP sums at 256, the slabs' counts at kEvalHead; pinned: a copy of
+// the first kEvalHead bytes
+constexpr size_t kEvalHead = 256 + (size_t)hk::kSpGroups * 16;
+struct EvalBuf {
+    char *dev = nullptr;
+    size_t cap = 0;
+    char *host = nullptr;
+    uint32_t tag = 0;
+};
+std::mutex g_eval_mutex;
+EvalBuf g_eval[kEvalDevices];
+int g_eval_live[kEvalDevices];   // contexts on each device
+
+void eval_free(EvalBuf &b) {
+    if (b.dev) (void)hipFree(b.dev);
+    if (b.host) (void)hipHostFree(b.host);
+    b = EvalBuf();
+}
+
+int eval_take(size_t part_bytes, int *device, EvalBuf *out, hipStream_t st) {
+    const size_t bytes = kEvalHead + part_bytes;
+    HCHK(hipGetDevice(device));
+    EvalBuf b;
+    if (*device < kEvalDevices) {
+        std::lock_guard<std::mutex> lk(g_eval_mutex);
+        std::swap(b, g_eval[*device]);
+    }
+    if (b.cap < bytes) {
+        eval_free(b);
+        if (hipMalloc((void **)&b.dev, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(HALIGN_E_NOMEM, "device allocation of %zu bytes failed", bytes);
+        }
+        b.cap = bytes;
+        if (hipHostMalloc((void **)&b.host, kEvalHead, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            b.host = nullptr;
+            eval_free(b);
+            return fail(HALIGN_E_DEVICE, "pinned allocation");
+        }
+        b.tag = 0;
+    }
+    if (b.tag == 0 || b.tag == 0xffffffffu) {   // a new buffer, or the tags are used up
+        b.tag = 0;
+        const int rc = launch_fill((uint32_t *)b.dev, 0u, 1, st);
+        if (rc != HALIGN_OK) {
+            eval_free(b);
+            return rc;
+        }
+    }
+    ++b.tag;
+    *out = b;
+    return HALIGN_OK;
+}
+
+void eval_give(int device, EvalBuf &b) {
+    if (device < kEvalDevices && b.cap <= kEvalKeep) {
+        std::lock_guard<std::mutex> lk(g_eval_mutex);
+        if (g_eval_live[device] > 0 && !g_eval[device].dev) std::swap(b, g_eval[device]);
+    }
+    eval_free(b);
+}
+
+}  // namespace
+
+// a context was created (+1) or destroyed (-1) on the device
+static void eval_contexts(int device, int change) {
+    if (device < 0 || device >= kEvalDevices) return;
+    EvalBuf b;
+    {
+        std::lock_guard<std::mutex> lk(g_eval_mutex);
+        g_eval_live[device] += change;
+        if (g_eval_live[device] == 0) std::swap(b, g_eval[device]);
+    }
+    eval_free(b);
 }
 
 extern "C" {
@@ -2157,19 +2248,32 @@ int halign_column_profile(const uint8_t *msa, int32_t n, int64_t width, int32_t 
         (n > 0 && width > 0 && !msa))
         return fail(HALIGN_E_INVALID, "bad arguments");
     hipStream_t st = (hipStream_t)stream;
-    int *dbad = nullptr;
-    HCHK(hipMalloc(&dbad, 256 + column_profile_part_bytes(n, width, alphabet)));
-    int rc = launch_fill((uint32_t *)dbad, 0u, 1, st);
-    if (rc == HALIGN_OK)
-        rc = column_profile_launch(msa, n, width, alphabet, profile, (uint16_t *)((char *)dbad + 256), dbad, st);
-    int hbad = 0;
-    if (rc == HALIGN_OK && hipMemcpyAsync(&hbad, dbad, 4, hipMemcpyDeviceToHost, st) != hipSuccess)
-        rc = fail(HALIGN_E_DEVICE, "profile flag copy");
-    if (rc == HALIGN_OK && hipStreamSynchronize(st) != hipSuccess) rc = fail(HALIGN_E_DEVICE, "profile sync");
-    (void)hipFree(dbad);
-    if (rc != HALIGN_OK) return rc;
-    if (hbad) return fail(HALIGN_E_INVALID, "MSA byte neither a residue code below %d nor the gap", alphabet);
-    return HALIGN_OK;
+    int device = 0;
+    EvalBuf b;
+    RCHK(eval_take(column_profile_part_bytes(n, width, alphabet), &device, &b, st));
+    const int64_t nelem = width * (alphabet + 1);
+    auto body = [&]() -> int {
+        if (n == 0 || width == 0) {
+            RCHK(launch_fill((uint32_t *)profile, 0u, nelem, st));
+            HCHK(hipStreamSynchronize(st));
+            return HALIGN_OK;
+        }
+        uint16_t *part = (uint16_t *)(b.dev + kEvalHead);
+        int nslab = 0;
+        RCHK(column_profile_launch(msa, n, width, alphabet, part, (uint32_t *)b.dev, b.tag, st, &nslab));
+        hipLaunchKernelGGL(hk::colprof_sum_kernel, dim3((unsigned)((nelem + 255) / 256)), dim3(256), 0, st,
+                           (const uint16_t *)part, nslab, nelem, profile);
+        HCHK(hipGetLastError());
+        HCHK(hipMemcpyAsync(b.host, b.dev, 4, hipMemcpyDeviceToHost, st));
+        HCHK(hipStreamSynchronize(st));
+        if (*(const uint32_t *)b.host == b.tag)
+            return fail(HALIGN_E_INVALID, "MSA byte neither a residue code below %d nor the gap", alphabet);
+        return HALIGN_OK;
+    };
+    const int rc = body();
+    if (rc != HALIGN_OK) (void)hipStreamSynchronize(st);
+    eval_give(device, b);
+    return rc;
 }
 
 int halign_sp_score(const halign_scoring *sc, const uint8_t *msa, int32_t n, int64_t width, int64_t *out_host,
@@ -2178,37 +2282,40 @@ int halign_sp_score(const halign_scoring *sc, const uint8_t *msa, int32_t n, int
     if (!out_host || n < 0 || width < 0 || (n > 0 && width > 0 && !msa)) return fail(HALIGN_E_INVALID, "bad arguments");
     hipStream_t st = (hipStream_t)stream;
     const int alpha = sc->alphabet;
-    // one allocation: matrix (1 KiB), sums (16 B), flag, profile
-    const size_t prof_b = ((size_t)std::max<int64_t>(width, 1) * (alpha + 1) * 4 + 255) & ~(size_t)255;
-    char *buf = nullptr;
-    HCHK(hipMalloc(&buf, 2048 + prof_b + column_profile_part_bytes(n, width, alpha)));
-    int8_t *dmat = (int8_t *)buf;
-    unsigned long long *dout = (unsigned long long *)(buf + 1024);
-    int *dbad = (int *)(buf + 1040);
-    int32_t *prof = (int32_t *)(buf + 2048);
-    int rc = HALIGN_OK;
-    unsigned long long h[2] = {0, 0};
-    int hbad = 0;
-    if (hipMemcpyAsync(dmat, sc->matrix_host, (size_t)alpha * alpha, hipMemcpyHostToDevice, st) != hipSuccess)
-        rc = fail(HALIGN_E_DEVICE, "matrix copy");
-    if (rc == HALIGN_OK) rc = launch_fill((uint32_t *)dout, 0u, 5, st);   // sums and flag
-    if (rc == HALIGN_OK)
-        rc = column_profile_launch(msa, n, width, alpha, prof, (uint16_t *)(buf + 2048 + prof_b), dbad, st);
-    if (rc == HALIGN_OK && n > 0 && width > 0) {
-        hipLaunchKernelGGL(hk::sp_profile_kernel, dim3((unsigned)((width + 255) / 256)), dim3(256), 0, st, prof,
-                           width, alpha, (const int8_t *)dmat, sc->gap_extend, dout);
-        if (hipGetLastError() != hipSuccess) rc = fail(HALIGN_E_DEVICE, "sp_profile_kernel launch");
+    if (n == 0 || width == 0) {
+        HCHK(hipStreamSynchronize(st));
+        out_host[0] = out_host[1] = 0;
+        return HALIGN_OK;
     }
-    if (rc == HALIGN_OK && (hipMemcpyAsync(h, dout, 16, hipMemcpyDeviceToHost, st) != hipSuccess ||
-                            hipMemcpyAsync(&hbad, dbad, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-                            hipStreamSynchronize(st) != hipSuccess))
-        rc = fail(HALIGN_E_DEVICE, "sp result copy");
-    (void)hipFree(buf);
-    if (rc != HALIGN_OK) return rc;
-    if (hbad) return fail(HALIGN_E_INVALID, "MSA byte neither a residue code below %d nor the gap", alpha);
-    out_host[0] = (int64_t)h[0];
-    out_host[1] = (int64_t)h[1];
-    return HALIGN_OK;
+    int device = 0;
+    EvalBuf b;
+    RCHK(eval_take(column_profile_part_bytes(n, width, alpha), &device, &b, st));
+    auto body = [&]() -> int {
+        uint16_t *part = (uint16_t *)(b.dev + kEvalHead);
+        int nslab = 0;
+        RCHK(column_profile_launch(msa, n, width, alpha, part, (uint32_t *)b.dev, b.tag, st, &nslab));
+        hk::SpMatrix mat;
+        memcpy(mat.s, sc->matrix_host, (size_t)alpha * alpha);
+        const int groups = (int)std::min<int64_t>(hk::kSpGroups, (width + hk::kSpCols - 1) / hk::kSpCols);
+        hipLaunchKernelGGL(hk::sp_profile_kernel, dim3((unsigned)groups), dim3(256), 0, st, (const uint16_t *)part,
+                           nslab, width, alpha, mat, sc->gap_extend, (int64_t *)(b.dev + 256));
+        HCHK(hipGetLastError());
+        HCHK(hipMemcpyAsync(b.host, b.dev, 256 + (size_t)groups * 16, hipMemcpyDeviceToHost, st));
+        HCHK(hipStreamSynchronize(st));
+        if (*(const uint32_t *)b.host == b.tag)
+            return fail(HALIGN_E_INVALID, "MSA byte neither a residue code below %d nor the gap", alpha);
+        const int64_t *h = (const int64_t *)(b.host + 256);
+        out_host[0] = out_host[1] = 0;
+        for (int q = 0; q < groups; ++q) {
+            out_host[0] += h[2 * q];
+            out_host[1] += h[2 * q + 1];
+        }
+        return HALIGN_OK;
+    };
+    const int rc = body();
+    if (rc != HALIGN_OK) (void)hipStreamSynchronize(st);
+    eval_give(device, b);
+    return rc;
 }
 
 int halign_msa(halign_ctx *ctx, const halign_scoring *sc, const halign_seqs *seqs, int32_t center,

@@ -484,109 +484,153 @@ __global__ void __launch_bounds__(256) rows_chunk_kernel(RowsArgs a, const int32
     }
 }
 
-constexpr int kProfCols = 256;      // columns per workgroup (one per lane)
+constexpr int kProfCols = 256;      // columns per workgroup (four per lane)
 constexpr int kProfMaxSlab = 65535; // rows per workgroup (16-bit partial counts)
-constexpr int kProfRows = 32;       // rows loaded per pass
+constexpr int kProfRows = 16;       // rows loaded per pass of a wavefront
 
-// rows of one column into the lane's LDS counters (stride 256 words): bin 0
-// gaps, 1 + a for residue code a, top = alpha + 1 anything else; EDGE: a lane
-// past the last column (in == false) reads the last column and counts into
-// bin top + 1, which is discarded, so the row loop has no branch
+// Column profile of an N x W MSA, first pass: workgroup (x, y) counts the
+// bytes of columns 256 x .. 256 x + 255 over the rows of slab y, its four
+// wavefronts taking rows in turn.  A lane loads four columns at once (a
+// wavefront 256 consecutive bytes of a row, at any alignment), 16 rows before
+// they are counted.  With a byte per lane the loads' issue bounded the kernel
+// (1e6 x 1,000: 234 us with the counting alone
+// against 163).  The counters sit in LDS:
+// word bin * 256 + 64 (column % 4) + column / 4, so the lanes of one count are on
+// distinct banks; bin 0 counts gaps, bin 1 + a residue code a, bin alpha + 1 any
+// other byte (which raises *bad).  The slab's counts go, without atomics, to
+// part[y][column][slot] (uint16; slot a < alpha a residue code, slot alpha the
+// gaps), written in contiguous runs.  EDGE: the last columns of an MSA at least
+// four wide; a lane with fewer than four (cols) loads the row's last four bytes
+// and shifts, and what lies past the end counts into a bin that is discarded.
 template <bool EDGE>
-__device__ __forceinline__ void colprof_rows(const uint8_t *p, int64_t width, int rows, uint32_t *lc, uint32_t top,
-                                             bool in) {
-    auto count = [&](uint32_t b) __attribute__((always_inline)) {
-        uint32_t bin = min((b + 1u) & 255u, top);
-        if (EDGE) bin = in ? bin : top + 1u;
-        atomicAdd(lc + bin * 256, 1u);
+__device__ __forceinline__ void colprof_rows(const uint8_t *p, int64_t step, int rows, int cols, uint32_t *lc,
+                                             uint32_t top) {
+    const int sh = EDGE ? 8 * (4 - cols) & 31 : 0;
+    auto load = [&](const uint8_t *q) __attribute__((always_inline)) {
+        uint32_t v;
+        __builtin_memcpy(&v, q, 4);
+        return EDGE ? v >> sh : v;
+    };
+    auto count = [&](uint32_t v) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            uint32_t bin = min((((v >> (8 * k)) & 255u) + 1u) & 255u, top);
+            if (EDGE && k >= cols) bin = top + 1u;
+            atomicAdd(lc + bin * 256 + 64 * k, 1u);
+        }
     };
     int r = 0;
-    for (; r + kProfRows <= rows; r += kProfRows, p += kProfRows * width) {
+    for (; r + kProfRows <= rows; r += kProfRows, p += kProfRows * step) {
         uint32_t v[kProfRows];
 #pragma unroll
-        for (int u = 0; u < kProfRows; ++u) v[u] = p[u * width];
+        for (int u = 0; u < kProfRows; ++u) v[u] = load(p + u * step);
 #pragma unroll
         for (int u = 0; u < kProfRows; ++u) count(v[u]);
     }
-    for (; r < rows; ++r, p += width) count(*p);
+    for (; r < rows; ++r, p += step) count(load(p));
 }
 
-// Column profile of an N x W MSA, first pass: workgroup (x, y) counts the
-// bytes of columns 256 x .. 256 x + 255 over the rows of slab y.  Lane t owns
-// column 256 x + t, so each byte load of a wavefront covers 64 consecutive
-// bytes of a row; 32 rows are loaded before they are counted.  The lane's
-// counters sit in LDS (word bin * 256 + t, no barrier needed): bin 0 counts
-// gaps, bin 1 + a residue code a, bin alpha + 1 any other byte (which raises
-// *bad).  The slab's counts go, without atomics, to part[y][column][slot]
-// (uint16; slot a < alpha a residue code, slot alpha the gaps), written in
-// contiguous runs.  A lane past the last column reads the last column and
-// counts into a discarded bin, so the row loop has no branch.
 __global__ void __launch_bounds__(256)
-colprof_kernel(const uint8_t *msa, int n, int64_t width, int alpha, int slab, uint16_t *part, int *bad) {
+colprof_kernel(const uint8_t *msa, int n, int64_t width, int alpha, int slab, uint16_t *part, uint32_t *bad, uint32_t tag) {
     extern __shared__ uint32_t pcnt[];
     const int nbin = alpha + 3;
-    const int t = threadIdx.x;
-    uint32_t *lc = pcnt + t;
-    for (int x = 0; x < nbin; ++x) lc[x * 256] = 0;
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    for (int x = t; x < nbin * 256; x += 256) pcnt[x] = 0;
+    __syncthreads();
     const int64_t cb = (int64_t)blockIdx.x * kProfCols;
-    const bool in = cb + t < width;
     const int r0 = blockIdx.y * slab;
     const int r1 = min(n, r0 + slab);
-    const uint8_t *p = msa + (int64_t)r0 * width + (in ? cb + t : width - 1);
-    if (cb + kProfCols <= width) colprof_rows<false>(p, width, r1 - r0, lc, (uint32_t)alpha + 1u, true);
-    else colprof_rows<true>(p, width, r1 - r0, lc, (uint32_t)alpha + 1u, in);
-    if (in && lc[(alpha + 1) * 256] != 0) atomicOr(bad, 1);
+    const int cols = (int)min((int64_t)4, max((int64_t)0, width - (cb + 4 * lane)));   // this lane's columns
+    const uint8_t *p = msa + (int64_t)(r0 + wave) * width + cb + 4 * lane;
+    const int rows = (r1 - r0 - wave + 3) >> 2;   // rows r0 + wave, + 4, ...
+    const uint32_t top = (uint32_t)alpha + 1u;
+    if (cb + kProfCols <= width) {
+        colprof_rows<false>(p, 4 * width, rows, 4, pcnt + lane, top);
+    } else if (width >= 4) {   // lanes past the end read the last four columns too
+        colprof_rows<true>(msa + (int64_t)(r0 + wave) * width + min(cb + 4 * lane, width - 4), 4 * width, rows, cols,
+                           pcnt + lane, top);
+    } else if (cols > 0) {
+        for (int r = 0; r < rows; ++r, p += 4 * width)
+            for (int k = 0; k < cols; ++k) atomicAdd(pcnt + min((p[k] + 1u) & 255u, top) * 256 + 64 * k + lane, 1u);
+    }
     __syncthreads();
+    if (pcnt[top * 256 + t] != 0) atomicMax(bad, tag);
     // slab counts out: element e of the workgroup's run is (column e / nsym, slot e % nsym)
     const int nsym = alpha + 1;
     const int64_t ncols = min((int64_t)kProfCols, width - cb);
     uint16_t *dst = part + ((int64_t)blockIdx.y * width + cb) * nsym;
     for (int e = t; e < ncols * nsym; e += 256) {
         const int c = e / nsym, slot = e - c * nsym;
-        dst[e] = (uint16_t)pcnt[(slot == alpha ? 0 : slot + 1) * 256 + c];
+        dst[e] = (uint16_t)pcnt[(slot == alpha ? 0 : slot + 1) * 256 + 64 * (c & 3) + (c >> 2)];
     }
+}
+
+// element e of the profile: its slabs' counts added, eight loads in flight
+__device__ __forceinline__ int32_t colprof_total(const uint16_t *part, int nslab, int64_t nelem, int64_t e) {
+    int32_t s = 0;
+#pragma unroll 8
+    for (int y = 0; y < nslab; ++y) s += part[(int64_t)y * nelem + e];
+    return s;
 }
 
 // Second pass: profile[e] = sum over slabs of part[slab][e], e < width * nsym.
 __global__ void __launch_bounds__(256)
 colprof_sum_kernel(const uint16_t *part, int nslab, int64_t nelem, int32_t *prof) {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= nelem) return;
-    int32_t s = 0;
-    for (int y = 0; y < nslab; ++y) s += part[(int64_t)y * nelem + e];
-    prof[e] = s;
+    if (e < nelem) prof[e] = colprof_total(part, nslab, nelem, e);
 }
 
-// avg SP numerator and BLOSUM column SP from a column profile, one thread
-// per column: out[0] += (pairs of different residues) + 2 * (residue-gap
-// pairs); out[1] += sum of S over residue pairs - ge * (residue-gap pairs).
+struct SpMatrix {
+    int8_t s[kAlphaMax * kAlphaMax];   // alpha x alpha
+};
+
+// avg SP numerator and BLOSUM column SP from the slabs' counts, summed over the
+// workgroup's columns into out[2 * workgroup] += (pairs of different residues) +
+// 2 * (residue-gap pairs) and out[.. + 1] += sum of S over residue pairs - ge *
+// (residue-gap pairs).  A workgroup totals eight columns at a time into LDS,
+// then its threads share the columns' residue pairs (with a thread per column
+// the 16 workgroups of 4,030 columns took 23 us, after a 20 us pass that wrote
+// the profile; now 15).
+constexpr int kSpCols = 8, kSpGroups = 512;   // columns at a time, workgroups at most
 __global__ void __launch_bounds__(256)
-sp_profile_kernel(const int32_t *prof, int64_t width, int alpha, const int8_t *mat, int ge,
-                  unsigned long long *out) {
-    __shared__ int smat[32][32];
-    const int tid = threadIdx.x;
-    for (int x = tid; x < 1024; x += 256) {
-        const int a = x >> 5, b = x & 31;
-        smat[a][b] = (a < alpha && b < alpha) ? mat[a * alpha + b] : 0;
+sp_profile_kernel(const uint16_t *part, int nslab, int64_t width, int alpha, SpMatrix mat, int ge, int64_t *out) {
+    __shared__ int32_t cnt[kSpCols * (kAlphaMax + 1)];
+    __shared__ int8_t smat[kAlphaMax * kAlphaMax];
+    __shared__ long long red[2][4];
+    const int tid = threadIdx.x, nsym = alpha + 1;
+    for (int x = tid; x < alpha * alpha; x += 256) smat[x] = mat.s[x];
+    long long sp = 0, bl = 0;
+    for (int64_t c0 = (int64_t)blockIdx.x * kSpCols; c0 < width; c0 += (int64_t)gridDim.x * kSpCols) {
+        const int nc = (int)min((int64_t)kSpCols, width - c0);
+        __syncthreads();   // the previous columns' counts are done with
+        for (int e = tid; e < nc * nsym; e += 256)
+            cnt[e] = colprof_total(part, nslab, width * nsym, c0 * nsym + e);
+        __syncthreads();
+        // item (column, a): residue a against itself and every later code
+        for (int q = tid; q < nc * alpha; q += 256) {
+            const int32_t *c = cnt + q / alpha * nsym;
+            const int a = q % alpha;
+            const int64_t ca = c[a], g = c[alpha];
+            if (!ca) continue;
+            int64_t later = 0;
+            bl += ca * (ca - 1) / 2 * smat[a * alpha + a] - (int64_t)ge * g * ca;
+            for (int b = a + 1; b < alpha; ++b) {
+                later += c[b];
+                bl += ca * (int64_t)c[b] * smat[a * alpha + b];
+            }
+            sp += ca * later + 2 * g * ca;
+        }
+    }
+    for (int d = 32; d > 0; d >>= 1) {
+        sp += __shfl_xor(sp, d);
+        bl += __shfl_xor(bl, d);
+    }
+    if ((tid & 63) == 0) {
+        red[0][tid >> 6] = sp;
+        red[1][tid >> 6] = bl;
     }
     __syncthreads();
-    const int64_t x = (int64_t)blockIdx.x * 256 + tid;
-    if (x >= width) return;
-    const int32_t *c = prof + x * (alpha + 1);
-    const int64_t g = c[alpha];
-    int64_t r = 0, same = 0, bl = 0;
-    for (int a = 0; a < alpha; ++a) {
-        const int64_t ca = c[a];
-        if (!ca) continue;
-        r += ca;
-        same += ca * (ca - 1) / 2;
-        bl += ca * (ca - 1) / 2 * smat[a][a];
-        for (int b = a + 1; b < alpha; ++b) bl += ca * (int64_t)c[b] * smat[a][b];
-    }
-    const int64_t sp = (r * (r - 1) / 2 - same) + 2 * g * r;
-    bl -= (int64_t)ge * g * r;
-    atomicAdd(out, (unsigned long long)sp);
-    atomicAdd(out + 1, (unsigned long long)bl);
+    if (tid < 2) out[2 * blockIdx.x + tid] = red[tid][0] + red[tid][1] + red[tid][2] + red[tid][3];
 }
 
 }  // namespace hk
