@@ -94,6 +94,7 @@ struct halign_ctx {
     size_t stage_off = 0, plan_off = 0;
     hipEvent_t ev_stage = nullptr;
     bool stage_pending = false;
+    bool stage_event = false;   // ev_stage was recorded after the pending copies
     // timing of the last call: one (start, forward end, walk end) event
     // triple per forward launch (chunk, route or graph replay)
     std::vector<std::array<hipEvent_t, 3>> tev;
@@ -138,7 +139,7 @@ struct halign_ctx {
     // against prejudge_part common partners (0: off)
     int prejudge_cand = 0, prejudge_part = 0;
     // host planning scratch, kept between calls (no allocation per call)
-    std::vector<int32_t> h_pids, h_plen, h_cnt, h_sof, h_head, h_nxt, h_scount, h_cur, h_split;
+    std::vector<int32_t> h_samp, h_pids, h_plen, h_cnt, h_sof, h_head, h_nxt, h_scount, h_cur, h_split;
     std::vector<int64_t> h_scols;
     // the last tuned-plan lookup, by its integer key
     int64_t tkey[4] = {-1, -1, -1, -1};
@@ -221,10 +222,27 @@ void graph_drop(halign_ctx *ctx) {
     g = halign_ctx::GraphEntry();
 }
 
+// Copies from the pinned stage are in flight on a stream.  Calls that wait for
+// their stream anyway clear stage_pending there; stage_close at a call's end
+// records the event for the others (an event after every copy left a gap of 5 us
+// before the forward kernel).
+void stage_copied(halign_ctx *ctx) {
+    if (ctx->capturing) return;
+    ctx->stage_pending = true;
+    ctx->stage_event = false;
+}
+int stage_close(halign_ctx *ctx, hipStream_t st) {
+    if (ctx->stage_pending && !ctx->stage_event && !ctx->capturing) {
+        HCHK(hipEventRecord(ctx->ev_stage, st));
+        ctx->stage_event = true;
+    }
+    return HALIGN_OK;
+}
 int stage_wait(halign_ctx *ctx) {
     if (ctx->capturing) return HALIGN_OK;
     if (ctx->stage_pending) {
-        HCHK(hipEventSynchronize(ctx->ev_stage));
+        if (ctx->stage_event) HCHK(hipEventSynchronize(ctx->ev_stage));
+        else HCHK(hipDeviceSynchronize());   // a call that failed halfway, or regions regrown within one
         ctx->stage_pending = false;
     }
     return HALIGN_OK;
@@ -336,18 +354,23 @@ int check_scoring(const halign_scoring *sc) {
     return HALIGN_OK;
 }
 
-int check_seqs(const halign_seqs *sq) {
+// *longest (optional): the longest sequence.
+int check_seqs(const halign_seqs *sq, int *longest = nullptr) {
+    if (longest) *longest = 0;
     if (!sq || sq->n < 0) return fail(HALIGN_E_INVALID, "seqs is NULL or n < 0");
     if (sq->n == 0) return HALIGN_OK;
     if (!sq->residues || !sq->offsets || !sq->offsets_host)
         return fail(HALIGN_E_INVALID, "seqs pointers are NULL");
     const int64_t *o = sq->offsets_host;
     if (o[0] != 0) return fail(HALIGN_E_INVALID, "offsets[0] must be 0");
+    int64_t top = 0;
     for (int k = 0; k < sq->n; ++k) {
         const int64_t L = o[k + 1] - o[k];
         if (L < 0) return fail(HALIGN_E_INVALID, "offsets decrease at %d", k);
         if (L >= 65536) return fail(HALIGN_E_UNSUPPORTED, "sequence %d has length %lld >= 65536", k, (long long)L);
+        top = std::max(top, L);
     }
+    if (longest) *longest = (int)top;
     return HALIGN_OK;
 }
 
@@ -381,13 +404,11 @@ int64_t strip_cols(int nmax_all) {
     return ((int64_t)std::max(1, nmax_all) + hk::kB - 1) / hk::kB * hk::kB;
 }
 
-void launch_inter(const hk::InterArgs &a, bool tb, bool endc, int grid, hipStream_t st) {
-    if (tb)
-        hipLaunchKernelGGL((hk::sw_inter_kernel<true, true>), dim3(grid), dim3(64), 0, st, a);
-    else if (endc)
-        hipLaunchKernelGGL((hk::sw_inter_kernel<false, true>), dim3(grid), dim3(64), 0, st, a);
-    else
-        hipLaunchKernelGGL((hk::sw_inter_kernel<false, false>), dim3(grid), dim3(64), 0, st, a);
+void launch_inter(const hk::InterArgs &a, bool tb, bool endc, int grid, hipStream_t st,
+                  const hk::Timed &t = hk::Timed()) {
+    if (tb) hk::launch_timed(t, hk::sw_inter_kernel<true, true>, dim3(grid), dim3(64), 0, st, a);
+    else if (endc) hk::launch_timed(t, hk::sw_inter_kernel<false, true>, dim3(grid), dim3(64), 0, st, a);
+    else hk::launch_timed(t, hk::sw_inter_kernel<false, false>, dim3(grid), dim3(64), 0, st, a);
 }
 
 // Geometry of the wavefront forward for a batch.
@@ -395,11 +416,18 @@ struct StreamGeom {
     int R = 8, passes = 1, LS = 64, pk = 0;
 };
 
+// Lengths by rank, longest first: all of them, or a sample of n of the np.
+struct Lens {
+    const int32_t *v;
+    int n, np;
+    int32_t operator[](int rank) const { return n == np ? v[rank] : v[(int64_t)rank * n / np]; }
+};
+
 // Streams of a batch of `np` non-empty pairs (lengths plen, longest first) when
 // `cap` streams are resident, and the columns that a wavefront's share of them
 // takes: the mean of the average and the longest stream (streams end apart,
 // and those that end early leave their issue slots to the others).
-double stream_cols(const int32_t *plen, int np, int64_t sum_len, int cap) {
+double stream_cols(const Lens &plen, int np, int64_t sum_len, int cap) {
     if (cap >= np) return 0.5 * ((double)sum_len / np + plen[0]);
     const double avg = (double)sum_len / cap;
     double top = std::max<double>(plen[0], 1.05 * avg);
@@ -418,7 +446,7 @@ double stream_cols(const int32_t *plen, int np, int64_t sum_len, int cap) {
 // 25%, and it orders the geometries as measured: packed streams of 32 or 16
 // lanes where they fill the chip, 64 lanes below.
 constexpr double kShare[7] = {1.28, 1.28, 2.2, 3.15, 4, 5, 6};
-double stream_cost(const halign_ctx *ctx, const StreamGeom &g, bool tb, const int32_t *plen, int np, int64_t sum_len,
+double stream_cost(const halign_ctx *ctx, const StreamGeom &g, bool tb, const Lens &plen, int np, int64_t sum_len,
                    int w) {
     const int per_wave = 64 / g.LS * (g.pk ? 2 : 1), simds = ctx->num_cu * 4;
     const double ops = g.pk ? (tb ? (g.R > 11 ? 21.8 : 17.8) * g.R + 65 : 10.5 * g.R + 65)
@@ -433,7 +461,7 @@ double stream_cost(const halign_ctx *ctx, const StreamGeom &g, bool tb, const in
 // Resident wavefronts per SIMD that the packed kernel's streams are sized for
 // (at most four fit its registers): four, or fewer where more pairs per stream
 // end closer together.
-int packed_waves(const halign_ctx *ctx, const StreamGeom &g, bool tb, const int32_t *plen, int np, int64_t sum_len,
+int packed_waves(const halign_ctx *ctx, const StreamGeom &g, bool tb, const Lens &plen, int np, int64_t sum_len,
                  int wmax) {
     int best = std::min(4, wmax);
     double cost = stream_cost(ctx, g, tb, plen, np, sum_len, best);
@@ -469,21 +497,30 @@ struct Tune {
 // pairs_in: the pair ids of the batch (NULL: 0 .. np-1).
 int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, const halign_seqs *sq,
               const int32_t *pids_in, int np, bool tb, bool endc, int route, const BatchOut &out, hipStream_t st,
-              const Tune &tune = Tune()) {
+              const Tune &tune = Tune(), int dev_longest = -1) {
     const int64_t *oh = sq->offsets_host;
-    const int N = sq->n;
     if (np == 0) return HALIGN_OK;
     auto pid_of = [&](int x) { return pids_in ? pids_in[x] : x; };
+    // Planned on the device (plan_kernels.hpp) from 2,048 pairs, where the caller
+    // allows it (dev_longest: the longest of all pairs), the batch is not a
+    // captured one (whose replays read the host's plan) and the knobs leave the
+    // dealing open; the host then only looks at a sample of the lengths.  Below,
+    // the host plans faster than the kernels' launches (64 pairs: 5 us).
+    bool dev = dev_longest >= 0 && !pids_in && np >= 2048 && !ctx->capturing && !getenv("HALIGN_DEAL");
+    int32_t *pids = nullptr, *plen = nullptr;
+    int64_t sum_len = 0;
+    int nonempty_all = np;   // (empty pairs sort last)
     // longest first (counting sort on length, stable); plen[x] = length of
     // pids[x], so that later passes read lengths in order
-    if ((int)ctx->h_pids.size() < np) {
-        ctx->h_pids.resize(np);
-        ctx->h_plen.resize(np);
-    }
-    int32_t *pids = ctx->h_pids.data(), *plen = ctx->h_plen.data();
-    int64_t sum_len = 0;
-    {
+    auto sort_pairs = [&]() {
+        if ((int)ctx->h_pids.size() < np) {
+            ctx->h_pids.resize(np);
+            ctx->h_plen.resize(np);
+        }
+        pids = ctx->h_pids.data();
+        plen = ctx->h_plen.data();
         int maxlen = 0;
+        sum_len = 0;
         for (int x = 0; x < np; ++x) {
             const int p = pid_of(x);
             maxlen = std::max(maxlen, (int)(oh[p + 1] - oh[p]));
@@ -505,6 +542,28 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
             pids[q] = p;
             plen[q] = L;
         }
+        nonempty_all = np;
+        while (nonempty_all > 0 && plen[nonempty_all - 1] == 0) --nonempty_all;
+    };
+    Lens lens{nullptr, 0, 0};
+    if (dev) {   // a strided sample of 1,024 lengths, sorted, its first one the longest of all
+        constexpr int kSample = 1024;
+        sum_len = oh[np] - oh[0];
+        dev = sum_len > 0;
+        std::vector<int32_t> &cnt = ctx->h_cnt, &smp = ctx->h_samp;
+        cnt.assign(dev_longest + 1, 0);
+        for (int x = 0; x < kSample; ++x) {
+            const int p = (int)((int64_t)x * np / kSample);
+            cnt[oh[p + 1] - oh[p]]++;
+        }
+        smp.clear();
+        for (int L = dev_longest; L >= 0; --L) smp.insert(smp.end(), cnt[L], L);
+        smp[0] = dev_longest;
+        lens = Lens{smp.data(), kSample, np};
+    }
+    if (!dev) {
+        sort_pairs();
+        lens = Lens{plen, nonempty_all > 0 ? nonempty_all : np, nonempty_all > 0 ? nonempty_all : np};
     }
     hmark(ctx, "sort");
     const int aw = (m + 31) / 32;
@@ -512,7 +571,7 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
     // max score <= max(S) * min(m, longest sequence)
     int smax = 1;
     for (int x = 0; x < S.alpha * S.alpha; ++x) smax = std::max(smax, (int)S.hmat[x]);
-    const int nlong = plen[0];
+    const int nlong = lens[0];
     const bool p16 = (int64_t)smax * std::min(m, nlong) <= 32000 && S.goe + 128 <= 32000 &&
                      !getenv("HALIGN_PROFILE32");
     int R = 8, passes = 1, LS = 64;
@@ -522,8 +581,6 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
     // the gap costs are small
     const bool pk_fits = p16 && (int64_t)smax * std::min(m, nlong) < 15000 && S.goe <= 256 && S.ge <= 256;
     bool pk = false;
-    int nonempty_all = np;   // (empty pairs sort last)
-    while (nonempty_all > 0 && plen[nonempty_all - 1] == 0) --nonempty_all;
     auto narrow = [&](int ls) {   // the fewest passes of streams of ls lanes, and the rows that fills
         StreamGeom g;
         g.LS = ls;
@@ -552,13 +609,13 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
     } else if (route == kRouteIntra && p16 && nonempty_all > 0 && !env_pk) {
         // no plan given: the cheapest geometry by stream_cost
         StreamGeom best{R, passes, 64, 0};
-        double cost = stream_cost(ctx, best, tb, plen, nonempty_all, sum_len, R > 6 ? 4 : 6);
+        double cost = stream_cost(ctx, best, tb, lens, nonempty_all, sum_len, R > 6 ? 4 : 6);
         for (int ls : {32, 16})
             for (int k = 0; k <= (pk_fits ? 1 : 0); ++k) {
                 StreamGeom g = narrow(ls);
                 g.pk = k;
-                const int w = k ? packed_waves(ctx, g, tb, plen, nonempty_all, sum_len, 4) : (g.R > 6 ? 4 : 6);
-                const double c = stream_cost(ctx, g, tb, plen, nonempty_all, sum_len, w);
+                const int w = k ? packed_waves(ctx, g, tb, lens, nonempty_all, sum_len, 4) : (g.R > 6 ? 4 : 6);
+                const double c = stream_cost(ctx, g, tb, lens, nonempty_all, sum_len, w);
                 if (c < cost) {
                     cost = c;
                     best = g;
@@ -585,6 +642,59 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
     if (route == kRouteIntra && lds_stream > ctx->lds_max) route = kRouteInter;
     ctx->last_stats[2] = route;
     ctx->last_pk = pk ? 1 : 0;
+    // streams of a set of pairs (lengths l, longest first): the pairs are dealt
+    // over the resident wavefronts so that every stream has about the same
+    // columns.  Resident workgroups per CU: by LDS, and by registers (the 32-bit
+    // kernel holds four waves per SIMD with R > 6, else six)
+    auto count_streams = [&](const Lens &l, int n, int64_t cols) {
+        const int wg_lds = std::max(1, (int)((pk ? ctx->lds_cu : ctx->lds_max) / lds_stream));
+        const int wg_per_cu = pk ? (n > 0 ? packed_waves(ctx, geom, tb, l, n, cols, wg_lds) : 1)
+                                 : std::max(1, std::min({4, wg_lds, (R > 6 ? 4 : 6) * 4 / 8}));
+        const int resident = ctx->num_cu * wg_per_cu * (pk ? 4 : 8) * NS * std::max(1, tune.smul) * (pk ? 2 : 1);
+        int ns = std::max(1, std::min(n, (int)std::max(1.0, resident * tune.scale)));
+        if (const char *e = getenv("HALIGN_MAX_STREAMS")) {   // test knob: many pairs per stream
+            const int cap_s = atoi(e);
+            if (cap_s > 0) ns = std::min(ns, cap_s);
+        }
+        return ns;
+    };
+    // The device's dealing by formula serves where its longest stream, estimated
+    // from the sample, is within 15% of the longest pair or of the average stream,
+    // and its equal regions take at most four times the columns.  Forward time
+    // against dealing to the least loaded stream: batch of 20,000 0.77 ms against
+    // 0.79; 300,000 10.7 against 11.1; a long tail of 50,001, whose longest
+    // stream would be 1.6 times the average, 1.36 against 0.89.
+    int dev_ns = 0;
+    int64_t dev_cols = 0;
+    size_t dev_code_words = 0, dev_bound = 0;
+    const int per_group = pk ? 2 : 1;
+    if (dev && route == kRouteIntra) {
+        dev_ns = count_streams(lens, np, sum_len);
+        const int64_t avg = sum_len / dev_ns;
+        dev = (np + dev_ns - 1) / dev_ns <= 64;
+        double top = 0;
+        for (int q = 0; dev && q <= 4; ++q) {
+            const int s2 = (int)((int64_t)(dev_ns - 1) * q / 4);
+            double load = 0;
+            for (int64_t r = 0; r * dev_ns < np; ++r) {
+                const int64_t x = r * dev_ns + ((r & 1) ? dev_ns - 1 - s2 : s2);
+                if (x < np) load += lens[(int)x];
+            }
+            top = std::max(top, load);
+        }
+        dev_cols = np <= dev_ns ? nlong : avg + nlong;
+        if (tb) dev_code_words = (size_t)passes * (size_t)((dev_cols + LS - 1 + 7) / 8) * LS * 8 * WQ;
+        dev_bound = (size_t)(passes - 1) * (size_t)dev_cols;
+        const size_t groups = (size_t)(dev_ns + per_group - 1) / per_group;
+        dev = dev && top <= 1.15 * (double)std::max<int64_t>(nlong, avg) && dev_cols <= 4 * avg && dev_cols < (1 << 30) &&
+              groups * (dev_code_words * 4 + dev_bound * 8) <= (ctx->cap ? ctx->cap : (size_t)1 << 62);
+    } else {
+        dev = false;
+    }
+    if (!dev && !pids) {
+        sort_pairs();
+        lens = Lens{plen, nonempty_all > 0 ? nonempty_all : np, nonempty_all > 0 ? nonempty_all : np};
+    }
 
     const char *deal_env = getenv("HALIGN_DEAL");   // test knob: snake dealing
     const bool deal_lpt = !(deal_env && !strcmp(deal_env, "snake"));
@@ -600,7 +710,7 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
         code_cols = std::min(code_cols, ((size_t)sum_len + (size_t)nlong * nonempty_all / 2) / 2 + (size_t)(LS + 8) * np);
     const size_t intra_bytes =
         (tb ? (size_t)passes * LS * 4 * WQ * code_cols : 0) + (size_t)(passes - 1) * 8 * (size_t)sum_len;
-    if (route == kRouteIntra && intra_bytes <= cap) {
+    if (dev || (route == kRouteIntra && intra_bytes <= cap)) {
         chunks.push_back({0, np});
     } else {
         const int nst = (m + hk::kT - 1) / hk::kT;
@@ -635,212 +745,259 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
     for (size_t ci = 0; ci < chunks.size(); ++ci) {
         const int lo = chunks[ci].first, hi = chunks[ci].second;
         const int cn = hi - lo;
-        PlanBuilder pb;
-        size_t code_words = 0, bound_elems = 0;
-        int nmax_all = 0;
-        nmax_all = plen[lo];
-        // strip route: the walk list and its walk descriptors, both in walk
-        // order (the wavefront route's walk reads the per-slot and per-stream
-        // plan)
-        const bool strip_plan = route != kRouteIntra;
-        const size_t o_cbase = strip_plan ? pb.add(sizeof(int64_t) * cn) : 0,
-                     o_cstr = strip_plan ? pb.add(sizeof(int32_t) * cn) : 0,
-                     o_ccol = strip_plan ? pb.add(sizeof(int32_t) * cn) : 0,
-                     o_walk = strip_plan ? pb.add(sizeof(int32_t) * cn) : 0;
-        size_t o_sbeg = 0, o_slot0 = 0, o_scb = 0, o_sbb = 0, o_spid = 0, o_scol = 0, o_sstr = 0;
-        size_t o_order = 0, o_gnmax = 0, o_gcb = 0;
+        size_t code_words = 0, bound_elems = 0;   // of the chunk
         int nstreams = 0, nslots = 0, ngroups = 0;
-        int64_t total_cols = 0, ch_len = 0;
-        int nonempty = 0;   // pairs [0, nonempty) of the chunk are non-empty: empty pairs sort last
-        for (int x = hi - 1; x >= lo && plen[x] == 0; --x) ++nonempty;
-        nonempty = cn - nonempty;
-        if (route == kRouteIntra) {
-            // streams: the pairs are dealt, longest first, over the resident
-            // wavefronts so that every stream has about the same columns.
-            // Resident workgroups per CU: by LDS, and by registers (the
-            // 32-bit kernel holds four waves per SIMD with R > 6, else six)
-            for (int x = 0; x < nonempty; ++x) ch_len += plen[lo + x];
-            const int wg_lds = std::max(1, (int)((pk ? ctx->lds_cu : ctx->lds_max) / lds_stream));
-            const int wg_per_cu =
-                pk ? (nonempty > 0 ? packed_waves(ctx, geom, tb, plen + lo, nonempty, ch_len, wg_lds) : 1)
-                   : std::max(1, std::min({4, wg_lds, (R > 6 ? 4 : 6) * 4 / 8}));
-            const int resident = ctx->num_cu * wg_per_cu * (pk ? 4 : 8) * NS * std::max(1, tune.smul) * (pk ? 2 : 1);
-            nstreams = std::max(1, std::min(nonempty, (int)std::max(1.0, resident * tune.scale)));
-            if (const char *e = getenv("HALIGN_MAX_STREAMS")) {   // test knob: many pairs per stream
-                const int cap_s = atoi(e);
-                if (cap_s > 0) nstreams = std::min(nstreams, cap_s);
-            }
+        int64_t total_cols = 0;
+        const bool strip_plan = route != kRouteIntra;
+        const int chunk_nmax = dev ? nlong : plen[lo];
+        // the plan's arrays, as offsets into the chunk's region of the device plan
+        size_t o_cbase = 0, o_cstr = 0, o_ccol = 0, o_walk = 0, o_sbeg = 0, o_slen = 0, o_slot0 = 0, o_scb = 0,
+               o_sbb = 0, o_spid = 0, o_scol = 0, o_sstr = 0, o_order = 0, o_gnmax = 0, o_gcb = 0;
+        char *dplan = nullptr;
+        if (dev) {
+            PlanBuilder pb;
+            nstreams = dev_ns;
             nslots = cn;
-            o_sbeg = pb.add(sizeof(int64_t) * (nstreams + 1));
+            o_sbeg = pb.add(sizeof(int64_t) * nstreams);
+            o_slen = pb.add(sizeof(int32_t) * nstreams);
             o_slot0 = pb.add(sizeof(int32_t) * nstreams);
             o_scb = pb.add(sizeof(int64_t) * nstreams);
             o_sbb = pb.add(sizeof(int64_t) * nstreams);
             o_spid = pb.add(sizeof(int32_t) * nslots);
             o_scol = pb.add(sizeof(int64_t) * nslots);
             o_sstr = pb.add(sizeof(int32_t) * nslots);
+            o_order = pb.add(sizeof(int2) * nslots);
+            const size_t o_hist = pb.add(sizeof(int32_t) * (nlong + 1));
+            RCHK(plan_dev(ctx, pb.total, st, &dplan));
+            total_cols = (int64_t)nstreams * dev_cols;
+            const size_t groups = (size_t)(nstreams + per_group - 1) / per_group;
+            code_words = groups * dev_code_words;
+            bound_elems = groups * dev_bound;
+            const size_t keys_b = ((size_t)nslots * 8 + 255) & ~size_t(255);
+            RCHK(grow(ctx, ctx->sbuf, keys_b + (size_t)total_cols + 64));
+            hk::DevPlanArgs d{};
+            d.res = sq->residues;
+            d.off = sq->offsets;
+            d.np = cn;
+            d.maxlen = nlong;
+            d.ns = nstreams;
+            d.clamp = p16 ? S.alpha : 31;
+            d.hist = (int32_t *)(dplan + o_hist);
+            d.order = (int2 *)(dplan + o_order);
+            d.per_group = per_group;
+            d.cols = dev_cols;
+            d.code_words = (int64_t)dev_code_words;
+            d.bound_elems = (int64_t)dev_bound;
+            d.spid = (int32_t *)(dplan + o_spid);
+            d.sstr = (int32_t *)(dplan + o_sstr);
+            d.slot0 = (int32_t *)(dplan + o_slot0);
+            d.slen = (int32_t *)(dplan + o_slen);
+            d.scol = (int64_t *)(dplan + o_scol);
+            d.sbeg = (int64_t *)(dplan + o_sbeg);
+            d.scb = (int64_t *)(dplan + o_scb);
+            d.sbb = (int64_t *)(dplan + o_sbb);
+            d.keys = (unsigned long long *)ctx->sbuf.p;
+            d.sres = (uint8_t *)ctx->sbuf.p + keys_b;
+            RCHK(launch_fill((uint32_t *)d.hist, 0u, nlong + 1, st));
+            hipLaunchKernelGGL(hk::plan_hist_kernel, dim3(grid_for(cn, 1024, 128)), dim3(256), 0, st, d);
+            hipLaunchKernelGGL(hk::plan_scan_kernel, dim3(1), dim3(1024), 0, st, d.hist, nlong);
+            hipLaunchKernelGGL(hk::plan_scatter_kernel, dim3(grid_for(cn, 256, 1 << 30)), dim3(256), 0, st, d);
+            hipLaunchKernelGGL(hk::plan_stage_kernel, dim3((unsigned)((cn + 3) / 4)), dim3(256), 0, st, d);
+            HCHK(hipGetLastError());
+            hmark(ctx, "dplan");
         } else {
-            ngroups = (cn + 63) / 64;
-            o_order = pb.add(sizeof(int32_t) * (size_t)ngroups * 64);
-            o_gnmax = pb.add(sizeof(int32_t) * ngroups);
-            o_gcb = pb.add(sizeof(int64_t) * ngroups);
-        }
-        char *hs = nullptr;
-        RCHK(stage_host(ctx, pb.total, &hs));
-        int32_t *h_walk = (int32_t *)(hs + o_walk);
-        int64_t *h_cbase = (int64_t *)(hs + o_cbase);
-        int32_t *h_cstr = (int32_t *)(hs + o_cstr);
-        int32_t *h_ccol = (int32_t *)(hs + o_ccol);
-        if (strip_plan)
-            for (int x = 0; x < cn; ++x) h_walk[x] = pids[lo + x];
-        if (route == kRouteIntra) {
-            int64_t *h_sbeg = (int64_t *)(hs + o_sbeg);
-            int32_t *h_slot0 = (int32_t *)(hs + o_slot0);
-            int64_t *h_scb = (int64_t *)(hs + o_scb);
-            int64_t *h_sbb = (int64_t *)(hs + o_sbb);
-            int32_t *h_spid = (int32_t *)(hs + o_spid);
-            int64_t *h_scol = (int64_t *)(hs + o_scol);
-            int32_t *h_sstr = (int32_t *)(hs + o_sstr);   // stream of each slot (for the walk)
-            // pairs and columns of each stream, then slots grouped by stream.
-            // Snake dealing: the k-th non-empty pair, k = r * nstreams + q, goes
-            // to stream q in even rounds r and nstreams - 1 - q in odd ones.
-            // Least-loaded dealing: each pair (longest first) goes to the stream
-            // with the fewest columns so far (a bucket queue on the column
-            // count, whose minimum only grows), so streams end within one pair
-            // length of each other.
-            std::vector<int32_t> &scount = ctx->h_scount;
-            std::vector<int64_t> &scols = ctx->h_scols;
-            scount.assign(nstreams, 0);
-            scols.assign(nstreams, 0);
-            std::vector<int32_t> &sof = ctx->h_sof;   // least-loaded dealing: stream of each non-empty pair
-            const int64_t maxload = (nonempty > 0 ? ch_len / nstreams + plen[lo] : 0) + 1;
-            const bool lpt = deal_lpt && maxload <= ((int64_t)1 << 22);
-            hmark(ctx, "p_setup");
-            if (lpt) {
-                if ((int)sof.size() < nonempty) sof.resize(nonempty);
-                std::vector<int32_t> &head = ctx->h_head, &nxt = ctx->h_nxt;
-                head.assign(maxload + 1, -1);
-                if ((int)nxt.size() < nstreams) nxt.resize(nstreams);
-                for (int s2 = 0; s2 < nstreams; ++s2) nxt[s2] = s2 + 1 < nstreams ? s2 + 1 : -1;
-                head[0] = 0;
-                int64_t minp = 0;
-                for (int x = 0; x < nonempty; ++x) {
-                    while (head[minp] < 0) ++minp;
-                    const int s2 = head[minp];
-                    head[minp] = nxt[s2];
-                    sof[x] = s2;
-                    scount[s2]++;
-                    scols[s2] += plen[lo + x];
-                    const int64_t l2 = minp + plen[lo + x];
-                    nxt[s2] = head[l2];
-                    head[l2] = s2;
-                }
+            PlanBuilder pb;
+            const int nmax_all = plen[lo];
+            // strip route: the walk list and its walk descriptors, both in walk
+            // order (the wavefront route's walk reads the per-slot and per-stream
+            // plan)
+            o_cbase = strip_plan ? pb.add(sizeof(int64_t) * cn) : 0;
+            o_cstr = strip_plan ? pb.add(sizeof(int32_t) * cn) : 0;
+            o_ccol = strip_plan ? pb.add(sizeof(int32_t) * cn) : 0;
+            o_walk = strip_plan ? pb.add(sizeof(int32_t) * cn) : 0;
+            int64_t ch_len = 0;
+            int nonempty = 0;   // pairs [0, nonempty) of the chunk are non-empty: empty pairs sort last
+            for (int x = hi - 1; x >= lo && plen[x] == 0; --x) ++nonempty;
+            nonempty = cn - nonempty;
+            if (route == kRouteIntra) {
+                for (int x = 0; x < nonempty; ++x) ch_len += plen[lo + x];
+                nstreams = count_streams(Lens{plen + lo, nonempty, nonempty}, nonempty, ch_len);
+                nslots = cn;
+                o_sbeg = pb.add(sizeof(int64_t) * nstreams);
+                o_slen = pb.add(sizeof(int32_t) * nstreams);
+                o_slot0 = pb.add(sizeof(int32_t) * nstreams);
+                o_scb = pb.add(sizeof(int64_t) * nstreams);
+                o_sbb = pb.add(sizeof(int64_t) * nstreams);
+                o_spid = pb.add(sizeof(int32_t) * nslots);
+                o_scol = pb.add(sizeof(int64_t) * nslots);
+                o_sstr = pb.add(sizeof(int32_t) * nslots);
             } else {
-                int r = 0, q = 0;   // round and position of the next non-empty pair
-                for (int x = 0; x < nonempty; ++x) {
-                    const int s2 = (r & 1) ? nstreams - 1 - q : q;
-                    scount[s2]++;
-                    scols[s2] += plen[lo + x];
-                    if (++q == nstreams) { q = 0; ++r; }
-                }
+                ngroups = (cn + 63) / 64;
+                o_order = pb.add(sizeof(int32_t) * (size_t)ngroups * 64);
+                o_gnmax = pb.add(sizeof(int32_t) * ngroups);
+                o_gcb = pb.add(sizeof(int64_t) * ngroups);
             }
-            hmark(ctx, "p_deal");
-            int slot = 0;
-            int64_t col = 0;
-            for (int s = 0; s < nstreams; ++s) {
-                h_slot0[s] = slot;
-                h_sbeg[s] = col;
-                slot += scount[s];
-                col += scols[s];
-                h_scb[s] = (int64_t)code_words;
-                h_sbb[s] = (int64_t)bound_elems;
-                if (pk) {
-                    // stream pair (s, s+1) shares the tiles and boundary rows of a
-                    // lane group, sized by the longer stream
-                    if (s & 1) {
-                        h_scb[s] = h_scb[s - 1];
-                        h_sbb[s] = h_sbb[s - 1];
+            char *hs = nullptr;
+            RCHK(stage_host(ctx, pb.total, &hs));
+            int32_t *h_walk = (int32_t *)(hs + o_walk);
+            int64_t *h_cbase = (int64_t *)(hs + o_cbase);
+            int32_t *h_cstr = (int32_t *)(hs + o_cstr);
+            int32_t *h_ccol = (int32_t *)(hs + o_ccol);
+            if (strip_plan)
+                for (int x = 0; x < cn; ++x) h_walk[x] = pids[lo + x];
+            if (route == kRouteIntra) {
+                int64_t *h_sbeg = (int64_t *)(hs + o_sbeg);
+                int32_t *h_slot0 = (int32_t *)(hs + o_slot0);
+                int64_t *h_scb = (int64_t *)(hs + o_scb);
+                int64_t *h_sbb = (int64_t *)(hs + o_sbb);
+                int32_t *h_spid = (int32_t *)(hs + o_spid);
+                int64_t *h_scol = (int64_t *)(hs + o_scol);
+                int32_t *h_sstr = (int32_t *)(hs + o_sstr);   // stream of each slot (for the walk)
+                // pairs and columns of each stream, then slots grouped by stream.
+                // Snake dealing: the k-th non-empty pair, k = r * nstreams + q, goes
+                // to stream q in even rounds r and nstreams - 1 - q in odd ones.
+                // Least-loaded dealing: each pair (longest first) goes to the stream
+                // with the fewest columns so far (a bucket queue on the column
+                // count, whose minimum only grows), so streams end within one pair
+                // length of each other.
+                std::vector<int32_t> &scount = ctx->h_scount;
+                std::vector<int64_t> &scols = ctx->h_scols;
+                scount.assign(nstreams, 0);
+                scols.assign(nstreams, 0);
+                std::vector<int32_t> &sof = ctx->h_sof;   // least-loaded dealing: stream of each non-empty pair
+                const int64_t maxload = (nonempty > 0 ? ch_len / nstreams + plen[lo] : 0) + 1;
+                const bool lpt = deal_lpt && maxload <= ((int64_t)1 << 22);
+                hmark(ctx, "p_setup");
+                if (lpt) {
+                    if ((int)sof.size() < nonempty) sof.resize(nonempty);
+                    std::vector<int32_t> &head = ctx->h_head, &nxt = ctx->h_nxt;
+                    head.assign(maxload + 1, -1);
+                    if ((int)nxt.size() < nstreams) nxt.resize(nstreams);
+                    for (int s2 = 0; s2 < nstreams; ++s2) nxt[s2] = s2 + 1 < nstreams ? s2 + 1 : -1;
+                    head[0] = 0;
+                    int64_t minp = 0;
+                    for (int x = 0; x < nonempty; ++x) {
+                        while (head[minp] < 0) ++minp;
+                        const int s2 = head[minp];
+                        head[minp] = nxt[s2];
+                        sof[x] = s2;
+                        scount[s2]++;
+                        scols[s2] += plen[lo + x];
+                        const int64_t l2 = minp + plen[lo + x];
+                        nxt[s2] = head[l2];
+                        head[l2] = s2;
+                    }
+                } else {
+                    int r = 0, q = 0;   // round and position of the next non-empty pair
+                    for (int x = 0; x < nonempty; ++x) {
+                        const int s2 = (r & 1) ? nstreams - 1 - q : q;
+                        scount[s2]++;
+                        scols[s2] += plen[lo + x];
+                        if (++q == nstreams) { q = 0; ++r; }
+                    }
+                }
+                hmark(ctx, "p_deal");
+                int slot = 0;
+                int64_t col = 0;
+                for (int s = 0; s < nstreams; ++s) {
+                    h_slot0[s] = slot;
+                    h_sbeg[s] = col;
+                    ((int32_t *)(hs + o_slen))[s] = (int32_t)scols[s];
+                    slot += scount[s];
+                    col += scols[s];
+                    h_scb[s] = (int64_t)code_words;
+                    h_sbb[s] = (int64_t)bound_elems;
+                    if (pk) {
+                        // stream pair (s, s+1) shares the tiles and boundary rows of a
+                        // lane group, sized by the longer stream
+                        if (s & 1) {
+                            h_scb[s] = h_scb[s - 1];
+                            h_sbb[s] = h_sbb[s - 1];
+                            continue;
+                        }
+                        const int64_t cq = std::max(scols[s], s + 1 < nstreams ? scols[s + 1] : (int64_t)0);
+                        if (tb) code_words += (size_t)passes * ((cq + LS - 1 + 7) / 8) * LS * 8 * WQ;
+                        if (passes > 1) bound_elems += (size_t)(passes - 1) * cq;
                         continue;
                     }
-                    const int64_t cq = std::max(scols[s], s + 1 < nstreams ? scols[s + 1] : (int64_t)0);
-                    if (tb) code_words += (size_t)passes * ((cq + LS - 1 + 7) / 8) * LS * 8 * WQ;
-                    if (passes > 1) bound_elems += (size_t)(passes - 1) * cq;
-                    continue;
+                    if (tb) code_words += (size_t)passes * ((scols[s] + LS - 1 + 7) / 8) * LS * 8 * W;
+                    if (passes > 1) bound_elems += (size_t)(passes - 1) * scols[s];
                 }
-                if (tb) code_words += (size_t)passes * ((scols[s] + LS - 1 + 7) / 8) * LS * 8 * W;
-                if (passes > 1) bound_elems += (size_t)(passes - 1) * scols[s];
-            }
-            h_sbeg[nstreams] = col;
-            total_cols = col;
-            hmark(ctx, "p_streams");
-            if (lpt) {
-                // slots of each stream in dealing order (longest first): the
-                // pairs are sorted by stream in host memory first, so that the
-                // pinned plan is written sequentially
-                std::vector<int32_t> &cur = ctx->h_cur, &ord = ctx->h_nxt;
-                cur.assign(h_slot0, h_slot0 + nstreams);
-                if ((int)ord.size() < nonempty) ord.resize(nonempty);
-                for (int x = 0; x < nonempty; ++x) ord[cur[sof[x]]++] = x;
-                for (int s2 = 0, qs = 0; s2 < nstreams; ++s2) {
-                    int64_t c = h_sbeg[s2];
-                    for (int pl = 0; pl < scount[s2]; ++pl, ++qs) {
-                        const int x = ord[qs];
-                        h_spid[qs] = pids[lo + x];
-                        h_scol[qs] = c;
-                        h_sstr[qs] = s2;
-                        c += plen[lo + x];
+                total_cols = col;
+                hmark(ctx, "p_streams");
+                if (lpt) {
+                    // slots of each stream in dealing order (longest first): the
+                    // pairs are sorted by stream in host memory first, so that the
+                    // pinned plan is written sequentially
+                    std::vector<int32_t> &cur = ctx->h_cur, &ord = ctx->h_nxt;
+                    cur.assign(h_slot0, h_slot0 + nstreams);
+                    if ((int)ord.size() < nonempty) ord.resize(nonempty);
+                    for (int x = 0; x < nonempty; ++x) ord[cur[sof[x]]++] = x;
+                    for (int s2 = 0, qs = 0; s2 < nstreams; ++s2) {
+                        int64_t c = h_sbeg[s2];
+                        for (int pl = 0; pl < scount[s2]; ++pl, ++qs) {
+                            const int x = ord[qs];
+                            h_spid[qs] = pids[lo + x];
+                            h_scol[qs] = c;
+                            h_sstr[qs] = s2;
+                            c += plen[lo + x];
+                        }
                     }
+                } else {
+                    // slots stream by stream (sequential writes): the pl-th pair of
+                    // stream s is non-empty pair pl * nstreams + (pl odd ? nstreams - 1 - s : s)
+                    for (int s = 0; s < nstreams; ++s) {
+                        int64_t c = h_sbeg[s];
+                        for (int pl = 0, qs = h_slot0[s]; pl < scount[s]; ++pl, ++qs) {
+                            const int x = pl * nstreams + ((pl & 1) ? nstreams - 1 - s : s);
+                            h_spid[qs] = pids[lo + x];
+                            h_scol[qs] = c;
+                            h_sstr[qs] = s;
+                            c += plen[lo + x];
+                        }
+                    }
+                }
+                for (int x = nonempty; x < cn; ++x) {   // empty pairs after the streamed ones
+                    h_spid[x] = pids[lo + x];
+                    h_scol[x] = 0;
+                    h_sstr[x] = 0;
                 }
             } else {
-                // slots stream by stream (sequential writes): the pl-th pair of
-                // stream s is non-empty pair pl * nstreams + (pl odd ? nstreams - 1 - s : s)
-                for (int s = 0; s < nstreams; ++s) {
-                    int64_t c = h_sbeg[s];
-                    for (int pl = 0, qs = h_slot0[s]; pl < scount[s]; ++pl, ++qs) {
-                        const int x = pl * nstreams + ((pl & 1) ? nstreams - 1 - s : s);
-                        h_spid[qs] = pids[lo + x];
-                        h_scol[qs] = c;
-                        h_sstr[qs] = s;
-                        c += plen[lo + x];
+                int32_t *h_order = (int32_t *)(hs + o_order);
+                int32_t *h_gnmax = (int32_t *)(hs + o_gnmax);
+                int64_t *h_gcb = (int64_t *)(hs + o_gcb);
+                const int nst = (m + hk::kT - 1) / hk::kT;
+                for (int g = 0; g < ngroups; ++g) {
+                    int nmax = 0;
+                    for (int l = 0; l < 64; ++l) {
+                        const int x = lo + g * 64 + l;
+                        h_order[g * 64 + l] = x < hi ? pids[x] : -1;
+                        if (x < hi) nmax = std::max(nmax, plen[x]);
                     }
+                    h_gnmax[g] = nmax;
+                    h_gcb[g] = (int64_t)code_words;
+                    // walk entry q = g * 64 + l is the pair in lane l of group g
+                    for (int l = 0; l < 64 && lo + g * 64 + l < hi; ++l) {
+                        const int q = g * 64 + l;
+                        h_cbase[q] = (int64_t)code_words;
+                        h_ccol[q] = l;
+                        h_cstr[q] = nmax;
+                    }
+                    if (tb) code_words += (size_t)nst * ((nmax + 3) / 4) * 512;
                 }
             }
-            for (int x = nonempty; x < cn; ++x) {   // empty pairs after the streamed ones
-                h_spid[x] = pids[lo + x];
-                h_scol[x] = 0;
-                h_sstr[x] = 0;
-            }
-        } else {
-            int32_t *h_order = (int32_t *)(hs + o_order);
-            int32_t *h_gnmax = (int32_t *)(hs + o_gnmax);
-            int64_t *h_gcb = (int64_t *)(hs + o_gcb);
-            const int nst = (m + hk::kT - 1) / hk::kT;
-            for (int g = 0; g < ngroups; ++g) {
-                int nmax = 0;
-                for (int l = 0; l < 64; ++l) {
-                    const int x = lo + g * 64 + l;
-                    h_order[g * 64 + l] = x < hi ? pids[x] : -1;
-                    if (x < hi) nmax = std::max(nmax, plen[x]);
-                }
-                h_gnmax[g] = nmax;
-                h_gcb[g] = (int64_t)code_words;
-                // walk entry q = g * 64 + l is the pair in lane l of group g
-                for (int l = 0; l < 64 && lo + g * 64 + l < hi; ++l) {
-                    const int q = g * 64 + l;
-                    h_cbase[q] = (int64_t)code_words;
-                    h_ccol[q] = l;
-                    h_cstr[q] = nmax;
-                }
-                if (tb) code_words += (size_t)nst * ((nmax + 3) / 4) * 512;
-            }
+            hmark(ctx, "plan");
+            RCHK(plan_dev(ctx, pb.total, st, &dplan));
+            HCHK(hipMemcpyAsync(dplan, hs, pb.total, hipMemcpyHostToDevice, st));
+            stage_copied(ctx);
         }
-        hmark(ctx, "plan");
-        char *dplan = nullptr;
-        RCHK(plan_dev(ctx, pb.total, st, &dplan));
-        HCHK(hipMemcpyAsync(dplan, hs, pb.total, hipMemcpyHostToDevice, st));
-        RCHK(record(ctx, ctx->ev_stage, st));
-        ctx->stage_pending = true;
         std::array<hipEvent_t, 3> *tv = nullptr;
         RCHK(tev_next(ctx, &tv));
+        hk::Timed tfwd, tend;   // (none while a graph is captured)
+        if (!ctx->capturing) {
+            tfwd = hk::Timed{(*tv)[0], (*tv)[1]};
+            tend = hk::Timed{nullptr, (*tv)[2]};
+        }
 
         if (tb) RCHK(grow(ctx, ctx->codes, std::max<size_t>(4, code_words * 4)));
         if (ctx->fault_chunk == (int)ci) {
@@ -854,11 +1011,12 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
             unsigned long long *keys = (unsigned long long *)ctx->sbuf.p;
             uint8_t *sres = (uint8_t *)ctx->sbuf.p + keys_b;
             if (passes > 1) RCHK(grow(ctx, ctx->bound, std::max<size_t>(8, bound_elems * 8)));
-            hipLaunchKernelGGL(hk::stage_stream_kernel, dim3(nslots), dim3(128), 0, st, sq->residues, sq->offsets,
-                               (const int32_t *)(dplan + o_spid), (const int64_t *)(dplan + o_scol), nslots,
-                               p16 ? S.alpha : 31, sres, keys);
-            HCHK(hipGetLastError());
-            RCHK(record(ctx, (*tv)[0], st));
+            if (!dev) {
+                hipLaunchKernelGGL(hk::stage_stream_kernel, dim3(nslots), dim3(128), 0, st, sq->residues, sq->offsets,
+                                   (const int32_t *)(dplan + o_spid), (const int64_t *)(dplan + o_scol), nslots,
+                                   p16 ? S.alpha : 31, sres, keys);
+                HCHK(hipGetLastError());
+            }
             hk::StreamArgs a{};
             a.mat = S.dmat;
             a.alpha = S.alpha;
@@ -867,6 +1025,7 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
             a.passes = passes;
             a.sres = sres;
             a.sbeg = (const int64_t *)(dplan + o_sbeg);
+            a.slen = (const int32_t *)(dplan + o_slen);
             a.nstreams = nstreams;
             a.ge = S.ge;
             a.goe = S.goe;
@@ -878,20 +1037,20 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
             a.sbbase = (const int64_t *)(dplan + o_sbb);
             const int waves = ((pk ? (nstreams + 1) / 2 : nstreams) + NS - 1) / NS;
             const int grid = (waves + wg_waves - 1) / wg_waves;
-            if (pk) launch_stream16(R, LS, a, tb, grid, wg_waves * 64, lds_stream, st);
-            else launch_stream(R, LS, a, tb, endc, p16, grid, wg_waves * 64, lds_stream, st);
+            if (pk) launch_stream16(R, LS, a, tb, grid, wg_waves * 64, lds_stream, st, tfwd);
+            else launch_stream(R, LS, a, tb, endc, p16, grid, wg_waves * 64, lds_stream, st, tfwd);
             HCHK(hipGetLastError());
-            RCHK(record(ctx, (*tv)[1], st));
-            hipLaunchKernelGGL(hk::decode_keys_kernel, dim3(grid_for(nslots, 256, 1 << 30)), dim3(256), 0, st,
-                               (const unsigned long long *)keys, (const int32_t *)(dplan + o_spid), nslots, out.score,
-                               endc ? out.endcell : (int32_t *)nullptr);
-            HCHK(hipGetLastError());
+            if (!tb) {   // (with traceback the walk reads the keys)
+                hk::launch_timed(tend, hk::decode_keys_kernel, dim3(grid_for(nslots, 256, 1 << 30)), dim3(256), 0, st,
+                                 (const unsigned long long *)keys, (const int32_t *)(dplan + o_spid), nslots, out.score,
+                                 endc ? out.endcell : (int32_t *)nullptr, (int4 *)out.cells);
+                HCHK(hipGetLastError());
+            }
         } else {
             const int slots = ctx->num_cu * 16;
             const int grid = std::max(1, std::min(ngroups, slots));
-            RCHK(grow(ctx, ctx->bound, (size_t)grid * 64 * strip_cols(nmax_all) * 8));
+            RCHK(grow(ctx, ctx->bound, (size_t)grid * 64 * strip_cols(chunk_nmax) * 8));
             RCHK(launch_fill((uint32_t *)counter, 0u, 2, st));
-            RCHK(record(ctx, (*tv)[0], st));
             hk::InterArgs a{};
             a.mat = S.dmat;
             a.alpha = S.alpha;
@@ -911,10 +1070,9 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
             a.codes = tb ? (uint32_t *)ctx->codes.p : nullptr;
             a.gcode_base = (const int64_t *)(dplan + o_gcb);
             a.bound = (int2 *)ctx->bound.p;
-            a.bstride = (int64_t)64 * strip_cols(nmax_all);
-            launch_inter(a, tb, endc, grid, st);
+            a.bstride = (int64_t)64 * strip_cols(chunk_nmax);
+            launch_inter(a, tb, endc, grid, st, tfwd);
             HCHK(hipGetLastError());
-            RCHK(record(ctx, (*tv)[1], st));
         }
         ++launches;
         if (tb) {
@@ -931,6 +1089,8 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
                 w.slot_pid = (const int32_t *)(dplan + o_spid);
                 w.slot_col = (const int64_t *)(dplan + o_scol);
                 w.sbeg = (const int64_t *)(dplan + o_sbeg);
+                w.slen = (const int32_t *)(dplan + o_slen);
+                w.keys = (const unsigned long long *)ctx->sbuf.p;
                 w.slot0 = (const int32_t *)(dplan + o_slot0);
                 w.slot_stream = (const int32_t *)(dplan + o_sstr);
                 w.scb = (const int64_t *)(dplan + o_scb);
@@ -965,19 +1125,20 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
             const size_t wlds = hk::walk_lds_bytes(route == kRouteIntra ? WQ : 1, m, cl, w.glds != 0);
             if (route == kRouteIntra) {
                 if (pk) {
-                    if (cl) hipLaunchKernelGGL((hk::walk_kernel<false, true, true>), wg, dim3(256), wlds, st, w);
-                    else hipLaunchKernelGGL((hk::walk_kernel<false, false, true>), wg, dim3(256), wlds, st, w);
+                    if (cl) hk::launch_timed(tend, (hk::walk_kernel<false, true, true>), wg, dim3(256), wlds, st, w);
+                    else hk::launch_timed(tend, (hk::walk_kernel<false, false, true>), wg, dim3(256), wlds, st, w);
                 } else {
-                    if (cl) hipLaunchKernelGGL((hk::walk_kernel<false, true, false>), wg, dim3(256), wlds, st, w);
-                    else hipLaunchKernelGGL((hk::walk_kernel<false, false, false>), wg, dim3(256), wlds, st, w);
+                    if (cl) hk::launch_timed(tend, (hk::walk_kernel<false, true, false>), wg, dim3(256), wlds, st, w);
+                    else hk::launch_timed(tend, (hk::walk_kernel<false, false, false>), wg, dim3(256), wlds, st, w);
                 }
             } else {
-                if (cl) hipLaunchKernelGGL((hk::walk_kernel<true, true, false>), wg, dim3(256), wlds, st, w);
-                else hipLaunchKernelGGL((hk::walk_kernel<true, false, false>), wg, dim3(256), wlds, st, w);
+                if (cl) hk::launch_timed(tend, (hk::walk_kernel<true, true, false>), wg, dim3(256), wlds, st, w);
+                else hk::launch_timed(tend, (hk::walk_kernel<true, false, false>), wg, dim3(256), wlds, st, w);
             }
             HCHK(hipGetLastError());
+        } else if (route != kRouteIntra) {
+            RCHK(record(ctx, (*tv)[2], st));
         }
-        RCHK(record(ctx, (*tv)[2], st));
         hmark(ctx, "launch");
         if (ctx->progress && chunks.size() > 1 && !ctx->capturing) {
             // progress lines wait for each chunk; otherwise the host plans the
@@ -1097,7 +1258,7 @@ int autotune(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, co
             RCHK(run_batch(ctx, S, center, m, sq, sample.data(), (int)sample.size(), tb, endc, c.route, out, st, c));
             float wk = 0.f;
             RCHK(tev_sum(ctx, &ms, &wk));
-            RCHK(stage_wait(ctx));
+            ctx->stage_pending = false;   // the last event follows the plan's copy
         }
         if (ms < best_ms) {
             best_ms = ms;
@@ -1130,8 +1291,7 @@ int upload_matrix(halign_ctx *ctx, const halign_scoring *sc, hipStream_t st, Sco
     RCHK(stage_host(ctx, bytes, &hs));
     memcpy(hs, sc->matrix_host, bytes);
     HCHK(hipMemcpyAsync(ctx->spbuf.p, hs, bytes, hipMemcpyHostToDevice, st));
-    RCHK(record(ctx, ctx->ev_stage, st));
-    ctx->stage_pending = true;
+    stage_copied(ctx);
     S->dmat = (const int8_t *)ctx->spbuf.p;
     S->hmat = sc->matrix_host;
     S->alpha = sc->alphabet;
@@ -1142,8 +1302,9 @@ int upload_matrix(halign_ctx *ctx, const halign_scoring *sc, hipStream_t st, Sco
 
 // Every residue code must be below the alphabet size (HALIGN_E_INVALID).
 // The check is enqueued without waiting: the kernels are memory-safe for any
-// code (they mask codes to 5 bits), and the result lands in pinned host memory
-// that validate_check() reads after the call's synchronisation point.
+// code (they mask codes to 5 bits), and its result comes to flag_host (by
+// flag_fetch, or with the merge's width) for validate_check() to read after the
+// call's synchronisation point.
 int validate_codes(halign_ctx *ctx, int alpha, const uint8_t *res, int64_t nres, const uint8_t *center, int m,
                    hipStream_t st) {
     RCHK(grow(ctx, ctx->counter, 256));
@@ -1172,8 +1333,13 @@ int validate_codes(halign_ctx *ctx, int alpha, const uint8_t *res, int64_t nres,
                            center, n2, tag << 8, flag);
         HCHK(hipGetLastError());
     }
-    HCHK(hipMemcpyAsync(ctx->flag_host, flag, 4, hipMemcpyDeviceToHost, st));
     ctx->flag_alpha = alpha;
+    return HALIGN_OK;
+}
+
+// The check's result to the host: flag_host holds it once the stream has passed.
+int flag_fetch(halign_ctx *ctx, hipStream_t st) {
+    HCHK(hipMemcpyAsync(ctx->flag_host, (uint32_t *)ctx->counter.p + 8, 4, hipMemcpyDeviceToHost, st));
     return HALIGN_OK;
 }
 
@@ -1190,7 +1356,9 @@ int validate_check(halign_ctx *ctx) {
 int validate_now(halign_ctx *ctx, int alpha, const uint8_t *res, int64_t nres, const uint8_t *center, int m,
                  hipStream_t st) {
     RCHK(validate_codes(ctx, alpha, res, nres, center, m, st));
+    RCHK(flag_fetch(ctx, st));
     HCHK(hipStreamSynchronize(st));
+    ctx->stage_pending = false;   // whatever was copied on the stream has been read
     return validate_check(ctx);
 }
 
@@ -1200,7 +1368,7 @@ int validate_now(halign_ctx *ctx, int alpha, const uint8_t *res, int64_t nres, c
 // 200 (93): packed streams 11.4 (5.1) ms, 32-bit streams of 16 lanes 16.7
 // (8.5), one pair per lane 20.7 (10.1); 270,000 pairs score-only on 200: packed
 // streams 3.7 ms, one pair per lane 7.3.
-int route_of(uint32_t flags, const halign_scoring *sc, int m, const halign_seqs *sq, bool tb) {
+int route_of(uint32_t flags, const halign_scoring *sc, int m, const halign_seqs *sq, bool tb, int longest) {
     const uint32_t r = flags & (3u << 4);
     if (r == HALIGN_ROUTE_INTER) return kRouteInter;
     if (r == HALIGN_ROUTE_INTRA) return kRouteIntra;
@@ -1209,11 +1377,9 @@ int route_of(uint32_t flags, const halign_scoring *sc, int m, const halign_seqs 
         if (!strcmp(e, "inter")) return kRouteInter;
     }
     if (sq->n < 64 * 4 * 1024) return kRouteIntra;
-    int64_t longest = 0;
-    for (int k = 0; k < sq->n; ++k) longest = std::max(longest, sq->offsets_host[k + 1] - sq->offsets_host[k]);
     int smax = 1;
     for (int x = 0; x < sc->alphabet * sc->alphabet; ++x) smax = std::max(smax, (int)sc->matrix_host[x]);
-    const int64_t top = smax * std::min<int64_t>(m, longest);
+    const int64_t top = (int64_t)smax * std::min(m, longest);
     if (tb) return top <= 32000 ? kRouteIntra : kRouteInter;
     return top < 15000 && sc->gap_open + sc->gap_extend <= 256 ? kRouteIntra : kRouteInter;
 }
@@ -1406,11 +1572,11 @@ int halign_encode(const uint8_t *ascii, int64_t len, uint8_t *codes, void *strea
 static int sw_batch_body(halign_ctx *ctx, const halign_scoring *sc, const uint8_t *center, int32_t m,
                           const halign_seqs *seqs, uint32_t flags, int32_t *score, int32_t *cells, uint16_t *ins,
                           uint32_t *aligned, void *stream, int32_t *G = nullptr, int gskip = -1,
-                          bool checked = false) {
+                          int longest = -1, bool fetch = true) {
     if (!ctx) return fail(HALIGN_E_INVALID, "ctx is NULL");
-    if (!checked) {   // halign_msa has checked both already
+    if (longest < 0) {   // halign_msa has checked both already
         RCHK(check_scoring(sc));
-        RCHK(check_seqs(seqs));
+        RCHK(check_seqs(seqs, &longest));
     }
     if (m <= 0 || !center) return fail(HALIGN_E_INVALID, "empty center");
     if (m >= 65536) return fail(HALIGN_E_UNSUPPORTED, "center length %d >= 65536", m);
@@ -1473,14 +1639,15 @@ static int sw_batch_body(halign_ctx *ctx, const halign_scoring *sc, const uint8_
     // residues run on the wavefront kernel, one pair per stream, in a launch
     // of their own; the rest keep the strip kernel.  Both write the same
     // outputs, each at its own pair ids.
-    const int route = tune.route >= 0 ? tune.route : route_of(flags, sc, m, seqs, tb);
+    const int route = tune.route >= 0 ? tune.route : route_of(flags, sc, m, seqs, tb, longest);
     const int64_t *oh = seqs->offsets_host;
     const bool split = route == kRouteInter && (flags & (3u << 4)) == HALIGN_ROUTE_AUTO;
     int nlong = 0;
     if (split)
         for (int k = 0; k < N; ++k) nlong += oh[k + 1] - oh[k] > kLongPair;
     if (nlong == 0) {
-        RCHK(run_batch(ctx, S, center, m, seqs, nullptr, N, tb, endc, route, out, st, tune));
+        RCHK(run_batch(ctx, S, center, m, seqs, nullptr, N, tb, endc, route, out, st, tune,
+                       (flags & HALIGN_GRAPH) ? -1 : longest));
     } else {
         // long pairs first in the id list, then the rest
         std::vector<int32_t> &ids = ctx->h_split;
@@ -1491,12 +1658,13 @@ static int sw_batch_body(halign_ctx *ctx, const halign_scoring *sc, const uint8_
         RCHK(run_batch(ctx, S, center, m, seqs, ids.data() + nlong, N - nlong, tb, endc, route, out, st, tune));
     }
     ctx->last_tune = {tune.route, tune.R, tune.smul, tune.LS > 0 ? tune.LS : 64, ctx->last_pk};
-    if (!tb && cells) {
-        // score-only with cells: report the end cell as (0, 0, i1, j1)
+    if (!tb && cells && ctx->last_stats[2] != kRouteIntra) {
+        // score-only with cells, one pair per lane: report the end cell as (0, 0, i1, j1)
         hipLaunchKernelGGL(hk::endcell_to_cells_kernel, dim3(grid_for(N, 256)), dim3(256), 0, st,
                            (const int32_t *)endcell, N, cells);
         HCHK(hipGetLastError());
     }
+    if (fetch) RCHK(flag_fetch(ctx, st));
     return HALIGN_OK;
 }
 
@@ -1527,9 +1695,10 @@ uint64_t fnv(uint64_t h, const void *p, size_t n) {
 static int sw_batch_async(halign_ctx *ctx, const halign_scoring *sc, const uint8_t *center, int32_t m,
                           const halign_seqs *seqs, uint32_t flags, int32_t *score, int32_t *cells, uint16_t *ins,
                           uint32_t *aligned, void *stream, int32_t *G = nullptr, int gskip = -1,
-                          bool checked = false) {
+                          int longest = -1, bool fetch = true) {
     if (!(flags & HALIGN_GRAPH))
-        return sw_batch_body(ctx, sc, center, m, seqs, flags, score, cells, ins, aligned, stream, G, gskip, checked);
+        return sw_batch_body(ctx, sc, center, m, seqs, flags, score, cells, ins, aligned, stream, G, gskip, longest,
+                             fetch);
     if (!ctx || !sc || !seqs || !sc->matrix_host || !seqs->offsets_host)
         return sw_batch_body(ctx, sc, center, m, seqs, flags, score, cells, ins, aligned, stream, G, gskip);
     hipStream_t st = (hipStream_t)stream;
@@ -1606,9 +1775,14 @@ extern "C" {
 int halign_sw_batch(halign_ctx *ctx, const halign_scoring *sc, const uint8_t *center, int32_t m,
                     const halign_seqs *seqs, uint32_t flags, int32_t *score, int32_t *cells, uint16_t *ins,
                     uint32_t *aligned, void *stream) {
-    RCHK(sw_batch_async(ctx, sc, center, m, seqs, flags, score, cells, ins, aligned, stream));
+    const int rc = sw_batch_async(ctx, sc, center, m, seqs, flags, score, cells, ins, aligned, stream);
+    if (rc != HALIGN_OK) {
+        if (ctx) RCHK(stage_close(ctx, (hipStream_t)stream));
+        return rc;
+    }
     if (ctx->flag_alpha) {
         HCHK(hipStreamSynchronize((hipStream_t)stream));
+        ctx->stage_pending = false;
         RCHK(validate_check(ctx));
     }
     return HALIGN_OK;
@@ -1616,16 +1790,22 @@ int halign_sw_batch(halign_ctx *ctx, const halign_scoring *sc, const uint8_t *ce
 
 }  // extern "C"
 
+static int emit_rows(halign_ctx *ctx, const halign_seqs *seqs, int32_t m, const uint16_t *ins,
+                     const uint32_t *aligned, const int32_t *G, const int64_t *col, int64_t width, uint8_t *msa,
+                     hipStream_t st);
+
 // col[p] = sum_{q<p} (G[q] + 1) and the MSA width (copied to the host and
 // synchronised when width_host is given).
+// check: the code check's flag comes to flag_host with the width.
 static int merge_offsets(halign_ctx *ctx, const int32_t *G, int m1, int64_t *col, int64_t *width_host,
-                         hipStream_t st) {
+                         hipStream_t st, bool check = false) {
     RCHK(grow(ctx, ctx->spbuf, 4096));
     int64_t *dwidth = (int64_t *)((char *)ctx->spbuf.p + 2048);
     const bool mail = width_host && ctx->mail_dev && !ctx->capturing;
     const int64_t seq = mail ? ++ctx->mail_seq : 0;
     hipLaunchKernelGGL(hk::merge_scan_kernel, dim3(1), dim3(1024), 0, st, G, m1, col, dwidth,
-                       mail ? ctx->mail_dev : nullptr, seq);
+                       mail ? ctx->mail_dev : nullptr, seq,
+                       check ? (const uint32_t *)ctx->counter.p + 8 : nullptr);
     HCHK(hipGetLastError());
     if (mail) {
         // spin on the mailbox (the kernel's release store of seq follows the
@@ -1644,7 +1824,9 @@ static int merge_offsets(halign_ctx *ctx, const int32_t *G, int m1, int64_t *col
         }
         __atomic_thread_fence(__ATOMIC_ACQUIRE);
         *width_host = mb[0];
+        if (check) *ctx->flag_host = (int)mb[2];
     } else if (width_host) {
+        if (check) RCHK(flag_fetch(ctx, st));
         HCHK(hipMemcpyAsync(width_host, dwidth, 8, hipMemcpyDeviceToHost, st));
         HCHK(hipStreamSynchronize(st));
     }
@@ -1684,7 +1866,15 @@ int halign_emit_rows(halign_ctx *ctx, const halign_seqs *seqs, int32_t m, const 
         return fail(HALIGN_E_INVALID, "bad arguments");
     RCHK(check_seqs(seqs));
     HCHK(hipSetDevice(ctx->device));
-    hipStream_t st = (hipStream_t)stream;
+    return emit_rows(ctx, seqs, m, ins, aligned, G, col, width, msa, (hipStream_t)stream);
+}
+
+}  // extern "C"
+
+// halign_emit_rows for checked arguments
+static int emit_rows(halign_ctx *ctx, const halign_seqs *seqs, int32_t m, const uint16_t *ins,
+                     const uint32_t *aligned, const int32_t *G, const int64_t *col, int64_t width, uint8_t *msa,
+                     hipStream_t st) {
     const int N = seqs->n;
     if (N == 0 || width == 0) return HALIGN_OK;
     const int m1 = m + 1, aw = (m + 31) / 32;
@@ -1738,6 +1928,8 @@ int halign_emit_rows(halign_ctx *ctx, const halign_seqs *seqs, int32_t m, const 
     return HALIGN_OK;
 }
 
+extern "C" {
+
 // Center selection -----------------------------------------------------------
 // The packed 16-bit score-only strip kernel applies when every H stays below
 // 15000: max S times the longest sequence (plus go + ge) stays below 15000,
@@ -1781,8 +1973,8 @@ static int run_groups(halign_ctx *ctx, const Scoring &S, const halign_seqs *sq, 
     char *dplan = nullptr;
     RCHK(plan_dev(ctx, pb.total, st, &dplan));
     HCHK(hipMemcpyAsync(dplan, hs, pb.total, hipMemcpyHostToDevice, st));
-    RCHK(record(ctx, ctx->ev_stage, st));
-    ctx->stage_pending = true;
+    stage_copied(ctx);
+    RCHK(stage_close(ctx, st));
     int nmax_all = 0;
     const int64_t *oh = sq->offsets_host;
     for (int k = 0; k < sq->n; ++k) nmax_all = std::max(nmax_all, (int)(oh[k + 1] - oh[k]));
@@ -2325,7 +2517,8 @@ int halign_msa(halign_ctx *ctx, const halign_scoring *sc, const halign_seqs *seq
     ctx->hmarks.clear();
     hmark(ctx, "start");
     RCHK(check_scoring(sc));
-    RCHK(check_seqs(seqs));
+    int longest = 0;
+    RCHK(check_seqs(seqs, &longest));
     hmark(ctx, "checks");
     const int N = seqs->n;
     if (N <= 0) return fail(HALIGN_E_INVALID, "empty set");
@@ -2363,19 +2556,25 @@ int halign_msa(halign_ctx *ctx, const halign_scoring *sc, const halign_seqs *seq
     int64_t *col = (int64_t *)(wb + o_col);
     const uint8_t *cen = seqs->residues + oh[c];
     // the walk max-merges every pair's insertion counts into G (the center's own are all zero)
-    RCHK(sw_batch_async(ctx, sc, cen, m, seqs, HALIGN_TRACEBACK | (ctx->use_graph ? HALIGN_GRAPH : 0u), score, cells,
-                        ins, al, stream, G, c, true));
-    hipLaunchKernelGGL(hk::center_row_kernel, dim3(1), dim3(256), 0, st, ins, al, c, m, aw);
-    HCHK(hipGetLastError());
+    // and leaves the center's own row; the code check's result comes with the
+    // width (a captured batch copies it itself)
+    const bool graph = ctx->use_graph != 0;
+    const int rcb = sw_batch_async(ctx, sc, cen, m, seqs, HALIGN_TRACEBACK | (graph ? HALIGN_GRAPH : 0u), score, cells,
+                                   ins, al, stream, G, c, longest, graph);
     int64_t width = 0;
     hmark(ctx, "batch");
-    RCHK(merge_offsets(ctx, G, m + 1, col, &width, st));   // synchronises
+    const int rcm = rcb != HALIGN_OK ? rcb : merge_offsets(ctx, G, m + 1, col, &width, st, !graph);   // synchronises
+    if (rcm != HALIGN_OK) {
+        RCHK(stage_close(ctx, st));
+        return rcm;
+    }
+    ctx->stage_pending = false;
     hmark(ctx, "sync");
     RCHK(validate_check(ctx));
     uint8_t *out = (uint8_t *)alloc((size_t)N * (size_t)width, user);
     if (!out && width > 0) return fail(HALIGN_E_NOMEM, "allocator returned NULL for %lld bytes", (long long)(N * width));
     hmark(ctx, "alloc");
-    RCHK(halign_emit_rows(ctx, seqs, m, ins, al, G, col, width, out, stream));
+    RCHK(emit_rows(ctx, seqs, m, ins, al, G, col, width, out, st));
     hmark(ctx, "rows");
     hmark_print(ctx);
     *msa = out;
@@ -2937,8 +3136,10 @@ int halign_nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seq
     // the code check and the center's copy to the host share one wait
     RCHK(validate_codes(ctx, sc->alphabet, seqs->residues, oh[N], nullptr, 0, st));
     std::vector<uint8_t> c(m);
+    RCHK(flag_fetch(ctx, st));
     if (m > 0) HCHK(hipMemcpyAsync(c.data(), dc, m, hipMemcpyDeviceToHost, st));
     HCHK(hipStreamSynchronize(st));
+    ctx->stage_pending = false;
     RCHK(validate_check(ctx));
     // the center's segments, on the host: segment q (k codes 0..3) is indexed
     // when no other such segment has the same string
@@ -3147,7 +3348,7 @@ int halign_nuc_msa(halign_ctx *ctx, const halign_scoring *sc, const halign_seqs 
     RCHK(merge_offsets(ctx, G, m + 1, col, &width, st));
     uint8_t *out = (uint8_t *)alloc((size_t)N * (size_t)width, user);
     if (!out && width > 0) return fail(HALIGN_E_NOMEM, "allocator returned NULL for %lld bytes", (long long)(N * width));
-    RCHK(halign_emit_rows(ctx, seqs, m, ins, al, G, col, width, out, stream));
+    RCHK(emit_rows(ctx, seqs, m, ins, al, G, col, width, out, st));
     *msa = out;
     *width_host = width;
     return HALIGN_OK;
@@ -3719,8 +3920,8 @@ int halign_nj_tree(halign_ctx *ctx, const uint8_t *msa, int32_t n, int64_t width
         }
         char *d = (char *)ctx->njrows.p;
         HCHK(hipMemcpyAsync(d, hs, bytes, hipMemcpyHostToDevice, st));
-        RCHK(record(ctx, ctx->ev_stage, st));
-        ctx->stage_pending = true;
+        stage_copied(ctx);
+        RCHK(stage_close(ctx, st));
         hipLaunchKernelGGL(hk::pd_gather_kernel, dim3((unsigned)nr), dim3(256), 0, st, (const double *)ctx->njF.p, N,
                            (const int32_t *)d, (const int32_t *)(d + o_lx), (const hk::PdList *)(d + o_ls),
                            (double *)ctx->njD.p);

@@ -4,8 +4,8 @@
 namespace hk {
 
 void launch_stream_r1(int R, int LS, const StreamArgs &a, bool tb, bool endc, bool p16, int grid, int threads, size_t lds,
-                      hipStream_t st) {
-    launch_stream_range<1, 5>(R, LS, a, tb, endc, p16, grid, threads, lds, st);
+                      hipStream_t st, const Timed &t) {
+    launch_stream_range<1, 5>(R, LS, a, tb, endc, p16, grid, threads, lds, st, t);
 }
 
 }  // namespace hk

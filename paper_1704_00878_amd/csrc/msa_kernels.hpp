@@ -129,9 +129,10 @@ __global__ void merge_max_kernel(const uint16_t *ins, int n, int m1, int32_t *G)
 // col[p] = sum_{q<p} (G[q] + 1); width = m + sum G.  One workgroup of 1024.
 // mail (optional, host memory mapped for the device): mail[0] = width, then
 // mail[1] = seq with a system-scope release, so a host spinning on mail[1]
-// reads the width without a stream synchronisation
+// reads the width (and, in mail[2], the flag word) without a stream
+// synchronisation
 __global__ void __launch_bounds__(1024) merge_scan_kernel(const int32_t *G, int m1, int64_t *col, int64_t *width,
-                                                          int64_t *mail, int64_t seq) {
+                                                          int64_t *mail, int64_t seq, const uint32_t *flag) {
     __shared__ int64_t part[1024];
     const int tid = threadIdx.x;
     const int per = (m1 + 1023) / 1024;
@@ -152,6 +153,7 @@ __global__ void __launch_bounds__(1024) merge_scan_kernel(const int32_t *G, int 
         *width = part[1023] - 1;
         if (mail) {
             __hip_atomic_store(mail, part[1023] - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            if (flag) __hip_atomic_store(mail + 2, (int64_t)*flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             __hip_atomic_store(mail + 1, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }

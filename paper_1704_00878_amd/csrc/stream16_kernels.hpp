@@ -130,12 +130,12 @@ sw_stream16_kernel(StreamArgs a) {
     int CA = 0, CB = 0, slotA = 0, slotB = 0;
     if (actA) {
         bA = a.sbeg[sA];
-        CA = (int)(a.sbeg[sA + 1] - bA);
+        CA = a.slen[sA];
         slotA = a.sslot0[sA];
     }
     if (actB) {
         bB = a.sbeg[sB];
-        CB = (int)(a.sbeg[sB + 1] - bB);
+        CB = a.slen[sB];
         slotB = a.sslot0[sB];
     }
     const int C = max(CA, CB);

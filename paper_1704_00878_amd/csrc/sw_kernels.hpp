@@ -127,7 +127,8 @@ struct StreamArgs {
     const uint8_t *center;    // m residues
     int m, passes;
     const uint8_t *sres;      // staged stream residues (bit 7: first column of a pair)
-    const int64_t *sbeg;      // per stream: first column in sres (nstreams + 1 entries)
+    const int64_t *sbeg;      // per stream: first column in sres
+    const int32_t *slen;      // per stream: columns
     int nstreams;
     int ge, goe;
     unsigned long long *keys; // per pair-slot end-cell keys (zeroed); score-only: H << 32
@@ -197,7 +198,7 @@ sw_stream_kernel(StreamArgs a) {
     int C = 0, slot0 = 0;
     if (active) {
         b0 = a.sbeg[sid];
-        C = (int)(a.sbeg[sid + 1] - b0);
+        C = a.slen[sid];
         slot0 = a.sslot0[sid];
     }
     // the wavefront runs to its longest stream

@@ -40,8 +40,8 @@ struct WalkArgs {
     const int32_t *pids;      // pairs to walk (indices into N)
     int npairs;
     int ge, goe;
-    const int32_t *score;
-    const int32_t *endcell;   // [N][2]
+    int32_t *score;           // read (strip layout) or written
+    const int32_t *endcell;   // [N][2] (strip layout)
     const uint32_t *codes;
     // layout per pair id: kind 0 = wavefront (R rows/lane), 1 = strip (16 rows)
     const int64_t *cbase;     // strip, per walk entry: word base of the group
@@ -62,7 +62,9 @@ struct WalkArgs {
     // empty pairs sit in slots after the streamed ones)
     const int32_t *slot_pid;
     const int64_t *slot_col;
-    const int64_t *sbeg;      // [nstreams + 1]
+    const int64_t *sbeg;      // [nstreams]
+    const int32_t *slen;      // [nstreams] columns
+    const unsigned long long *keys;   // [slots] end-cell keys (wavefront layout; the walk writes the scores)
     const int32_t *slot0;     // [nstreams]
     const int32_t *slot_stream;   // [slots] the stream s of each slot
     const int64_t *scb;       // [nstreams] code word base
@@ -146,9 +148,21 @@ walk_kernel(WalkArgs a) {
         const int n = (int)(a.off[pid + 1] - so);
         uint16_t *ins = a.ins + (int64_t)pid * (m + 1);
         uint32_t *al = a.aligned + (int64_t)pid * a.aw;
-        int v = a.score[pid];
+        int v;
+        unsigned long long key = 0;
+        if (STRIP) {
+            v = a.score[pid];
+        } else {
+            key = a.keys[w];
+            v = (int)(key >> 32);
+            if (k == 0) a.score[pid] = v;
+        }
         int4 *cp = reinterpret_cast<int4 *>(a.cells) + pid;
         int32_t *gmax = (a.G && pid != a.gskip) ? (glds ? sG : a.G) : nullptr;
+        if (a.G && pid == a.gskip) {   // the center: its row is the gapped center itself
+            for (int x = k; x < a.aw; x += 16) al[x] = x == a.aw - 1 && (m & 31) ? (1u << (m & 31)) - 1u : 0xffffffffu;
+            return;
+        }
         if (v <= 0) {
             if (k == 0) {
                 ins[0] = (uint16_t)n;
@@ -157,7 +171,8 @@ walk_kernel(WalkArgs a) {
             }
             return;
         }
-        const int i1 = a.endcell[2 * pid], j1 = a.endcell[2 * pid + 1];
+        const int i1 = STRIP ? a.endcell[2 * pid] : 0xffff - (int)(key & 0xffff) + 1;
+        const int j1 = STRIP ? a.endcell[2 * pid + 1] : 0xffff - (int)((key >> 16) & 0xffff);
         int64_t base;
         int half = 0;   // packed wavefront layout: the stream's half of each code word
         int ccol, stride;
@@ -169,10 +184,10 @@ walk_kernel(WalkArgs a) {
             const int lo = a.slot_stream[w];
             base = a.scb[lo];
             ccol = (int)(a.slot_col[w] - a.sbeg[lo]);
-            int cs = (int)(a.sbeg[lo + 1] - a.sbeg[lo]);
+            int cs = a.slen[lo];
             if (PK) {   // the stream pair shares the longer stream's tiles
                 const int o = lo ^ 1;
-                if (o < a.nstreams) cs = max(cs, (int)(a.sbeg[o + 1] - a.sbeg[o]));
+                if (o < a.nstreams) cs = max(cs, a.slen[o]);
                 half = lo & 1;
             }
             stride = cs + (1 << a.lg_ls) - 1;

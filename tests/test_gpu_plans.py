@@ -95,3 +95,70 @@ def test_default_plan_many_pairs(H, ctx, tall):
     for tb in (False, True):
         plan, route = _same(H, ctx, H.Scoring(mat), H.DeviceSeqs(seqs), center, tb)
         assert route == (1 if tall else 0) and plan["packed"] == (0 if tall else 1)
+
+
+# batches planned on the device (from 2,048 pairs): the line and its neighbours,
+# a last round that is full, empty or nearly so, one pair per stream with empty
+# pairs among them, up to 64 rounds and beyond (planned on the host), one and
+# several center passes, on each kernel
+@pytest.mark.parametrize("lanes,pack", [(64, 0), (32, 0), (16, 0), (32, 1), (16, 1)])
+@pytest.mark.parametrize("n,streams,m", [(2047, 0, 70), (2048, 0, 70), (2049, 2048, 40), (2050, 1025, 530),
+                                         (2100, 1050, 40), (2100, 33, 40), (2113, 33, 40), (2053, 64, 1100),
+                                         (5003, 1000, 300)])
+def test_device_plan(H, ctx, n, streams, m, lanes, pack, monkeypatch):
+    if lanes != 64:
+        monkeypatch.setenv("HALIGN_STREAM_LANES", str(lanes))
+    monkeypatch.setenv("HALIGN_STREAM_PACK", str(pack))
+    if streams:
+        monkeypatch.setenv("HALIGN_MAX_STREAMS", str(streams))
+    rng = np.random.default_rng(n + m)
+    lens = rng.integers(30, 60, n)
+    lens[rng.integers(0, n, 40)] = 0
+    lens[rng.integers(0, n, 3)] = 75
+    ds = H.DeviceSeqs(synth.SeqSet.from_list([rng.integers(0, 20, int(L)).astype(np.uint8) for L in lens]))
+    for tb in (False, True):
+        plan, route = _same(H, ctx, H.Scoring(), ds, _center(rng, m), tb)
+        assert plan["packed"] == pack and route == 0
+
+
+# lengths on both sides of the line between the two planners
+@pytest.mark.parametrize("lanes,pack", [(64, 0), (32, 1)])
+@pytest.mark.parametrize("n,streams,long", [(2048, 700, 60), (3001, 1111, 300), (2500, 65, 8), (4096, 2048, 1)])
+def test_device_plan_long_tail(H, ctx, n, streams, long, lanes, pack, monkeypatch):
+    if lanes != 64:
+        monkeypatch.setenv("HALIGN_STREAM_LANES", str(lanes))
+    monkeypatch.setenv("HALIGN_STREAM_PACK", str(pack))
+    monkeypatch.setenv("HALIGN_MAX_STREAMS", str(streams))
+    rng = np.random.default_rng(n)
+    lens = rng.integers(10, 40, n)
+    lens[rng.permutation(n)[:long]] = rng.integers(2, 4, long) * 25 * n // streams // 2
+    ds = H.DeviceSeqs(synth.SeqSet.from_list([rng.integers(0, 20, int(L)).astype(np.uint8) for L in lens]))
+    for tb in (False, True):
+        plan, route = _same(H, ctx, H.Scoring(), ds, _center(rng, 90), tb)
+        assert plan["packed"] == pack and route == 0
+
+
+# whole alignments on the device's plan and on the host's (forced by the dealing
+# knob, in chunks under a small workspace, and captured), and with the code
+# check's error still raised
+@pytest.mark.parametrize("n,center", [(2048, 2047), (6001, 5)])
+def test_device_plan_msa(H, ctx, n, center, monkeypatch):
+    import torch
+    rng = np.random.default_rng(n)
+    seqs = synth.random_set(rng, n, 60, 130)
+    ds = H.DeviceSeqs(seqs)
+    rows = [H.halign_msa(ctx, H.Scoring(), ds, center)[0].cpu().clone()]
+    small = H.Context(0, workspace_cap=1 << 20)
+    rows.append(H.halign_msa(small, H.Scoring(), ds, center)[0].cpu().clone())
+    small.close()
+    monkeypatch.setenv("HALIGN_DEAL", "lpt")
+    rows.append(H.halign_msa(ctx, H.Scoring(), ds, center)[0].cpu().clone())
+    monkeypatch.delenv("HALIGN_DEAL")
+    for r in rows[1:]:
+        assert torch.equal(r, rows[0])
+    bad = ds.residues.clone()
+    ds.residues[int(seqs.offsets[n // 2])] = 25
+    with pytest.raises(H.HalignError):
+        H.halign_msa(ctx, H.Scoring(), ds, center)
+    ds.residues.copy_(bad)
+    assert torch.equal(H.halign_msa(ctx, H.Scoring(), ds, center)[0].cpu(), rows[0])
