@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <fstream>
 #include <initializer_list>
+#include <functional>
 #include <map>
 #include <sstream>
 #include <cstdarg>
@@ -119,8 +120,9 @@ struct halign_ctx {
     std::map<std::string, std::array<int, 5>> tuned;   // bucket -> {route, R, stream multiplier, lanes per stream, packed}
     std::string tune_file;    // optional cache file (HALIGN_TUNE_CACHE)
     int *flag_host = nullptr; // pinned: (tag << 8 | largest residue code) of the last validated call
-    int64_t *mail_host = nullptr, *mail_dev = nullptr;   // coherent pinned mailbox: width, sequence number
-    DevBuf nuctab, nucscr, nucdp;   // nucleotide path: segment table, matches and chains, stretch scratch
+    int64_t *mail_host = nullptr, *mail_dev = nullptr;   // coherent pinned mailbox: width, sequence number, flag, five counts
+    DevBuf nuctab, nucscr, nucdp;   // nucleotide path: segment table and matches, stretch lists, stretch scratch
+    int64_t nuc_list = 0, nuc_rows = 0, nuc_codes = 0, nuc_big = 0;   // entries that nucscr and nucdp are laid out for
     DevBuf rowck;                   // chunked rows: residues before each chunk of blocks, per row
     HostBuf njhost, njout;          // pinned: the tree's distances and the trees coming back
     DevBuf njF;                     // all rows' distances (sets where they are computed at once)
@@ -1794,6 +1796,25 @@ static int emit_rows(halign_ctx *ctx, const halign_seqs *seqs, int32_t m, const 
                      const uint32_t *aligned, const int32_t *G, const int64_t *col, int64_t width, uint8_t *msa,
                      hipStream_t st);
 
+// Spin until the mailbox holds seq or a later one (a kernel's release store, after its other
+// words); now and then ask the stream whether it failed or finished.
+static int mail_wait(halign_ctx *ctx, int64_t seq, hipStream_t st) {
+    volatile int64_t *mb = ctx->mail_host;
+    for (uint64_t it = 1;; ++it) {
+        if (mb[1] >= seq) break;
+        if ((it & 4095) == 0) {
+            const hipError_t q = hipStreamQuery(st);
+            if (q == hipSuccess) {
+                if (mb[1] >= seq) break;
+                return fail(HALIGN_E_DEVICE, "the stream finished without its message");
+            }
+            if (q != hipErrorNotReady) return fail(HALIGN_E_DEVICE, "%s", hipGetErrorString(q));
+        }
+    }
+    __atomic_thread_fence(__ATOMIC_ACQUIRE);
+    return HALIGN_OK;
+}
+
 // col[p] = sum_{q<p} (G[q] + 1) and the MSA width (copied to the host and
 // synchronised when width_host is given).
 // check: the code check's flag comes to flag_host with the width.
@@ -1808,23 +1829,9 @@ static int merge_offsets(halign_ctx *ctx, const int32_t *G, int m1, int64_t *col
                        check ? (const uint32_t *)ctx->counter.p + 8 : nullptr);
     HCHK(hipGetLastError());
     if (mail) {
-        // spin on the mailbox (the kernel's release store of seq follows the
-        // width); now and then ask the stream whether it failed or finished
-        volatile int64_t *mb = ctx->mail_host;
-        for (uint64_t it = 1;; ++it) {
-            if (mb[1] == seq) break;
-            if ((it & 4095) == 0) {
-                const hipError_t q = hipStreamQuery(st);
-                if (q == hipSuccess) {
-                    if (mb[1] == seq) break;
-                    return fail(HALIGN_E_DEVICE, "merge scan finished without its width");
-                }
-                if (q != hipErrorNotReady) return fail(HALIGN_E_DEVICE, "%s", hipGetErrorString(q));
-            }
-        }
-        __atomic_thread_fence(__ATOMIC_ACQUIRE);
-        *width_host = mb[0];
-        if (check) *ctx->flag_host = (int)mb[2];
+        RCHK(mail_wait(ctx, seq, st));
+        *width_host = ctx->mail_host[0];
+        if (check) *ctx->flag_host = (int)ctx->mail_host[2];
     } else if (width_host) {
         if (check) RCHK(flag_fetch(ctx, st));
         HCHK(hipMemcpyAsync(width_host, dwidth, 8, hipMemcpyDeviceToHost, st));
@@ -1890,8 +1897,8 @@ static int emit_rows(halign_ctx *ctx, const halign_seqs *seqs, int32_t m, const 
         RCHK(grow(ctx, ctx->rowck, 4 * (size_t)N * nck));
         int32_t *ck = (int32_t *)ctx->rowck.p;
         hk::RowsArgs ra{seqs->residues, seqs->offsets, N, m, ins, aligned, aw, G, col, width, 0, 0, 0, msa};
-        const int cgrid = std::max(1, std::min((N + 3) / 4, ctx->num_cu * 8));
-        hipLaunchKernelGGL(hk::rows_count_kernel, dim3(cgrid), dim3(256), 0, st, ra, ck, nck);
+        const int cgrid = std::max(1, std::min(N, ctx->num_cu * 8));
+        hipLaunchKernelGGL(hk::rows_count_kernel, dim3(cgrid), dim3(512), 0, st, ra, ck, nck);
         HCHK(hipGetLastError());
         const int64_t ntask = (int64_t)N * nck;
         const int egrid = (int)std::max<int64_t>(1, std::min<int64_t>((ntask + 3) / 4, (int64_t)ctx->num_cu * 8));
@@ -3085,40 +3092,16 @@ int halign_center_learned(halign_ctx *ctx, const halign_scoring *sc, const halig
 // ===========================================================================
 namespace {
 
-// exclusive sums of n int64 values (+ add each) into out, the total into
-// *total_dev (device, may be out + n) and *total_host
-int scan_i64(halign_ctx *ctx, const int64_t *in, int64_t n, int64_t add, int64_t *out, int64_t *total_dev,
-             int64_t *total_host, hipStream_t st) {
-    if (n <= hk::kScanTile) {
-        hipLaunchKernelGGL(hk::scan_i64_kernel, dim3(1), dim3(1024), 0, st, in, (int)n, add, out, total_dev);
-        HCHK(hipGetLastError());
-    } else {
-        const int64_t nt = (n + hk::kScanTile - 1) / hk::kScanTile;
-        if (nt > 0x7fffffff) return fail(HALIGN_E_UNSUPPORTED, "scan of %lld values", (long long)n);
-        RCHK(grow(ctx, ctx->sbuf, 16 * (size_t)nt + 256));
-        int64_t *part = (int64_t *)ctx->sbuf.p, *poff = part + nt;
-        hipLaunchKernelGGL(hk::scan_tile_kernel, dim3((unsigned)nt), dim3(1024), 0, st, in, n, add, out, part);
-        hipLaunchKernelGGL(hk::scan_i64_kernel, dim3(1), dim3(1024), 0, st, (const int64_t *)part, (int)nt,
-                           (int64_t)0, poff, total_dev);
-        hipLaunchKernelGGL(hk::scan_add_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, out, n,
-                           (const int64_t *)poff);
-        HCHK(hipGetLastError());
-    }
-    if (total_host) {   // NULL: the caller reads total_dev itself
-        HCHK(hipMemcpyAsync(total_host, total_dev, 8, hipMemcpyDeviceToHost, st));
-        HCHK(hipStreamSynchronize(st));
-    }
-    return HALIGN_OK;
-}
-
 size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 }  // namespace
 
-extern "C" {
-
-int halign_nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seqs *seqs, int32_t center, int32_t k,
-                     int32_t *score, uint16_t *ins, uint32_t *aligned, int32_t *G, void *stream) {
+// halign_nuc_align; with own_row the center's row is the gapped center itself.
+// after: enqueued behind the stretches (each time, where the scratch had to grow
+// and they ran again).
+static int nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seqs *seqs, int32_t center, int32_t k,
+                     int32_t *score, uint16_t *ins, uint32_t *aligned, int32_t *G, bool own_row,
+                     const std::function<int()> &after, void *stream) {
     if (!ctx || !score || !ins || !aligned) return fail(HALIGN_E_INVALID, "bad arguments");
     RCHK(check_scoring(sc));
     RCHK(check_seqs(seqs));
@@ -3133,69 +3116,33 @@ int halign_nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seq
     const uint8_t *dc = seqs->residues + oh[center];
     Scoring S;
     RCHK(upload_matrix(ctx, sc, st, &S));
-    // the code check and the center's copy to the host share one wait
     RCHK(validate_codes(ctx, sc->alphabet, seqs->residues, oh[N], nullptr, 0, st));
-    std::vector<uint8_t> c(m);
-    RCHK(flag_fetch(ctx, st));
-    if (m > 0) HCHK(hipMemcpyAsync(c.data(), dc, m, hipMemcpyDeviceToHost, st));
-    HCHK(hipStreamSynchronize(st));
-    ctx->stage_pending = false;
-    RCHK(validate_check(ctx));
-    // the center's segments, on the host: segment q (k codes 0..3) is indexed
-    // when no other such segment has the same string
+    // the center's segments: at most this many different strings, so the table
+    // is at most half full
     const int nsg = m / k;
-    std::vector<unsigned long long> key(nsg);
-    std::vector<int32_t> segscore(std::max(nsg, 1), 0);
-    std::vector<uint8_t> clean(nsg, 1);
-    for (int q = 0; q < nsg; ++q) {
-        unsigned long long kk = 0;
-        for (int t = 0; t < k; ++t) {
-            const int b = c[q * k + t];
-            if (b > 3) clean[q] = 0;
-            kk |= (unsigned long long)(b & 3) << (2 * t);   // base t at bits 2t, 2t + 1
-            segscore[q] += sc->matrix_host[b * sc->alphabet + b];
-        }
-        key[q] = kk;
-    }
-    std::map<unsigned long long, int> seen;
-    for (int q = 0; q < nsg; ++q)
-        if (clean[q]) seen[key[q]]++;
-    int nidx = 0;
-    for (int q = 0; q < nsg; ++q)
-        if (clean[q] && seen[key[q]] == 1) ++nidx;
+    const int distinct = k < 12 ? std::min(nsg, 1 << (2 * k)) : nsg;
     int lg_t = 6;
-    while ((1 << lg_t) < 2 * nidx) ++lg_t;
+    while ((1 << lg_t) < 2 * distinct) ++lg_t;
     const int T = 1 << lg_t;
-    std::vector<unsigned long long> tkey(T, 0);
-    std::vector<int32_t> tseg(T, -1);
-    for (int q = 0; q < nsg; ++q) {
-        if (!clean[q] || seen[key[q]] != 1) continue;
-        uint32_t h = hk::nuc_hash(key[q], lg_t);
-        while (tseg[h] >= 0) h = (h + 1) & (T - 1);
-        tkey[h] = key[q];
-        tseg[h] = q;
-    }
     // scan chunks: sequence x covers the match starts 0 .. n - k in chunks
-    std::vector<int64_t> cbase(N + 1, 0);
+    int64_t nchunk = 0;
+    int longest = 0;
     for (int x = 0; x < N; ++x) {
-        const int64_t w = std::max<int64_t>(0, oh[x + 1] - oh[x] - k + 1);
-        cbase[x + 1] = cbase[x] + (w + hk::kNucChunk - 1) / hk::kNucChunk;
+        const int64_t n = oh[x + 1] - oh[x], w = std::max<int64_t>(0, n - k + 1);
+        nchunk += (w + hk::kNucChunk - 1) / hk::kNucChunk;
+        longest = std::max<int>(longest, (int)n);
     }
-    const int64_t nchunk = cbase[N];
-    // device tables: segment table, segment scores, chunk bases, two totals,
-    // and per chunk: counts (int32), the same widened, offsets (nchunk + 1)
-    const size_t o_tk = 0, o_ts = al256(8 * (size_t)T), o_ss = o_ts + al256(4 * (size_t)T),
-                 o_cb = o_ss + al256(4 * segscore.size()), o_tot = o_cb + al256(8 * (size_t)(N + 1)),
-                 o_lc = o_tot + 128, o_cc = o_tot + 256, o_cw = o_cc + al256(4 * (size_t)nchunk + 4),
-                 o_co = o_cw + al256(8 * (size_t)nchunk + 8), tab_bytes = o_co + al256(8 * (size_t)(nchunk + 1));
+    // device tables: segment table and its making, chunk bases, counters; per
+    // chunk: its count and its matches
+    const size_t o_tk = 0, o_ts = al256(8 * (size_t)T), o_sk = o_ts + al256(4 * (size_t)T),
+                 o_ss = o_sk + al256(8 * (size_t)nsg + 8), o_st = o_ss + al256(4 * (size_t)nsg + 4),
+                 o_cb = o_st + al256(4 * (size_t)nsg + 4), o_n = o_cb + al256(8 * (size_t)(N + 1)),
+                 o_cc = o_n + 8 * hk::kNucCounts, o_cm = o_cc + al256(4 * (size_t)nchunk + 4),
+                 tab_bytes = o_cm + 4 * (size_t)nchunk * hk::kNucChunk;
     RCHK(grow(ctx, ctx->nuctab, tab_bytes));
     char *tb = (char *)ctx->nuctab.p;
-    HCHK(hipMemcpyAsync(tb + o_tk, tkey.data(), 8 * (size_t)T, hipMemcpyHostToDevice, st));
-    HCHK(hipMemcpyAsync(tb + o_ts, tseg.data(), 4 * (size_t)T, hipMemcpyHostToDevice, st));
-    HCHK(hipMemcpyAsync(tb + o_ss, segscore.data(), 4 * segscore.size(), hipMemcpyHostToDevice, st));
-    HCHK(hipMemcpyAsync(tb + o_cb, cbase.data(), 8 * (size_t)(N + 1), hipMemcpyHostToDevice, st));
     const int aw = (m + 31) / 32;
-    {   // zero the vectors (ins as words plus an odd tail) and G
+    {   // zero the vectors (ins as words plus an odd tail), G and the counters
         const int64_t n16 = (int64_t)N * (m + 1);
         hk::ZeroArgs z{};
         z.p[0] = (uint32_t *)ins;
@@ -3204,12 +3151,30 @@ int halign_nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seq
         z.n[1] = (int64_t)N * aw;
         z.p[2] = (uint32_t *)G;
         z.n[2] = G ? m + 1 : 0;
-        z.p[3] = (uint32_t *)(tb + o_lc);   // the stretch list counts
-        z.n[3] = 3;
+        z.p[3] = (uint32_t *)(tb + o_n);
+        z.n[3] = 2 * hk::kNucCounts;
         z.tail16 = (n16 & 1) ? ins + (n16 - 1) : nullptr;
         hipLaunchKernelGGL(hk::zero_kernel, dim3(grid_for(z.n[0] + z.n[1], 256, 4096)), dim3(256), 0, st, z);
         HCHK(hipGetLastError());
     }
+    hk::NucSetup su{};
+    su.center = dc;
+    su.m = m;
+    su.k = k;
+    su.nsg = nsg;
+    su.alpha = S.alpha;
+    su.lg_t = lg_t;
+    su.mat = S.dmat;
+    su.tkey = (unsigned long long *)(tb + o_tk);
+    su.tseg = (int32_t *)(tb + o_ts);
+    su.segkey = (unsigned long long *)(tb + o_sk);
+    su.segscore = (int32_t *)(tb + o_ss);
+    su.segstate = (int32_t *)(tb + o_st);
+    su.off = seqs->offsets;
+    su.nseq = N;
+    su.cbase = (int64_t *)(tb + o_cb);
+    hipLaunchKernelGGL(hk::nuc_setup_kernel, dim3(2), dim3(1024), 0, st, su);
+    HCHK(hipGetLastError());
     hk::NucArgs a{};
     a.res = seqs->residues;
     a.off = seqs->offsets;
@@ -3217,108 +3182,118 @@ int halign_nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seq
     a.center = dc;
     a.m = m;
     a.k = k;
-    a.tkey = (const unsigned long long *)(tb + o_tk);
-    a.tseg = (const int32_t *)(tb + o_ts);
+    a.tkey = su.tkey;
+    a.tseg = su.tseg;
     a.lg_t = lg_t;
-    a.segscore = (const int32_t *)(tb + o_ss);
+    a.segscore = su.segscore;
     a.mat = S.dmat;
     a.alpha = S.alpha;
     a.go = S.goe - S.ge;
     a.ge = S.ge;
-    a.cbase = (const int64_t *)(tb + o_cb);
+    a.cbase = su.cbase;
     a.nchunk = nchunk;
     a.ccount = (int32_t *)(tb + o_cc);
-    a.cmoff = (const int64_t *)(tb + o_co);
+    a.cmatch = (uint32_t *)(tb + o_cm);
     a.score = score;
     a.ins = ins;
     a.aligned = aligned;
     a.aw = aw;
     a.G = G;
     a.gskip = center;
-    int64_t *dtot = (int64_t *)(tb + o_tot);
-    const unsigned cgrid = (unsigned)std::max<int64_t>(1, (nchunk + 255) / 256);
-    // wavefront scan: one chunk per wavefront, 16 per workgroup sharing the table
-    const unsigned wgrid_scan = (unsigned)std::max<int64_t>(1, std::min<int64_t>((nchunk + 15) / 16, (int64_t)ctx->num_cu * 3));
+    a.own_row = own_row ? 1 : 0;
+    a.count = (unsigned long long *)(tb + o_n);
+    a.lane_min = hk::kNucLaneMin;
+    if (const char *e = getenv("HALIGN_NUC_LANES")) a.lane_min = atoll(e);   // test knob: lanes from this many narrow stretches
     if (nchunk > 0) {
-        if (k <= hk::kNucWaveMaxK)
-            hipLaunchKernelGGL(hk::nuc_count_wave_kernel, dim3(wgrid_scan), dim3(1024), 0, st, a);
-        else
-            hipLaunchKernelGGL(hk::nuc_count_kernel, dim3(cgrid), dim3(256), 0, st, a);
-        HCHK(hipGetLastError());
-        hipLaunchKernelGGL(hk::widen_kernel, dim3(cgrid), dim3(256), 0, st, (const int32_t *)a.ccount, (int)nchunk,
-                           (int64_t *)(tb + o_cw));
+        if (k <= hk::kNucWaveMaxK) {
+            // 16 wavefronts per workgroup share the table, two workgroups a CU
+            const int64_t waves = (int64_t)ctx->num_cu * 2 * 16, longest = (nchunk + N - 1) / N;
+            a.wparts = (int)std::max<int64_t>(1, std::min(waves / N, longest));
+            const int64_t items = (int64_t)N * a.wparts;
+            const unsigned grid = (unsigned)std::min<int64_t>((items + 15) / 16, (int64_t)ctx->num_cu * 2);
+            hipLaunchKernelGGL(hk::nuc_scan_wave_kernel, dim3(grid), dim3(1024), 0, st, a);
+        } else {
+            hipLaunchKernelGGL(hk::nuc_scan_kernel, dim3((unsigned)((nchunk + 255) / 256)), dim3(256), 0, st, a);
+        }
         HCHK(hipGetLastError());
     }
-    int64_t nmt = 0;
-    int64_t *cm = (int64_t *)(tb + o_co);
-    RCHK(scan_i64(ctx, (const int64_t *)(tb + o_cw), nchunk, 0, cm, cm + nchunk, &nmt, st));
-    // per match (4 x int32) and per slot (matches + N): chain table, stretch
-    // descriptor, sequence, sizes and their offsets (+ a total each)
-    const int64_t nslot = nmt + N;
-    if (nslot >= ((int64_t)1 << 31)) return fail(HALIGN_E_UNSUPPORTED, "%lld segment matches", (long long)nmt);
-    const size_t m_q = 0, m_p = al256(4 * (size_t)nmt), m_b = m_p + al256(4 * (size_t)nmt),
-                 m_r = m_b + al256(4 * (size_t)nmt), s_tl = m_r + al256(4 * (size_t)nmt),
-                 s_d = s_tl + al256(4 * (size_t)nslot), s_x = s_d + al256(16 * (size_t)nslot),
-                 s_r = s_x + al256(4 * (size_t)nslot), s_c = s_r + al256(8 * (size_t)nslot),
-                 s_ro = s_c + al256(8 * (size_t)nslot), s_co = s_ro + al256(8 * (size_t)nslot + 8),
-                 s_sl = s_co + al256(8 * (size_t)nslot + 8), s_bl = s_sl + al256(4 * (size_t)nslot),
-                 scr_bytes = s_bl + al256(4 * (size_t)nslot);
-    RCHK(grow(ctx, ctx->nucscr, scr_bytes));
-    char *sb = (char *)ctx->nucscr.p;
-    a.mq = (int32_t *)(sb + m_q);
-    a.mp = (int32_t *)(sb + m_p);
-    a.mbest = (int32_t *)(sb + m_b);
-    a.mpred = (int32_t *)(sb + m_r);
-    a.tails = (int32_t *)(sb + s_tl);
-    a.sdesc = (int4 *)(sb + s_d);
-    a.sseq = (int32_t *)(sb + s_x);
-    a.srow = (int64_t *)(sb + s_r);
-    a.scode = (int64_t *)(sb + s_c);
-    a.nslot = nslot;
-    a.slist = (int32_t *)(sb + s_sl);
-    a.blist = (int32_t *)(sb + s_bl);
-    a.lcount = (int32_t *)(tb + o_lc);
-    if (nchunk > 0) {
-        if (k <= hk::kNucWaveMaxK)
-            hipLaunchKernelGGL(hk::nuc_store_wave_kernel, dim3(wgrid_scan), dim3(1024), 0, st, a);
-        else
-            hipLaunchKernelGGL(hk::nuc_store_kernel, dim3(cgrid), dim3(256), 0, st, a);
-        HCHK(hipGetLastError());
-    }
-    // LDS sized for twice the mean match count (a power of two, 64 ..
-    // kChainLdsMax), so several workgroups share a CU; a sequence with more
-    // matches is chained in the global arrays
-    int cap = 64;
-    while (cap < hk::kChainLdsMax && (int64_t)cap * N < 2 * nmt) cap *= 2;
+    // LDS of the chain for a quarter more matches than anchors can fit (each
+    // position of the center matches once in a related sequence), so that several
+    // workgroups share a CU (1,035 anchors: 18 KB); a sequence with more matches
+    // is chained in global arrays
+    const int fit = std::min(longest, m) / k;
+    const int cap = std::min(hk::kChainLdsMax, (fit + fit / 4 + 127) & ~63);
     a.chain_cap = cap;
-    hipLaunchKernelGGL(hk::nuc_chain_kernel, dim3((unsigned)N), dim3(64), hk::nuc_chain_lds_bytes(cap, aw), st, a);
-    HCHK(hipGetLastError());
-    // stretch scratch: row buffers and codes, one region per stretch
-    int64_t nrow = 0, ncode = 0;
-    int64_t *ro = (int64_t *)(sb + s_ro), *co = (int64_t *)(sb + s_co);
-    RCHK(scan_i64(ctx, a.srow, nslot, 0, ro, dtot, nullptr, st));
-    RCHK(scan_i64(ctx, a.scode, nslot, 0, co, dtot + 1, nullptr, st));
-    {   // both totals in one copy and one wait
-        int64_t t2[2] = {0, 0};
-        HCHK(hipMemcpyAsync(t2, dtot, 16, hipMemcpyDeviceToHost, st));
-        HCHK(hipStreamSynchronize(st));
-        nrow = t2[0];
-        ncode = t2[1];
+    // The lists and the scratch of the stretches are as large as the last calls
+    // needed, or a first guess: the kernels count what they need, and where it
+    // is more the buffers grow and both kernels run again.
+    ctx->nuc_list = std::max<int64_t>(ctx->nuc_list, (int64_t)N * 8 + 4096);
+    ctx->nuc_codes = std::max<int64_t>(ctx->nuc_codes, ctx->nuc_list * 64);
+    ctx->nuc_rows = std::max<int64_t>(ctx->nuc_rows, ctx->nuc_list * 8);
+    for (;;) {
+        const size_t lc = (size_t)ctx->nuc_list;
+        const size_t l_nd = 0, l_wd = al256(16 * lc), l_no = l_wd + al256(16 * lc), l_wo = l_no + al256(16 * lc),
+                     l_nx = l_wo + al256(16 * lc), l_wx = l_nx + al256(4 * lc), l_big = l_wx + al256(4 * lc),
+                     scr_bytes = l_big + 20 * (size_t)ctx->nuc_big + 4;
+        RCHK(grow(ctx, ctx->nucscr, scr_bytes));
+        const size_t d_co = al256(8 * (size_t)ctx->nuc_rows);
+        RCHK(grow(ctx, ctx->nucdp, d_co + 4 * (size_t)ctx->nuc_codes));
+        char *sb = (char *)ctx->nucscr.p;
+        a.nd = (int4 *)(sb + l_nd);
+        a.wd = (int4 *)(sb + l_wd);
+        a.no = (longlong2 *)(sb + l_no);
+        a.wo = (longlong2 *)(sb + l_wo);
+        a.nx = (int32_t *)(sb + l_nx);
+        a.wx = (int32_t *)(sb + l_wx);
+        a.big = (int32_t *)(sb + l_big);
+        a.bigcap = ctx->nuc_big;
+        a.listcap = ctx->nuc_list;
+        a.rows = (int2 *)ctx->nucdp.p;
+        a.codes = (uint32_t *)((char *)ctx->nucdp.p + d_co);
+        a.rowcap = ctx->nuc_rows;
+        a.codecap = ctx->nuc_codes;
+        a.flag = (const uint32_t *)ctx->counter.p + 8;
+        a.mail = ctx->mail_dev;
+        a.seq = ctx->mail_dev ? ++ctx->mail_seq : 0;
+        hipLaunchKernelGGL(hk::nuc_chain_kernel, dim3((unsigned)N), dim3(256), hk::nuc_chain_lds_bytes(cap, aw), st, a);
+        HCHK(hipGetLastError());
+        // (33 KB of LDS: four workgroups a CU)
+        const int64_t sgrid = std::max<int64_t>(1, std::min<int64_t>(((int64_t)N * 8 + 3) / 4, (int64_t)ctx->num_cu * 4));
+        hipLaunchKernelGGL(hk::nuc_stretch_kernel, dim3((unsigned)sgrid), dim3(256), 0, st, a);
+        HCHK(hipGetLastError());
+        RCHK(after());
+        int64_t need[5];   // boundary entries, code words, narrow (front | back << 32), wide, big
+        if (ctx->mail_dev) {
+            RCHK(mail_wait(ctx, a.seq, st));
+            for (int c = 0; c < 5; ++c) need[c] = ctx->mail_host[3 + c];
+            *ctx->flag_host = (int)ctx->mail_host[2];
+        } else {
+            RCHK(flag_fetch(ctx, st));
+            HCHK(hipMemcpy2DAsync(need, 8, a.count, 256, 8, 5, hipMemcpyDeviceToHost, st));
+            HCHK(hipStreamSynchronize(st));
+        }
+        ctx->stage_pending = false;
+        const int64_t narrow = (need[2] & 0xffffffffll) + (int64_t)((uint64_t)need[2] >> 32);
+        if (need[0] <= a.rowcap && need[1] <= a.codecap && narrow <= a.listcap && need[3] <= a.listcap &&
+            need[4] <= a.bigcap)
+            break;
+        RCHK(validate_check(ctx));
+        if (narrow >= ((int64_t)1 << 31) || need[3] >= ((int64_t)1 << 31))
+            return fail(HALIGN_E_UNSUPPORTED, "%lld stretches", (long long)(narrow + need[3]));
+        ctx->nuc_rows = std::max(ctx->nuc_rows, need[0]);
+        ctx->nuc_codes = std::max(ctx->nuc_codes, need[1]);
+        ctx->nuc_list = std::max({ctx->nuc_list, narrow, need[3]});
+        ctx->nuc_big = std::max(ctx->nuc_big, need[4]);
+        RCHK(launch_fill((uint32_t *)a.count, 0u, 2 * hk::kNucCounts, st));
     }
-    const size_t d_co = al256(8 * (size_t)nrow), dp_bytes = d_co + al256(4 * (size_t)ncode);
-    RCHK(grow(ctx, ctx->nucdp, dp_bytes));
-    a.srowoff = ro;
-    a.scodeoff = co;
-    a.rows = (int2 *)ctx->nucdp.p;
-    a.codes = (uint32_t *)((char *)ctx->nucdp.p + d_co);
-    // the stretches: lists sized on the device, grids bounded by the slots
-    const int sgrid = (int)std::max<int64_t>(1, std::min<int64_t>((nslot + 255) / 256, (int64_t)ctx->num_cu * 8));
-    hipLaunchKernelGGL(hk::nuc_stretch_small_kernel, dim3(sgrid), dim3(256), 0, st, a);
-    HCHK(hipGetLastError());
-    const int wgrid = (int)std::max<int64_t>(1, std::min<int64_t>(nslot, (int64_t)ctx->num_cu * 16));
-    hipLaunchKernelGGL(hk::nuc_stretch_wave_kernel, dim3(wgrid), dim3(64), 0, st, a);
-    HCHK(hipGetLastError());
-    return HALIGN_OK;
+    return validate_check(ctx);
+}
+
+extern "C" {
+
+int halign_nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seqs *seqs, int32_t center, int32_t k,
+                     int32_t *score, uint16_t *ins, uint32_t *aligned, int32_t *G, void *stream) {
+    return nuc_align(ctx, sc, seqs, center, k, score, ins, aligned, G, false, [] { return HALIGN_OK; }, stream);
 }
 
 int halign_nuc_msa(halign_ctx *ctx, const halign_scoring *sc, const halign_seqs *seqs, int32_t center, int32_t k,
@@ -3341,11 +3316,9 @@ int halign_nuc_msa(halign_ctx *ctx, const halign_scoring *sc, const halign_seqs 
     uint32_t *al = (uint32_t *)(mb + o_al);
     int32_t *G = (int32_t *)(mb + o_g);
     int64_t *col = (int64_t *)(mb + o_col);
-    RCHK(halign_nuc_align(ctx, sc, seqs, center, k, score, ins, al, G, stream));
-    hipLaunchKernelGGL(hk::center_row_kernel, dim3(1), dim3(256), 0, st, ins, al, center, m, aw);
-    HCHK(hipGetLastError());
     int64_t width = 0;
-    RCHK(merge_offsets(ctx, G, m + 1, col, &width, st));
+    RCHK(nuc_align(ctx, sc, seqs, center, k, score, ins, al, G, true,
+                   [&] { return merge_offsets(ctx, G, m + 1, col, &width, st); }, stream));
     uint8_t *out = (uint8_t *)alloc((size_t)N * (size_t)width, user);
     if (!out && width > 0) return fail(HALIGN_E_NOMEM, "allocator returned NULL for %lld bytes", (long long)(N * width));
     RCHK(emit_rows(ctx, seqs, m, ins, al, G, col, width, out, st));

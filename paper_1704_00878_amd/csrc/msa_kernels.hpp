@@ -100,18 +100,6 @@ __global__ void encode_kernel(const uint8_t *ascii, int64_t len, uint8_t *codes,
         codes[x] = table[ascii[x]];
 }
 
-// The center's own row: no insertions, every center position aligned.
-__global__ void center_row_kernel(uint16_t *ins, uint32_t *aligned, int center, int m, int aw) {
-    uint16_t *ir = ins + (int64_t)center * (m + 1);
-    uint32_t *ar = aligned + (int64_t)center * aw;
-    for (int p = threadIdx.x; p <= m; p += blockDim.x) ir[p] = 0;
-    for (int w = threadIdx.x; w < aw; w += blockDim.x) {
-        const int lo = w * 32;
-        const int nb = min(32, m - lo);
-        ar[w] = nb >= 32 ? 0xffffffffu : ((1u << nb) - 1u);
-    }
-}
-
 // G[p] = max_k ins[k][p].  Block (256 threads) covers 256 slots x kRows rows,
 // reduces in registers and publishes with one integer atomicMax per slot
 // (max is order-independent, so the result is deterministic).
@@ -131,28 +119,61 @@ __global__ void merge_max_kernel(const uint16_t *ins, int n, int m1, int32_t *G)
 // mail[1] = seq with a system-scope release, so a host spinning on mail[1]
 // reads the width (and, in mail[2], the flag word) without a stream
 // synchronisation
+//
+// Tiles of 4,096 positions, four per lane, the next tile's loads in flight while
+// one is summed (32-bit sums fit a tile: 4,096 x 65,536), one barrier each.
+// At 16,570 positions 21.5 us with a contiguous run per lane.
 __global__ void __launch_bounds__(1024) merge_scan_kernel(const int32_t *G, int m1, int64_t *col, int64_t *width,
                                                           int64_t *mail, int64_t seq, const uint32_t *flag) {
-    __shared__ int64_t part[1024];
-    const int tid = threadIdx.x;
-    const int per = (m1 + 1023) / 1024;
-    const int lo = min(m1, tid * per), hi = min(m1, lo + per);
-    int64_t sum = 0;
-    for (int p = lo; p < hi; ++p) sum += G[p] + 1;
-    part[tid] = sum;
-    __syncthreads();
-    for (int d = 1; d < 1024; d <<= 1) {
-        const int64_t v = tid >= d ? part[tid - d] : 0;
-        __syncthreads();
-        part[tid] += v;
-        __syncthreads();
+    __shared__ int s_sum[2][16];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    int nx[4];
+    auto load = [&](int t0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int p = t0 + 4 * tid + u;
+            nx[u] = p < m1 ? G[p] + 1 : 0;
+        }
+    };
+    int64_t base = 0;   // of the tile
+    load(0);
+    int b = 0;
+    for (int t0 = 0; t0 < m1; t0 += 4096, b ^= 1) {
+        int v[4], sum = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            v[u] = nx[u];
+            sum += v[u];
+        }
+        load(t0 + 4096);
+        int inc = sum;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int t = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += t;
+        }
+        if (lane == 63) s_sum[b][wv] = inc;
+        __syncthreads();   // (the other buffer is still being read by late wavefronts)
+        int before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const int x = s_sum[b][w];
+            before += w < wv ? x : 0;
+            all += x;
+        }
+        int64_t acc = base + before + inc - sum;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int p = t0 + 4 * tid + u;
+            if (p < m1) col[p] = acc;
+            acc += v[u];
+        }
+        base += all;
     }
-    int64_t acc = tid > 0 ? part[tid - 1] : 0;
-    for (int p = lo; p < hi; ++p) { col[p] = acc; acc += G[p] + 1; }
-    if (tid == 1023) {
-        *width = part[1023] - 1;
+    if (tid == 0) {
+        *width = base - 1;
         if (mail) {
-            __hip_atomic_store(mail, part[1023] - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(mail, base - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             if (flag) __hip_atomic_store(mail + 2, (int64_t)*flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             __hip_atomic_store(mail + 1, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
         }
@@ -338,33 +359,60 @@ constexpr int kRowWin = 2048;               // LDS bytes of a task's column wind
 constexpr int kRowRes = 2048;               // LDS bytes of a task's residues (more: read from global memory)
 constexpr int kRowWave = kRowWin + 16 + kRowRes;   // LDS bytes per wavefront
 
-// Chunked rows, first pass, one wavefront per row: ck[k][c] = residues of row
-// k before block c * kRowChunk (insertions plus aligned bits), lane L counting
-// blocks 4L .. 4L + 3 of each chunk (coalesced loads).
-__global__ void __launch_bounds__(256) rows_count_kernel(RowsArgs a, int32_t *ck, int nck) {
-    const int lane = threadIdx.x & 63;
-    const int wave = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-    const int nwave = (int)((gridDim.x * blockDim.x) >> 6);
+// Chunked rows, first pass, one workgroup per row: ck[k][c] = residues of row
+// k before block c * kRowChunk (insertions plus aligned bits).  A wavefront counts a
+// chunk with two loads of aligned words (pairs of counts) per lane, four chunks in
+// flight on each of eight wavefronts; the chunks' counts meet in LDS.  One wavefront per row that
+// carried its sum from chunk to chunk took 66 us at 672 rows of 16,570 blocks (22 MB).
+__global__ void __launch_bounds__(512) rows_count_kernel(RowsArgs a, int32_t *ck, int nck) {
+    __shared__ int s_cnt[288], s_wave[8];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int m = a.m, m1 = m + 1;
-    for (int k = wave; k < a.nrows; k += nwave) {
+    for (int k = blockIdx.x; k < a.nrows; k += gridDim.x) {
         const uint16_t *ir = a.ins + (int64_t)k * m1;
         const uint32_t *ar = a.aligned + (int64_t)k * a.aw;
-        int run = 0;
-        for (int c = 0; c < nck; ++c) {
-            const int b = c * kRowChunk + 4 * lane;
-            int v = 0;
+        for (int c0 = wv; c0 < nck; c0 += 32) {
+            int v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (b + u < m1) v += (int)ir[b + u];
-            if (b < m) {   // blocks b .. b + 3 share an aligned word (b is a multiple of 4)
-                const uint32_t nb = (uint32_t)min(4, m - b);
-                v += __popc((ar[b >> 5] >> (b & 31)) & ((1u << nb) - 1u));
+            for (int u = 0; u < 4; ++u) {
+                const int b = (c0 + 8 * u) * kRowChunk, nb = min(kRowChunk, m1 - b);   // (nb <= 0: no such chunk)
+                const uintptr_t p = (uintptr_t)(ir + b);
+                const int odd = (int)((p >> 1) & 1);
+                const uint32_t *w = reinterpret_cast<const uint32_t *>(p & ~(uintptr_t)3);
+                v[u] = 0;
+#pragma unroll
+                for (int r = 0; r < 3; ++r) {   // word i holds the counts 2i - odd and 2i + 1 - odd
+                    const int i = 64 * r + lane, lo = 2 * i - odd;
+                    if (r == 2 && (lane > 0 || !odd)) continue;
+                    if (lo >= nb) continue;
+                    const uint32_t x = w[i];
+                    v[u] += (lo >= 0 ? (int)(x & 0xffffu) : 0) + (lo + 1 < nb ? (int)(x >> 16) : 0);
+                }
+                if (lane < 8 && b + 32 * lane < m) {   // the aligned words of center positions b + 32 lane ..
+                    const int left = m - (b + 32 * lane);
+                    v[u] += __popc(ar[(b >> 5) + lane] & (left >= 32 ? ~0u : (1u << left) - 1u));
+                }
             }
 #pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-            if (lane == 0) ck[(int64_t)k * nck + c] = run;
-            run += v;
+            for (int o = 32; o >= 1; o >>= 1)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] += __shfl_xor(v[u], o, 64);
+            if (lane < 4 && c0 + 8 * lane < nck) s_cnt[c0 + 8 * lane] = lane == 0 ? v[0] : lane == 1 ? v[1] : lane == 2 ? v[2] : v[3];
         }
+        __syncthreads();
+        const int own = tid < nck ? s_cnt[tid] : 0;   // (nck is at most 257)
+        int inc = own;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int t = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += t;
+        }
+        if (lane == 63) s_wave[wv] = inc;
+        __syncthreads();
+        int before = inc - own;
+        for (int w = 0; w < wv; ++w) before += s_wave[w];
+        if (tid < nck) ck[(int64_t)k * nck + tid] = before;
+        __syncthreads();
     }
 }
 
