@@ -1938,9 +1938,9 @@ static int emit_rows(halign_ctx *ctx, const halign_seqs *seqs, int32_t m, const 
 extern "C" {
 
 // Center selection -----------------------------------------------------------
-// The packed 16-bit score-only strip kernel applies when every H stays below
-// 15000: max S times the longest sequence (plus go + ge) stays below 15000,
-// and go + ge <= 256.
+// The packed 16-bit score-only strip kernel applies when every H (max S times
+// the longest sequence) plus go + ge stays below 15000, also plus 18 ge (its rows'
+// offsets) below 16000, and go + ge <= 256.
 // HALIGN_STRIP32=1 keeps the 32-bit kernel (tests of both paths).
 static bool strip16_ok(const Scoring &S, const halign_seqs *sq) {
     const char *e = getenv("HALIGN_STRIP32");
@@ -1949,14 +1949,16 @@ static bool strip16_ok(const Scoring &S, const halign_seqs *sq) {
     for (int x = 0; x < S.alpha * S.alpha; ++x) smax = std::max(smax, (int)S.hmat[x]);
     int64_t lmax = 0;
     for (int k = 0; k < sq->n; ++k) lmax = std::max(lmax, sq->offsets_host[k + 1] - sq->offsets_host[k]);
-    return S.goe <= 256 && S.ge <= 256 && (int64_t)smax * lmax + S.goe < 15000;
+    const int64_t top = (int64_t)smax * lmax + S.goe;
+    return S.goe <= 256 && S.ge <= 256 && top < 15000 && top + 18 * S.ge < 16000;
 }
 
-// Groups: one center, 64 partners (32-bit kernel) or 128 (16-bit kernel).
+// Groups: 64 partners and one center (32-bit kernel) or two (16-bit kernel).
 // Mode 1 (all pairs a < b of `perm`, in length order): the groups follow the
-// closed-form triangular tiling of tiling.hpp, ngroups = tri_groups(N, step),
-// with no per-group arrays.  Mode 2 (anchored groups): gcen, gb0 and gslot
-// list the groups.
+// closed-form triangular tilings of tiling.hpp, ngroups = tri_groups(N, 64) or
+// pair_groups(N), with no per-group arrays.  Mode 2 (anchored groups): gcen, gb0
+// and gslot list the groups; 16-bit, gcen and gslot hold the second centers
+// and slots behind the first ones.
 constexpr int64_t kGroupSlice = (int64_t)1 << 21;   // all-pairs groups per launch
 
 static int run_groups(halign_ctx *ctx, const Scoring &S, const halign_seqs *sq, int mode, int64_t ngroups,
@@ -1965,16 +1967,38 @@ static int run_groups(halign_ctx *ctx, const Scoring &S, const halign_seqs *sq, 
                       int32_t *score, hipStream_t st, int nperm = -1, bool p16 = false) {
     if (p16 && (score || mode == 0)) return fail(HALIGN_E_INVALID, "16-bit strip kernel: score-only center selection");
     if (ngroups <= 0) return HALIGN_OK;
-    const size_t ng2 = mode == 2 ? (size_t)ngroups : 1;
+    const size_t ng2 = mode == 2 ? (size_t)ngroups : 1, nc2 = p16 ? 2 * ng2 : ng2;
     PlanBuilder pb;
-    const size_t o_gcen = pb.add(4 * ng2), o_gb0 = pb.add(4 * ng2), o_perm = pb.add(4 * perm.size()),
-                 o_gslot = pb.add(4 * ng2);
+    const size_t o_gcen = pb.add(4 * nc2), o_gb0 = pb.add(4 * ng2), o_perm = pb.add(4 * perm.size()),
+                 o_gslot = pb.add(4 * nc2);
+    // few groups for each of the resident wavefronts: run in order of falling cost
+    // (by length buckets), so that they end together (9,600 groups of 1,500 proteins:
+    // 21.2 ms against 22.4 from the last group down); from 65,536 on the order is worth under 1%
+    const bool ordered = p16 && mode == 1 && ngroups < 65536 && !getenv("HALIGN_GROUP_SLICE");
+    const size_t o_order = pb.add(ordered ? 4 * (size_t)ngroups : 0);
     char *hs = nullptr;
     RCHK(stage_host(ctx, pb.total, &hs));
+    if (ordered) {
+        const int64_t *off = sq->offsets_host;
+        const int np = (int)perm.size();
+        auto len = [&](int64_t pos) { return off[perm[pos] + 1] - off[perm[pos]]; };   // (longest last)
+        const double top = (double)len(np - 1) * (double)len(np - 1) + 1;
+        std::vector<int32_t> bucket(ngroups), first(1025, 0);
+        for (int64_t g = 0; g < ngroups; ++g) {
+            int64_t p0, b0;
+            hk::pair_group(g, np, &p0, &b0);
+            const double cost = (double)len(p0 + 1) * (double)len(std::min<int64_t>(np, b0 + 64) - 1);
+            bucket[g] = 1023 - (int)(1024.0 * cost / top);
+            ++first[bucket[g] + 1];
+        }
+        for (int q = 0; q < 1024; ++q) first[q + 1] += first[q];
+        int32_t *order = (int32_t *)(hs + o_order);
+        for (int64_t g = ngroups - 1; g >= 0; --g) order[first[bucket[g]]++] = (int32_t)g;
+    }
     if (mode == 2) {
-        memcpy(hs + o_gcen, gcen.data(), 4 * ng2);
+        memcpy(hs + o_gcen, gcen.data(), 4 * nc2);
         memcpy(hs + o_gb0, gb0.data(), 4 * ng2);
-        memcpy(hs + o_gslot, gslot.data(), 4 * ng2);
+        memcpy(hs + o_gslot, gslot.data(), 4 * nc2);
     }
     memcpy(hs + o_perm, perm.data(), 4 * perm.size());
     char *dplan = nullptr;
@@ -1985,8 +2009,8 @@ static int run_groups(halign_ctx *ctx, const Scoring &S, const halign_seqs *sq, 
     int nmax_all = 0;
     const int64_t *oh = sq->offsets_host;
     for (int k = 0; k < sq->n; ++k) nmax_all = std::max(nmax_all, (int)(oh[k + 1] - oh[k]));
-    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(ngroups, (int64_t)ctx->num_cu * 16));
-    RCHK(grow(ctx, ctx->bound, (size_t)grid * 64 * strip_cols(nmax_all) * (p16 ? 16 : 8)));
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(ngroups, (int64_t)ctx->num_cu * (p16 ? 12 : 16)));
+    RCHK(grow(ctx, ctx->bound, (size_t)grid * 64 * strip_cols(nmax_all) * (p16 ? 9 : 8)));
     RCHK(grow(ctx, ctx->counter, 256));
     RCHK(launch_fill((uint32_t *)ctx->counter.p, 0u, 2, st));
     hk::InterArgs a{};
@@ -2000,6 +2024,9 @@ static int run_groups(halign_ctx *ctx, const Scoring &S, const halign_seqs *sq, 
     a.perm = (const int32_t *)(dplan + o_perm);
     a.nseq = nperm >= 0 ? nperm : sq->n;
     a.gslot = (const int32_t *)(dplan + o_gslot);
+    a.gorder = ordered ? (const int32_t *)(dplan + o_order) : nullptr;
+    a.gcen2 = a.gcen + ng2;
+    a.gslot2 = a.gslot + ng2;
     a.sums = sums;
     a.ngroups = ngroups;
     a.ge = S.ge;
@@ -2088,8 +2115,7 @@ int halign_center_exact(halign_ctx *ctx, const halign_scoring *sc, const halign_
     // form (tiling.hpp), so the host holds O(N) plan data
     std::vector<int32_t> perm = length_perm(seqs), none;
     const bool p16 = strip16_ok(S, seqs);
-    const int step = p16 ? 128 : 64;
-    RCHK(run_groups(ctx, S, seqs, 1, hk::tri_groups(N, step), none, none, perm, none, sums, nullptr, st, -1, p16));
+    RCHK(run_groups(ctx, S, seqs, 1, p16 ? hk::pair_groups(N) : hk::tri_groups(N, 64), none, none, perm, none, sums, nullptr, st, -1, p16));
     if (center_host) RCHK(argmax_sums(ctx, sums, nullptr, N, center_host, st));
     return HALIGN_OK;
 }
@@ -2121,14 +2147,20 @@ static int judge_impl(halign_ctx *ctx, const halign_scoring *sc, const halign_se
     }
     const int np = (int)perm.size();
     const bool p16 = strip16_ok(S, seqs);
-    const int step = p16 ? 128 : 64;
-    for (int q = 0; q < ncand; ++q)
-        for (int b = 0; b < np; b += step) {
+    const int cand_step = p16 ? 2 : 1;
+    for (int q = 0; q < ncand; q += cand_step)
+        for (int b = 0; b < np; b += 64) {
             gcen.push_back(hc[q]);
             gb0.push_back(b);
             gslot.push_back(q);
         }
-    RCHK(run_groups(ctx, S, seqs, 2, (int64_t)gcen.size(), gcen, gb0, perm, gslot, sums, nullptr, st, np, p16));
+    if (p16)   // the second centers
+        for (int q = 1; q < ncand + 1; q += 2)
+            for (int b = 0; b < np; b += 64) {
+                gcen.push_back(q < ncand ? hc[q] : -1);
+                gslot.push_back(std::min(q, ncand - 1));
+            }
+    RCHK(run_groups(ctx, S, seqs, 2, (int64_t)gb0.size(), gcen, gb0, perm, gslot, sums, nullptr, st, np, p16));
     if (center_host) RCHK(argmax_sums(ctx, sums, hc.data(), ncand, center_host, st));
     return HALIGN_OK;
 }

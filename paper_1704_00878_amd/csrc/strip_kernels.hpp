@@ -45,10 +45,12 @@ struct InterArgs {
     const int32_t *perm;      // modes 1/2: sequence ids (mode 1: sorted by length)
     int nseq;
     const int32_t *gslot;     // mode 2: sums slot of the group's center
+    const int32_t *gorder;    // mode 1, 16-bit: the groups in running order (NULL: from the last one down)
+    const int32_t *gcen2, *gslot2;   // the same of its second center (16-bit kernel; center -1: none)
     int64_t *sums;            // modes 1/2: integer score sums (atomic adds)
     int64_t ngroups;          // groups of this launch
     int64_t gfirst, gtotal;   // mode 1: this launch runs groups gfirst .. gfirst + ngroups - 1 of the
-                              // gtotal = tri_groups(nseq, partners per group), largest first
+                              // gtotal = tri_groups(nseq, 64) or, 16-bit, pair_groups(nseq), largest first
     int ge, goe;
     unsigned long long *counter;   // next group (zeroed before the launch)
     int32_t *score;           // mode 0: per pair id; mode 2: per lane slot (optional)
@@ -276,26 +278,44 @@ sw_inter_kernel(InterArgs a) {
 
 // ---------------------------------------------------------------------------
 // Packed 16-bit score-only strip kernel (center selection: modes 1 and 2).
-// Each lane scores two pairs of the group at once, pair A (partner gb0+lane)
-// in the low and pair B (partner gb0+64+lane) in the high half of every
-// register, with v_pk_* 16-bit integer ops: a group holds 128 partners.
-// E* and F* are clamped at 0 as in the 32-bit kernel, and all values are
-// biased (below) so that each three-way maximum is one v_pk_maximum3_f16:
-//   eext = e - ge; en = max(eext, Hg, 0); fext = F - ge; fn = max(fext, Hg_up, 0);
-//   hd = Hg_diag + P; h = max(hd, en, fn); Hg = h - goe
-// that is 8 packed ops per two cells plus half a maximum for the running
-// maximum.  The host uses this kernel only when every H stays below 15000
-// (max S * longest sequence + go + ge < 15000), so that no biased value
-// leaves [0, 0x7c00) and a padding profile entry can never be a source.  The
-// profile (int16 [r][16]) of the two lanes' residues is interleaved into
-// (A, B) pairs with v_perm_b32.
-// Strip boundaries per lane and column: packed Hg and packed F (int2) and the
-// two residue codes (uint16), written by every strip and read by the next one
+// Each lane scores one partner against two centers at once, the first
+// center in the low and the second in the high half of every register, with
+// v_pk_* 16-bit integer ops.  Both halves read the profile at the partner's residue, so one
+// LDS row holds the two centers' scores side by side and is used as it
+// comes (two partners per lane against one center took a v_perm_b32 per cell to
+// put two rows together), and a group has 64 partners rather than 128.
+//
+// Rows 2k and 2k + 1 of a strip hold every value plus ge (k + 1) (and the bias):
+// going down into an even row then costs F nothing, and E pays its ge after its
+// maximum.  With H - go kept in hg,
+//   E = max(E', hg', floor + ge) - ge;   F = max(F_up, hg_up) (- ge into an odd row);
+//   H = max(hg_diag + P, E, F);          hg = H - go
+// (' the previous column), which is six and a half packed ops per two cells, and
+// half a maximum for the running maximum of each pair of rows (one register for
+// both, as they share their offset; they meet at the group's end).  The last row gives
+// 16 ge back at the strip's boundary.  F needs no floor: H has E's.
+//
+// A strip has 32 rows, at three wavefronts per SIMD: the boundaries of all groups
+// in flight (1.1 GB) go through memory, and with 16 rows the kernel was bound by that
+// (4.2 TB/s of a copy's 4.66).  Now VALU issue bounds it (238 instructions per
+// column).  1,500 proteins of 150-600, all pairs: 31.3 ms with 16 rows, 8.5 ops and
+// groups of 128 partners; 25.2 with 16 rows; 23.6 with four wavefronts per SIMD, which
+// leaves 128 registers and spills around the loops; 22.4; 21.2 with the groups in order of
+// cost.  The host uses this kernel only when
+// every H plus go + ge plus 18 ge stays below 16000 and every H below 15000, so that no
+// biased value leaves [0, 0x7c00) and a padding profile entry can never be a source.
+//
+// Strip boundaries per lane and column: packed hg and packed F (int2) and the
+// residue code (a byte), written by every strip and read by the next one
 // with agent-scope loads (as in the 32-bit kernel).
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
+constexpr int kC = 2;         // columns per prefetch block
+constexpr int kT2 = 32;       // rows of a strip
+constexpr int kPS2 = kT2 + 4; // LDS row stride of the profile: residues spread over the banks
+
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
 sw_inter16_kernel(InterArgs a) {
-    __shared__ uint32_t prof[kAlphaMax * 8];   // int16 [r][16], 8 words per residue
+    __shared__ __attribute__((aligned(16))) uint32_t prof[kAlphaMax * kPS2];   // [r][32] (first, second center)
     __shared__ int8_t smat[kAlphaMax * kAlphaMax];
     __shared__ unsigned long long s_next;
     const int lane = threadIdx.x;
@@ -303,158 +323,172 @@ sw_inter16_kernel(InterArgs a) {
         const int r = x >> 5, q = x & 31;
         smat[x] = (r < a.alpha && q < a.alpha) ? a.mat[r * a.alpha + q] : (int8_t)0;
     }
-    // per workgroup: int2 (packed Hg, packed F) per lane and column, then the
-    // lane's two residue codes (uint16) per column
-    int2 *bnd = reinterpret_cast<int2 *>(reinterpret_cast<int4 *>(a.bound) + (int64_t)blockIdx.x * a.bstride);
-    uint16_t *bres = reinterpret_cast<uint16_t *>(bnd + a.bstride);
-    const pk16 ge2 = pk16{(short)a.ge, (short)a.ge};
-    const pk16 goe2 = pk16{(short)a.goe, (short)a.goe};
-    const pk16 bias2 = pk16{(short)kBias16, (short)kBias16};             // 0, biased
-    const pk16 init2 = pk16{(short)(kBias16 - a.goe), (short)(kBias16 - a.goe)};   // -go - ge, biased
+    // per workgroup: int2 (packed hg, packed F) per lane and column, then the
+    // lane's residue code (a byte) per column
+    int2 *bnd = reinterpret_cast<int2 *>(reinterpret_cast<uint8_t *>(a.bound) + (int64_t)blockIdx.x * a.bstride * 9);
+    uint8_t *bres = reinterpret_cast<uint8_t *>(bnd + a.bstride);
+    const uint32_t ulane = (uint32_t)lane;   // (unsigned: a scalar column address plus a lane offset)
+    auto both = [](int v) __attribute__((always_inline)) { return pk16{(short)v, (short)v}; };
+    const int go = a.goe - a.ge;
+    const pk16 ge2 = both(a.ge), go2 = both(go), last2 = both(kT2 / 2 * a.ge);
+    pk16 flo[kT2 / 2];   // the floor of each pair of rows, plus ge
+#pragma unroll
+    for (int k = 0; k < kT2 / 2; ++k) flo[k] = both(kBias16 + a.ge * (k + 2));
+    const pk16 top2 = both(kBias16 - go);   // hg above the first row: no offset
     for (;;) {
         __syncthreads();
         if (lane == 0) s_next = atomicAdd(a.counter, 1ull);
         __syncthreads();
         const int64_t g = uniform64(s_next);
         if (g >= a.ngroups) break;
-        int64_t apos = -1, b0;
-        int cid;
+        int64_t p0 = -1, p1 = -1, b0;   // positions that a partner has to be above
+        int c0, c1;
         if (a.mode == 1) {
-            tri_group(a.gtotal - 1 - (a.gfirst + g), a.nseq, 128, &apos, &b0);
-            cid = a.perm[apos];
+            pair_group(a.gorder ? a.gorder[g] : a.gtotal - 1 - (a.gfirst + g), a.nseq, &p0, &b0);
+            p1 = p0 + 1;
+            c0 = a.perm[p0];
+            c1 = a.perm[p1];
         } else {
             b0 = a.gb0[g];
-            cid = a.gcen[g];
+            c0 = a.gcen[g];
+            c1 = a.gcen2[g];   // -1: none
         }
-        const int64_t pa = b0 + lane, pbp = pa + 64;
-        int sa = (pa < a.nseq && pa > apos) ? a.perm[pa] : -1;
-        int sb = (pbp < a.nseq && pbp > apos) ? a.perm[pbp] : -1;
-        sa = sa == cid ? -1 : sa;   // a self pair scores 0
-        sb = sb == cid ? -1 : sb;
-        const uint8_t *cen = a.res + a.off[cid];
-        const int m = __builtin_amdgcn_readfirstlane((int)(a.off[cid + 1] - a.off[cid]));
-        const int64_t soa = sa >= 0 ? a.off[sa] : 0, sob = sb >= 0 ? a.off[sb] : 0;
-        const int na = sa >= 0 ? (int)(a.off[sa + 1] - soa) : 0;
-        const int nb = sb >= 0 ? (int)(a.off[sb + 1] - sob) : 0;
-        // prefetch bases: the set's first residue for an empty lane (a group
+        const int64_t pos = b0 + lane;
+        int sid = pos < a.nseq && pos > p0 ? a.perm[pos] : -1;
+        const bool ok0 = sid >= 0 && sid != c0, ok1 = sid >= 0 && c1 >= 0 && pos > p1 && sid != c1;   // a self pair scores 0
+        if (!ok0 && !ok1) sid = -1;
+        const uint8_t *cen0 = a.res + a.off[c0], *cen1 = a.res + a.off[max(c1, 0)];
+        const int m0 = __builtin_amdgcn_readfirstlane((int)(a.off[c0 + 1] - a.off[c0]));
+        const int m1 = c1 < 0 ? 0 : __builtin_amdgcn_readfirstlane((int)(a.off[c1 + 1] - a.off[c1]));
+        const int64_t so = sid >= 0 ? a.off[sid] : 0;
+        const int n = sid >= 0 ? (int)(a.off[sid + 1] - so) : 0;
+        // prefetch base: the set's first residue for an empty lane (a group
         // that runs any column holds at least one residue)
-        const uint8_t *qa = na > 0 ? a.res + soa : a.res;
-        const uint8_t *qb = nb > 0 ? a.res + sob : a.res;
-        int nmax = max(na, nb);
+        const uint8_t *sq = n > 0 ? a.res + so : a.res;
+        int nmax = n;
 #pragma unroll
         for (int sh = 1; sh < 64; sh <<= 1) nmax = max(nmax, __shfl_xor(nmax, sh));
         nmax = __builtin_amdgcn_readfirstlane(nmax);
-        const int nstrips = (m + kT - 1) / kT;
-        const int nmaxp = (nmax + kB - 1) / kB * kB;
-        const int la = max(na - 1, 0), lb = max(nb - 1, 0);
-        pk16 hmax = bias2;
+        const int nstrips = (max(m0, m1) + kT2 - 1) / kT2;
+        const int nmaxp = (nmax + kC - 1) / kC * kC;
+        const int nlast = max(n - 1, 0);
+        pk16 hm[kT2 / 2];   // running maxima of the pairs of rows
+#pragma unroll
+        for (int k = 0; k < kT2 / 2; ++k) hm[k] = flo[k] - ge2;
         for (int st = 0; st < nstrips && nmax > 0; ++st) {
-            const int i0 = st * kT;
+            const int i0 = st * kT2;
             __syncthreads();
-            for (int x = lane; x < kAlphaMax * 8; x += 64) {
-                const int r = x >> 3, t = 2 * (x & 7);
+            for (int x = lane; x < kAlphaMax * kT2; x += 64) {
+                const int r = x >> 5, t = x & 31;
+                const int add = (t & 1) ? go : a.goe;   // (from hg of a row with one ge less above an even row)
                 int v0 = kPadProf16, v1 = kPadProf16;
-                if (r < a.alpha && i0 + t < m) v0 = (int)smat[(cen[i0 + t] & 31) * 32 + r] + a.goe;
-                if (r < a.alpha && i0 + t + 1 < m) v1 = (int)smat[(cen[i0 + t + 1] & 31) * 32 + r] + a.goe;
-                prof[x] = (uint32_t)(v0 & 0xffff) | ((uint32_t)v1 << 16);
+                if (r < a.alpha && i0 + t < m0) v0 = (int)smat[(cen0[i0 + t] & 31) * 32 + r] + add;
+                if (r < a.alpha && i0 + t < m1) v1 = (int)smat[(cen1[i0 + t] & 31) * 32 + r] + add;
+                prof[r * kPS2 + t] = (uint32_t)(v0 & 0xffff) | ((uint32_t)v1 << 16);
             }
             __syncthreads();
-            pk16 hg[kT], e[kT];
+            pk16 hg[kT2], e[kT2];
 #pragma unroll
-            for (int t = 0; t < kT; ++t) { hg[t] = init2; e[t] = init2; }
-            pk16 diag0 = init2;
+            for (int t = 0; t < kT2; ++t) hg[t] = e[t] = flo[t / 2] - ge2 - go2;
+            pk16 diag0 = top2;
             auto strip = [&](auto first_tag) {
                 constexpr bool FIRST = decltype(first_tag)::value;
-                auto fetch = [&](int j0, int4 (&bq)[kB]) __attribute__((always_inline)) {
+                auto fetch = [&](int j0, int4 (&bq)[kC]) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int b = 0; b < kB; ++b) {
+                    for (int b = 0; b < kC; ++b) {
                         const int j = min(j0 + b, nmaxp);
                         if (FIRST) {
-                            bq[b].x = (int)qa[min(j - 1, la)];
-                            bq[b].y = (int)qb[min(j - 1, lb)];
+                            bq[b].x = (int)sq[min(j - 1, nlast)];
                         } else {
-                            const int2 v = load_agent(bnd + (int64_t)(j - 1) * 64 + lane);
+                            const uint32_t at = __builtin_amdgcn_readfirstlane((j - 1) * 64);
+                            const int2 v = load_agent(bnd + at + ulane);
                             const uint32_t rw = __hip_atomic_load(
-                                reinterpret_cast<const uint32_t *>(bres + (int64_t)(j - 1) * 64 + (lane & ~1)),
+                                reinterpret_cast<const uint32_t *>(bres + at + (ulane & ~3u)),
                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            bq[b] = make_int4(v.x, v.y, (int)(rw >> (16 * (lane & 1))), 0);
+                            bq[b] = make_int4(v.x, v.y, (int)(rw >> (8 * (lane & 3))) & 255, 0);
                         }
                     }
                 };
-                auto block = [&](int j0, const int4 (&bc)[kB]) {
+                // two columns, the second a row behind the first: two chains of
+                // dependent ops side by side
+                auto block = [&](int j0, const int4 (&bc)[kC]) __attribute__((always_inline)) {
+                    pk16 upg[kC], upf[kC], diag[kC], heven[kC];
+                    int r[kC];
+                    const uint4 *p4[kC];
+                    uint4 w[kC];
 #pragma unroll
-                    for (int b = 0; b < kB; ++b) {
-                        const int j = j0 + b;
-                        pk16 upg, upf;
-                        int ra, rb;
+                    for (int b = 0; b < kC; ++b) {
                         if (FIRST) {
-                            upg = init2;
-                            upf = init2;
-                            ra = (j <= na) ? (bc[b].x & 31) : kPad;
-                            rb = (j <= nb) ? (bc[b].y & 31) : kPad;
+                            upg[b] = top2;
+                            upf[b] = top2;
+                            r[b] = (j0 + b <= n) ? (bc[b].x & 31) : kPad;
                         } else {
-                            upg = as_pk((uint32_t)bc[b].x);
-                            upf = as_pk((uint32_t)bc[b].y);
-                            ra = bc[b].z & 255;
-                            rb = (bc[b].z >> 8) & 255;
+                            upg[b] = as_pk((uint32_t)bc[b].x);
+                            upf[b] = as_pk((uint32_t)bc[b].y);
+                            r[b] = bc[b].z;
                         }
-                        pk16 diag = diag0;
-                        diag0 = upg;
-                        const uint4 *pa4 = reinterpret_cast<const uint4 *>(prof + ra * 8);
-                        const uint4 *pb4 = reinterpret_cast<const uint4 *>(prof + rb * 8);
-                        const uint4 a0 = pa4[0], a1 = pa4[1], b0 = pb4[0], b1 = pb4[1];
-                        const uint32_t wa[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-                        const uint32_t wb[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-                        pk16 hh0 = bias2;
+                        diag[b] = diag0;
+                        diag0 = upg[b];
+                        p4[b] = reinterpret_cast<const uint4 *>(prof + r[b] * kPS2);
+                    }
 #pragma unroll
-                        for (int k = 0; k < 8; ++k) {
+                    for (int s = 0; s <= kT2; ++s) {
 #pragma unroll
-                            for (int h = 0; h < 2; ++h) {
-                                const int t = 2 * k + h;
-                                const pk16 p = as_pk(__builtin_amdgcn_perm(wb[k], wa[k], h ? 0x07060302u : 0x05040100u));
-                                const pk16 en = max3h(e[t] - ge2, hg[t], bias2);
-                                const pk16 fn = max3h(upf - ge2, upg, bias2);
-                                const pk16 hd = diag + p;
-                                const pk16 hh = max3h(hd, en, fn);
-                                if (h) hmax = max3h(hmax, hh0, hh);
-                                else hh0 = hh;
-                                diag = hg[t];
-                                hg[t] = hh - goe2;
-                                e[t] = en;
-                                upg = hg[t];
-                                upf = fn;
-                            }
+                        for (int b = 0; b < kC; ++b) {
+                            const int t = s - b;
+                            if (t < 0 || t >= kT2) continue;
+                            if ((t & 3) == 0) w[b] = p4[b][t >> 2];
+                            const uint32_t p = (t & 3) == 0 ? w[b].x : (t & 3) == 1 ? w[b].y : (t & 3) == 2 ? w[b].z : w[b].w;
+                            const pk16 en = max3h(e[t], hg[t], flo[t / 2]) - ge2;
+                            const pk16 fn = (t & 1) ? pmax(upf[b], upg[b]) - ge2 : pmax(upf[b], upg[b]);
+                            const pk16 hh = max3h(diag[b] + as_pk(p), en, fn);
+                            if (t & 1) hm[t / 2] = max3h(hm[t / 2], heven[b], hh);
+                            else heven[b] = hh;
+                            diag[b] = hg[t];
+                            hg[t] = hh - go2;
+                            e[t] = en;
+                            upg[b] = hg[t];
+                            upf[b] = fn;
                         }
-                        bnd[(int64_t)(j - 1) * 64 + lane] = make_int2((int)as_u(upg), (int)as_u(upf));
-                        bres[(int64_t)(j - 1) * 64 + lane] = (uint16_t)(ra | (rb << 8));
+                    }
+#pragma unroll
+                    for (int b = 0; b < kC; ++b) {
+                        const uint32_t at = __builtin_amdgcn_readfirstlane((j0 + b - 1) * 64);
+                        (bnd + at)[ulane] = make_int2((int)as_u(upg[b] - last2), (int)as_u(upf[b] - last2));
+                        (bres + at)[ulane] = (uint8_t)r[b];
                     }
                 };
-                int4 bA[kB], bB[kB];
+                int4 bA[kC], bB[kC];
                 fetch(1, bA);
-                for (int j0 = 1; j0 <= nmaxp; j0 += 2 * kB) {
-                    fetch(j0 + kB, bB);
+                for (int j0 = 1; j0 <= nmaxp; j0 += 2 * kC) {
+                    fetch(j0 + kC, bB);
                     block(j0, bA);
-                    if (j0 + kB > nmaxp) break;
-                    fetch(j0 + 2 * kB, bA);
-                    block(j0 + kB, bB);
+                    if (j0 + kC > nmaxp) break;
+                    fetch(j0 + 2 * kC, bA);
+                    block(j0 + kC, bB);
                 }
             };
             if (st == 0) strip(std::true_type{});
             else strip(std::false_type{});
         }
-        const uint32_t hm = as_u(hmax);
-        const int va = sa >= 0 ? (int)(hm & 0xffff) - kBias16 : 0;
-        const int vb = sb >= 0 ? (int)(hm >> 16) - kBias16 : 0;
-        if (a.mode == 1) {
-            if (sa >= 0) atomicAdd(reinterpret_cast<unsigned long long *>(a.sums + sa), (unsigned long long)va);
-            if (sb >= 0) atomicAdd(reinterpret_cast<unsigned long long *>(a.sums + sb), (unsigned long long)vb);
-        }
-        int tot = va + vb;
+        pk16 hmax = both(kBias16);
 #pragma unroll
-        for (int sh = 1; sh < 64; sh <<= 1) tot += __shfl_xor(tot, sh);
+        for (int k = 0; k < kT2 / 2; ++k) hmax = pmax(hmax, hm[k] - (flo[k] - ge2 - both(kBias16)));
+        const uint32_t hx = as_u(hmax);
+        const int v0 = ok0 ? (int)(hx & 0xffff) - kBias16 : 0;
+        const int v1 = ok1 ? (int)(hx >> 16) - kBias16 : 0;
+        if (a.mode == 1 && sid >= 0)
+            atomicAdd(reinterpret_cast<unsigned long long *>(a.sums + sid), (unsigned long long)(v0 + v1));
+        int t0 = v0, t1 = v1;
+#pragma unroll
+        for (int sh = 1; sh < 64; sh <<= 1) {
+            t0 += __shfl_xor(t0, sh);
+            t1 += __shfl_xor(t1, sh);
+        }
         if (lane == 0) {
-            const int slot = a.mode == 1 ? cid : a.gslot[g];
-            atomicAdd(reinterpret_cast<unsigned long long *>(a.sums + slot), (unsigned long long)(int64_t)tot);
+            const int s0 = a.mode == 1 ? c0 : a.gslot[g], s1 = a.mode == 1 ? c1 : a.gslot2[g];
+            atomicAdd(reinterpret_cast<unsigned long long *>(a.sums + s0), (unsigned long long)(int64_t)t0);
+            if (c1 >= 0) atomicAdd(reinterpret_cast<unsigned long long *>(a.sums + s1), (unsigned long long)(int64_t)t1);
         }
     }
 }

@@ -35,4 +35,25 @@ __host__ __device__ inline void tri_group(int64_t g, int64_t n, int step, int64_
     *b0 = q * step;
 }
 
+// The 16-bit kernel's groups: two neighbouring center positions 2p and 2p + 1
+// and 64 partner positions [64 q, 64 q + 64).  Block q holds p = 0 .. c_q - 1 with
+// c_q = min(64 (q + 1), n) / 2 (the first center stays below some partner of its block),
+// numbered block by block from 16 q (q + 1).
+__host__ __device__ inline int64_t pair_groups(int64_t n) {
+    if (n < 2) return 0;
+    const int64_t nb = (n + 63) / 64;
+    return 16 * (nb - 1) * nb + n / 2;
+}
+
+// group g (0 <= g < pair_groups(n)) -> first center position, first partner position
+__host__ __device__ inline void pair_group(int64_t g, int64_t n, int64_t *p0, int64_t *b0) {
+    const int64_t nb = (n + 63) / 64;
+    int64_t q = (int64_t)sqrt((double)g / 16.0);
+    if (q > nb - 1) q = nb - 1;
+    while (q > 0 && 16 * q * (q + 1) > g) --q;
+    while (q + 1 <= nb - 1 && 16 * (q + 1) * (q + 2) <= g) ++q;
+    *p0 = 2 * (g - 16 * q * (q + 1));
+    *b0 = 64 * q;
+}
+
 }  // namespace hk
