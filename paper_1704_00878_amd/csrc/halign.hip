@@ -1794,7 +1794,7 @@ int halign_sw_batch(halign_ctx *ctx, const halign_scoring *sc, const uint8_t *ce
 
 static int emit_rows(halign_ctx *ctx, const halign_seqs *seqs, int32_t m, const uint16_t *ins,
                      const uint32_t *aligned, const int32_t *G, const int64_t *col, int64_t width, uint8_t *msa,
-                     hipStream_t st);
+                     int longest, hipStream_t st);
 
 // Spin until the mailbox holds seq or a later one (a kernel's release store, after its other
 // words); now and then ask the stream whether it failed or finished.
@@ -1871,17 +1871,18 @@ int halign_emit_rows(halign_ctx *ctx, const halign_seqs *seqs, int32_t m, const 
                      void *stream) {
     if (!ctx || !seqs || m < 0 || width < m || (seqs->n > 0 && (!ins || !aligned || !G || !col || !msa)))
         return fail(HALIGN_E_INVALID, "bad arguments");
-    RCHK(check_seqs(seqs));
+    int longest = 0;
+    RCHK(check_seqs(seqs, &longest));
     HCHK(hipSetDevice(ctx->device));
-    return emit_rows(ctx, seqs, m, ins, aligned, G, col, width, msa, (hipStream_t)stream);
+    return emit_rows(ctx, seqs, m, ins, aligned, G, col, width, msa, longest, (hipStream_t)stream);
 }
 
 }  // extern "C"
 
-// halign_emit_rows for checked arguments
+// halign_emit_rows for checked arguments (longest: the longest sequence)
 static int emit_rows(halign_ctx *ctx, const halign_seqs *seqs, int32_t m, const uint16_t *ins,
                      const uint32_t *aligned, const int32_t *G, const int64_t *col, int64_t width, uint8_t *msa,
-                     hipStream_t st) {
+                     int longest, hipStream_t st) {
     const int N = seqs->n;
     if (N == 0 || width == 0) return HALIGN_OK;
     const int m1 = m + 1, aw = (m + 31) / 32;
@@ -1896,7 +1897,7 @@ static int emit_rows(halign_ctx *ctx, const halign_seqs *seqs, int32_t m, const 
         const int nck = (m1 + hk::kRowChunk - 1) / hk::kRowChunk;
         RCHK(grow(ctx, ctx->rowck, 4 * (size_t)N * nck));
         int32_t *ck = (int32_t *)ctx->rowck.p;
-        hk::RowsArgs ra{seqs->residues, seqs->offsets, N, m, ins, aligned, aw, G, col, width, 0, 0, 0, msa};
+        hk::RowsArgs ra{seqs->residues, seqs->offsets, N, m, ins, aligned, aw, G, col, width, 0, 0, 0, 0, msa};
         const int cgrid = std::max(1, std::min(N, ctx->num_cu * 8));
         hipLaunchKernelGGL(hk::rows_count_kernel, dim3(cgrid), dim3(512), 0, st, ra, ck, nck);
         HCHK(hipGetLastError());
@@ -1907,13 +1908,12 @@ static int emit_rows(halign_ctx *ctx, const halign_seqs *seqs, int32_t m, const 
         HCHK(hipGetLastError());
         return HALIGN_OK;
     }
-    // LDS per wavefront: (m+1) block starts and counts, the aligned bits and
-    // a chunk of ch columns
+    // LDS per wavefront: (m+1) insertion counts, the aligned bits, the residues
+    // and a chunk of ch columns
     size_t lim = std::min<size_t>(ctx->lds_max, 64 * 1024);
+    const int res_bytes = (std::min(longest, 4096) + 4 + 15) & ~15;   // of a row staged at most
     auto wave_bytes = [&](int ch) {
-        const size_t h2 = ((size_t)m1 * 2 + 3) & ~(size_t)3;
-        const size_t head = (2 * h2 + 4 * (size_t)aw + 15) & ~(size_t)15;
-        return head + (size_t)ch + 32;
+        return hk::rows_ins_bytes(m1) + hk::rows_bit_bytes(aw) + (size_t)res_bytes + 16 + (size_t)ch + 32;
     };
     int ch = (int)std::min<int64_t>(8192, (width + 15) & ~(int64_t)15), wpb = hk::kWaveRows;
     while (ch > 1024 && (size_t)wpb * wave_bytes(ch) > lim) ch = ((ch / 2) + 15) & ~15;
@@ -1926,7 +1926,7 @@ static int emit_rows(halign_ctx *ctx, const halign_seqs *seqs, int32_t m, const 
         lim = ctx->lds_cu;   // the column table in LDS too
     const int gc_lds = (size_t)wpb * wave_bytes(ch) + gcb <= lim ? 1 : 0;
     hk::RowsArgs ra{seqs->residues, seqs->offsets, N, m, ins, aligned, aw, G, col, width, ch, (int)wave_bytes(ch),
-                    gc_lds, msa};
+                    res_bytes, gc_lds, msa};
     const size_t lds = (size_t)wpb * wave_bytes(ch) + (gc_lds ? gcb : 0);
     const int per_cu = std::max(1, std::min(8, (int)(ctx->lds_max / lds)));
     const int grid = std::max(1, std::min((N + wpb - 1) / wpb, ctx->num_cu * per_cu));
@@ -2613,7 +2613,7 @@ int halign_msa(halign_ctx *ctx, const halign_scoring *sc, const halign_seqs *seq
     uint8_t *out = (uint8_t *)alloc((size_t)N * (size_t)width, user);
     if (!out && width > 0) return fail(HALIGN_E_NOMEM, "allocator returned NULL for %lld bytes", (long long)(N * width));
     hmark(ctx, "alloc");
-    RCHK(emit_rows(ctx, seqs, m, ins, al, G, col, width, out, st));
+    RCHK(emit_rows(ctx, seqs, m, ins, al, G, col, width, out, longest, st));
     hmark(ctx, "rows");
     hmark_print(ctx);
     *msa = out;
@@ -3332,7 +3332,8 @@ int halign_nuc_msa(halign_ctx *ctx, const halign_scoring *sc, const halign_seqs 
                    int32_t *score, halign_alloc_fn alloc, void *user, uint8_t **msa, int64_t *width_host,
                    void *stream) {
     if (!ctx || !alloc || !msa || !width_host || !score) return fail(HALIGN_E_INVALID, "bad arguments");
-    RCHK(check_seqs(seqs));
+    int longest = 0;
+    RCHK(check_seqs(seqs, &longest));
     const int N = seqs->n;
     if (center < 0 || center >= N) return fail(HALIGN_E_INVALID, "center %d of %d", center, N);
     hipStream_t st = (hipStream_t)stream;
@@ -3353,7 +3354,7 @@ int halign_nuc_msa(halign_ctx *ctx, const halign_scoring *sc, const halign_seqs 
                    [&] { return merge_offsets(ctx, G, m + 1, col, &width, st); }, stream));
     uint8_t *out = (uint8_t *)alloc((size_t)N * (size_t)width, user);
     if (!out && width > 0) return fail(HALIGN_E_NOMEM, "allocator returned NULL for %lld bytes", (long long)(N * width));
-    RCHK(emit_rows(ctx, seqs, m, ins, al, G, col, width, out, st));
+    RCHK(emit_rows(ctx, seqs, m, ins, al, G, col, width, out, longest, st));
     *msa = out;
     *width_host = width;
     return HALIGN_OK;

@@ -181,15 +181,23 @@ __global__ void __launch_bounds__(1024) merge_scan_kernel(const int32_t *G, int 
 }
 
 // Rows: one wavefront per row, up to four wavefronts per workgroup, each
-// with its own LDS region.  Per row the wavefront stages the row's insertion
-// counts and aligned bits, finds where each block starts in the sequence
-// with a wave-wide prefix sum, and builds the row in LDS a chunk of columns
-// at a time: fill with gaps, place every residue at its column (block p by
-// binary search over the block starts; offset t < ins[p] goes to col[p] + t,
-// the aligned residue to the center column col[p] + G[p]), then copy the
-// chunk out with 16-byte stores.  The chunk sits in LDS at the row's
-// misalignment, so aligned LDS words map onto aligned global words.
+// with its own LDS region.  A row's insertion counts, aligned bits and residues
+// are staged in LDS as aligned words, loaded while the row before is built;
+// then the row is built in LDS a chunk of columns at a time: filled with
+// gaps, its blocks shared by the lanes (a wave-wide prefix sum of their
+// residues gives each lane its first one), and copied out with 16-byte stores.
+// Block p's insertion t goes to column col[p] + t, its aligned residue to the center
+// column col[p] + G[p]; blocks with more than kRowFew insertions (the ends of
+// a local alignment) are placed by the whole wavefront.  The chunk sits in LDS at the
+// row's misalignment, so aligned LDS words map onto aligned global words.
+//
+// Bound by latency: with the loads in line, a binary search per lane and each
+// residue read from memory where it was placed, 20,000 rows of 311 + 1 blocks and
+// 4,208 columns took 67 us, 300,000 of 200 + 1 and 5,015 902 us; now 43 and 535
+// (2.8 TB/s of bytes written).
 constexpr int kWaveRows = 4;
+constexpr int kRowFew = 4;
+constexpr int kRowPre = 4;        // aligned words per lane of counts and of residues loaded a row ahead
 
 struct RowsArgs {
     const uint8_t *res;
@@ -203,25 +211,26 @@ struct RowsArgs {
     int64_t width;
     int ch;                   // columns per chunk (multiple of 16)
     int wave_bytes;           // LDS bytes per wavefront region
+    int res_bytes;            // residues of a row staged there at most (longer rows are read from memory)
     int gc_lds;               // col staged in LDS for the workgroup (after the wave regions)
     uint8_t *msa;             // [nrows][width]
 };
+__host__ __device__ inline size_t rows_ins_bytes(int m1) { return (2 * (size_t)m1 + 4 + 15) & ~(size_t)15; }
+__host__ __device__ inline size_t rows_bit_bytes(int aw) { return (4 * (size_t)aw + 15) & ~(size_t)15; }
 
 __global__ void __launch_bounds__(64 * kWaveRows) rows_kernel(RowsArgs a) {
     extern __shared__ uint4 lds_rows[];
-    const int tid = threadIdx.x, wid = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, wid = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int wpb = blockDim.x >> 6;
     const int m = a.m, m1 = m + 1;
     const int64_t width = a.width;
-    // per wavefront: block starts in the sequence (uint16: lengths < 65536),
-    // insertion counts, aligned bits, then the row chunk
-    const size_t h2 = ((size_t)m1 * 2 + 3) & ~(size_t)3;
+    // per wavefront: insertion counts (uint16), aligned bits, residues, then
+    // the row chunk [ch + 16]
     char *wsh = reinterpret_cast<char *>(lds_rows) + (size_t)wid * a.wave_bytes;
-    uint16_t *spos = reinterpret_cast<uint16_t *>(wsh);                         // [m1]
-    uint16_t *sins = reinterpret_cast<uint16_t *>(wsh + h2);                   // [m1]
-    uint32_t *abit = reinterpret_cast<uint32_t *>(wsh + 2 * h2);
-    const size_t bo = (2 * h2 + 4 * (size_t)a.aw + 15) & ~(size_t)15;
-    uint8_t *buf = reinterpret_cast<uint8_t *>(wsh + bo);                     // [ch + 16], 16-byte aligned
+    uint32_t *iw = reinterpret_cast<uint32_t *>(wsh);
+    uint32_t *abit = reinterpret_cast<uint32_t *>(wsh + rows_ins_bytes(m1));
+    uint32_t *rw = abit + rows_bit_bytes(a.aw) / 4;
+    uint8_t *buf = reinterpret_cast<uint8_t *>(rw) + a.res_bytes + 16;
     uint4 *buf16 = reinterpret_cast<uint4 *>(buf);
     // the workgroup's column table: col[p] for p <= m and width + 1 after
     // it, so block p's gap count is col[p + 1] - col[p] - 1
@@ -233,123 +242,165 @@ __global__ void __launch_bounds__(64 * kWaveRows) rows_kernel(RowsArgs a) {
     auto colg = [&](int p) __attribute__((always_inline)) -> int2 {
         return a.gc_lds ? make_int2(gcl[p], gcl[p + 1] - gcl[p] - 1) : make_int2((int)a.col[p], a.G[p]);
     };
-    auto colv = [&](int p) __attribute__((always_inline)) -> int64_t {   // col[p], p <= m
-        return a.gc_lds ? (int64_t)gcl[p] : a.col[p];
+    auto colv = [&](int p) __attribute__((always_inline)) -> int {   // col[p], p <= m (below 2^31)
+        return a.gc_lds ? gcl[p] : (int)a.col[p];
     };
-    const int per = (m1 + 63) / 64;
-    const int lo = min(m1, lane * per), hi = min(m1, lo + per);
-    for (int k = blockIdx.x * wpb + wid; k < a.nrows; k += gridDim.x * wpb) {
-        const int64_t so = a.off[k];
-        const int n = (int)(a.off[k + 1] - so);
-        const uint8_t *s = a.res + so;
-        const uint16_t *ir = a.ins + (int64_t)k * m1;
-        const uint32_t *ar = a.aligned + (int64_t)k * a.aw;
+    // a row's words: counts (from the aligned word that holds the first one),
+    // residues (likewise), aligned bits
+    struct Row {
+        int64_t so;
+        int n, iodd, rodd, ni, nr;   // words of counts and of residues
+        const uint32_t *ip, *rp, *ap;
+    };
+    auto row_at = [&](int k, int64_t so, int64_t eo) __attribute__((always_inline)) {
+        Row r;
+        r.so = so;
+        r.n = (int)(eo - so);
+        const uintptr_t ia = (uintptr_t)(a.ins + (int64_t)k * m1), ra = (uintptr_t)(a.res + so);
+        r.iodd = (int)(ia & 3) >> 1;
+        r.rodd = (int)(ra & 3);
+        r.ip = reinterpret_cast<const uint32_t *>(ia & ~(uintptr_t)3);
+        r.rp = reinterpret_cast<const uint32_t *>(ra & ~(uintptr_t)3);
+        r.ap = a.aligned + (int64_t)k * a.aw;
+        r.ni = (r.iodd + m1 + 1) >> 1;
+        r.nr = r.n > 0 && r.n <= a.res_bytes ? (r.rodd + r.n + 3) >> 2 : 0;
+        return r;
+    };
+    const int step = gridDim.x * wpb;
+    int k = blockIdx.x * wpb + wid;
+    if (k >= a.nrows) return;
+    uint32_t pi[kRowPre], pr[kRowPre], pa0 = 0;
+    auto fetch = [&](const Row &r) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kRowPre; ++u) {
+            const int i = 64 * u + lane;
+            pi[u] = i < r.ni ? r.ip[i] : 0u;
+            pr[u] = i < r.nr ? r.rp[i] : 0u;
+        }
+        pa0 = lane < a.aw ? r.ap[lane] : 0u;
+    };
+    Row r = row_at(k, a.off[k], a.off[k + 1]);
+    fetch(r);
+    int64_t no = 0, ne = 0;   // the next row's residues
+    if (k + step < a.nrows) {
+        no = a.off[k + step];
+        ne = a.off[k + step + 1];
+    }
+    for (;;) {
         __builtin_amdgcn_wave_barrier();   // the previous row is done with this region
-        // staged with 8 loads in flight per lane (a long center's counts are
-        // hundreds of loads per lane)
-        for (int q0 = 0; q0 < a.aw; q0 += 512) {
-            uint32_t v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int q = q0 + 64 * u + lane;
-                v[u] = q < a.aw ? ar[q] : 0u;
+        for (int u = 0; u < kRowPre; ++u) {
+            const int i = 64 * u + lane;
+            if (i < r.ni) iw[i] = pi[u];
+            if (i < r.nr) rw[i] = pr[u];
+        }
+        if (lane < a.aw) abit[lane] = pa0;
+        // what a long center or row has past the prefetched words
+        for (int i0 = 64 * kRowPre; i0 < r.ni || i0 < r.nr; i0 += 256) {
+            uint32_t v[4], w[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = i0 + 64 * u + lane;
+                v[u] = i < r.ni ? r.ip[i] : 0u;
+                w[u] = i < r.nr ? r.rp[i] : 0u;
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int q = q0 + 64 * u + lane;
-                if (q < a.aw) abit[q] = v[u];
+            for (int u = 0; u < 4; ++u) {
+                const int i = i0 + 64 * u + lane;
+                if (i < r.ni) iw[i] = v[u];
+                if (i < r.nr) rw[i] = w[u];
             }
         }
-        for (int p0 = 0; p0 < m1; p0 += 512) {
-            uint16_t v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int p = p0 + 64 * u + lane;
-                v[u] = p < m1 ? ir[p] : (uint16_t)0;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int p = p0 + 64 * u + lane;
-                if (p < m1) sins[p] = v[u];
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        int sum = 0;
-        for (int p = lo; p < hi; ++p)
-            sum += (int)sins[p] + ((p < m) ? (int)((abit[p >> 5] >> (p & 31)) & 1u) : 0);
-        int inc = sum;   // inclusive prefix over the 64 lanes
-        for (int d = 1; d < 64; d <<= 1) {
-            const int v = __shfl_up(inc, d, 64);
-            if (lane >= d) inc += v;
-        }
-        int acc = inc - sum;
-        for (int p = lo; p < hi; ++p) {
-            spos[p] = (uint16_t)acc;
-            acc += (int)sins[p] + ((p < m) ? (int)((abit[p >> 5] >> (p & 31)) & 1u) : 0);
-        }
-        __builtin_amdgcn_wave_barrier();
+        for (int q = 64 + lane; q < a.aw; q += 64) abit[q] = r.ap[q];
+        const uint16_t *sins = reinterpret_cast<const uint16_t *>(iw) + r.iodd;
+        const uint8_t *sres = reinterpret_cast<const uint8_t *>(rw) + r.rodd, *gres = a.res + r.so;
+        const bool rl = r.n <= a.res_bytes;
+        const int n = r.n;
         uint8_t *row = a.msa + (int64_t)k * width;
         const int a0 = (int)((uintptr_t)row & 15);
-        // Residues are split over the lanes chunk by chunk.  Columns grow with
-        // the residue index, so a chunk of columns [x0, x1) holds the residues
-        // first_at(x0) .. first_at(x1) - 1; first_at(x) is found from block p,
-        // the last with col[p] <= x: block p's residues before column x are its
-        // first min(x - col[p], ins[p]) (its insertions sit at col[p] + t, its
-        // aligned residue at col[p + 1] - 1).  Each lane then places a
-        // contiguous run of that range: one binary search for the block of its
-        // first residue (within the chunk's blocks), then a short forward walk.
-        auto first_at = [&](int64_t x, int &pblk) __attribute__((always_inline)) -> int {
-            int l0 = pblk, h0 = m;   // col[pblk] <= x
-            while (l0 < h0) {
-                const int mid = (l0 + h0 + 1) >> 1;
-                if (colv(mid) <= x) l0 = mid;
-                else h0 = mid - 1;
+        const bool more = k + step < a.nrows;
+        if (more) {   // the next row's words, and the offsets after it
+            k += step;
+            r = row_at(k, no, ne);
+            fetch(r);
+            if (k + step < a.nrows) {
+                no = a.off[k + step];
+                ne = a.off[k + step + 1];
             }
-            pblk = l0;
-            return (int)spos[l0] + (int)min<int64_t>(x - colv(l0), (int64_t)sins[l0]);
+        }
+        auto count = [&](int p) __attribute__((always_inline)) -> int {   // residues of block p
+            return (int)sins[p] + (p < m ? (int)((abit[p >> 5] >> (p & 31)) & 1u) : 0);
         };
-        auto search = [&](int q, int l, int h) __attribute__((always_inline)) {   // last block in [l, h] with start <= q
-            while (l < h) {
-                const int mid = (l + h + 1) >> 1;
-                if (spos[mid] <= q) l = mid;
-                else h = mid - 1;
-            }
-            return l;
-        };
-        int qa = 0, pa = 0;   // the chunk's first residue and its block
+        int pa = 0, qa = 0;   // first block of the chunk, its first residue
         for (int64_t x0 = 0; x0 < width; x0 += a.ch) {
-            const int len = (int)min<int64_t>(a.ch, width - x0);
-            int pb = pa;
-            const int qb = x0 + len >= width ? n : first_at(x0 + len, pb);
+            const int len = (int)min<int64_t>(a.ch, width - x0), x1 = (int)x0 + len;
+            int pe = m1;      // blocks with a column before x1: [pa, pe)
+            if (x1 < width) {
+                int lo = pa, hi = m1;   // the first block from x1 on
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (colv(mid) < x1) lo = mid + 1;
+                    else hi = mid;
+                }
+                pe = lo;
+            }
             const int nw = (a0 + len + 15) >> 4;
             for (int q = lane; q < nw; q += 64) buf16[q] = make_uint4(~0u, ~0u, ~0u, ~0u);
+            const int per = (pe - pa + 63) >> 6;
+            const int lo = min(pe, pa + lane * per), hi = min(pe, lo + per);
+            int sum = 0;
+            for (int p = lo; p < hi; ++p) sum += count(p);
+            int inc = sum;   // inclusive prefix over the 64 lanes
+            for (int d = 1; d < 64; d <<= 1) {
+                const int v = __shfl_up(inc, d, 64);
+                if (lane >= d) inc += v;
+            }
             __builtin_amdgcn_wave_barrier();
-            const int pc = (qb - qa + 63) >> 6;
-            const int r0 = min(qb, qa + lane * pc), r1 = min(qb, r0 + pc);
-            int l = r0 < r1 ? search(r0, pa, x0 + len >= width ? m : pb) : 0;
-            for (int q = r0; q < r1; ++q) {
-                for (int st = 0; st < 4 && l < m && spos[l + 1] <= q; ++st) ++l;
-                if (l < m && spos[l + 1] <= q) l = search(q, l, m);
-                const int tq = q - spos[l];
-                const int2 cg = colg(l);
-                const int64_t dest = cg.x + (tq < (int)sins[l] ? tq : cg.y);
-                if (dest >= x0 && dest < x0 + len) buf[a0 + (int)(dest - x0)] = s[q];
+            const int base = (int)x0 - a0;   // column of LDS byte 0
+            auto put = [&](int c, int q) __attribute__((always_inline)) {   // residue q in column c
+                if (c >= (int)x0 && c < x1 && q < n) buf[c - base] = rl ? sres[q] : gres[q];
+            };
+            int q = qa + inc - sum;
+            for (int u = 0; u < per; ++u) {   // uniform trip count (ballots)
+                const int p = lo + u;
+                const bool act = p < hi;
+                const int ni = act ? (int)sins[p] : 0;
+                const int2 cg = act ? colg(p) : make_int2(0, 0);
+                if (ni <= kRowFew)
+                    for (int t = 0; t < ni; ++t) put(cg.x + t, q + t);
+                uint64_t big = __ballot(ni > kRowFew);
+                while (big) {
+                    const int l = __builtin_ctzll(big);
+                    big &= big - 1;
+                    const int bn = __builtin_amdgcn_readlane(ni, l), bc = __builtin_amdgcn_readlane(cg.x, l),
+                              bq = __builtin_amdgcn_readlane(q, l);
+                    for (int t = lane; t < bn; t += 64) put(bc + t, bq + t);
+                }
+                q += ni;
+                if (act && p < m && ((abit[p >> 5] >> (p & 31)) & 1u)) {
+                    put(cg.x + cg.y, q);
+                    ++q;
+                }
             }
             __builtin_amdgcn_wave_barrier();
             // copy out: LDS byte a0 + c holds column x0 + c
             uint8_t *dst = row + x0 - a0;   // 16-byte aligned (x0 is a multiple of 16)
-            for (int q = lane; q < nw; q += 64) {
-                const int b0 = 16 * q;
+            for (int w = lane; w < nw; w += 64) {
+                const int b0 = 16 * w;
                 if (b0 >= a0 && b0 + 16 <= a0 + len) {
-                    *reinterpret_cast<uint4 *>(dst + b0) = buf16[q];
+                    *reinterpret_cast<uint4 *>(dst + b0) = buf16[w];
                 } else {
                     for (int c = max(b0, a0); c < min(b0 + 16, a0 + len); ++c) dst[c] = buf[c];
                 }
             }
             __builtin_amdgcn_wave_barrier();
-            qa = qb;
-            pa = pb;
+            if (x1 < width) {   // the next chunk's first block holds column x1 or starts there
+                const bool whole = pe < m1 && colv(pe) == x1;
+                qa += __builtin_amdgcn_readlane(inc, 63) - (whole ? 0 : count(pe - 1));
+                pa = whole ? pe : pe - 1;
+            }
         }
+        if (!more) break;
     }
 }
 
