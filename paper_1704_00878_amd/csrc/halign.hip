@@ -72,6 +72,7 @@ struct DevBuf {
 
 struct HostBuf {
     void *p = nullptr;
+    void *dev = nullptr;   // the device's address of p (the stage)
     size_t cap = 0;
 };
 
@@ -86,7 +87,7 @@ struct halign_ctx {
     size_t lds_cu = 65536;      // LDS of a CU: what one workgroup may take with the attribute set
     int last_pk = 0;          // the last batch ran the packed 16-bit wavefront kernel
     // device scratch
-    DevBuf codes, bound, plan, counter, pairbuf, msabuf, spbuf, sbuf;
+    DevBuf codes, bound, plan, counter, pairbuf, msabuf, spbuf, sbuf, histbuf;
     DevBuf mlp[10];          // learned-center scratch (features, activations, gradients, moments)
     // pinned host staging for plans: regions are taken in order within a
     // call (stage_off, plan_off) and never reused before the call ends, so the
@@ -273,10 +274,16 @@ int stage_host(halign_ctx *ctx, size_t bytes, char **host) {
         const size_t want = std::max<size_t>(2 * (o + bytes), 1 << 16);
         HCHK(hipHostMalloc(&ctx->stage.p, want, hipHostMallocDefault));
         ctx->stage.cap = want;
+        if (hipHostGetDevicePointer(&ctx->stage.dev, ctx->stage.p, 0) != hipSuccess) ctx->stage.dev = nullptr;
     }
     *host = (char *)ctx->stage.p + o;
     ctx->stage_off = o + bytes;
     return HALIGN_OK;
+}
+
+// What a kernel reads a region of the stage by (nullptr: not mapped).
+void *stage_dev(const halign_ctx *ctx, const char *host) {
+    return ctx->stage.dev ? (char *)ctx->stage.dev + (host - (char *)ctx->stage.p) : nullptr;
 }
 
 // `bytes` of the device plan buffer, after the regions this call took already
@@ -485,6 +492,10 @@ struct BatchOut {
     int gskip = -1;         // pair left out of G (the center itself)
 };
 
+constexpr int kDevPlanMin = 2048;   // pairs from which the device plans a batch
+constexpr int kHistParts = 16;      // workgroups that count them
+constexpr int kPlanFetch = 1 << 15; // plan bytes up to which a kernel fetches them from the stage
+
 // Plans and runs the forward pass (+ walk when tb) for the pairs `pids_in`
 // against center (device) of length m.
 struct Tune {
@@ -499,16 +510,17 @@ struct Tune {
 // pairs_in: the pair ids of the batch (NULL: 0 .. np-1).
 int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, const halign_seqs *sq,
               const int32_t *pids_in, int np, bool tb, bool endc, int route, const BatchOut &out, hipStream_t st,
-              const Tune &tune = Tune(), int dev_longest = -1) {
+              const Tune &tune = Tune(), int dev_longest = -1, bool counted = false) {
     const int64_t *oh = sq->offsets_host;
     if (np == 0) return HALIGN_OK;
     auto pid_of = [&](int x) { return pids_in ? pids_in[x] : x; };
     // Planned on the device (plan_kernels.hpp) from 2,048 pairs, where the caller
-    // allows it (dev_longest: the longest of all pairs), the batch is not a
+    // allows it (dev_longest: the longest of all pairs; counted: the call's first
+    // kernel has counted them by length), the batch is not a
     // captured one (whose replays read the host's plan) and the knobs leave the
     // dealing open; the host then only looks at a sample of the lengths.  Below,
     // the host plans faster than the kernels' launches (64 pairs: 5 us).
-    bool dev = dev_longest >= 0 && !pids_in && np >= 2048 && !ctx->capturing && !getenv("HALIGN_DEAL");
+    bool dev = dev_longest >= 0 && !pids_in && np >= kDevPlanMin && !ctx->capturing && !getenv("HALIGN_DEAL");
     int32_t *pids = nullptr, *plen = nullptr;
     int64_t sum_len = 0;
     int nonempty_all = np;   // (empty pairs sort last)
@@ -755,7 +767,8 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
         // the plan's arrays, as offsets into the chunk's region of the device plan
         size_t o_cbase = 0, o_cstr = 0, o_ccol = 0, o_walk = 0, o_sbeg = 0, o_slen = 0, o_slot0 = 0, o_scb = 0,
                o_sbb = 0, o_spid = 0, o_scol = 0, o_sstr = 0, o_order = 0, o_gnmax = 0, o_gcb = 0;
-        char *dplan = nullptr;
+        char *dplan = nullptr, *zplan = nullptr;
+        size_t plan_bytes = 0;
         if (dev) {
             PlanBuilder pb;
             nstreams = dev_ns;
@@ -800,10 +813,14 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
             d.sbb = (int64_t *)(dplan + o_sbb);
             d.keys = (unsigned long long *)ctx->sbuf.p;
             d.sres = (uint8_t *)ctx->sbuf.p + keys_b;
-            RCHK(launch_fill((uint32_t *)d.hist, 0u, nlong + 1, st));
-            hipLaunchKernelGGL(hk::plan_hist_kernel, dim3(grid_for(cn, 1024, 128)), dim3(256), 0, st, d);
-            hipLaunchKernelGGL(hk::plan_scan_kernel, dim3(1), dim3(1024), 0, st, d.hist, nlong);
-            hipLaunchKernelGGL(hk::plan_scatter_kernel, dim3(grid_for(cn, 256, 1 << 30)), dim3(256), 0, st, d);
+            if (!counted) {
+                RCHK(launch_fill((uint32_t *)d.hist, 0u, nlong + 1, st));
+                hipLaunchKernelGGL(hk::plan_hist_kernel, dim3(grid_for(cn, 1024, 128)), dim3(256), 0, st, d);
+            }
+            hipLaunchKernelGGL(hk::plan_scan_kernel, dim3(1), dim3(1024), 0, st, d.hist, nlong,
+                               counted ? (const int32_t *)ctx->histbuf.p : nullptr, counted ? kHistParts : 0);
+            hipLaunchKernelGGL(hk::plan_scatter_kernel, dim3(grid_for(cn, 1024 * hk::kScatterPer, 1 << 30)), dim3(1024), 0,
+                               st, d);
             hipLaunchKernelGGL(hk::plan_stage_kernel, dim3((unsigned)((cn + 3) / 4)), dim3(256), 0, st, d);
             HCHK(hipGetLastError());
             hmark(ctx, "dplan");
@@ -840,6 +857,7 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
                 o_gcb = pb.add(sizeof(int64_t) * ngroups);
             }
             char *hs = nullptr;
+            pb.total = (pb.total + 15) & ~size_t(15);
             RCHK(stage_host(ctx, pb.total, &hs));
             int32_t *h_walk = (int32_t *)(hs + o_walk);
             int64_t *h_cbase = (int64_t *)(hs + o_cbase);
@@ -990,7 +1008,10 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
             }
             hmark(ctx, "plan");
             RCHK(plan_dev(ctx, pb.total, st, &dplan));
-            HCHK(hipMemcpyAsync(dplan, hs, pb.total, hipMemcpyHostToDevice, st));
+            // a small plan goes with the residues' staging (stage_stream_kernel)
+            if (route == kRouteIntra && pb.total <= (size_t)kPlanFetch && !ctx->capturing) zplan = (char *)stage_dev(ctx, hs);
+            plan_bytes = pb.total;
+            if (!zplan) HCHK(hipMemcpyAsync(dplan, hs, pb.total, hipMemcpyHostToDevice, st));
             stage_copied(ctx);
         }
         std::array<hipEvent_t, 3> *tv = nullptr;
@@ -1014,9 +1035,12 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
             uint8_t *sres = (uint8_t *)ctx->sbuf.p + keys_b;
             if (passes > 1) RCHK(grow(ctx, ctx->bound, std::max<size_t>(8, bound_elems * 8)));
             if (!dev) {
-                hipLaunchKernelGGL(hk::stage_stream_kernel, dim3(nslots), dim3(128), 0, st, sq->residues, sq->offsets,
-                                   (const int32_t *)(dplan + o_spid), (const int64_t *)(dplan + o_scol), nslots,
-                                   p16 ? S.alpha : 31, sres, keys);
+                const char *pl = zplan ? zplan : dplan;
+                const int n16 = zplan ? (int)(plan_bytes / 16) : 0;
+                hipLaunchKernelGGL(hk::stage_stream_kernel, dim3((nslots + 3) / 4 + (n16 + 255) / 256), dim3(256), 0, st,
+                                   sq->residues, sq->offsets, (const int32_t *)(pl + o_spid),
+                                   (const int64_t *)(pl + o_scol), nslots, p16 ? S.alpha : 31, sres, keys,
+                                   (const uint4 *)zplan, (uint4 *)dplan, n16);
                 HCHK(hipGetLastError());
             }
             hk::StreamArgs a{};
@@ -1277,7 +1301,9 @@ int autotune(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, co
 }
 
 // The first staging step of every call: starts the call's stage regions.
-int upload_matrix(halign_ctx *ctx, const halign_scoring *sc, hipStream_t st, Scoring *S) {
+// prep (optional): the call's first kernel fetches the matrix itself.
+int upload_matrix(halign_ctx *ctx, const halign_scoring *sc, hipStream_t st, Scoring *S,
+                  hk::PrepArgs *prep = nullptr) {
     const size_t bytes = (size_t)sc->alphabet * sc->alphabet;
     RCHK(stage_begin(ctx));
     if (ctx->capturing) {   // the device copy from the uncaptured run is kept by the graph
@@ -1290,9 +1316,15 @@ int upload_matrix(halign_ctx *ctx, const halign_scoring *sc, hipStream_t st, Sco
     }
     RCHK(grow(ctx, ctx->spbuf, 4096));
     char *hs = nullptr;
-    RCHK(stage_host(ctx, bytes, &hs));
+    RCHK(stage_host(ctx, (bytes + 3) & ~size_t(3), &hs));
     memcpy(hs, sc->matrix_host, bytes);
-    HCHK(hipMemcpyAsync(ctx->spbuf.p, hs, bytes, hipMemcpyHostToDevice, st));
+    if (prep && stage_dev(ctx, hs)) {
+        prep->msrc = (const uint32_t *)stage_dev(ctx, hs);
+        prep->mdst = (uint32_t *)ctx->spbuf.p;
+        prep->mwords = (int)((bytes + 3) / 4);
+    } else {
+        HCHK(hipMemcpyAsync(ctx->spbuf.p, hs, bytes, hipMemcpyHostToDevice, st));
+    }
     stage_copied(ctx);
     S->dmat = (const int8_t *)ctx->spbuf.p;
     S->hmat = sc->matrix_host;
@@ -1306,9 +1338,9 @@ int upload_matrix(halign_ctx *ctx, const halign_scoring *sc, hipStream_t st, Sco
 // The check is enqueued without waiting: the kernels are memory-safe for any
 // code (they mask codes to 5 bits), and its result comes to flag_host (by
 // flag_fetch, or with the merge's width) for validate_check() to read after the
-// call's synchronisation point.
+// call's synchronisation point.  with: what else the launch does.
 int validate_codes(halign_ctx *ctx, int alpha, const uint8_t *res, int64_t nres, const uint8_t *center, int m,
-                   hipStream_t st) {
+                   hipStream_t st, const hk::PrepArgs &with = hk::PrepArgs{}) {
     RCHK(grow(ctx, ctx->counter, 256));
     uint32_t *flag = (uint32_t *)ctx->counter.p + 8;
     // the flag holds (call tag << 8 | largest code) and is raised with
@@ -1329,12 +1361,18 @@ int validate_codes(halign_ctx *ctx, int alpha, const uint8_t *res, int64_t nres,
         tag = ++ctx->vtag;
     }
     ctx->check_tag = tag;
-    const int64_t n1 = nres > 0 ? nres : 0, n2 = (center && m > 0) ? m : 0;
-    if (n1 + n2 > 0) {
-        hipLaunchKernelGGL(hk::maxcode_kernel, dim3(grid_for((n1 + 15) / 16 + 1, 256, 1024)), dim3(256), 0, st, res, n1,
-                           center, n2, tag << 8, flag);
-        HCHK(hipGetLastError());
-    }
+    hk::PrepArgs a = with;
+    a.n = nres > 0 ? nres : 0;
+    a.nq = (center && m > 0) ? m : 0;
+    a.p = res;
+    a.q = center;
+    a.tag = tag << 8;
+    a.out = flag;
+    int64_t work = (a.n + 15) / 16 + 1;
+    for (int r = 0; r < 4; ++r) work += a.nz[r] / 4;
+    hipLaunchKernelGGL(hk::prep_kernel, dim3(grid_for(work, 256, 1024) + a.hwgs), dim3(256),
+                       a.hwgs ? 4 * (size_t)(a.maxlen + 1) : 0, st, a);
+    HCHK(hipGetLastError());
     ctx->flag_alpha = alpha;
     return HALIGN_OK;
 }
@@ -1463,7 +1501,7 @@ void halign_ctx_destroy(halign_ctx *ctx) {
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
     if (ctx->aux_stream) (void)hipStreamDestroy(ctx->aux_stream);
     for (DevBuf *b : {&ctx->codes, &ctx->bound, &ctx->plan, &ctx->counter, &ctx->pairbuf, &ctx->msabuf, &ctx->spbuf,
-                      &ctx->sbuf, &ctx->nuctab, &ctx->nucscr, &ctx->nucdp, &ctx->rowck,
+                      &ctx->sbuf, &ctx->histbuf, &ctx->nuctab, &ctx->nucscr, &ctx->nucdp, &ctx->rowck,
                       &ctx->njrows, &ctx->njD, &ctx->njS, &ctx->njacc, &ctx->njB, &ctx->njF})
         if (b->p) (void)hipFree(b->p);
     for (DevBuf &b : ctx->mlp)
@@ -1590,14 +1628,15 @@ static int sw_batch_body(halign_ctx *ctx, const halign_scoring *sc, const uint8_
     const int N = seqs->n;
     if (N == 0) return HALIGN_OK;
     Scoring S;
-    RCHK(upload_matrix(ctx, sc, st, &S));
+    const bool want_tune = ctx->autotune && (flags & (3u << 4)) == HALIGN_ROUTE_AUTO;
+    hk::PrepArgs pa{};
+    RCHK(upload_matrix(ctx, sc, st, &S, want_tune ? nullptr : &pa));   // (the tuner runs before)
     // endcells: needed by the walk, or to fill cells in score-only mode
     const bool endc = tb || cells != nullptr;
     RCHK(grow(ctx, ctx->pairbuf, (size_t)N * 8 + 256));
     int32_t *endcell = (int32_t *)ctx->pairbuf.p;
     hmark(ctx, "upload");
     Tune tune;
-    const bool want_tune = ctx->autotune && (flags & (3u << 4)) == HALIGN_ROUTE_AUTO;
     if (want_tune) {
         BatchOut tout{score, cells, endcell, ins, aligned};
         bool ran = false;
@@ -1609,24 +1648,31 @@ static int sw_batch_body(halign_ctx *ctx, const halign_scoring *sc, const uint8_
     // the code check and the zeroing of the outputs go in before the host
     // plans the batch, so these small kernels run while the host works (the
     // forward kernels read codes masked to 5 bits, the check is read after the
-    // batch, and the outputs are first written by the walk)
+    // batch, and the outputs are first written by the walk); with them the matrix
+    // and the device planner's count of the pairs by length
+    const bool graph_call = (flags & HALIGN_GRAPH) != 0;
+    const bool count = !graph_call && N >= kDevPlanMin && longest < hk::kPrepHistMax;
     auto prep = [&]() -> int {
         if (tb) {
-            // ins (as 32-bit words; an odd trailing uint16 on its own), aligned
-            // and G zeroed in one launch
-            hk::ZeroArgs z{};
+            // ins (as 32-bit words; an odd trailing uint16 on its own), aligned and G zeroed
             const int64_t nins = (int64_t)N * (m + 1);
-            z.p[0] = reinterpret_cast<uint32_t *>(ins);
-            z.n[0] = nins / 2;
-            z.p[1] = aligned;
-            z.n[1] = (int64_t)N * ((m + 31) / 32);
-            z.p[2] = reinterpret_cast<uint32_t *>(G);
-            z.n[2] = G ? (int64_t)m + 1 : 0;
-            z.tail16 = (nins & 1) ? ins + (nins - 1) : nullptr;
-            hipLaunchKernelGGL(hk::zero_kernel, dim3(grid_for(z.n[0] + z.n[1], 256, 4096)), dim3(256), 0, st, z);
-            HCHK(hipGetLastError());
+            pa.z[0] = reinterpret_cast<uint32_t *>(ins);
+            pa.nz[0] = nins / 2;
+            pa.z[1] = aligned;
+            pa.nz[1] = (int64_t)N * ((m + 31) / 32);
+            pa.z[2] = reinterpret_cast<uint32_t *>(G);
+            pa.nz[2] = G ? (int64_t)m + 1 : 0;
+            pa.tail16 = (nins & 1) ? ins + (nins - 1) : nullptr;
         }
-        RCHK(validate_codes(ctx, sc->alphabet, seqs->residues, seqs->offsets_host[N], center, m, st));
+        if (count) {
+            RCHK(grow(ctx, ctx->histbuf, 4 * (size_t)kHistParts * hk::kPrepHistMax));
+            pa.off = seqs->offsets;
+            pa.np = N;
+            pa.maxlen = longest;
+            pa.hwgs = kHistParts;
+            pa.hpart = (int32_t *)ctx->histbuf.p;
+        }
+        RCHK(validate_codes(ctx, sc->alphabet, seqs->residues, seqs->offsets_host[N], center, m, st, pa));
         return HALIGN_OK;
     };
     BatchOut out{score, cells, endcell, ins, aligned};
@@ -1649,7 +1695,7 @@ static int sw_batch_body(halign_ctx *ctx, const halign_scoring *sc, const uint8_
         for (int k = 0; k < N; ++k) nlong += oh[k + 1] - oh[k] > kLongPair;
     if (nlong == 0) {
         RCHK(run_batch(ctx, S, center, m, seqs, nullptr, N, tb, endc, route, out, st, tune,
-                       (flags & HALIGN_GRAPH) ? -1 : longest));
+                       graph_call ? -1 : longest, count));
     } else {
         // long pairs first in the id list, then the rest
         std::vector<int32_t> &ids = ctx->h_split;
@@ -3147,8 +3193,8 @@ static int nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seq
     const int m = (int)(oh[center + 1] - oh[center]);
     const uint8_t *dc = seqs->residues + oh[center];
     Scoring S;
-    RCHK(upload_matrix(ctx, sc, st, &S));
-    RCHK(validate_codes(ctx, sc->alphabet, seqs->residues, oh[N], nullptr, 0, st));
+    hk::PrepArgs pa{};
+    RCHK(upload_matrix(ctx, sc, st, &S, &pa));
     // the center's segments: at most this many different strings, so the table
     // is at most half full
     const int nsg = m / k;
@@ -3174,20 +3220,18 @@ static int nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seq
     RCHK(grow(ctx, ctx->nuctab, tab_bytes));
     char *tb = (char *)ctx->nuctab.p;
     const int aw = (m + 31) / 32;
-    {   // zero the vectors (ins as words plus an odd tail), G and the counters
+    {   // the code check, and the vectors (ins as words plus an odd tail), G and the counters zeroed
         const int64_t n16 = (int64_t)N * (m + 1);
-        hk::ZeroArgs z{};
-        z.p[0] = (uint32_t *)ins;
-        z.n[0] = n16 / 2;
-        z.p[1] = aligned;
-        z.n[1] = (int64_t)N * aw;
-        z.p[2] = (uint32_t *)G;
-        z.n[2] = G ? m + 1 : 0;
-        z.p[3] = (uint32_t *)(tb + o_n);
-        z.n[3] = 2 * hk::kNucCounts;
-        z.tail16 = (n16 & 1) ? ins + (n16 - 1) : nullptr;
-        hipLaunchKernelGGL(hk::zero_kernel, dim3(grid_for(z.n[0] + z.n[1], 256, 4096)), dim3(256), 0, st, z);
-        HCHK(hipGetLastError());
+        pa.z[0] = (uint32_t *)ins;
+        pa.nz[0] = n16 / 2;
+        pa.z[1] = aligned;
+        pa.nz[1] = (int64_t)N * aw;
+        pa.z[2] = (uint32_t *)G;
+        pa.nz[2] = G ? m + 1 : 0;
+        pa.z[3] = (uint32_t *)(tb + o_n);
+        pa.nz[3] = 2 * hk::kNucCounts;
+        pa.tail16 = (n16 & 1) ? ins + (n16 - 1) : nullptr;
+        RCHK(validate_codes(ctx, sc->alphabet, seqs->residues, oh[N], nullptr, 0, st, pa));
     }
     hk::NucSetup su{};
     su.center = dc;

@@ -40,9 +40,7 @@ __global__ void endcell_to_cells_kernel(const int32_t *endcell, int n, int32_t *
     reinterpret_cast<int4 *>(cells)[k] = make_int4(0, 0, endcell[2 * k], endcell[2 * k + 1]);
 }
 
-// Largest code in [p, p + n) and [q, q + nq), raised into *out as
-// (tag | code) with atomicMax (one atomic per workgroup).  16-byte loads where
-// aligned.
+// Largest code in [p, p + n), 16-byte loads where aligned.
 __device__ __forceinline__ int maxcode_range(const uint8_t *p, int64_t n, int64_t tid, int64_t stride) {
     int mx = 0;
     const int64_t head = min<int64_t>(n, (int64_t)((16 - ((uintptr_t)p & 15)) & 15));
@@ -61,36 +59,59 @@ __device__ __forceinline__ int maxcode_range(const uint8_t *p, int64_t n, int64_
     return mx;
 }
 
-__global__ void __launch_bounds__(256) maxcode_kernel(const uint8_t *p, int64_t n, const uint8_t *q, int64_t nq,
-                                                      uint32_t tag, uint32_t *out) {
-    __shared__ int red[4];
-    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    int mx = n > 0 ? maxcode_range(p, n, tid, stride) : 0;
-    if (nq > 0) mx = max(mx, maxcode_range(q, nq, tid, stride));
-    for (int sh = 32; sh > 0; sh >>= 1) mx = max(mx, __shfl_xor(mx, sh));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const int b = max(max(red[0], red[1]), max(red[2], red[3]));
-        atomicMax(out, tag | (uint32_t)b);
-    }
-}
-
-// Zero up to four word ranges (and one trailing uint16) in one launch.
-struct ZeroArgs {
-    uint32_t *p[4];
-    int64_t n[4];
+// What a call does before its first real kernel, in one launch: up to four word
+// ranges (and one trailing uint16) zeroed; the largest code of two ranges raised
+// into *out as (tag | code) with atomicMax, one atomic per workgroup; the score
+// matrix fetched from pinned host memory; and, by the last hwgs workgroups, the
+// pairs counted by length, each into a row of hpart.  Apart, each cost its launch
+// (5 us at 64 pairs, whose kernels wait for the host) and the copy 8 us.
+struct PrepArgs {
+    uint32_t *z[4];
+    int64_t nz[4];
     uint16_t *tail16;
+    const uint8_t *p, *q;
+    int64_t n, nq;
+    uint32_t tag, *out;
+    const uint32_t *msrc;
+    uint32_t *mdst;
+    int mwords;
+    const int64_t *off;
+    int np, maxlen, hwgs;
+    int32_t *hpart;           // [hwgs][maxlen + 1]
 };
+constexpr int kPrepHistMax = 4096;   // lengths counted there
 
-__global__ void zero_kernel(ZeroArgs z) {
-    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+__global__ void __launch_bounds__(256) prep_kernel(PrepArgs a) {
+    extern __shared__ int32_t s_hist[];   // [maxlen + 1] where pairs are counted
+    __shared__ int red[4];
+    const int t = threadIdx.x, wgs = gridDim.x - a.hwgs;
+    if ((int)blockIdx.x >= wgs) {
+        const int b = blockIdx.x - wgs;
+        for (int x = t; x <= a.maxlen; x += 256) s_hist[x] = 0;
+        __syncthreads();
+        for (int x = b * 256 + t; x < a.np; x += a.hwgs * 256)
+            atomicAdd(s_hist + (int)min<int64_t>(a.maxlen, a.off[x + 1] - a.off[x]), 1);
+        __syncthreads();
+        for (int x = t; x <= a.maxlen; x += 256) a.hpart[b * (a.maxlen + 1) + x] = s_hist[x];
+        return;
+    }
+    const int64_t tid = (int64_t)blockIdx.x * 256 + t, stride = (int64_t)wgs * 256;
+    if (tid < a.mwords) a.mdst[tid] = a.msrc[tid];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-        for (int64_t x = tid; x < z.n[r]; x += stride) z.p[r][x] = 0u;
-    if (tid == 0 && z.tail16) *z.tail16 = 0;
+    for (int r = 0; r < 4; ++r) {
+        uint32_t *z = a.z[r];
+        const int64_t n = a.nz[r], n4 = ((uintptr_t)z & 15) == 0 ? n >> 2 : 0;
+        for (int64_t x = tid; x < n4; x += stride) reinterpret_cast<uint4 *>(z)[x] = make_uint4(0u, 0u, 0u, 0u);
+        for (int64_t x = 4 * n4 + tid; x < n; x += stride) z[x] = 0u;
+    }
+    if (tid == 0 && a.tail16) *a.tail16 = 0;
+    if (a.n + a.nq <= 0) return;
+    int mx = a.n > 0 ? maxcode_range(a.p, a.n, tid, stride) : 0;
+    if (a.nq > 0) mx = max(mx, maxcode_range(a.q, a.nq, tid, stride));
+    for (int sh = 32; sh > 0; sh >>= 1) mx = max(mx, __shfl_xor(mx, sh));
+    if ((t & 63) == 0) red[t >> 6] = mx;
+    __syncthreads();
+    if (t == 0) atomicMax(a.out, a.tag | (uint32_t)max(max(red[0], red[1]), max(red[2], red[3])));
 }
 
 // ASCII -> residue code through a 256-entry table.

@@ -23,21 +23,50 @@ __global__ void decode_keys_kernel(const unsigned long long *keys, const int32_t
     if (cells) cells[pid] = make_int4(0, 0, i1, j1);
 }
 
-// Stage the residues of every stream: sres[sbase + c0(q) + x] = s_q[x], with
-// kFirstCol on x = 0, and clear the slot's end-cell key.  One workgroup per
-// pair slot.
-__global__ void stage_stream_kernel(const uint8_t *res, const int64_t *off, const int32_t *slot_pid,
-                                    const int64_t *slot_col, int nslots, int clamp, uint8_t *sres,
-                                    unsigned long long *keys) {
-    const int q = blockIdx.x;
+// The n residues at src into dst by a wavefront, each code & 31 and at most
+// clamp (<= 31), with kFirstCol on the first one: aligned words of dst, each put
+// together from two aligned words of src (a word that holds a residue never leaves
+// its page), and single bytes at both ends, whose words other pairs share.  A byte
+// per lane took 220 us for 300,000 pairs (157 MB).
+__device__ __forceinline__ void stage_pair(const uint8_t *src, int n, uint8_t *dst, int clamp, int lane) {
+    const int head = min(n, (int)((4 - ((uintptr_t)dst & 3)) & 3)), nw = (n - head) >> 2, tail = n - head - 4 * nw;
+    const uint32_t c4 = (uint32_t)clamp * 0x01010101u;
+    const uintptr_t sa = (uintptr_t)(src + head);
+    const uint32_t *sw = reinterpret_cast<const uint32_t *>(sa & ~(uintptr_t)3);
+    const int sh = 8 * (int)(sa & 3);
+    uint32_t *dw = reinterpret_cast<uint32_t *>(dst + head);
+    for (int i = lane; i < nw; i += 64) {
+        const uint32_t w0 = sw[i], w1 = sh ? sw[i + 1] : 0u;
+        const uint32_t x = (uint32_t)(((uint64_t)w1 << 32 | w0) >> sh) & 0x1f1f1f1fu;
+        const uint32_t over = ((((x | 0x80808080u) - c4) & 0x80808080u) >> 7) * 255u;   // bytes >= clamp
+        const uint32_t y = (x & ~over) | (c4 & over);
+        dw[i] = y | (i == 0 && head == 0 ? (uint32_t)kFirstCol : 0u);
+    }
+    const int e = lane < head ? lane : n - tail + lane - 8;   // lanes 0 .. 2: the head, 8 .. 10: the tail
+    if (lane < head || (lane >= 8 && lane < 8 + tail))
+        dst[e] = (uint8_t)(min((int)(src[e] & 31), clamp) | (e == 0 ? kFirstCol : 0));
+}
+
+// Stage the residues of every stream: sres[c(q) + x] = s_q[x], and clear the
+// slot's end-cell key.  One wavefront per pair slot.  A small plan is read from
+// pinned host memory, and further workgroups copy it to the device (psrc, n16
+// 16-byte words) for the kernels after this one: a copy of its own cost 8 us.
+__global__ void __launch_bounds__(256) stage_stream_kernel(const uint8_t *res, const int64_t *off,
+                                                           const int32_t *slot_pid, const int64_t *slot_col, int nslots,
+                                                           int clamp, uint8_t *sres, unsigned long long *keys,
+                                                           const uint4 *psrc, uint4 *pdst, int n16) {
+    const int wgs = (nslots + 3) / 4;
+    if ((int)blockIdx.x >= wgs) {
+        const int x = ((int)blockIdx.x - wgs) * 256 + threadIdx.x;
+        if (x < n16) pdst[x] = psrc[x];
+        return;
+    }
+    const int q = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (q >= nslots) return;
-    if (threadIdx.x == 0) keys[q] = 0ull;
+    if (lane == 0) keys[q] = 0ull;
     const int pid = slot_pid[q];
     const int64_t so = off[pid];
-    const int n = (int)(off[pid + 1] - so);
-    uint8_t *dst = sres + slot_col[q];
-    for (int x = threadIdx.x; x < n; x += blockDim.x)
-        dst[x] = (uint8_t)(min((int)(res[so + x] & 31), clamp) | (x == 0 ? kFirstCol : 0));
+    stage_pair(res + so, (int)(off[pid + 1] - so), sres + slot_col[q], clamp, lane);
 }
 
 // ---- streams planned on the device ---------------------------------------------
@@ -52,7 +81,7 @@ struct DevPlanArgs {
     const uint8_t *res;
     const int64_t *off;
     int np, maxlen, ns, clamp;   // ns <= np
-    int32_t *hist;        // [maxlen + 1], zeroed; then each length's next place
+    int32_t *hist;        // [maxlen + 1]: each length's next place
     int2 *order;          // [np] (pair, length), longest first
     int per_group;        // streams that share codes and boundary rows (2: packed)
     int64_t cols, code_words, bound_elems;   // region sizes: columns per stream, the others per group
@@ -61,39 +90,43 @@ struct DevPlanArgs {
     unsigned long long *keys;
     uint8_t *sres;
 };
-constexpr int kPlanHistLds = 8192;   // lengths counted in LDS first
+constexpr int kPlanHistLds = 8192;   // lengths counted in LDS
 
+// Counts into zeroed hist, where the call's first kernel has not counted (from
+// lengths of kPrepHistMax on).
 __global__ void __launch_bounds__(256) plan_hist_kernel(DevPlanArgs a) {
-    __shared__ int32_t h[kPlanHistLds];
-    const bool lds = a.maxlen < kPlanHistLds;
-    if (lds) {
-        for (int x = threadIdx.x; x <= a.maxlen; x += 256) h[x] = 0;
-        __syncthreads();
-    }
     for (int x = blockIdx.x * 256 + threadIdx.x; x < a.np; x += gridDim.x * 256)
-        atomicAdd((lds ? h : a.hist) + (int)(a.off[x + 1] - a.off[x]), 1);
-    if (!lds) return;
-    __syncthreads();
-    for (int x = threadIdx.x; x <= a.maxlen; x += 256)
-        if (h[x]) atomicAdd(a.hist + x, h[x]);
+        atomicAdd(a.hist + (int)(a.off[x + 1] - a.off[x]), 1);
 }
 
-// hist[L] -> pairs longer than L, one workgroup
-__global__ void __launch_bounds__(1024) plan_scan_kernel(int32_t *hist, int maxlen) {
-    __shared__ int32_t part[1024];
+// hist[L] -> pairs longer than L, one workgroup; part (optional): nparts rows
+// of counts to add up instead
+__global__ void __launch_bounds__(1024) plan_scan_kernel(int32_t *hist, int maxlen, const int32_t *part, int nparts) {
+    __shared__ int32_t psum[1024];
     const int tid = threadIdx.x, n = maxlen + 1, per = (n + 1023) / 1024;
     const int lo = min(n, tid * per), hi = min(n, lo + per);   // positions in descending length
     int sum = 0;
-    for (int p = lo; p < hi; ++p) sum += hist[maxlen - p];
-    part[tid] = sum;
+    for (int p = lo; p < hi; ++p) {
+        const int L = maxlen - p;
+        if (part) {
+            int c = 0;
+#pragma unroll 8
+            for (int b = 0; b < nparts; ++b) c += part[b * n + L];
+            hist[L] = c;
+            sum += c;
+        } else {
+            sum += hist[L];
+        }
+    }
+    psum[tid] = sum;
     __syncthreads();
     for (int d = 1; d < 1024; d <<= 1) {
-        const int v = tid >= d ? part[tid - d] : 0;
+        const int v = tid >= d ? psum[tid - d] : 0;
         __syncthreads();
-        part[tid] += v;
+        psum[tid] += v;
         __syncthreads();
     }
-    int acc = tid > 0 ? part[tid - 1] : 0;
+    int acc = tid > 0 ? psum[tid - 1] : 0;
     for (int p = lo; p < hi; ++p) {
         const int c = hist[maxlen - p];
         hist[maxlen - p] = acc;
@@ -101,15 +134,41 @@ __global__ void __launch_bounds__(1024) plan_scan_kernel(int32_t *hist, int maxl
     }
 }
 
-__global__ void __launch_bounds__(256) plan_scatter_kernel(DevPlanArgs a) {
-    const int x = blockIdx.x * 256 + threadIdx.x;
-    if (x >= a.np) return;
-    const int L = (int)(a.off[x + 1] - a.off[x]);
-    a.order[atomicAdd(a.hist + L, 1)] = make_int2(x, L);
+// Pairs to their places in length order.  A workgroup ranks its pairs within
+// each length in LDS and takes a length's places with one atomic (an atomic per
+// pair on its length took 66 us at 300,000 pairs of 1,000 lengths).
+constexpr int kScatterPer = 2;
+__global__ void __launch_bounds__(1024) plan_scatter_kernel(DevPlanArgs a) {
+    __shared__ int32_t h[kPlanHistLds];
+    const int tid = threadIdx.x;
+    const bool lds = a.maxlen < kPlanHistLds;
+    int len[kScatterPer], at[kScatterPer];
+    if (lds) {
+        for (int x = tid; x <= a.maxlen; x += 1024) h[x] = 0;
+        __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < kScatterPer; ++u) {
+        const int x = (blockIdx.x * kScatterPer + u) * 1024 + tid;
+        len[u] = x < a.np ? (int)(a.off[x + 1] - a.off[x]) : -1;
+        at[u] = len[u] >= 0 ? atomicAdd((lds ? h : a.hist) + len[u], 1) : 0;
+    }
+    if (lds) {
+        __syncthreads();
+        for (int x = tid; x <= a.maxlen; x += 1024) {
+            const int c = h[x];
+            if (c) h[x] = atomicAdd(a.hist + x, c);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < kScatterPer; ++u)
+        if (len[u] >= 0)
+            a.order[at[u] + (lds ? h[len[u]] : 0)] = make_int2((blockIdx.x * kScatterPer + u) * 1024 + tid, len[u]);
 }
 
 // One wavefront per pair in length order: its slot, its stream column, its
-// residues staged as stage_stream_kernel does; the first round's wavefronts also
+// residues staged; the first round's wavefronts also
 // write their stream's entries.
 __global__ void __launch_bounds__(256) plan_stage_kernel(DevPlanArgs a) {
     const int x = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -144,10 +203,7 @@ __global__ void __launch_bounds__(256) plan_stage_kernel(DevPlanArgs a) {
         a.sstr[q] = s;
         a.keys[q] = 0ull;
     }
-    const uint8_t *src = a.res + a.off[pl.x];
-    uint8_t *dst = a.sres + base + c;
-    for (int y = lane; y < pl.y; y += 64)
-        dst[y] = (uint8_t)(min((int)(src[y] & 31), a.clamp) | (y == 0 ? kFirstCol : 0));
+    stage_pair(a.res + a.off[pl.x], pl.y, a.sres + base + c, a.clamp, lane);
 }
 
 }  // namespace hk

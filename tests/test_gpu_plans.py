@@ -162,3 +162,30 @@ def test_device_plan_msa(H, ctx, n, center, monkeypatch):
         H.halign_msa(ctx, H.Scoring(), ds, center)
     ds.residues.copy_(bad)
     assert torch.equal(H.halign_msa(ctx, H.Scoring(), ds, center)[0].cpu(), rows[0])
+
+
+# residues staged as aligned words with single bytes at the ends: pairs of 0 .. 9
+# residues next to each other at every alignment, codes at and past a small
+# alphabet's padding, on both planners; and lengths that the call's first kernel does
+# not count
+@pytest.mark.parametrize("n", [40, 2300])
+def test_staged_residues(H, ctx, n):
+    rng = np.random.default_rng(n)
+    mat = rng.integers(-4, 6, (5, 5)).astype(np.int8)
+    mat = np.minimum(mat, mat.T)
+    ds = H.DeviceSeqs(synth.SeqSet.from_list([rng.integers(0, 5, int(L)).astype(np.uint8) for L in rng.integers(0, 10, n)]))
+    import torch
+    center = torch.from_numpy(rng.integers(0, 5, 37).astype(np.uint8)).cuda()
+    for tb in (False, True):
+        _same(H, ctx, H.Scoring(mat, 3, 1), ds, center, tb)
+
+
+@pytest.mark.parametrize("length", [4095, 4096, 9000])
+def test_device_plan_long_pairs(H, ctx, length):
+    rng = np.random.default_rng(length)
+    lens = np.full(2048, length // 2)
+    lens[7] = length
+    res = rng.integers(0, 20, int(lens.sum())).astype(np.uint8)
+    ds = H.DeviceSeqs(synth.SeqSet(res, np.concatenate([[0], np.cumsum(lens)])))
+    for tb in (False, True):
+        _same(H, ctx, H.Scoring(), ds, _center(rng, 40), tb)
