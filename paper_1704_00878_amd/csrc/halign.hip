@@ -458,7 +458,7 @@ constexpr double kShare[7] = {1.28, 1.28, 2.2, 3.15, 4, 5, 6};
 double stream_cost(const halign_ctx *ctx, const StreamGeom &g, bool tb, const Lens &plen, int np, int64_t sum_len,
                    int w) {
     const int per_wave = 64 / g.LS * (g.pk ? 2 : 1), simds = ctx->num_cu * 4;
-    const double ops = g.pk ? (tb ? (g.R > 11 ? 21.8 : 17.8) * g.R + 65 : 10.5 * g.R + 65)
+    const double ops = g.pk ? (tb ? 17.8 * g.R + 65 : 10.5 * g.R + 65)
                             : (tb ? 16.4 * g.R + 38 : 9.0 * g.R + 30);
     const double cols = stream_cols(plen, np, sum_len, simds * w * per_wave);
     const int waves = (std::min(np, simds * w * per_wave) + per_wave - 1) / per_wave;
@@ -468,11 +468,11 @@ double stream_cost(const halign_ctx *ctx, const StreamGeom &g, bool tb, const Le
 }
 
 // Resident wavefronts per SIMD that the packed kernel's streams are sized for
-// (at most four fit its registers): four, or fewer where more pairs per stream
-// end closer together.
+// (stream16_waves fit its registers): that many, or fewer where more pairs per
+// stream end closer together.
 int packed_waves(const halign_ctx *ctx, const StreamGeom &g, bool tb, const Lens &plen, int np, int64_t sum_len,
                  int wmax) {
-    int best = std::min(4, wmax);
+    int best = std::min(hk::stream16_waves(g.R, tb), wmax);
     double cost = stream_cost(ctx, g, tb, plen, np, sum_len, best);
     for (int w = best - 1; w >= 1; --w) {
         const double c = stream_cost(ctx, g, tb, plen, np, sum_len, w);
@@ -826,7 +826,6 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
             hmark(ctx, "dplan");
         } else {
             PlanBuilder pb;
-            const int nmax_all = plen[lo];
             // strip route: the walk list and its walk descriptors, both in walk
             // order (the wavefront route's walk reads the per-slot and per-stream
             // plan)

@@ -22,6 +22,15 @@ __device__ __forceinline__ pk16 pmax(pk16 a, pk16 b) { return __builtin_elementw
 constexpr int kBias16 = 15616;
 constexpr int kPadProf16 = -15360;
 
+// Wavefronts per SIMD of the packed wavefront kernel with R rows per lane.  With
+// code words and packed end cells, more than ten rows need over 128 registers:
+// three wavefronts hold them.  Forward time against four with 32-bit end-cell keys
+// from R = 12 on: R = 13 (20,000 pairs on m = 400) 0.97 ms against 1.10, R = 16
+// (m = 500) 1.17 against 1.36, 300,000 on 200 (R = 13) 10.0 against 10.8; against four
+// that spill, R = 11 (m = 350) 0.85 against 0.88, R = 10 (m = 311) the same, R = 9 (60,000 on
+// 280) 1.55 against 1.53.
+constexpr int stream16_waves(int R, bool tb) { return tb && R >= 11 ? 3 : 4; }
+
 // max(a, b, c) per half with one v_pk_maximum3_f16 (operands as above)
 __device__ __forceinline__ pk16 max3h(pk16 a, pk16 b, pk16 c) {
     typedef _Float16 h2 __attribute__((ext_vector_type(2)));

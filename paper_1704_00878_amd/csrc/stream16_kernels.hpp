@@ -34,8 +34,7 @@
 // copied (v_bfi_b32).  The first step that reaches the best H is the smallest
 // column, and at publication the smallest row of that step holding the best H
 // completes the key (max H, then min j, then min i per lane).  This needs R
-// more registers; above R = 11 both halves unpack H into 32-bit keys
-// (H << 5 | 31 - t) per row instead, as the 32-bit kernel does.
+// more registers, for which the larger R give up a wavefront (stream16_waves).
 #pragma once
 #include "sw_kernels.hpp"
 #include "pk16.hpp"
@@ -88,13 +87,10 @@ __device__ __forceinline__ int row_take(int x) {
 }
 
 template <int R, int LS, bool TB>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(stream16_waves(R, TB))))
 sw_stream16_kernel(StreamArgs a) {
     static_assert(LS == 32 || LS == 16, "lanes per stream");
     static_assert(R >= 2 && R <= 16, "rows per lane");
-    // packed end cells need R more registers: with code words, up to R = 11
-    // they fit the 128 of four waves per SIMD
-    constexpr bool SNAP = R <= 11 || !TB;
     constexpr int NW = (R + 1) / 2;          // profile dwords a step reads per stream
     // profile planes per residue: rows 0..7 (NA dwords per lane, lane stride
     // SA dwords), then rows 8..R-1 (NB dwords, stride SB); strides of 1, 2 or 4
@@ -228,45 +224,32 @@ sw_stream16_kernel(StreamArgs a) {
             };
             prof_read(rcur, wa, wb);
             int plA = -1, plB = -1;
-            // running end cell of the current pair, per half.  SNAP: the best
+            // running end cell of the current pair, per half: the best
             // H, the step (mod 2^16) that first reached it and the lane's rows
-            // (as H - go - ge) at that step, the row resolved at publication.
-            // Otherwise 32-bit keys (H << 5 | 31 - t) per step.
+            // (as H - go - ge) at that step, the row resolved at publication
             pk16 bh = zero2;
             uint32_t bk = 0;
-            pk16 hs[SNAP ? R : 1];
+            pk16 hs[R];
 #pragma unroll
-            for (int t = 0; t < (SNAP ? R : 1); ++t) hs[t] = init2;
-            int bhA = 0, bcolA = 0, bkA = 0;
-            int bhB = 0, bcolB = 0, bkB = 0;
+            for (int t = 0; t < R; ++t) hs[t] = init2;
             int kfA = 0, kfB = 0;
             auto publish = [&](int h, int kf, int sh, int slot, int pl) __attribute__((always_inline)) {
                 int t0 = 0;
 #pragma unroll
                 for (int t = R - 1; t >= 0; --t)
-                    if ((int)(short)(as_u(hs[SNAP ? t : 0]) >> sh) == h - goe) t0 = t;
+                    if ((int)(short)(as_u(hs[t]) >> sh) == h - goe) t0 = t;
                 // j - 1 < 2^16 for every cell of a pair, so the low 16 bits of
                 // the step difference are the column
                 BestCell b{h - kBias16, (int)(((bk >> sh) - (uint32_t)kf) & 0xffffu) + 1, myrow + t0};
                 atomicMax(a.keys + slot + pl, cell_key(b, true));
             };
             auto publishA = [&]() __attribute__((always_inline)) {
-                if constexpr (SNAP) {
-                    const int h = (int)(as_u(bh) & 0xffffu);
-                    if (actA && plA >= 0 && h > kBias16) publish(h, kfA, 0, slotA, plA);
-                } else if (actA && plA >= 0 && bhA > kBias16) {
-                    BestCell b{bhA - kBias16, bkA - kfA + 1, myrow + (31 - (bcolA & 31))};
-                    atomicMax(a.keys + slotA + plA, cell_key(b, true));
-                }
+                const int h = (int)(as_u(bh) & 0xffffu);
+                if (actA && plA >= 0 && h > kBias16) publish(h, kfA, 0, slotA, plA);
             };
             auto publishB = [&]() __attribute__((always_inline)) {
-                if constexpr (SNAP) {
-                    const int h = (int)(as_u(bh) >> 16);
-                    if (actB && plB >= 0 && h > kBias16) publish(h, kfB, 16, slotB, plB);
-                } else if (actB && plB >= 0 && bhB > kBias16) {
-                    BestCell b{bhB - kBias16, bkB - kfB + 1, myrow + (31 - (bcolB & 31))};
-                    atomicMax(a.keys + slotB + plB, cell_key(b, true));
-                }
+                const int h = (int)(as_u(bh) >> 16);
+                if (actB && plB >= 0 && h > kBias16) publish(h, kfB, 16, slotB, plB);
             };
             auto step = [&](auto u_tag, int k8) __attribute__((always_inline)) {
                 constexpr int u = decltype(u_tag)::value;
@@ -291,17 +274,11 @@ sw_stream16_kernel(StreamArgs a) {
                         publishA();
                         ++plA;
                         kfA = k;
-                        bhA = 0;
-                        bcolA = 0;
-                        bkA = k;
                     }
                     if (fB) {
                         publishB();
                         ++plB;
                         kfB = k;
-                        bhB = 0;
-                        bcolB = 0;
-                        bkB = k;
                     }
                     const uint32_t msk = (fA ? 0xffffu : 0u) | (fB ? 0xffff0000u : 0u);
                     bh = as_pk(as_u(bh) & ~msk);
@@ -320,7 +297,6 @@ sw_stream16_kernel(StreamArgs a) {
                 for (int w = 0; w < WQ; ++w) word[w] = 0;
                 pk16 sm = bias2;   // step maximum over the lane's rows, per half
                 pk16 hprev = bias2;
-                int ckA = 0, ckB = 0, kpA = 0, kpB = 0;
 #pragma unroll
                 for (int t = 0; t < R; ++t) {
                     const pk16 p = as_pk(__builtin_amdgcn_perm(wb[t >> 1], wa[t >> 1],
@@ -341,25 +317,9 @@ sw_stream16_kernel(StreamArgs a) {
                         wd = bfi_s(m1, f1, wd);
                         word[t >> 2] = wd;
                     }
-                    if constexpr (SNAP) {
-                        if (t & 1) sm = max3h(sm, hprev, h);
-                        else if (t == R - 1) sm = pmax(sm, h);
-                        else hprev = h;
-                    } else {
-                        const uint32_t hu = as_u(h);
-                        const int kA = (int)((hu & 0xffffu) << 5) | (31 - t);
-                        const int kB = (int)((hu >> 16) << 5) | (31 - t);
-                        if (t & 1) {
-                            ckA = vmax3(ckA, kpA, kA);
-                            ckB = vmax3(ckB, kpB, kB);
-                        } else if (t == R - 1) {
-                            ckA = max(ckA, kA);
-                            ckB = max(ckB, kB);
-                        } else {
-                            kpA = kA;
-                            kpB = kB;
-                        }
-                    }
+                    if (t & 1) sm = max3h(sm, hprev, h);
+                    else if (t == R - 1) sm = pmax(sm, h);
+                    else hprev = h;
                     diag = hg[t];
                     hg[t] = h - goe2;
                     e[t] = en;
@@ -384,30 +344,13 @@ sw_stream16_kernel(StreamArgs a) {
                     const int K = k - ll;
                     if (ll == LS - 1 && K >= 0 && K < C) bout[K] = make_int2((int)botg, (int)botf);
                 }
-                if constexpr (SNAP) {
-                    // 0xffff in each half whose step maximum beats its best
-                    const uint32_t imp = as_u((bh - sm) >> pk16{15, 15});
-                    bh = pmax(bh, sm);
-                    const uint32_t kw = (uint32_t)(k & 0xffff) * 0x10001u;
-                    bk = bfi(imp, kw, bk);
+                // 0xffff in each half whose step maximum beats its best
+                const uint32_t imp = as_u((bh - sm) >> pk16{15, 15});
+                bh = pmax(bh, sm);
+                const uint32_t kw = (uint32_t)(k & 0xffff) * 0x10001u;
+                bk = bfi(imp, kw, bk);
 #pragma unroll
-                    for (int t = 0; t < R; ++t) hs[t] = as_pk(bfi(imp, as_u(hg[t]), as_u(hs[t])));
-                } else {
-                    {
-                        const int ch = ckA >> 5;
-                        const bool up = ch > bhA;
-                        bcolA = up ? ckA : bcolA;
-                        bkA = up ? k : bkA;
-                        bhA = max(bhA, ch);
-                    }
-                    {
-                        const int ch = ckB >> 5;
-                        const bool up = ch > bhB;
-                        bcolB = up ? ckB : bcolB;
-                        bkB = up ? k : bkB;
-                        bhB = max(bhB, ch);
-                    }
-                }
+                for (int t = 0; t < R; ++t) hs[t] = as_pk(bfi(imp, as_u(hg[t]), as_u(hs[t])));
                 rcur = rnx;
 #pragma unroll
                 for (int w = 0; w < NW; ++w) {

@@ -44,10 +44,10 @@ def _center(rng, m):
 
 
 # rows per lane at both ends of the packed kernel's range (2 and 16), around
-# its change of end-cell tracking (11, 12), one and two passes; few pairs (one
+# its change of wavefronts per SIMD (10, 11), one and two passes; few pairs (one
 # per stream, most streams idle) and several per stream; empty sequences
 @pytest.mark.parametrize("lanes", [16, 32])
-@pytest.mark.parametrize("rows", [2, 11, 12, 16, 17])
+@pytest.mark.parametrize("rows", [2, 10, 11, 12, 16, 17])
 @pytest.mark.parametrize("n,streams", [(3, 0), (700, 0), (700, 37)])
 def test_packed_score_only(H, ctx, lanes, rows, n, streams, monkeypatch):
     monkeypatch.setenv("HALIGN_STREAM_LANES", str(lanes))
