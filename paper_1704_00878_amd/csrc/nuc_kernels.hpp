@@ -1216,10 +1216,11 @@ __device__ __forceinline__ void nuc_stretch_wave(const NucArgs &a, const int8_t 
     __builtin_amdgcn_wave_barrier();
 }
 
-// Narrow stretches take a lane each from this many on, a wavefront each below
-// (a wavefront ends in a tenth of the time of a lane, but a lane's work costs
-// a tenth of the issue slots).
-constexpr int64_t kNucLaneMin = 65536;
+// Narrow stretches take a lane each from this many on, a wavefront each below:
+// a wavefront ends sooner, but takes more issue slots.  Whole calls, a lane each
+// against a wavefront each: 3,600 stretches (672 genomes of 16,569) 356 against 264 us,
+// 16,000 (3,000 genomes) 1,145 against 1,099, 32,000 (6,000) 2,093 against 2,188.
+constexpr int64_t kNucLaneMin = 24576;
 
 __global__ void __launch_bounds__(256) nuc_stretch_kernel(NucArgs a) {
     NUC_SMAT_SETUP

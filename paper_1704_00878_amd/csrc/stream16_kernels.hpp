@@ -101,7 +101,6 @@ sw_stream16_kernel(StreamArgs a) {
     constexpr int WQ = (R + 3) / 4;          // code words per step (both halves)
     constexpr int NS = 64 / LS;              // lane groups per wavefront
     constexpr int SPAN = LS * R;             // rows per pass
-    constexpr int LG = LS == 32 ? 5 : 4;
     // profile int16 per residue r (PRW dwords): plane A [lane][SA dwords] holds
     // lane l's rows 0..7 (two rows per dword), plane B [lane][SB dwords] its
     // rows 8..R-1, so the lanes of a read touch consecutive slots whatever
