@@ -3286,7 +3286,8 @@ static int nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seq
             a.wparts = (int)std::max<int64_t>(1, std::min(waves / N, longest));
             const int64_t items = (int64_t)N * a.wparts;
             const unsigned grid = (unsigned)std::min<int64_t>((items + 15) / 16, (int64_t)ctx->num_cu * 2);
-            hipLaunchKernelGGL(hk::nuc_scan_wave_kernel, dim3(grid), dim3(1024), 0, st, a);
+            if (k <= hk::kNucKey32) hipLaunchKernelGGL(hk::nuc_scan_wave_kernel<uint32_t>, dim3(grid), dim3(1024), 0, st, a);
+            else hipLaunchKernelGGL(hk::nuc_scan_wave_kernel<unsigned long long>, dim3(grid), dim3(1024), 0, st, a);
         } else {
             hipLaunchKernelGGL(hk::nuc_scan_kernel, dim3((unsigned)((nchunk + 255) / 256)), dim3(256), 0, st, a);
         }

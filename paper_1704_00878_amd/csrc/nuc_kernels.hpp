@@ -88,6 +88,7 @@ __device__ __forceinline__ bool nuc_overflow(const NucArgs &a, unsigned long lon
 }
 
 constexpr int kNucChunk = 256;   // match starts per scan chunk
+constexpr int kNucKey32 = 16;    // segments up to this long: 32-bit keys in the table (scan of 672 x 16,569 46.4 us against 48.3)
 constexpr int kNucSmallW = 32;   // stretches at most this many columns wide: one lane, the row in registers
 constexpr int kNucTinyW = 20;    // narrow stretches at most this size both ways are listed apart
 constexpr int kNucTallH = 40;    // stretches taller than this take a wavefront too (rows across lanes)
@@ -100,9 +101,9 @@ __host__ __device__ __forceinline__ uint32_t nuc_hash(unsigned long long key, in
 }
 
 // segment q whose packed string is key, or a negative number (several
-// segments with that string: -2)
-__device__ __forceinline__ int nuc_lookup(const unsigned long long *tk, const int32_t *ts, int lg_t,
-                                          unsigned long long key) {
+// segments with that string: -2); K: 32 bits where strings fit (k <= 16)
+template <typename K>
+__device__ __forceinline__ int nuc_lookup(const K *tk, const int32_t *ts, int lg_t, K key) {
     const uint32_t mask = (1u << lg_t) - 1u;
     uint32_t h = nuc_hash(key, lg_t);
     for (;;) {
@@ -113,21 +114,23 @@ __device__ __forceinline__ int nuc_lookup(const unsigned long long *tk, const in
     }
 }
 
-// Table in LDS when it fits (48 KiB), else read from global memory.
+// Table in LDS when it fits (32 or 48 KiB), else read from global memory.
 constexpr int kNucLdsSlots = 4096;
 
-#define NUC_TABLE_SETUP                                                                  \
-    __shared__ unsigned long long s_tk[kNucLdsSlots];                                    \
+// Keys of type K (a.tkey holds 32-bit ones where k <= 16).
+#define NUC_TABLE_SETUP(K)                                                               \
+    __shared__ K s_tk[kNucLdsSlots];                                                     \
     __shared__ int32_t s_ts[kNucLdsSlots];                                               \
     const int T = 1 << a.lg_t;                                                           \
     const bool tl = T <= kNucLdsSlots;                                                   \
+    const K *gk = reinterpret_cast<const K *>(a.tkey);                                   \
     if (tl)                                                                              \
         for (int x = threadIdx.x; x < T; x += blockDim.x) {                              \
-            s_tk[x] = a.tkey[x];                                                         \
+            s_tk[x] = gk[x];                                                             \
             s_ts[x] = a.tseg[x];                                                         \
         }                                                                                \
     __syncthreads();                                                                     \
-    const unsigned long long *tk = tl ? s_tk : a.tkey;                                   \
+    const K *tk = tl ? s_tk : gk;                                                        \
     const int32_t *ts = tl ? s_ts : a.tseg;
 
 // Workgroup 0: the segment table.  Each segment's string, cleanness (codes 0..3
@@ -219,7 +222,8 @@ __global__ void __launch_bounds__(1024) nuc_setup_kernel(NucSetup a) {
     for (int h = tid; h < T; h += 1024) {
         const int q = __hip_atomic_load(a.tseg + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (q < 0) continue;
-        a.tkey[h] = a.segkey[q];
+        if (k <= kNucKey32) reinterpret_cast<uint32_t *>(a.tkey)[h] = (uint32_t)a.segkey[q];
+        else a.tkey[h] = a.segkey[q];
         if (__hip_atomic_load(a.segstate + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 1) a.tseg[h] = -2;
     }
 }
@@ -279,8 +283,10 @@ constexpr int kNucWaveMaxK = 29;   // the wavefront scan's window: k + 3 bases i
 // q[r].  The chunk's bytes come in coalesced aligned words (one per lane, nine
 // more for the last k - 1 bases), are realigned to the chunk's start, turned
 // into 2-bit codes plus an invalid bit per base, and each lane gathers the
-// codes of its 32 bases (4 lane .. 4 lane + 31) from the next seven lanes.
-__device__ __forceinline__ void nuc_scan_wave(const NucArgs &a, const unsigned long long *tk, const int32_t *ts,
+// codes of its 32 bases (4 lane .. 4 lane + 31) from the next seven lanes (20 bases
+// and four lanes with 32-bit keys).
+template <typename K>
+__device__ __forceinline__ void nuc_scan_wave(const NucArgs &a, const K *tk, const int32_t *ts,
                                               int64_t so, int n, int c, int lane, int q[4]) {
     const int k = a.k;
     const int p0 = c * kNucChunk;
@@ -310,7 +316,7 @@ __device__ __forceinline__ void nuc_scan_wave(const NucArgs &a, const unsigned l
     uint64_t W = 0;   // base 4 lane + t at bits 2t
     uint32_t V = 0;   // its invalid bit at bit t
 #pragma unroll
-    for (int d = 0; d < 8; ++d) {
+    for (int d = 0; d < (sizeof(K) == 4 ? 5 : 8); ++d) {   // k + 3 bases
         const int src = lane + d;
         const uint32_t va = __shfl(ca, src & 63, 64), vb = __shfl(cb, src & 63, 64);
         const uint32_t v = src < 64 ? va : vb;
@@ -323,7 +329,7 @@ __device__ __forceinline__ void nuc_scan_wave(const NucArgs &a, const unsigned l
     for (int r = 0; r < 4; ++r) {
         const int p = p0 + 4 * lane + r;
         const bool ok = p + k <= n && ((V >> r) & vmask) == 0u;
-        q[r] = ok ? nuc_lookup(tk, ts, a.lg_t, (W >> (2 * r)) & kmask) : -1;
+        q[r] = ok ? nuc_lookup(tk, ts, a.lg_t, (K)((W >> (2 * r)) & kmask)) : -1;
     }
 }
 
@@ -334,8 +340,11 @@ static_assert(kNucChunk == 4 * 64, "the wavefront scan takes four match starts p
 // wavefronts.  One pass that stores (a chunk has at most kNucChunk matches, so each
 // has its own place) instead of one that counts and one that stores: 105 us for both,
 // and a search for each wavefront's sequence, at 672 x 16,569.
+// Bound by VALU issue (about 370 instructions a chunk, half of them probes), not by
+// its loads: with the next chunk's words loaded ahead it took as long.
+template <typename K>
 __global__ void __launch_bounds__(1024) nuc_scan_wave_kernel(NucArgs a) {
-    NUC_TABLE_SETUP   // shared by the workgroup's 16 wavefronts
+    NUC_TABLE_SETUP(K)   // shared by the workgroup's 16 wavefronts
     const int lane = threadIdx.x & 63;
     const uint64_t below = (1ull << lane) - 1ull;
     const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6), items = (int64_t)a.nseq * a.wparts;
@@ -365,7 +374,7 @@ __global__ void __launch_bounds__(1024) nuc_scan_wave_kernel(NucArgs a) {
 
 // Scan, one lane per chunk (any k).
 __global__ void __launch_bounds__(256) nuc_scan_kernel(NucArgs a) {
-    NUC_TABLE_SETUP
+    NUC_TABLE_SETUP(unsigned long long)
     int x, c;
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (!nuc_chunk(a, g, x, c)) return;

@@ -55,9 +55,9 @@ def _mutate(rng, c, p_sub, p_indel):
     return np.array(out, np.uint8)
 
 
-# every string repeated; tables at and past the LDS size; both scans; the
-# center not a multiple of k
-@pytest.mark.parametrize("k,m", [(1, 300), (2, 301), (3, 1000), (4, 3000), (6, 13000), (16, 33000), (29, 2000),
+# every string repeated; tables at and past the LDS size; 32- and 64-bit keys; both
+# scans; the center not a multiple of k
+@pytest.mark.parametrize("k,m", [(1, 300), (2, 301), (3, 1000), (4, 3000), (6, 13000), (16, 33000), (17, 3000), (29, 2000),
                                  (30, 2000), (32, 2031), (16, 15), (16, 16)])
 def test_segments(H, k, m):
     ctx = H.Context(0)
