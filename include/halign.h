@@ -208,15 +208,16 @@ int halign_emit_rows(halign_ctx *ctx, const halign_seqs *seqs, int32_t m,
  * ties to the lowest index (Methods: the center is the sequence most similar
  * to the others).  *center_host is written (synchronises).
  * Both calls score pairs in packed 16-bit arithmetic when every score stays
- * below 15000 (max matrix entry x longest sequence + go + ge < 15000, go + ge
- * and ge at most 256), else in 32-bit; the
+ * below 15000 (max matrix entry x longest sequence + go + ge < 15000, with 18 ge
+ * more < 16000, go + ge and ge at most 256), else in 32-bit; the
  * sums are the same either way.  HALIGN_STRIP32=1 forces the 32-bit kernel. */
 int halign_center_exact(halign_ctx *ctx, const halign_scoring *sc, const halign_seqs *seqs,
                         int64_t *sums, int32_t *center_host, void *stream);
 /* Group tiling of halign_center_exact (host only, no device needed): all
  * pairs a < b of n positions (in length order) fall into *ngroups_host groups
  * of one center position and `step` consecutive partner positions (64 for
- * the 32-bit kernel, 128 for the packed one), numbered in closed form, so
+ * the 32-bit kernel; the packed one takes two neighbouring center positions and
+ * 64 partners, numbered likewise), in closed form, so
  * the search holds O(n) host data.  With g >= 0, group g is decoded into its
  * center position and first partner position (partners [p0, p0 + step),
  * those not above the center position are idle).  A caller sharding the
