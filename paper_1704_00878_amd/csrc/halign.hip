@@ -672,35 +672,49 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
         }
         return ns;
     };
-    // The device's dealing by formula serves where its longest stream, estimated
-    // from the sample, is within 15% of the longest pair or of the average stream,
-    // and its equal regions take at most four times the columns.  Forward time
-    // against dealing to the least loaded stream: batch of 20,000 0.77 ms against
-    // 0.79; 300,000 10.7 against 11.1; a long tail of 50,001, whose longest
-    // stream would be 1.6 times the average, 1.36 against 0.89.
-    int dev_ns = 0;
+    // The device's dealing by formula (the dev_own longest pairs on streams of
+    // their own, the rest dealt in alternating order) serves where its longest
+    // stream, estimated from the sample, is within 30% of the longest pair or of
+    // the average stream, and its equal regions take at most four times the
+    // columns.  Forward time against dealing to the least loaded stream: batch of
+    // 20,000 0.77 ms against 0.79; 300,000 10.7 against 11.1; a long tail of 50,001
+    // 0.99-1.04 against 0.885, for 0.23 ms less on the host (whole call 1.25-1.28
+    // against 1.34; 1.36 forward without streams of their own).
+    int dev_ns = 0, dev_own = 0;
     int64_t dev_cols = 0;
     size_t dev_code_words = 0, dev_bound = 0;
     const int per_group = pk ? 2 : 1;
     if (dev && route == kRouteIntra) {
         dev_ns = count_streams(lens, np, sum_len);
         const int64_t avg = sum_len / dev_ns;
-        dev = (np + dev_ns - 1) / dev_ns <= 64;
-        double top = 0;
-        for (int q = 0; dev && q <= 4; ++q) {
-            const int s2 = (int)((int64_t)(dev_ns - 1) * q / 4);
-            double load = 0;
-            for (int64_t r = 0; r * dev_ns < np; ++r) {
-                const int64_t x = r * dev_ns + ((r & 1) ? dev_ns - 1 - s2 : s2);
-                if (x < np) load += lens[(int)x];
+        const int rounds = (np + dev_ns - 1) / dev_ns;
+        dev = rounds <= 64;
+        dev_cols = nlong;
+        double top = nlong;
+        if (dev && rounds > 1) {
+            for (int sh : {0, 5, 4, 3}) {   // no pair on its own, or 1/32, 1/16, 1/8 of the streams
+                const int k = sh ? dev_ns >> sh : 0, n2 = dev_ns - k;
+                double most = nlong;
+                for (int q = 0; q <= 4; ++q) {
+                    const int s2 = (int)((int64_t)(n2 - 1) * q / 4);
+                    double load = 0;
+                    for (int64_t r = 0; k + r * n2 < np; ++r) {
+                        const int64_t x = k + r * n2 + ((r & 1) ? n2 - 1 - s2 : s2);
+                        if (x < np) load += lens[(int)x];
+                    }
+                    most = std::max(most, load);
+                }
+                if (sh == 0 || most < 0.95 * top) {
+                    top = most;
+                    dev_own = k;
+                }
             }
-            top = std::max(top, load);
+            dev_cols = sum_len / (dev_ns - dev_own) + nlong;
         }
-        dev_cols = np <= dev_ns ? nlong : avg + nlong;
         if (tb) dev_code_words = (size_t)passes * (size_t)((dev_cols + LS - 1 + 7) / 8) * LS * 8 * WQ;
         dev_bound = (size_t)(passes - 1) * (size_t)dev_cols;
         const size_t groups = (size_t)(dev_ns + per_group - 1) / per_group;
-        dev = dev && top <= 1.15 * (double)std::max<int64_t>(nlong, avg) && dev_cols <= 4 * avg && dev_cols < (1 << 30) &&
+        dev = dev && top <= 1.3 * (double)std::max<int64_t>(nlong, avg) && dev_cols <= 4 * avg && dev_cols < (1 << 30) &&
               groups * (dev_code_words * 4 + dev_bound * 8) <= (ctx->cap ? ctx->cap : (size_t)1 << 62);
     } else {
         dev = false;
@@ -796,6 +810,7 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
             d.np = cn;
             d.maxlen = nlong;
             d.ns = nstreams;
+            d.own = dev_own;
             d.clamp = p16 ? S.alpha : 31;
             d.hist = (int32_t *)(dplan + o_hist);
             d.order = (int2 *)(dplan + o_order);

@@ -72,15 +72,16 @@ __global__ void __launch_bounds__(256) stage_stream_kernel(const uint8_t *res, c
 // ---- streams planned on the device ---------------------------------------------
 // The host's counting sort, dealing and slot arrays take about 140 us at 20,000
 // pairs and 1.6 ms at 300,000, during which the device waits.  Here the pairs are
-// sorted by length (three small kernels) and dealt by formula: the x-th longest, x =
-// r * ns + j, goes to stream j in even rounds r and ns - 1 - j in odd ones, so
-// two streams differ by at most the longest pair, and every stream gets a region
-// of the same size for its columns, codes and boundary rows, bounded by the
-// average load plus the longest pair.
+// sorted by length (three small kernels) and dealt by formula: the `own` longest to
+// a stream each, and of the rest the x-th longest, x = r * (ns - own) + j, to the
+// j-th other stream in even rounds r and to the j-th from the end in odd ones.  Two of
+// those streams differ by at most their longest pair, and every stream gets a
+// region of the same size for its columns, codes and boundary rows, bounded by
+// the average of all pairs over ns - own streams plus the longest pair.
 struct DevPlanArgs {
     const uint8_t *res;
     const int64_t *off;
-    int np, maxlen, ns, clamp;   // ns <= np
+    int np, maxlen, ns, own, clamp;   // own < ns <= np
     int32_t *hist;        // [maxlen + 1]: each length's next place
     int2 *order;          // [np] (pair, length), longest first
     int per_group;        // streams that share codes and boundary rows (2: packed)
@@ -173,26 +174,32 @@ __global__ void __launch_bounds__(1024) plan_scatter_kernel(DevPlanArgs a) {
 __global__ void __launch_bounds__(256) plan_stage_kernel(DevPlanArgs a) {
     const int x = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (x >= a.np) return;
-    const int ns = a.ns, r = x / ns, j = x - r * ns;
+    const bool own = x < a.own;   // (the only pair of stream x)
+    const int ns = a.ns - a.own, np = a.np - a.own;   // the dealt pairs and their streams
+    const int xd = x - a.own, r = own ? 0 : xd / ns, j = xd - r * ns;
     const int s = (r & 1) ? ns - 1 - j : j;
-    const int rounds = a.np / ns, rem = a.np - rounds * ns;   // full rounds, pairs of the last one
+    const int rounds = np / ns, rem = np - rounds * ns;   // full rounds, pairs of the last one
     // pairs of the streams before s in the last round, and whether s has one
     const int before = (rounds & 1) ? max(0, s - (ns - rem)) : min(s, rem);
     const bool last = (rounds & 1) ? s >= ns - rem : s < rem;
-    const int first = s * rounds + before;
+    const int first = own ? x : a.own + s * rounds + before, sg = own ? x : a.own + s;   // first slot, stream of all
     const int upto = r == 0 ? rounds + (last ? 1 : 0) : r;   // all pairs of the stream, or the earlier ones
     const int2 pl = a.order[x];
     int64_t c = 0;
-    for (int q = lane; q < upto; q += 64) c += a.order[(int64_t)q * ns + ((q & 1) ? ns - 1 - s : s)].y;
-    for (int d = 32; d > 0; d >>= 1) c += __shfl_xor(c, d);
-    const int64_t base = (int64_t)s * a.cols;
+    if (own) {
+        c = pl.y;
+    } else {
+        for (int q = lane; q < upto; q += 64) c += a.order[a.own + (int64_t)q * ns + ((q & 1) ? ns - 1 - s : s)].y;
+        for (int d = 32; d > 0; d >>= 1) c += __shfl_xor(c, d);
+    }
+    const int64_t base = (int64_t)sg * a.cols;
     if (r == 0) {
         if (lane == 0) {
-            a.sbeg[s] = base;
-            a.slen[s] = (int32_t)c;
-            a.slot0[s] = first;
-            a.scb[s] = s / a.per_group * a.code_words;
-            a.sbb[s] = s / a.per_group * a.bound_elems;
+            a.sbeg[sg] = base;
+            a.slen[sg] = (int32_t)c;
+            a.slot0[sg] = first;
+            a.scb[sg] = sg / a.per_group * a.code_words;
+            a.sbb[sg] = sg / a.per_group * a.bound_elems;
         }
         c = 0;
     }
@@ -200,7 +207,7 @@ __global__ void __launch_bounds__(256) plan_stage_kernel(DevPlanArgs a) {
         const int q = first + r;
         a.spid[q] = pl.x;
         a.scol[q] = base + c;
-        a.sstr[q] = s;
+        a.sstr[q] = sg;
         a.keys[q] = 0ull;
     }
     stage_pair(a.res + a.off[pl.x], pl.y, a.sres + base + c, a.clamp, lane);

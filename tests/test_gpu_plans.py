@@ -138,6 +138,22 @@ def test_device_plan_long_tail(H, ctx, n, streams, long, lanes, pack, monkeypatc
         assert plan["packed"] == pack and route == 0
 
 
+# log-normal lengths: the longest pairs take streams of their own
+@pytest.mark.parametrize("lanes,pack", [(64, 0), (16, 1)])
+@pytest.mark.parametrize("n,streams", [(4099, 600), (2048, 257), (9000, 3000)])
+def test_device_plan_log_normal(H, ctx, n, streams, lanes, pack, monkeypatch):
+    if lanes != 64:
+        monkeypatch.setenv("HALIGN_STREAM_LANES", str(lanes))
+    monkeypatch.setenv("HALIGN_STREAM_PACK", str(pack))
+    monkeypatch.setenv("HALIGN_MAX_STREAMS", str(streams))
+    rng = np.random.default_rng(n)
+    lens = np.clip(40 * np.exp(0.5 * rng.standard_normal(n)), 0, 240).astype(int)
+    ds = H.DeviceSeqs(synth.SeqSet.from_list([rng.integers(0, 20, int(L)).astype(np.uint8) for L in lens]))
+    for tb in (False, True):
+        plan, route = _same(H, ctx, H.Scoring(), ds, _center(rng, 101), tb)
+        assert plan["packed"] == pack and route == 0
+
+
 # whole alignments on the device's plan and on the host's (forced by the dealing
 # knob, in chunks under a small workspace, and captured), and with the code
 # check's error still raised
