@@ -434,57 +434,70 @@ constexpr int kRowWave = kRowWin + 16 + kRowRes + 16;   // LDS bytes per wavefro
 // Chunked rows, first pass, one workgroup per row: ck[k][c] = residues of row
 // k before block c * kRowChunk (insertions plus aligned bits).  A wavefront counts a
 // chunk with two loads of aligned words (pairs of counts) per lane, four chunks in
-// flight on each of eight wavefronts; the chunks' counts meet in LDS.  One wavefront per row that
+// flight on each of eight wavefronts; the counts of up to kRowTile chunks (65,536
+// blocks, which hold the center of any sequence; vectors made elsewhere may have more) meet
+// in LDS, and the row's sum is carried from one such tile to the next.  One wavefront per row that
 // carried its sum from chunk to chunk took 66 us at 672 rows of 16,570 blocks (22 MB).
+constexpr int kRowTile = 256;
 __global__ void __launch_bounds__(512) rows_count_kernel(RowsArgs a, int32_t *ck, int nck) {
-    __shared__ int s_cnt[288], s_wave[8];
+    __shared__ int s_cnt[kRowTile], s_wave[8];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int m = a.m, m1 = m + 1;
     for (int k = blockIdx.x; k < a.nrows; k += gridDim.x) {
         const uint16_t *ir = a.ins + (int64_t)k * m1;
         const uint32_t *ar = a.aligned + (int64_t)k * a.aw;
-        for (int c0 = wv; c0 < nck; c0 += 32) {
-            int v[4];
+        int carry = 0;   // residues before the tile
+        for (int t0 = 0; t0 < nck; t0 += kRowTile) {
+            const int nt = min(kRowTile, nck - t0);
+            for (int c0 = wv; c0 < nt; c0 += 32) {
+                int v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int b = (c0 + 8 * u) * kRowChunk, nb = min(kRowChunk, m1 - b);   // (nb <= 0: no such chunk)
-                const uintptr_t p = (uintptr_t)(ir + b);
-                const int odd = (int)((p >> 1) & 1);
-                const uint32_t *w = reinterpret_cast<const uint32_t *>(p & ~(uintptr_t)3);
-                v[u] = 0;
+                for (int u = 0; u < 4; ++u) {
+                    const int b = (t0 + c0 + 8 * u) * kRowChunk, nb = min(kRowChunk, m1 - b);   // (nb <= 0: no such chunk)
+                    const uintptr_t p = (uintptr_t)(ir + b);
+                    const int odd = (int)((p >> 1) & 1);
+                    const uint32_t *w = reinterpret_cast<const uint32_t *>(p & ~(uintptr_t)3);
+                    v[u] = 0;
+                    if (nb <= 0) continue;
 #pragma unroll
-                for (int r = 0; r < 3; ++r) {   // word i holds the counts 2i - odd and 2i + 1 - odd
-                    const int i = 64 * r + lane, lo = 2 * i - odd;
-                    if (r == 2 && (lane > 0 || !odd)) continue;
-                    if (lo >= nb) continue;
-                    const uint32_t x = w[i];
-                    v[u] += (lo >= 0 ? (int)(x & 0xffffu) : 0) + (lo + 1 < nb ? (int)(x >> 16) : 0);
+                    for (int r = 0; r < 3; ++r) {   // word i holds the counts 2i - odd and 2i + 1 - odd
+                        const int i = 64 * r + lane, lo = 2 * i - odd;
+                        if (r == 2 && (lane > 0 || !odd)) continue;
+                        if (lo >= nb) continue;
+                        const uint32_t x = w[i];
+                        v[u] += (lo >= 0 ? (int)(x & 0xffffu) : 0) + (lo + 1 < nb ? (int)(x >> 16) : 0);
+                    }
+                    if (lane < 8 && b + 32 * lane < m) {   // the aligned words of center positions b + 32 lane ..
+                        const int left = m - (b + 32 * lane);
+                        v[u] += __popc(ar[(b >> 5) + lane] & (left >= 32 ? ~0u : (1u << left) - 1u));
+                    }
                 }
-                if (lane < 8 && b + 32 * lane < m) {   // the aligned words of center positions b + 32 lane ..
-                    const int left = m - (b + 32 * lane);
-                    v[u] += __popc(ar[(b >> 5) + lane] & (left >= 32 ? ~0u : (1u << left) - 1u));
-                }
+#pragma unroll
+                for (int o = 32; o >= 1; o >>= 1)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] += __shfl_xor(v[u], o, 64);
+                if (lane < 4 && c0 + 8 * lane < nt)
+                    s_cnt[c0 + 8 * lane] = lane == 0 ? v[0] : lane == 1 ? v[1] : lane == 2 ? v[2] : v[3];
             }
+            __syncthreads();
+            const int own = tid < nt ? s_cnt[tid] : 0;
+            int inc = own;
 #pragma unroll
-            for (int o = 32; o >= 1; o >>= 1)
+            for (int d = 1; d < 64; d <<= 1) {
+                const int t = __shfl_up(inc, d, 64);
+                if (lane >= d) inc += t;
+            }
+            if (lane == 63) s_wave[wv] = inc;
+            __syncthreads();
+            int before = carry + inc - own;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] += __shfl_xor(v[u], o, 64);
-            if (lane < 4 && c0 + 8 * lane < nck) s_cnt[c0 + 8 * lane] = lane == 0 ? v[0] : lane == 1 ? v[1] : lane == 2 ? v[2] : v[3];
+            for (int w = 0; w < 8; ++w) {
+                if (w < wv) before += s_wave[w];
+                carry += s_wave[w];
+            }
+            if (tid < nt) ck[(int64_t)k * nck + t0 + tid] = before;
+            __syncthreads();
         }
-        __syncthreads();
-        const int own = tid < nck ? s_cnt[tid] : 0;   // (nck is at most 257)
-        int inc = own;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int t = __shfl_up(inc, d, 64);
-            if (lane >= d) inc += t;
-        }
-        if (lane == 63) s_wave[wv] = inc;
-        __syncthreads();
-        int before = inc - own;
-        for (int w = 0; w < wv; ++w) before += s_wave[w];
-        if (tid < nck) ck[(int64_t)k * nck + tid] = before;
-        __syncthreads();
     }
 }
 
