@@ -219,6 +219,7 @@ __global__ void __launch_bounds__(1024) merge_scan_kernel(const int32_t *G, int 
 constexpr int kWaveRows = 4;
 constexpr int kRowFew = 4;
 constexpr int kRowPre = 4;        // aligned words per lane of counts and of residues loaded a row ahead
+typedef uint16_t __attribute__((may_alias)) row_count_t;   // half of a staged word
 
 struct RowsArgs {
     const uint8_t *res;
@@ -333,7 +334,11 @@ __global__ void __launch_bounds__(64 * kWaveRows) rows_kernel(RowsArgs a) {
             }
         }
         for (int q = 64 + lane; q < a.aw; q += 64) abit[q] = r.ap[q];
-        const uint16_t *sins = reinterpret_cast<const uint16_t *>(iw) + r.iodd;
+        // other lanes read what this one staged (the wavefront's LDS accesses
+        // stay in order once the compiler keeps them so)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const row_count_t *sins = reinterpret_cast<const row_count_t *>(iw) + r.iodd;
         const uint8_t *sres = reinterpret_cast<const uint8_t *>(rw) + r.rodd, *gres = a.res + r.so;
         const bool rl = r.n <= a.res_bytes;
         const int n = r.n;
