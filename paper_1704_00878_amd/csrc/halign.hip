@@ -3558,63 +3558,102 @@ bool nj_mesh_ok(const halign_ctx *ctx, int n) {
            hk::nj_mesh_lds(n) + 1024 <= ctx->lds_max && !(env && atoi(env) == 0);
 }
 
-// Neighbour joining of one problem over the chip: D (device, n x n, modified);
-// the tree to the host (2n + 1 entries).
-int nj_big(halign_ctx *ctx, double *D, int n, std::vector<int32_t> &parent, std::vector<double> &blen, int *nodes,
-           hipStream_t st) {
+// Scratch of one problem that is joined alone.  Parents, lengths and the node
+// count lie together: they come back in one copy.
+struct NjAlone {
+    size_t o_p, o_b, o_nodes, o_fail, o_mesh, o_M;
+    int G;   // workgroups of the mesh
+    hk::NjBigArgs a;
+};
+int nj_alone(halign_ctx *ctx, double *D, int n, bool mesh, NjAlone *w) {
     const int64_t nn = (int64_t)n * n;
     const int nparts = (int)std::max<int64_t>(1, std::min<int64_t>(2048, (nn + 255) / 256));
     const size_t nt = 2 * (size_t)n + 1;
-    const int G = (n + hk::kNjMeshRows - 1) / hk::kNjMeshRows;
-    const bool mesh = nj_mesh_ok(ctx, n);
-    // (parents, lengths and the node count lie together: they come back in one copy)
-    const size_t o_r = 0, o_id = al256z(8 * (size_t)n), o_p = o_id + al256z(4 * (size_t)n), o_b = o_p + al256z(4 * nt),
-                 o_nodes = o_b + al256z(8 * nt), o_fail = o_nodes + 64, o_part = o_nodes + 256,
-                 o_pd = o_part + al256z(sizeof(hk::NjBest) * nparts), o_ctrl = o_pd + al256z(8 * (size_t)nparts),
-                 o_act = o_ctrl + 256, o_mesh = o_act + al256z(n),
-                 o_M = o_mesh + (mesh ? al256z(8 * (3 * (size_t)n + 9 * (size_t)G)) : 0),
-                 bytes = o_M + (mesh ? al256z(8 * (size_t)nn) : 0);
-    RCHK(grow(ctx, ctx->njB, bytes));
-    RCHK(grow_host(ctx->njout, o_nodes + 4 - o_p));
+    w->G = (n + hk::kNjMeshRows - 1) / hk::kNjMeshRows;
+    const size_t o_r = 0, o_id = al256z(8 * (size_t)n);
+    w->o_p = o_id + al256z(4 * (size_t)n);
+    w->o_b = w->o_p + al256z(4 * nt);
+    w->o_nodes = w->o_b + al256z(8 * nt);
+    w->o_fail = w->o_nodes + 64;
+    const size_t o_part = w->o_nodes + 256, o_pd = o_part + al256z(sizeof(hk::NjBest) * nparts),
+                 o_ctrl = o_pd + al256z(8 * (size_t)nparts), o_act = o_ctrl + 256;
+    w->o_mesh = o_act + al256z(n);
+    w->o_M = w->o_mesh + (mesh ? al256z(8 * (3 * (size_t)n + 9 * (size_t)w->G)) : 0);
+    RCHK(grow(ctx, ctx->njB, w->o_M + (mesh ? al256z(8 * (size_t)nn) : 0)));
+    RCHK(grow_host(ctx->njout, w->o_nodes + 4 - w->o_p));
     char *b = (char *)ctx->njB.p;
-    hk::NjBigArgs a{n, D, (double *)(b + o_r), (uint8_t *)(b + o_act), (int32_t *)(b + o_id), (int32_t *)(b + o_p),
-                    (double *)(b + o_b), (hk::NjBest *)(b + o_part), (double *)(b + o_pd), nparts, (hk::NjCtrl *)(b + o_ctrl)};
+    w->a = hk::NjBigArgs{n, D, (double *)(b + o_r), (uint8_t *)(b + o_act), (int32_t *)(b + o_id), (int32_t *)(b + w->o_p),
+                         (double *)(b + w->o_b), (hk::NjBest *)(b + o_part), (double *)(b + o_pd), nparts,
+                         (hk::NjCtrl *)(b + o_ctrl)};
+    return HALIGN_OK;
+}
+
+// The last joins on the matrix M, and the tree to the host (2n + 1 entries; -1
+// nodes where *failed is set).
+int nj_alone_finish(halign_ctx *ctx, const NjAlone &w, double *M, const uint32_t *failed, std::vector<int32_t> &parent,
+                    std::vector<double> &blen, int *nodes, hipStream_t st) {
+    char *b = (char *)ctx->njB.p;
+    const size_t nt = 2 * (size_t)w.a.n + 1;
+    hk::NjBigArgs f = w.a;
+    f.D = M;
+    hipLaunchKernelGGL(hk::nj_big_finish_kernel, dim3(1), dim3(1), 0, st, f, failed, (int32_t *)(b + w.o_nodes));
+    HCHK(hipGetLastError());
+    const char *h = (const char *)ctx->njout.p;
+    HCHK(hipMemcpyAsync(ctx->njout.p, b + w.o_p, w.o_nodes + 4 - w.o_p, hipMemcpyDeviceToHost, st));
+    HCHK(hipStreamSynchronize(st));
+    parent.assign((const int32_t *)h, (const int32_t *)h + nt);
+    blen.assign((const double *)(h + w.o_b - w.o_p), (const double *)(h + w.o_b - w.o_p) + nt);
     int32_t nd = 0;
-    auto finish = [&](double *M, const uint32_t *failed) -> int {
-        hk::NjBigArgs f = a;
-        f.D = M;
-        hipLaunchKernelGGL(hk::nj_big_finish_kernel, dim3(1), dim3(1), 0, st, f, failed, (int32_t *)(b + o_nodes));
-        HCHK(hipGetLastError());
-        const char *h = (const char *)ctx->njout.p;
-        HCHK(hipMemcpyAsync(ctx->njout.p, b + o_p, o_nodes + 4 - o_p, hipMemcpyDeviceToHost, st));
-        HCHK(hipStreamSynchronize(st));
-        parent.assign((const int32_t *)h, (const int32_t *)h + nt);
-        blen.assign((const double *)(h + o_b - o_p), (const double *)(h + o_b - o_p) + nt);
-        memcpy(&nd, h + o_nodes - o_p, 4);
-        *nodes = nd;
-        return HALIGN_OK;
-    };
-    if (mesh) {
-        hk::NjMeshArgs g{n, G, D, (double *)(b + o_M), (uint64_t *)(b + o_mesh), (uint64_t *)(b + o_mesh) + 3 * (size_t)n,
-                         (uint32_t *)(b + o_fail), a};
-        RCHK(launch_fill((uint32_t *)(b + o_mesh), 0xffffffffu, 2 * (3 * (int64_t)n + 9 * (int64_t)G), st));
-        RCHK(launch_fill(g.failed, 0u, 1, st));
-        hipLaunchKernelGGL(hk::nj_mesh_kernel, dim3((unsigned)G), dim3(256), hk::nj_mesh_lds(n), st, g);
-        HCHK(hipGetLastError());
-        RCHK(finish(g.M, g.failed));
-        if (nd >= 0) return HALIGN_OK;
-    }
+    memcpy(&nd, h + w.o_nodes - w.o_p, 4);
+    *nodes = nd;
+    return HALIGN_OK;
+}
+
+// Neighbour joining of one problem on the mesh: D (device, n x n, not modified);
+// the tree to the host (2n + 1 entries).  *nodes < 0: the mesh left the problem
+// to the other kernels (its workgroups were not resident together, or a sum of
+// distances is infinite or NaN, whose order among pairs is the other kernels').
+int nj_mesh(halign_ctx *ctx, double *D, int n, std::vector<int32_t> &parent, std::vector<double> &blen, int *nodes,
+            hipStream_t st) {
+    NjAlone w;
+    RCHK(nj_alone(ctx, D, n, true, &w));
+    char *b = (char *)ctx->njB.p;
+    hk::NjMeshArgs g{n, w.G, D, (double *)(b + w.o_M), (uint64_t *)(b + w.o_mesh), (uint64_t *)(b + w.o_mesh) + 3 * (size_t)n,
+                     (uint32_t *)(b + w.o_fail), w.a};
+    RCHK(launch_fill((uint32_t *)(b + w.o_mesh), 0xffffffffu, 2 * (3 * (int64_t)n + 9 * (int64_t)w.G), st));
+    RCHK(launch_fill(g.failed, 0u, 1, st));
+    hipLaunchKernelGGL(hk::nj_mesh_kernel, dim3((unsigned)w.G), dim3(256), hk::nj_mesh_lds(n), st, g);
+    HCHK(hipGetLastError());
+    return nj_alone_finish(ctx, w, g.M, g.failed, parent, blen, nodes, st);
+}
+
+// The same over the whole chip, three launches a join; D is modified.
+int nj_big(halign_ctx *ctx, double *D, int n, std::vector<int32_t> &parent, std::vector<double> &blen, int *nodes,
+           hipStream_t st) {
+    NjAlone w;
+    RCHK(nj_alone(ctx, D, n, false, &w));
+    const hk::NjBigArgs &a = w.a;
     const unsigned rg = (unsigned)((n + 255) / 256);
     hipLaunchKernelGGL(hk::nj_big_init_kernel, dim3(rg), dim3(256), 0, st, a);
     HCHK(hipGetLastError());
     for (int t = 0; t < n - 3; ++t) {
         hipLaunchKernelGGL(hk::nj_big_rows_kernel, dim3((unsigned)((n + hk::kNjRowsCols - 1) / hk::kNjRowsCols)),
                            dim3(256), 0, st, a);
-        hipLaunchKernelGGL(hk::nj_big_q_kernel, dim3((unsigned)nparts), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(hk::nj_big_q_kernel, dim3((unsigned)a.nparts), dim3(256), 0, st, a);
         hipLaunchKernelGGL(hk::nj_big_join_kernel, dim3(1), dim3(256), 0, st, a);
     }
     HCHK(hipGetLastError());
-    return finish(D, nullptr);
+    return nj_alone_finish(ctx, w, D, nullptr, parent, blen, nodes, st);
+}
+
+// One problem of a tree by itself: on the mesh where it fits, else over the chip.
+int nj_one(halign_ctx *ctx, double *D, int n, std::vector<int32_t> &parent, std::vector<double> &blen, int *nodes,
+           hipStream_t st) {
+    if (nj_mesh_ok(ctx, n)) {
+        RCHK(nj_mesh(ctx, D, n, parent, blen, nodes, st));
+        if (*nodes >= 0) return HALIGN_OK;
+    }
+    return nj_big(ctx, D, n, parent, blen, nodes, st);
 }
 
 // labels[i] = nearest of the nb columns of D (na x nb, device), to the host
@@ -3692,9 +3731,10 @@ int halign_nj(halign_ctx *ctx, const double *D, int32_t n, int32_t *parent_host,
     HCHK(hipMemcpyAsync(ctx->njD.p, D, bytes, hipMemcpyDeviceToDevice, st));
     std::vector<int32_t> parent, nd;
     std::vector<double> blen;
-    if (n > kNjBigMin || (n >= kNjMeshMin && nj_mesh_ok(ctx, n))) {
-        int nn = 0;
-        RCHK(nj_big(ctx, (double *)ctx->njD.p, n, parent, blen, &nn, st));
+    int nn = -1;
+    if (n >= kNjMeshMin && nj_mesh_ok(ctx, n)) RCHK(nj_mesh(ctx, (double *)ctx->njD.p, n, parent, blen, &nn, st));
+    if (nn < 0 && n > kNjBigMin) RCHK(nj_big(ctx, (double *)ctx->njD.p, n, parent, blen, &nn, st));
+    if (nn >= 0) {
         nd.assign(1, nn);
     } else {
         std::vector<hk::NjGroup> groups(1);
@@ -4076,7 +4116,7 @@ int halign_nj_tree(halign_ctx *ctx, const uint8_t *msa, int32_t n, int64_t width
             std::vector<int32_t> bp;
             std::vector<double> bb;
             int nn = 0;
-            const int rc = nj_big(ctx, (double *)ctx->njD.p + ng[c].d0, ng[c].n, bp, bb, &nn, st);
+            const int rc = nj_one(ctx, (double *)ctx->njD.p + ng[c].d0, ng[c].n, bp, bb, &nn, st);
             if (rc != HALIGN_OK) {   // the small joins finish before the scratch can be reused
                 if (sst != st) (void)hipStreamSynchronize(sst);
                 return rc;

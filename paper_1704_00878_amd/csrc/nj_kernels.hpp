@@ -725,8 +725,10 @@ __global__ void __launch_bounds__(256) nj_big_join_kernel(NjBigArgs a) {
 //
 // The grid (at most 64 workgroups of 256 threads) has to be resident at once.
 // Every wait is bounded: a workgroup that polls kNjSpin times, or sees the
-// failure word, sets it and leaves, and the host joins the problem over the
-// chip instead (D itself is not changed).
+// failure word, sets it and leaves, and the host joins the problem with the
+// other kernels instead (D itself is not changed).  So does one whose row sum is
+// infinite or NaN: a pair that scores NaN comes before or after the others by its
+// place in those kernels' reductions, and the trees are theirs.
 constexpr uint64_t kNjEmpty = ~0ull;
 constexpr int kNjSpin = 1 << 17;
 constexpr int kNjMeshRows = 16, kNjMeshMax = 1024, kNjMeshAhead = kNjMeshMax / 256, kNjMeshPack = 32;
@@ -854,6 +856,10 @@ __global__ void __launch_bounds__(256) nj_mesh_kernel(NjMeshArgs a) {
 #pragma unroll
                 for (int u = 0; u < 8; ++u) sum = sum + v1[u];
             }
+        }
+        if (!(__builtin_fabs(sum) < __builtin_inf())) {
+            __hip_atomic_store(a.failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            bad = 1;
         }
         // this wavefront's updates of M and its emptied words are in memory
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
