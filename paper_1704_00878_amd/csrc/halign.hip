@@ -3619,7 +3619,8 @@ int nj_mesh(halign_ctx *ctx, double *D, int n, std::vector<int32_t> &parent, std
     RCHK(nj_alone(ctx, D, n, true, &w));
     char *b = (char *)ctx->njB.p;
     hk::NjMeshArgs g{n, w.G, D, (double *)(b + w.o_M), (uint64_t *)(b + w.o_mesh), (uint64_t *)(b + w.o_mesh) + 3 * (size_t)n,
-                     (uint32_t *)(b + w.o_fail), w.a};
+                     (uint32_t *)(b + w.o_fail), hk::kNjSpin, w.a};
+    if (const char *e = getenv("HALIGN_NJ_SPIN")) g.spin = atoi(e);   // test knob: 0 = every wait gives up at once
     RCHK(launch_fill((uint32_t *)(b + w.o_mesh), 0xffffffffu, 2 * (3 * (int64_t)n + 9 * (int64_t)w.G), st));
     RCHK(launch_fill(g.failed, 0u, 1, st));
     hipLaunchKernelGGL(hk::nj_mesh_kernel, dim3((unsigned)w.G), dim3(256), hk::nj_mesh_lds(n), st, g);

@@ -724,13 +724,13 @@ __global__ void __launch_bounds__(256) nj_big_join_kernel(NjBigArgs a) {
 // the others' and has it when it wins.
 //
 // The grid (at most 64 workgroups of 256 threads) has to be resident at once.
-// Every wait is bounded: a workgroup that polls kNjSpin times, or sees the
+// Every wait is bounded: a workgroup that polls `spin` times, or sees the
 // failure word, sets it and leaves, and the host joins the problem with the
 // other kernels instead (D itself is not changed).  So does one whose row sum is
 // infinite or NaN: a pair that scores NaN comes before or after the others by its
 // place in those kernels' reductions, and the trees are theirs.
 constexpr uint64_t kNjEmpty = ~0ull;
-constexpr int kNjSpin = 1 << 17;
+constexpr int kNjSpin = 1 << 17;   // polls of one wait at most (a poll is a read across XCDs, about 1 us)
 constexpr int kNjMeshRows = 16, kNjMeshMax = 1024, kNjMeshAhead = kNjMeshMax / 256, kNjMeshPack = 32;
 
 struct NjMeshArgs {
@@ -740,6 +740,7 @@ struct NjMeshArgs {
     uint64_t *rs;      // [3][n] row sums, by slot
     uint64_t *part;    // [3][G][3]: Q, D(i, j), i << 16 | j (positions)
     uint32_t *failed;
+    int spin;          // polls of one wait at most
     NjBigArgs o;       // act, id, parent, blen, ctrl
 };
 
@@ -762,10 +763,10 @@ __device__ __forceinline__ double nj_val(uint64_t v) { return __longlong_as_doub
 // wait.
 template <int N>
 __device__ __forceinline__ bool nj_poll(const uint64_t *const (&p)[N], const bool (&on)[N], uint64_t (&v)[N],
-                                        uint32_t *failed) {
+                                        int spin, uint32_t *failed) {
 #pragma unroll
     for (int u = 0; u < N; ++u) v[u] = kNjEmpty;
-    for (int it = 1; it <= kNjSpin; ++it) {
+    for (int it = 1; it <= spin; ++it) {
 #pragma unroll
         for (int u = 0; u < N; ++u)
             if (on[u] && v[u] == kNjEmpty) v[u] = nj_get(p[u]);
@@ -874,7 +875,7 @@ __global__ void __launch_bounds__(256) nj_mesh_kernel(NjMeshArgs a) {
                 on[u] = p < mp && slot[p] != kGone;
                 src[u] = rs + (on[u] ? slot[p] : 0);
             }
-            if (!nj_poll(src, on, v, a.failed)) bad = 1;
+            if (!nj_poll(src, on, v, a.spin, a.failed)) bad = 1;
 #pragma unroll
             for (int u = 0; u < kNjMeshAhead; ++u)
                 if (on[u]) r[tid + 256 * u] = nj_val(v[u]);
@@ -946,7 +947,7 @@ __global__ void __launch_bounds__(256) nj_mesh_kernel(NjMeshArgs a) {
                 const uint64_t *w = part + (int64_t)lane * 3, *const src[3] = {w, w + 1, w + 2};
                 const bool on[3] = {true, true, true};
                 uint64_t v[3];
-                if (!nj_poll(src, on, v, a.failed)) bad = 1;
+                if (!nj_poll(src, on, v, a.spin, a.failed)) bad = 1;
                 q = nj_val(v[0]);
                 d = v[1];
                 ij = (uint32_t)v[2];
