@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <fstream>
 #include <initializer_list>
 #include <functional>
@@ -124,6 +125,7 @@ struct halign_ctx {
     int64_t *mail_host = nullptr, *mail_dev = nullptr;   // coherent pinned mailbox: width, sequence number, flag, five counts
     DevBuf nuctab, nucscr, nucdp;   // nucleotide path: segment table and matches, stretch lists, stretch scratch
     int64_t nuc_list = 0, nuc_rows = 0, nuc_codes = 0, nuc_big = 0;   // entries that nucscr and nucdp are laid out for
+    int nuc_crowded[2] = {0, 0};    // k and segments of the last call whose matches outgrew the chain's LDS
     DevBuf rowck;                   // chunked rows: residues before each chunk of blocks, per row
     HostBuf njhost, njout;          // pinned: the tree's distances and the trees coming back
     DevBuf njF;                     // all rows' distances (sets where they are computed at once)
@@ -3310,18 +3312,32 @@ static int nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seq
     }
     // LDS of the chain for a quarter more matches than anchors can fit (each
     // position of the center matches once in a related sequence), so that several
-    // workgroups share a CU (1,035 anchors: 18 KB); a sequence with more matches
-    // is chained in global arrays
+    // workgroups share a CU (1,035 anchors: 18 KB).  A sequence with more, as short
+    // segments match by chance, is chained by one lane in global arrays.  Up to two
+    // sequences per CU, which fit with the largest LDS too, there is LDS for half more
+    // than the chance matches (of `indexed` strings that occur once in the center,
+    // among 4^k), and for kChainLdsMax where that fell short in every eighth sequence (an uneven
+    // composition), here and in later calls of this k and number of segments.
+    // Whole calls with matches in global arrays against LDS, sequences of 16,500: 100 with
+    // k = 7 4.55 against 3.71 ms, with k = 9 and 80% A and T 3.32 against 2.76; 672, which then
+    // no longer fit at once, 5.15 against 7.13 and 3.72 against 5.22.
     const int fit = std::min(longest, m) / k;
-    const int cap = std::min(hk::kChainLdsMax, (fit + fit / 4 + 127) & ~63);
-    a.chain_cap = cap;
+    int cap = std::min(hk::kChainLdsMax, (fit + fit / 4 + 127) & ~63);
+    const bool roomy = N <= 2 * ctx->num_cu && cap < hk::kChainLdsMax;
+    if (roomy) {
+        const double strings = std::pow(4.0, k), indexed = nsg * std::exp(-nsg / strings);
+        const double chance = std::min<double>(hk::kChainLdsMax, 1.5 * longest * indexed / strings);
+        cap = std::min(hk::kChainLdsMax, (fit + fit / 4 + (int)chance + 127) & ~63);
+        if (ctx->nuc_crowded[0] == k && ctx->nuc_crowded[1] == nsg) cap = hk::kChainLdsMax;
+    }
     // The lists and the scratch of the stretches are as large as the last calls
     // needed, or a first guess: the kernels count what they need, and where it
-    // is more the buffers grow and both kernels run again.
+    // is more the buffers grow and the stretches run again, the chain too where it
+    // had no place for a match or a stretch.
     ctx->nuc_list = std::max<int64_t>(ctx->nuc_list, (int64_t)N * 8 + 4096);
     ctx->nuc_codes = std::max<int64_t>(ctx->nuc_codes, ctx->nuc_list * 64);
     ctx->nuc_rows = std::max<int64_t>(ctx->nuc_rows, ctx->nuc_list * 8);
-    for (;;) {
+    for (bool chain = true;;) {
         const size_t lc = (size_t)ctx->nuc_list;
         const size_t l_nd = 0, l_wd = al256(16 * lc), l_no = l_wd + al256(16 * lc), l_wo = l_no + al256(16 * lc),
                      l_nx = l_wo + al256(16 * lc), l_wx = l_nx + al256(4 * lc), l_big = l_wx + al256(4 * lc),
@@ -3346,13 +3362,17 @@ static int nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seq
         a.flag = (const uint32_t *)ctx->counter.p + 8;
         a.mail = ctx->mail_dev;
         a.seq = ctx->mail_dev ? ++ctx->mail_seq : 0;
-        hipLaunchKernelGGL(hk::nuc_chain_kernel, dim3((unsigned)N), dim3(256), hk::nuc_chain_lds_bytes(cap, aw), st, a);
-        HCHK(hipGetLastError());
+        a.chain_cap = cap;
+        if (chain) {
+            hipLaunchKernelGGL(hk::nuc_chain_kernel, dim3((unsigned)N), dim3(256), hk::nuc_chain_lds_bytes(cap, aw), st, a);
+            HCHK(hipGetLastError());
+        }
         // (33 KB of LDS: four workgroups a CU)
         const int64_t sgrid = std::max<int64_t>(1, std::min<int64_t>(((int64_t)N * 8 + 3) / 4, (int64_t)ctx->num_cu * 4));
         hipLaunchKernelGGL(hk::nuc_stretch_kernel, dim3((unsigned)sgrid), dim3(256), 0, st, a);
         HCHK(hipGetLastError());
         RCHK(after());
+        if (!chain) break;   // (its counts were read the first time)
         int64_t need[5];   // boundary entries, code words, narrow (front | back << 32), wide, big
         if (ctx->mail_dev) {
             RCHK(mail_wait(ctx, a.seq, st));
@@ -3364,18 +3384,23 @@ static int nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seq
             HCHK(hipStreamSynchronize(st));
         }
         ctx->stage_pending = false;
+        const bool crowded = roomy && cap < hk::kChainLdsMax && need[4] > (int64_t)N * cap / 8;
+        if (crowded) {
+            ctx->nuc_crowded[0] = k;
+            ctx->nuc_crowded[1] = nsg;
+        }
         const int64_t narrow = (need[2] & 0xffffffffll) + (int64_t)((uint64_t)need[2] >> 32);
-        if (need[0] <= a.rowcap && need[1] <= a.codecap && narrow <= a.listcap && need[3] <= a.listcap &&
-            need[4] <= a.bigcap)
-            break;
+        chain = narrow > a.listcap || need[3] > a.listcap || need[4] > a.bigcap;
+        if (!chain && need[0] <= a.rowcap && need[1] <= a.codecap) break;
         RCHK(validate_check(ctx));
         if (narrow >= ((int64_t)1 << 31) || need[3] >= ((int64_t)1 << 31))
             return fail(HALIGN_E_UNSUPPORTED, "%lld stretches", (long long)(narrow + need[3]));
         ctx->nuc_rows = std::max(ctx->nuc_rows, need[0]);
         ctx->nuc_codes = std::max(ctx->nuc_codes, need[1]);
         ctx->nuc_list = std::max({ctx->nuc_list, narrow, need[3]});
+        if (crowded) cap = hk::kChainLdsMax;
         ctx->nuc_big = std::max(ctx->nuc_big, need[4]);
-        RCHK(launch_fill((uint32_t *)a.count, 0u, 2 * hk::kNucCounts, st));
+        if (chain) RCHK(launch_fill((uint32_t *)a.count, 0u, 2 * hk::kNucCounts, st));
     }
     return validate_check(ctx);
 }
