@@ -3334,7 +3334,10 @@ static int nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seq
     // needed, or a first guess: the kernels count what they need, and where it
     // is more the buffers grow and the stretches run again, the chain too where it
     // had no place for a match or a stretch.
-    ctx->nuc_list = std::max<int64_t>(ctx->nuc_list, (int64_t)N * 8 + 4096);
+    // The guess: eight stretches a sequence (672 genomes of 16,569 bases: seven), fewer
+    // where sequences are short, four million at most (1.6 GB in all).
+    ctx->nuc_list = std::max<int64_t>(
+        ctx->nuc_list, std::min({(int64_t)N * 8, oh[N] / 32, (int64_t)1 << 22}) + 4096);
     ctx->nuc_codes = std::max<int64_t>(ctx->nuc_codes, ctx->nuc_list * 64);
     ctx->nuc_rows = std::max<int64_t>(ctx->nuc_rows, ctx->nuc_list * 8);
     for (bool chain = true;;) {

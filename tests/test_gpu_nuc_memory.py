@@ -1,0 +1,39 @@
+"""Scratch of the nucleotide path: short sequences in large numbers."""
+import numpy as np
+import pytest
+
+from paper_1704_00878_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def H():
+    import paper_1704_00878_amd as H
+    return H
+
+
+def _align(H, ctx, n, length, m, k=16):
+    """n random sequences against a random center of m bases."""
+    import torch
+    rng = np.random.default_rng(n)
+    off = np.concatenate([[0], m + length * np.arange(n, dtype=np.int64)])
+    seqs = synth.SeqSet(rng.integers(0, 4, off[-1]).astype(np.uint8), off)
+    ds = H.DeviceSeqs(seqs)
+    score = torch.empty(n, dtype=torch.int32, device="cuda")
+    ins = torch.empty((n, m + 1), dtype=torch.int16, device="cuda")
+    al = torch.empty((n, (m + 31) // 32), dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    H.halign_nuc_align(ctx, H.Scoring(synth.NUC_MATRIX, synth.NUC_GAP_OPEN, synth.NUC_GAP_EXTEND), ds, 0, k, score, ins,
+                       al)
+    torch.cuda.synchronize()
+    return before - torch.cuda.mem_get_info()[0]
+
+
+# 300,000 sequences of 8 bases against a center of 16 (8 x 16 codes each, at most
+# 16 words): 0.3 KB of matches and lists a sequence, not 3 KB of guessed scratch
+def test_guess_follows_the_residues(H):
+    ctx = H.Context(0)
+    assert _align(H, ctx, 300000, 8, 16) < 500 << 20
+    ctx.close()
