@@ -3227,12 +3227,12 @@ static int nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seq
         longest = std::max<int>(longest, (int)n);
     }
     // device tables: segment table and its making, chunk bases, counters; per
-    // chunk: its count and its matches
+    // chunk its count; a place per residue for the matches
     const size_t o_tk = 0, o_ts = al256(8 * (size_t)T), o_sk = o_ts + al256(4 * (size_t)T),
                  o_ss = o_sk + al256(8 * (size_t)nsg + 8), o_st = o_ss + al256(4 * (size_t)nsg + 4),
                  o_cb = o_st + al256(4 * (size_t)nsg + 4), o_n = o_cb + al256(8 * (size_t)(N + 1)),
                  o_cc = o_n + 8 * hk::kNucCounts, o_cm = o_cc + al256(4 * (size_t)nchunk + 4),
-                 tab_bytes = o_cm + 4 * (size_t)nchunk * hk::kNucChunk;
+                 tab_bytes = o_cm + 4 * (size_t)oh[N] + 4;
     RCHK(grow(ctx, ctx->nuctab, tab_bytes));
     char *tb = (char *)ctx->nuctab.p;
     const int aw = (m + 31) / 32;

@@ -43,7 +43,8 @@ struct NucArgs {
     int64_t nchunk;
     int wparts;               // wavefronts that share a sequence's chunks in the scan
     int32_t *ccount;          // [nchunk] matches per chunk
-    uint32_t *cmatch;         // [nchunk][kNucChunk] matches in order of p: q << 8 | p within the chunk
+    uint32_t *cmatch;         // matches in order of p: q << 8 | p within the chunk; those of chunk c of sequence x
+                              // from off[x] + c * kNucChunk on (a place for every match start)
     int32_t *score;           // [N]
     uint16_t *ins;            // [N][m + 1] (zeroed)
     uint32_t *aligned;        // [N][aw] (zeroed)
@@ -363,7 +364,7 @@ __global__ void __launch_bounds__(1024) nuc_scan_wave_kernel(NucArgs a) {
                 before += __popcll(b & below);
                 total += __popcll(b);
             }
-            uint32_t *out = a.cmatch + (cb + c) * kNucChunk + before;
+            uint32_t *out = a.cmatch + so + (int64_t)c * kNucChunk + before;
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (q[r] >= 0) *out++ = (uint32_t)q[r] << 8 | (uint32_t)(4 * lane + r);
@@ -378,7 +379,7 @@ __global__ void __launch_bounds__(256) nuc_scan_kernel(NucArgs a) {
     int x, c;
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (!nuc_chunk(a, g, x, c)) return;
-    uint32_t *out = a.cmatch + g * kNucChunk;
+    uint32_t *out = a.cmatch + a.off[x] + (int64_t)c * kNucChunk;
     int cnt = 0;
     nuc_scan_chunk(a, tk, ts, x, c, [&](int q, int p) { out[cnt++] = (uint32_t)q << 8 | (uint32_t)(p - c * kNucChunk); });
     a.ccount[g] = cnt;
@@ -611,7 +612,7 @@ __global__ void __launch_bounds__(256) nuc_chain_kernel(NucArgs a) {
     if (room) {
         for (int c = tid >> 4; c < nc; c += 16) {
             const int at = s_coff[c], e = s_coff[c + 1] - at;
-            const uint32_t *src = a.cmatch + (cb + c) * kNucChunk;
+            const uint32_t *src = a.cmatch + so + (int64_t)c * kNucChunk;
             for (int i = tid & 15; i < e; i += 16) {
                 const uint32_t v = src[i];
                 const int q = (int)(v >> 8), p = c * kNucChunk + (int)(v & 255u);

@@ -37,3 +37,11 @@ def test_guess_follows_the_residues(H):
     ctx = H.Context(0)
     assert _align(H, ctx, 300000, 8, 16) < 500 << 20
     ctx.close()
+
+
+# 200,000 sequences of 20 bases, one scan chunk each: places for matches by the
+# residue (16 MB), not by the chunk (205 MB)
+def test_matches_by_the_residue(H):
+    ctx = H.Context(0)
+    assert _align(H, ctx, 200000, 20, 40) < 200 << 20
+    ctx.close()
