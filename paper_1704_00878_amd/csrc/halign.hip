@@ -3336,18 +3336,21 @@ static int nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seq
     // had no place for a match or a stretch.
     // The guess: eight stretches a sequence (672 genomes of 16,569 bases: seven), fewer
     // where sequences are short, four million at most (1.6 GB in all).
-    ctx->nuc_list = std::max<int64_t>(
-        ctx->nuc_list, std::min({(int64_t)N * 8, oh[N] / 32, (int64_t)1 << 22}) + 4096);
-    ctx->nuc_codes = std::max<int64_t>(ctx->nuc_codes, ctx->nuc_list * 64);
-    ctx->nuc_rows = std::max<int64_t>(ctx->nuc_rows, ctx->nuc_list * 8);
+    int64_t list = std::max<int64_t>(ctx->nuc_list, std::min({(int64_t)N * 8, oh[N] / 32, (int64_t)1 << 22}) + 4096);
+    int64_t codes = std::max<int64_t>(ctx->nuc_codes, list * 64), rows = std::max<int64_t>(ctx->nuc_rows, list * 8);
+    int64_t big = ctx->nuc_big;
     for (bool chain = true;;) {
-        const size_t lc = (size_t)ctx->nuc_list;
+        const size_t lc = (size_t)list;
         const size_t l_nd = 0, l_wd = al256(16 * lc), l_no = l_wd + al256(16 * lc), l_wo = l_no + al256(16 * lc),
                      l_nx = l_wo + al256(16 * lc), l_wx = l_nx + al256(4 * lc), l_big = l_wx + al256(4 * lc),
-                     scr_bytes = l_big + 20 * (size_t)ctx->nuc_big + 4;
+                     scr_bytes = l_big + 20 * (size_t)big + 4;
         RCHK(grow(ctx, ctx->nucscr, scr_bytes));
-        const size_t d_co = al256(8 * (size_t)ctx->nuc_rows);
-        RCHK(grow(ctx, ctx->nucdp, d_co + 4 * (size_t)ctx->nuc_codes));
+        const size_t d_co = al256(8 * (size_t)rows);
+        RCHK(grow(ctx, ctx->nucdp, d_co + 4 * (size_t)codes));
+        ctx->nuc_list = list;   // (kept once they are allocated)
+        ctx->nuc_codes = codes;
+        ctx->nuc_rows = rows;
+        ctx->nuc_big = big;
         char *sb = (char *)ctx->nucscr.p;
         a.nd = (int4 *)(sb + l_nd);
         a.wd = (int4 *)(sb + l_wd);
@@ -3356,12 +3359,12 @@ static int nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seq
         a.nx = (int32_t *)(sb + l_nx);
         a.wx = (int32_t *)(sb + l_wx);
         a.big = (int32_t *)(sb + l_big);
-        a.bigcap = ctx->nuc_big;
-        a.listcap = ctx->nuc_list;
+        a.bigcap = big;
+        a.listcap = list;
         a.rows = (int2 *)ctx->nucdp.p;
         a.codes = (uint32_t *)((char *)ctx->nucdp.p + d_co);
-        a.rowcap = ctx->nuc_rows;
-        a.codecap = ctx->nuc_codes;
+        a.rowcap = rows;
+        a.codecap = codes;
         a.flag = (const uint32_t *)ctx->counter.p + 8;
         a.mail = ctx->mail_dev;
         a.seq = ctx->mail_dev ? ++ctx->mail_seq : 0;
@@ -3398,11 +3401,11 @@ static int nuc_align(halign_ctx *ctx, const halign_scoring *sc, const halign_seq
         RCHK(validate_check(ctx));
         if (narrow >= ((int64_t)1 << 31) || need[3] >= ((int64_t)1 << 31))
             return fail(HALIGN_E_UNSUPPORTED, "%lld stretches", (long long)(narrow + need[3]));
-        ctx->nuc_rows = std::max(ctx->nuc_rows, need[0]);
-        ctx->nuc_codes = std::max(ctx->nuc_codes, need[1]);
-        ctx->nuc_list = std::max({ctx->nuc_list, narrow, need[3]});
+        rows = std::max(rows, need[0]);
+        codes = std::max(codes, need[1]);
+        list = std::max({list, narrow, need[3]});
         if (crowded) cap = hk::kChainLdsMax;
-        ctx->nuc_big = std::max(ctx->nuc_big, need[4]);
+        big = std::max(big, need[4]);
         if (chain) RCHK(launch_fill((uint32_t *)a.count, 0u, 2 * hk::kNucCounts, st));
     }
     return validate_check(ctx);

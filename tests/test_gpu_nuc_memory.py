@@ -45,3 +45,14 @@ def test_matches_by_the_residue(H):
     ctx = H.Context(0)
     assert _align(H, ctx, 200000, 20, 40) < 200 << 20
     ctx.close()
+
+
+# 4,000 stretches of 16,000 by 16,500 need 530 GB of codes: refused, and the
+# context goes on
+def test_context_serves_after_a_refusal(H):
+    ctx = H.Context(0)
+    with pytest.raises(H.HalignError) as e:
+        _align(H, ctx, 4000, 16500, 16000)
+    assert "allocation" in str(e.value)
+    _align(H, ctx, 20, 300, 400)
+    ctx.close()
