@@ -840,7 +840,7 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
                                st, d);
             hipLaunchKernelGGL(hk::plan_stage_kernel, dim3((unsigned)((cn + 3) / 4)), dim3(256), 0, st, d);
             HCHK(hipGetLastError());
-            hmark(ctx, "dplan");
+            hmark(ctx, dev_own > 0 ? "dplan_own" : "dplan");
         } else {
             PlanBuilder pb;
             // strip route: the walk list and its walk descriptors, both in walk
