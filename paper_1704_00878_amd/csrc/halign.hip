@@ -1262,6 +1262,10 @@ int autotune(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, co
         return HALIGN_OK;
     }
     *ran = true;
+    // the trials write their plans into the stage from its start, where the matrix
+    // of this call may still be on its way from
+    HCHK(hipStreamSynchronize(st));
+    ctx->stage_pending = false;
     // the batch itself (up to 4e10 cells: a few tens of ms per candidate), or a
     // strided sample of 65,536 pairs that keeps the length mix and, through the
     // stream count, the number of pairs per stream
