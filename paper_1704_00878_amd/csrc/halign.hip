@@ -1236,8 +1236,10 @@ void tune_save(halign_ctx *ctx, const std::string &key, const std::array<int, 5>
 }
 
 // *ran: whether candidate plans were run (the stage is then drained).
+// dev_longest: as in run_batch; the whole batch is timed under the planner that will run it
+// (a sample's ids are planned on the host).
 int autotune(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, const halign_seqs *sq, bool tb,
-             bool endc, const BatchOut &out, hipStream_t st, Tune *best, bool *ran) {
+             bool endc, const BatchOut &out, int dev_longest, hipStream_t st, Tune *best, bool *ran) {
     *ran = false;
     const int N = sq->n;
     const int mean = N > 0 ? (int)((sq->offsets_host[N] - sq->offsets_host[0]) / N) : 0;
@@ -1271,8 +1273,8 @@ int autotune(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, co
     // stream count, the number of pairs per stream
     const double bcells = (double)m * (double)(sq->offsets_host[N] - sq->offsets_host[0]);
     const int ns = bcells <= 4e10 ? N : std::min(N, 65536);
-    std::vector<int32_t> sample(ns);
-    for (int q = 0; q < ns; ++q) sample[q] = (int32_t)((int64_t)q * N / ns);
+    std::vector<int32_t> sample(ns < N ? ns : 0);
+    for (size_t q = 0; q < sample.size(); ++q) sample[q] = (int32_t)((int64_t)q * N / ns);
     int R0 = 8, p0 = 1;
     pick_geom(m, &R0, &p0);
     const double scale = (double)ns / N;
@@ -1301,7 +1303,8 @@ int autotune(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, co
             // (the previous run has synchronised)
             ctx->stage_off = ctx->plan_off = 0;
             ctx->ntev = 0;
-            RCHK(run_batch(ctx, S, center, m, sq, sample.data(), (int)sample.size(), tb, endc, c.route, out, st, c));
+            RCHK(run_batch(ctx, S, center, m, sq, sample.empty() ? nullptr : sample.data(), ns, tb, endc, c.route, out, st,
+                           c, dev_longest));
             float wk = 0.f;
             RCHK(tev_sum(ctx, &ms, &wk));
             ctx->stage_pending = false;   // the last event follows the plan's copy
@@ -1656,11 +1659,12 @@ static int sw_batch_body(halign_ctx *ctx, const halign_scoring *sc, const uint8_
     RCHK(grow(ctx, ctx->pairbuf, (size_t)N * 8 + 256));
     int32_t *endcell = (int32_t *)ctx->pairbuf.p;
     hmark(ctx, "upload");
+    const bool graph_call = (flags & HALIGN_GRAPH) != 0;   // planned on the host
     Tune tune;
     if (want_tune) {
         BatchOut tout{score, cells, endcell, ins, aligned};
         bool ran = false;
-        RCHK(autotune(ctx, S, center, m, seqs, tb, endc, tout, st, &tune, &ran));
+        RCHK(autotune(ctx, S, center, m, seqs, tb, endc, tout, graph_call ? -1 : longest, st, &tune, &ran));
         if (ran) RCHK(stage_begin(ctx));   // the tuner's runs have synchronised
     }
     for (auto &v : ctx->last_stats) v = 0;
@@ -1670,7 +1674,6 @@ static int sw_batch_body(halign_ctx *ctx, const halign_scoring *sc, const uint8_
     // forward kernels read codes masked to 5 bits, the check is read after the
     // batch, and the outputs are first written by the walk); with them the matrix
     // and the device planner's count of the pairs by length
-    const bool graph_call = (flags & HALIGN_GRAPH) != 0;
     const bool count = !graph_call && N >= kDevPlanMin && longest < hk::kPrepHistMax;
     auto prep = [&]() -> int {
         if (tb) {

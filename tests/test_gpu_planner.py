@@ -94,3 +94,29 @@ def test_captured(H, monkeypatch, capfd):
         assert int(out["score"].argmax()) == 7
     assert ctx.graph_launches() == 3
     ctx.close()
+
+
+# a tuned batch is timed under the planner that then runs it: the device's for all
+# candidates but one pair per lane (each is run twice)
+@pytest.mark.parametrize("n,want", [(4000, "dplan"), (2000, "plan")])
+def test_tuner_times_what_runs(H, n, want, monkeypatch, capfd):
+    import torch
+    monkeypatch.setenv("HALIGN_HOST_TIMING", "1")
+    rng = np.random.default_rng(3)
+    ds = H.DeviceSeqs(synth.random_set(rng, n, 100, 130))
+    ctx = H.Context(0)
+    rows = H.halign_msa(ctx, H.Scoring(), ds, 5)[0].cpu()
+    ctx.set_autotune(True)
+    _labels(capfd)
+    assert torch.equal(H.halign_msa(ctx, H.Scoring(), ds, 5)[0].cpu(), rows)
+    first = _labels(capfd)[0]
+    assert torch.equal(H.halign_msa(ctx, H.Scoring(), ds, 5)[0].cpu(), rows)
+    again = _labels(capfd)[0]
+    ctx.close()
+    trials = first[:first.index("tune")]
+    assert "tune" in again and _planner(again[:again.index("tune")]) is None
+    if "p_deal" in again or _planner(again) != "plan":   # streams were chosen
+        assert _planner(again) == want
+    assert trials.count(want) >= 2 * 6
+    assert trials.count("plan") + trials.count("dplan") + trials.count("dplan_own") >= 2 * 7
+
