@@ -2838,13 +2838,12 @@ int halign_pair_loss_grouped(halign_ctx *ctx, const float *E, const float *targe
     hipStream_t st = (hipStream_t)stream;
     const int G = npairs / group;
     const size_t b_sq = ((size_t)npairs * 4 + 255) & ~size_t(255), b_g = ((size_t)G * 4 + 255) & ~size_t(255);
-    RCHK(grow(ctx, ctx->mlp[0], b_sq + b_g + (size_t)2 * npairs * hk::kEmb * 2 + 512));
+    RCHK(grow(ctx, ctx->mlp[0], b_sq + b_g + 512));
     float *sq = (float *)ctx->mlp[0].p;
     float *gsq = (float *)((char *)ctx->mlp[0].p + b_sq);
-    uint16_t *dEb = (uint16_t *)((char *)ctx->mlp[0].p + b_sq + b_g);
     if (G > 0) {
         hipLaunchKernelGGL(hk::pair_group_loss_kernel, dim3(G), dim3(64), 0, st, E, target, npairs, group, lam, dE,
-                           dEb, sq, gsq);
+                           sq, gsq);
         HCHK(hipGetLastError());
     }
     hipLaunchKernelGGL(hk::mean2_kernel, dim3(1), dim3(256), 0, st, (const float *)sq, npairs, (const float *)gsq, G,

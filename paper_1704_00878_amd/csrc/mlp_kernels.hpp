@@ -630,8 +630,7 @@ __global__ void __launch_bounds__(256) mean_kernel(const float *v, int n, float 
 // one wavefront per group), loss = mean(diff^2) + lam * mean over groups of
 // (mean diff of the group)^2.  dpred = 2 diff / P + 2 lam gmean / (G K).
 __global__ void __launch_bounds__(64) pair_group_loss_kernel(const float *E, const float *target, int P, int K,
-                                                             float lam, float *dE, uint16_t *dEb, float *sq,
-                                                             float *gsq) {
+                                                             float lam, float *dE, float *sq, float *gsq) {
     const int g = blockIdx.x, l = threadIdx.x;
     const int G = P / K;
     const int r = g * K + l;
@@ -649,13 +648,9 @@ __global__ void __launch_bounds__(64) pair_group_loss_kernel(const float *E, con
     if (l >= K) return;
     const float gsc = 2.f * diff / (float)P + 2.f * lam * gm / ((float)G * (float)K);
     float *da = dE + (int64_t)r * kEmb, *db = dE + (int64_t)(r + P) * kEmb;
-    uint16_t *dab = dEb + (int64_t)r * kEmb, *dbb = dEb + (int64_t)(r + P) * kEmb;
     for (int d = 0; d < kEmb; ++d) {
-        const float ga = gsc * b[d], gb = gsc * a[d];
-        da[d] = ga;
-        db[d] = gb;
-        dab[d] = f2bf(ga);
-        dbb[d] = f2bf(gb);
+        da[d] = gsc * b[d];
+        db[d] = gsc * a[d];
     }
 }
 

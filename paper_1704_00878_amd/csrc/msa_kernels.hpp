@@ -17,12 +17,6 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, int64_t n) {
         p[x] = v;
 }
 
-__global__ void fill_u16_kernel(uint16_t *p, uint16_t v, int64_t n) {
-    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n;
-         x += (int64_t)gridDim.x * blockDim.x)
-        p[x] = v;
-}
-
 // A substitution matrix passed by value (kernel argument), copied into device
 // memory by one workgroup: no host staging buffer is involved.
 struct MatrixArg {
