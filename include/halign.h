@@ -213,15 +213,17 @@ int halign_emit_rows(halign_ctx *ctx, const halign_seqs *seqs, int32_t m,
  * sums are the same either way.  HALIGN_STRIP32=1 forces the 32-bit kernel. */
 int halign_center_exact(halign_ctx *ctx, const halign_scoring *sc, const halign_seqs *seqs,
                         int64_t *sums, int32_t *center_host, void *stream);
-/* Group tiling of halign_center_exact (host only, no device needed): all
- * pairs a < b of n positions (in length order) fall into *ngroups_host groups
- * of one center position and `step` consecutive partner positions (64 for
- * the 32-bit kernel; the packed one takes two neighbouring center positions and
- * 64 partners, numbered likewise), in closed form, so
- * the search holds O(n) host data.  With g >= 0, group g is decoded into its
- * center position and first partner position (partners [p0, p0 + step),
- * those not above the center position are idle).  A caller sharding the
- * exhaustive search over devices can split [0, *ngroups_host). */
+/* Group tilings of halign_center_exact (host only, no device needed): all
+ * pairs a < b of n positions (in length order) fall into *ngroups_host groups,
+ * numbered in closed form, so the search holds O(n) host data.  step >= 1: one
+ * center position and `step` consecutive partner positions (64 in the 32-bit
+ * kernel).  step = HALIGN_TILING_PACKED: the packed kernel's, two neighbouring
+ * center positions and 64 partners.  With g >= 0, group g is decoded into its
+ * (first) center position and first partner position (partners [p0, p0 + step)
+ * or [p0, p0 + 64), each paired with the group's center positions below it).  A
+ * caller sharding the exhaustive search over devices can split
+ * [0, *ngroups_host). */
+#define HALIGN_TILING_PACKED (-64)
 int halign_exact_tiling(int64_t n, int32_t step, int64_t g, int64_t *ngroups_host, int64_t *center_pos_host,
                         int64_t *partner0_host);
 /* The judge over a partner sample: sums[q] = sum over the listed partners

@@ -30,6 +30,7 @@ HALIGN_ROUTE_INTRA = 2 << 4
 HALIGN_GRAPH = 1 << 8
 HALIGN_CENTER_EXACT = -1
 HALIGN_CENTER_LEARNED = -2
+HALIGN_TILING_PACKED = -64
 
 
 class HalignError(RuntimeError):
@@ -562,8 +563,9 @@ def halign_f32_to_bf16(src, dst, stream=None):
 
 
 def halign_exact_tiling(n: int, step: int, g: int = -1):
-    """Group count of the exhaustive center's tiling and, for g >= 0, the
-    (center position, first partner position) of group g (host only)."""
+    """Group count of the exhaustive center's tiling (step partners a group, or
+    HALIGN_TILING_PACKED) and, for g >= 0, the (center position, first partner
+    position) of group g (host only)."""
     ng, a, b0 = ctypes.c_int64(0), ctypes.c_int64(-1), ctypes.c_int64(-1)
     _check(lib().halign_exact_tiling(n, step, g, ctypes.byref(ng), ctypes.byref(a), ctypes.byref(b0)))
     return (int(ng.value), int(a.value), int(b0.value)) if g >= 0 else int(ng.value)

@@ -2157,12 +2157,14 @@ static int argmax_sums(halign_ctx *ctx, const int64_t *sums, const int32_t *cand
 
 int halign_exact_tiling(int64_t n, int32_t step, int64_t g, int64_t *ngroups_host, int64_t *center_pos_host,
                         int64_t *partner0_host) {
-    if (n < 0 || step < 1 || !ngroups_host) return fail(HALIGN_E_INVALID, "bad arguments");
-    const int64_t ng = hk::tri_groups(n, step);
+    const bool packed = step == HALIGN_TILING_PACKED;
+    if (n < 0 || (step < 1 && !packed) || !ngroups_host) return fail(HALIGN_E_INVALID, "bad arguments");
+    const int64_t ng = packed ? hk::pair_groups(n) : hk::tri_groups(n, step);
     *ngroups_host = ng;
     if (g < 0) return HALIGN_OK;
     if (g >= ng || !center_pos_host || !partner0_host) return fail(HALIGN_E_INVALID, "group %lld of %lld", (long long)g, (long long)ng);
-    hk::tri_group(g, n, step, center_pos_host, partner0_host);
+    if (packed) hk::pair_group(g, n, center_pos_host, partner0_host);
+    else hk::tri_group(g, n, step, center_pos_host, partner0_host);
     return HALIGN_OK;
 }
 
