@@ -3805,13 +3805,17 @@ int halign_nj_tree(halign_ctx *ctx, const uint8_t *msa, int32_t n, int64_t width
     const int N = n, S = (N + 9) / 10;
     std::vector<int32_t> seed(perm_host, perm_host + S);
     // Where all rows' distances are cheap (up to 2e10 pair-columns in one
-    // triangle, about 0.5 ms, and 2,048 rows, 32 MB), they are computed at once
+    // triangle, about 0.5 ms) and few (768 rows, 4.7 MB), they are computed at once
     // and copied to the host, which labels and divides from them: a divide pass
     // costs a distance launch, a nearest launch and two waits otherwise, about
-    // 0.2 ms, and there are up to 20.  The values are the same either way.
+    // 0.2 ms, and there are up to 20.  The host's part grows with the square of the
+    // rows: of 300 to 18,000 columns, a launch per step takes 4.0 times as long at
+    // 64 rows, 1.58 at 400, 1.15 at 672, 1.04 at 760, 0.99 at 840, 0.96 at 1,000,
+    // 0.71 at 2,000 (whole trees, geometric means).
+    // The values are the same either way.
     const char *env_full = getenv("HALIGN_NJ_FULL");   // test knob: 0 = per step
     const bool full =
-        N <= 2048 && 0.5 * (double)N * N * (double)width <= 2e10 && !(env_full && atoi(env_full) == 0);
+        N <= 768 && 0.5 * (double)N * N * (double)width <= 2e10 && !(env_full && atoi(env_full) == 0);
     const double *F = nullptr;
     // the first of `nb` rows b with the smallest distance to row x
     auto nearest = [&](int x, const int32_t *rb, int nb) {
