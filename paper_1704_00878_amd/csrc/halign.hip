@@ -645,8 +645,7 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
     pk = pk && route == kRouteIntra;
     const int W = (R + 7) / 8, NS = 64 / LS;
     const int WQ = pk ? (R + 3) / 4 : W;   // code words per step
-    const size_t prof_bytes =
-        p16 ? (size_t)(S.alpha + 1) * LS * 16 * W : (size_t)hk::kAlphaMax * LS * R * 4;
+    const size_t prof_bytes = (size_t)(S.alpha + 1) * LS * (p16 ? 16 * W : 4 * R);
     // wavefronts per workgroup: one per SIMD, so that any number per SIMD spreads
     // evenly over the CUs (300 pairs of 300-900 on m = 800: 0.71 against 1.08 ms);
     // eight in large batches of the 32-bit kernel, which share a profile
@@ -813,7 +812,7 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
             d.maxlen = nlong;
             d.ns = nstreams;
             d.own = dev_own;
-            d.clamp = p16 ? S.alpha : 31;
+            d.clamp = S.alpha;
             d.hist = (int32_t *)(dplan + o_hist);
             d.order = (int2 *)(dplan + o_order);
             d.per_group = per_group;
@@ -1055,7 +1054,7 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
                 const int n16 = zplan ? (int)(plan_bytes / 16) : 0;
                 hipLaunchKernelGGL(hk::stage_stream_kernel, dim3((nslots + 3) / 4 + (n16 + 255) / 256), dim3(256), 0, st,
                                    sq->residues, sq->offsets, (const int32_t *)(pl + o_spid),
-                                   (const int64_t *)(pl + o_scol), nslots, p16 ? S.alpha : 31, sres, keys,
+                                   (const int64_t *)(pl + o_scol), nslots, S.alpha, sres, keys,
                                    (const uint4 *)zplan, (uint4 *)dplan, n16);
                 HCHK(hipGetLastError());
             }

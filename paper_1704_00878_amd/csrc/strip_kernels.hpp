@@ -28,7 +28,7 @@ namespace hk {
 constexpr int kT = 16;
 constexpr int kPS = kT + 4;  // LDS row stride of the strip profile
 constexpr int kB = 4;        // columns per prefetch block (the 4 columns of a code chunk)
-constexpr int kFMask = (1 << 27) - 1;  // F* bits of a strip boundary cell (residue code above)
+constexpr int kFBits = 26, kFMask = (1 << kFBits) - 1;  // F* bits of a strip boundary cell (residue code above)
 
 struct InterArgs {
     const int8_t *mat;
@@ -78,7 +78,7 @@ __device__ __forceinline__ int2 load_agent(const int2 *p) {
 template <bool TB, bool ENDC>
 __global__ void __launch_bounds__(64)
 sw_inter_kernel(InterArgs a) {
-    __shared__ int prof[kAlphaMax * kPS];
+    __shared__ int prof[(kAlphaMax + 1) * kPS];
     __shared__ uint32_t stage_all[64 * 8];
     __shared__ int8_t smat[kAlphaMax * kAlphaMax];
     const int lane = threadIdx.x;
@@ -146,7 +146,7 @@ sw_inter_kernel(InterArgs a) {
         for (int st = 0; st < nstrips; ++st) {
             const int i0 = st * kT;
             __syncthreads();
-            for (int x = lane; x < kAlphaMax * kT; x += 64) {
+            for (int x = lane; x < (kAlphaMax + 1) * kT; x += 64) {
                 const int r = x / kT, t = x - r * kT;
                 int v = kNegProf;
                 if (r < a.alpha && i0 + t < m) v = (int)smat[(cen[i0 + t] & 31) * 32 + r] + goe;
@@ -158,7 +158,7 @@ sw_inter_kernel(InterArgs a) {
             for (int t = 0; t < kT; ++t) { hg[t] = -goe; e[t] = 0; }
             int diag0 = -goe;
             // The first strip reads residues from the lane's sequence and
-            // leaves each column's code in its boundary cell (bits 27-31 of
+            // leaves each column's code in its boundary cell (bits 26-31 of
             // F*, which stays below 2^23 for lengths < 65536 and |scores| <
             // 128); later strips get residue and boundary in one load.  A
             // block of kB columns is fetched one block ahead into the other of
@@ -193,7 +193,7 @@ sw_inter_kernel(InterArgs a) {
                         } else {
                             upg = bc[b].x;
                             upf = bc[b].y & kFMask;
-                            r = (int)((uint32_t)bc[b].y >> 27);
+                            r = (int)((uint32_t)bc[b].y >> kFBits);
                         }
                         int diag = diag0;
                         diag0 = upg;
@@ -212,7 +212,7 @@ sw_inter_kernel(InterArgs a) {
                             if (ENDC) colkey = vmax3(colkey, (h0 << 5) | (31 - t), (h1 << 5) | (30 - t));
                             else hmax = vmax3(hmax, h0, h1);
                         }
-                        bnd[(int64_t)(j - 1) * 64 + lane] = make_int2(upg, upf | (r << 27));
+                        bnd[(int64_t)(j - 1) * 64 + lane] = make_int2(upg, (int)((uint32_t)upf | (uint32_t)r << kFBits));
                         if (TB) {
                             stage[2 * b] = w0;
                             stage[2 * b + 1] = w1;
@@ -315,7 +315,7 @@ constexpr int kPS2 = kT2 + 4; // LDS row stride of the profile: residues spread 
 
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
 sw_inter16_kernel(InterArgs a) {
-    __shared__ __attribute__((aligned(16))) uint32_t prof[kAlphaMax * kPS2];   // [r][32] (first, second center)
+    __shared__ __attribute__((aligned(16))) uint32_t prof[(kAlphaMax + 1) * kPS2];   // [r][32] (first, second center)
     __shared__ int8_t smat[kAlphaMax * kAlphaMax];
     __shared__ unsigned long long s_next;
     const int lane = threadIdx.x;
@@ -378,7 +378,7 @@ sw_inter16_kernel(InterArgs a) {
         for (int st = 0; st < nstrips && nmax > 0; ++st) {
             const int i0 = st * kT2;
             __syncthreads();
-            for (int x = lane; x < kAlphaMax * kT2; x += 64) {
+            for (int x = lane; x < (kAlphaMax + 1) * kT2; x += 64) {
                 const int r = x >> 5, t = x & 31;
                 const int add = (t & 1) ? go : a.goe;   // (from hg of a row with one ge less above an even row)
                 int v0 = kPadProf16, v1 = kPadProf16;

@@ -33,8 +33,8 @@
 
 namespace hk {
 
-constexpr int kPad = 31;             // residue code of padding columns / alphabet filler
 constexpr int kAlphaMax = 32;
+constexpr int kPad = kAlphaMax;      // residue code of padding columns in the strip kernels: past every alphabet
 constexpr int kNegProf = -(1 << 22); // profile value of padding: never a source
 
 // v_max3_i32 (the compiler splits max(max(a,b),c) into a signed and an
@@ -182,8 +182,8 @@ sw_stream_kernel(StreamArgs a) {
     constexpr int NS = 64 / LS;              // streams per wavefront
     constexpr int SPAN = LS * R;             // rows per pass
     extern __shared__ int prof[];   // profile, then code staging [waves][8 steps][W][64 lanes]
-    const int nprow = P16 ? a.alpha + 1 : kAlphaMax;
-    const int prof_words = P16 ? nprow * LS * 4 * W : kAlphaMax * SPAN;
+    const int nprow = a.alpha + 1;           // (the last one for padding columns)
+    const int prof_words = nprow * (P16 ? LS * 4 * W : SPAN);
     uint32_t *stage = reinterpret_cast<uint32_t *>(prof + prof_words) + (threadIdx.x >> 6) * 512 * W +
                       (threadIdx.x & 63);   // word (u, q) at stage[64 * (u*W + q)]: no bank conflicts
     const int tid = threadIdx.x;
@@ -225,7 +225,7 @@ sw_stream_kernel(StreamArgs a) {
                 p16[x] = (int16_t)(tt < R ? staged_score(tmp, a.alpha, l * R + tt, r, goe, -32768) : -32768);
             }
         } else {
-            for (int x = tid; x < kAlphaMax * SPAN; x += nthreads) {
+            for (int x = tid; x < nprow * SPAN; x += nthreads) {
                 const int r = x / SPAN, i = row0 + (x - r * SPAN);
                 int v = kNegProf;
                 if (r < a.alpha && i < a.m) v = (int)a.mat[(a.center[i] & 31) * a.alpha + r] + goe;
@@ -241,7 +241,7 @@ sw_stream_kernel(StreamArgs a) {
         uint32_t *cw = (TB && active) ? a.codes + a.scbase[sid] + (int64_t)pass * G * LS * 8 * W + ll * 8 * W : nullptr;
         // staged residue codes are already clamped to the profile rows; the
         // first-column flag moves to bit 31 (so the profile index shifts it out)
-        const int padc = P16 ? a.alpha : kPad;
+        const int padc = a.alpha;
         auto conv = [&](int b) __attribute__((always_inline)) { return (b & 0x7f) | ((b & 0x80) << 24); };
         // the loop, specialised on whether boundary rows come in or go out
         auto run = [&](auto hb_tag) __attribute__((always_inline)) {
@@ -337,7 +337,7 @@ sw_stream_kernel(StreamArgs a) {
                             }
                         }
                     } else {
-                        const int *prow = pbase + (rcur & 31) * SPAN;
+                        const int *prow = pbase + (rcur & 63) * SPAN;
 #pragma unroll
                         for (int t = 0; t < R; ++t) p[t] = prow[t];
                     }
