@@ -1,9 +1,9 @@
 // Host runtime and C ABI of the center-star MSA library (gfx950).
 //
 // The runtime owns device scratch (traceback codes, boundary rows, plans) in
-// a halign_ctx, plans each batch on the host (length sort, grouping, chunking
-// under a workspace cap), and launches the kernels of sw_kernels.hpp and
-// msa_kernels.hpp on the caller's stream.
+// a halign_ctx, plans each batch -- on the device from 2,048 pairs where its rule
+// fits (plan_kernels.hpp), else on the host (length sort, grouping, chunking under a
+// workspace cap) -- and launches the kernels on the caller's stream.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -451,11 +451,13 @@ double stream_cols(const Lens &plen, int np, int64_t sum_len, int cap) {
 // SIMD of it resident.  A step issues about ops(R) instructions of 4 cycles;
 // w wavefronts on a SIMD take kShare[w] issue times per step of each (a serial
 // chain alone: 1.28; four together fill the issue slots), and no stream ends
-// before its longest pair.  Against the measured forward times (20,000 pairs of
+// before its longest pair.  A model for choosing, not for timing: with traceback it gives
+// 0.67 to 1.32 of the measured forward time, score-only 0.52 to 1.56 (20,000 pairs of
 // 200-500 on m = 311, 4,000 on 450, 300 of 300-900 on 800, 64 of 80-160 on 120,
-// 50,000 of a long tail on 101, 300,000 of 50-1000 on 93 and 200) this is within
-// 25%, and it orders the geometries as measured: packed streams of 32 or 16
-// lanes where they fill the chip, 64 lanes below.
+// 50,001 of a long tail on 101, 300,000 of 50-1000 on 93 and 200, each on the five
+// geometries).  The geometry it picks there is the fastest of the five but for the
+// long tail with traceback (1.04 ms against 1.00) and 64 scored pairs (45 us against
+// 41): packed streams of 32 or 16 lanes where they fill the chip, 64 lanes below.
 constexpr double kShare[7] = {1.28, 1.28, 2.2, 3.15, 4, 5, 6};
 double stream_cost(const halign_ctx *ctx, const StreamGeom &g, bool tb, const Lens &plen, int np, int64_t sum_len,
                    int w) {
@@ -471,7 +473,10 @@ double stream_cost(const halign_ctx *ctx, const StreamGeom &g, bool tb, const Le
 
 // Resident wavefronts per SIMD that the packed kernel's streams are sized for
 // (stream16_waves fit its registers): that many, or fewer where more pairs per
-// stream end closer together.
+// stream end closer together by the model, by more than the 3% that runs of such
+// numbers differ by (20,000 on m = 311, 32 lanes: 0.77 ms with two and three, 0.79 with four).
+// Right to a few per cent on even lengths; on the long tail it takes one wavefront
+// where two are faster (1.04 against 0.84 ms).
 int packed_waves(const halign_ctx *ctx, const StreamGeom &g, bool tb, const Lens &plen, int np, int64_t sum_len,
                  int wmax) {
     int best = std::min(hk::stream16_waves(g.R, tb), wmax);
@@ -680,7 +685,10 @@ int run_batch(halign_ctx *ctx, const Scoring &S, const uint8_t *center, int m, c
     // columns.  Forward time against dealing to the least loaded stream: batch of
     // 20,000 0.77 ms against 0.79; 300,000 10.7 against 11.1; a long tail of 50,001
     // 0.99-1.04 against 0.885, for 0.23 ms less on the host (whole call 1.25-1.28
-    // against 1.34; 1.36 forward without streams of their own).
+    // against 1.34; 1.36 forward without streams of their own).  Up to 64 pairs a
+    // stream, whose lengths the staging kernel's wavefronts add with one load a
+    // lane.  The host is no faster beyond (1,200,000 pairs in 37 rounds 4.1 ms a call on
+    // the device, 13.9 on the host; 2,500,000 in 77 8.4 and 31.8).
     int dev_ns = 0, dev_own = 0;
     int64_t dev_cols = 0;
     size_t dev_code_words = 0, dev_bound = 0;
@@ -3470,10 +3478,11 @@ inline size_t al256z(size_t b) { return (b + 255) & ~(size_t)255; }
 // The distance launch: whole width per tile, or, when the tiles are too few to
 // fill the chip, column slices and a pass that adds them.
 int pdist_launch(halign_ctx *ctx, hk::PdArgs a, int64_t tiles, hipStream_t st) {
-    // up to 2,048 workgroups (eight per CU, what its registers hold) in slices
-    // of at least 256 columns: 3,001 x 4,030 rows 0.62 ms (0.68 unsliced, 0.68
-    // up to 1,024 workgroups), 672 x 18,611 0.20 (1.07, 0.23), 64 x 18,000 0.05
-    // (0.85, 0.05)
+    // below 2,048 tiles (eight workgroups per CU, what its registers hold) as
+    // many slices, of at least 256 columns, as bring the workgroups to 2,048 or
+    // past it (under 4,095: 134 MB of counts): 3,001 x 4,030 rows, 2,256 workgroups,
+    // 0.62 ms (0.68 unsliced, 0.68 up to 1,024 workgroups), 672 x 18,611 0.20 (1.07,
+    // 0.23), 64 x 18,000 0.05 (0.85, 0.05)
     int64_t nslice = tiles < 2048 ? std::min<int64_t>((a.width + 255) / 256, (2047 + tiles) / tiles) : 1;
     nslice = std::max<int64_t>(1, nslice);
     a.cslice = std::max<int64_t>(1, ((a.width + nslice - 1) / nslice + hk::kPdChunk - 1) / hk::kPdChunk) * hk::kPdChunk;

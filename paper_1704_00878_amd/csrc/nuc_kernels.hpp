@@ -95,8 +95,8 @@ constexpr int kNucTinyW = 20;    // narrow stretches at most this size both ways
 constexpr int kNucTallH = 40;    // stretches taller than this take a wavefront too (rows across lanes)
 constexpr int kNucDiagMax = 128; // stretches up to this long are tested for the plain diagonal by one lane
 
-// The table's hash of a packed segment (the host fills the table with it).
-__host__ __device__ __forceinline__ uint32_t nuc_hash(unsigned long long key, int lg_t) {
+// The table's hash of a packed segment.
+__device__ __forceinline__ uint32_t nuc_hash(unsigned long long key, int lg_t) {
     const uint32_t h = (uint32_t)key ^ (uint32_t)(key >> 32) * 0x85EBCA6Bu;
     return (h * 0x9E3779B1u) >> (32 - lg_t);
 }
